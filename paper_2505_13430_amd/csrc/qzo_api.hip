@@ -48,6 +48,7 @@ struct Workspace {
   unsigned char *h, *a, *qkv, *att, *ff, *act;
   float *ce_part, *tgt, *rowloss, *losses, *skinny;
   float *xs_a, *xs_act;     // few-token path: block sums of the norm output and of the MLP's hidden activation
+  float* mid;               // mid_gemm_kernel's partial sums
   float* split;             // K-slice partial sums of the int4 tile kernel (too few tiles for the chip)
   unsigned char* wexp;      // one linear's expanded bf16 weights (expand-then-multiply paths)
   float* se;                // expand-then-multiply of int4 / NormalFloat-4: every perturbed scale of the model, fp32
@@ -183,6 +184,28 @@ void table_layout(const qzo_model_config& c, std::vector<uint64_t>& need, std::v
   b16(V * d);
 }
 
+// Token counts per pass that take mid_gemm_kernel (int4, beyond the few-token kernel's stacked range).  Its time grows
+// by tiles of 32 tokens, the tile kernel's by tiles of 256, and the wider the layer the better the tile kernel fills
+// the chip.  Whole steps, mid_gemm_kernel's time over the other route's: 7B widths 0.65 (33-96 tokens), 0.85 (132), 0.90
+// (192), 1.00 (224), 1.03 (256); 13B widths 0.66 (40), 0.73 (96), 0.98 (132), 1.2 (256); OPT-1.3B widths 0.62 (40),
+// 0.81 (132), 0.90 (256); smaller models 0.53-0.97 up to 256.  A route that the caller chose stays: 1 (fused) keeps
+// the tile kernel beyond the few-token kernel's 64 tokens.
+bool mid_route(const qzo_model* m, uint64_t M1) {
+  const qzo_model_config& c = m->cfg;
+  if (!(c.quant == 0 || c.quant == 2) || c.act_order || M1 <= SKINNY_MAX_M_DUAL) return false;
+  if (m->int4_path == 2 || (m->int4_path == 1 && M1 > SKINNY_MAX_M)) return false;
+  uint64_t weights = 0;
+  for (int i = 0; i < 4; ++i) weights += (uint64_t)m->lin[i].N * m->lin[i].K;
+  if (M1 > (weights <= (1u << 26) ? 256u : (weights <= (1u << 28) ? 192u : 128u))) return false;
+  for (int i = 0; i < 4; ++i)
+    if (!mid_fits((uint32_t)M1, m->lin[i].N, m->lin[i].K, true)) return false;
+  return true;
+}
+
+// One pass on its own (qzo_forward_loss, joint mode): the few-token kernel is the faster one over its whole range
+// (7B widths, 33 / 57 tokens: 3.34 / 3.65 ms a pass against 3.60 / 3.92; OPT-1.3B, 57: 1.88 against 2.22).
+bool mid_single_pass(uint64_t M1) { return M1 > SKINNY_MAX_M; }
+
 // Whether qzo_step runs its two perturbed passes as one forward over 2 * batch sequences.  With at
 // most 32 tokens the few-token kernel reads the int4 weights once for both.  Beyond the few-token
 // kernel's range and as long as the fused kernel serves (at most 4096 tokens per pass), a launch of
@@ -193,7 +216,7 @@ void table_layout(const qzo_model_config& c, std::vector<uint64_t>& need, std::v
 bool passes_stacked(const qzo_model* m, uint64_t M1) {
   const qzo_model_config& c = m->cfg;
   if (!(c.quant == 0 || c.quant == 2) || m->dense_master || c.act_order) return false;
-  if (M1 <= SKINNY_MAX_M_DUAL) return true;
+  if (M1 <= SKINNY_MAX_M_DUAL || mid_route(m, M1)) return true;
   if (M1 <= SKINNY_MAX_M || M1 > STACK_TILE_MAX_M || m->int4_path == 2) return false;
   // Stacked, the fused kernel stays ahead of expand-then-multiply for a fifth more tokens than the
   // break-even of separate passes (7B widths: 72.2 against 74.9 ms per step at 2560 tokens, 83.8
@@ -204,14 +227,16 @@ bool passes_stacked(const qzo_model* m, uint64_t M1) {
   return true;
 }
 // Row at which the second pass of a stacked forward starts.
-uint64_t stacked_pass_stride(uint64_t M1) { return M1 <= SKINNY_MAX_M_DUAL ? M1 : (M1 + 255) / 256 * 256; }
+uint64_t stacked_pass_stride(const qzo_model* m, uint64_t M1) {
+  return M1 <= SKINNY_MAX_M_DUAL || mid_route(m, M1) ? M1 : (M1 + 255) / 256 * 256;
+}
 
 Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   const qzo_model_config& c = m->cfg;
   const uint64_t M1 = (uint64_t)batch * seq;
   const bool int4 = c.quant == 0 || c.quant == 2;
   const bool stack = passes_stacked(m, M1);
-  const uint64_t M = stack ? stacked_pass_stride(M1) + M1 : M1, d = c.d_model, F = c.d_ffn;
+  const uint64_t M = stack ? stacked_pass_stride(m, M1) + M1 : M1, d = c.d_model, F = c.d_ffn;
   const uint64_t n_slices = ((c.vocab + 255) / 256) * 4;
   Workspace w;
   uint64_t off = 0;
@@ -232,16 +257,24 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   w.losses = (float*)take(256);
   // few-token path of the int4 GEMM: fp32 partial sums of the K slices of the largest linear
   uint64_t sk = 0;
+  const bool mid = mid_route(m, M1);
   if (M1 <= SKINNY_MAX_M && int4 && !c.act_order)
     for (int i = 0; i < 4; ++i)
-      sk = std::max<uint64_t>(sk, skinny_ws_floats((uint32_t)M, m->lin[i].N, m->lin[i].K));
+      sk = std::max<uint64_t>(sk, skinny_ws_floats((uint32_t)(mid ? M1 : M), m->lin[i].N, m->lin[i].K));
   w.skinny = (float*)take(sk * 4);
   if (sk == 0) w.skinny = nullptr;
-  w.xs_a = sk ? (float*)take((d / 128) * M * 4) : nullptr;
-  w.xs_act = sk ? (float*)take((F / 128) * M * 4) : nullptr;
+  w.xs_a = sk || mid ? (float*)take((d / 128) * M * 4) : nullptr;
+  w.xs_act = sk || mid ? (float*)take((F / 128) * M * 4) : nullptr;
+  uint64_t mw = 0;
+  if (mid)
+    for (int i = 0; i < 4; ++i)
+      for (int dual = mid_single_pass(M1) ? 0 : 1; dual < (stack ? 2 : 1); ++dual)
+        mw = std::max<uint64_t>(mw, mid_ws_floats((uint32_t)M1, m->lin[i].N, m->lin[i].K, dual != 0));
+  w.mid = (float*)take(mw * 4);
+  if (mw == 0) w.mid = nullptr;
   // more tokens than that but still too few output tiles for the chip: split-K partial sums
   uint64_t sp = 0;
-  if ((M1 > SKINNY_MAX_M && int4) || c.act_order || c.quant == 3 || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK))
+  if ((M1 > SKINNY_MAX_M && int4 && !mid) || c.act_order || c.quant == 3 || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK))
     for (int i = 0; i < 4; ++i) {
       sp = std::max<uint64_t>(sp, tile_split_ws_floats((uint32_t)M, m->lin[i].N, m->lin[i].K));
       // a single pass (qzo_forward_loss) of a batch whose step stacks its two passes
@@ -281,7 +314,7 @@ qzo_status check_batch(const qzo_model* m, const void* tok, uint32_t batch, uint
     // bf16, must stay below 2^31 bytes (stacked passes count twice)
     const qzo_model_config& c = m->cfg;
     const uint64_t M1 = (uint64_t)batch * seq +
-                        (passes_stacked(m, (uint64_t)batch * seq) ? stacked_pass_stride((uint64_t)batch * seq) : 0);
+                        (passes_stacked(m, (uint64_t)batch * seq) ? stacked_pass_stride(m, (uint64_t)batch * seq) : 0);
     const uint64_t widest = std::max<uint64_t>({3ull * c.d_model, (c.arch == 0 ? 2ull : 1ull) * c.d_ffn});
     if (M1 * widest * 2 >= (1ull << 31))
       return fail(QZO_ERR_SHAPE, "batch*seq too large for this model: an activation tensor would exceed 2^31 bytes");
@@ -322,14 +355,14 @@ enum { PK_W4GEMM = 0, PK_LMHEAD = 1, PK_ATTN = 2, PK_UPDATE = 3, PK_OTHER = 4, P
 
 // The decoder forward with every quantized linear perturbed by sign*eps*z.
 // n_pass = 2 (int4 only; see passes_stacked): both passes of a step stacked, rows [0,M1) perturbed by
-// +eps_signed and rows [P, P + M1) by -eps_signed, P = stacked_pass_stride(M1); their losses go to
+// +eps_signed and rows [P, P + M1) by -eps_signed, P = stacked_pass_stride(m, M1); their losses go to
 // loss_out and loss_out2.
 qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t seq, uint64_t seed,
                    float eps_signed, const Workspace& w, float* loss_out, hipStream_t st,
                    void* hidden_out = nullptr, uint32_t n_pass = 1, float* loss_out2 = nullptr) {
   const qzo_model_config& c = m->cfg;
   const uint32_t batch = batch1 * n_pass, M1 = batch1 * seq;
-  const uint32_t P = n_pass == 2 ? (uint32_t)stacked_pass_stride(M1) : M1;     // rows per pass
+  const uint32_t P = n_pass == 2 ? (uint32_t)stacked_pass_stride(m, M1) : M1;     // rows per pass
   const bool padded = P != M1;                                                // rows [M1, P) are padding
   const uint32_t M = n_pass == 2 ? P + M1 : M1;                               // rows of every activation
   const uint32_t d = c.d_model, F = c.d_ffn, H = c.n_heads, dh = d / H;
@@ -369,7 +402,8 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
   (void)other;
   bool rope_fused = false;     // set by a qkv linear whose GEMM applied the rotary embedding itself
   // few-token linears take the block sums of their input from its producer
-  const bool few = w.skinny && M1 <= SKINNY_MAX_M && (c.quant == 0 || c.quant == 2) && !c.act_order;
+  float* const mid_ws = n_pass == 2 || mid_single_pass(M1) ? w.mid : nullptr;
+  const bool few = mid_ws || (w.skinny && M1 <= SKINNY_MAX_M && (c.quant == 0 || c.quant == 2) && !c.act_order);
   float* const xs_a = few ? w.xs_a : nullptr;
   for (uint32_t l = 0; l < c.n_layers; ++l) {
     const qzo_buf* T = &m->T[m->first_layer_tensor + (size_t)l * m->tensors_per_layer];
@@ -397,11 +431,17 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       g.seed_lo = seed_lo; g.seed_hi = seed_hi; g.eps_signed = eps_signed;
       g.epi = epi & ~EPI_ROPE;                // a request: only the plain GEMM of the int4 expansion route serves it
       g.s_fp16 = c.scale_fp16;
-      g.skinny_ws = w.skinny;
+      g.skinny_ws = mid_ws ? nullptr : w.skinny;
       g.split_ws = w.split;
+      g.mid_ws = mid_ws;
       if (few) {     // the few-token kernel takes the block sums of its input from the kernel that wrote it
         g.xsum = (li == 0 || li == 2) ? w.xs_a : (li == 3 ? w.xs_act : nullptr);
         g.xsum_out = li == 2 ? w.xs_act : nullptr;
+        if (mid_ws && li == 1) {      // the attention output's block sums, where the norm's were
+          hipError_t e = launch_block_sums(x, M, g.K, w.xs_a, st);
+          if (e != hipSuccess) return e;
+          g.xsum = w.xs_a;
+        }
       }
       if (c.act_order) {
         // a group index per column: scale and zero-point are looked up per weight while the perturbed

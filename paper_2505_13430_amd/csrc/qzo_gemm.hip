@@ -1010,6 +1010,7 @@ hipError_t launch_w4a16_gemm(const GemmArgs& a0, hipStream_t st) {
   }
   if (a0.M == 0 || a0.N == 0) return hipSuccess;
   if (a0.M <= SKINNY_MAX_M && a0.skinny_ws) return launch_skinny_gemm(a0, a0.skinny_ws, st);
+  if (a0.mid_ws) return launch_mid_gemm(a0, a0.mid_ws, st);
   GemmArgs a = a0;
   if (a0.dual) {
     // both passes of a step stacked: the second pass starts on a tile boundary and its tiles take -eps

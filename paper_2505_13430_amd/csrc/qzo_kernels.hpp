@@ -47,6 +47,7 @@ struct GemmArgs {
   void* y;              // bf16 [M,N]
   float* partials;      // EPI_SUMSQ: one float per workgroup
   float* skinny_ws;     // fp32 scratch of skinny_ws_floats(rows, N, K) floats: enables the few-token path (M <= 64)
+  float* mid_ws;        // fp32 scratch of mid_ws_floats(M, N, K, dual) floats: enables mid_gemm_kernel
   float* split_ws;      // fp32 scratch of tile_split_ws_floats(M, N, K) floats: enables split-K of the int4 tile kernel
   uint32_t ksplit, kt_per;   // set by the launcher: K slices and k-tiles per slice
   const float* rope;    // EPI_ROPE: (cos, sin) of [rope_S positions][dh/2 pairs]; row m sits at position m % rope_S
@@ -85,6 +86,25 @@ uint32_t skinny_reduce_blocks(uint32_t M, uint32_t N, uint32_t epi);   // EPI_SU
 hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st);
 // Adds K-slice partial sums part[slice][M][N] in slice order and applies a's epilogue.
 hipError_t launch_partial_reduce(const GemmArgs& a, const float* part, uint32_t ksplit, hipStream_t st);
+// Some dozen to a few hundred tokens per pass (mid_gemm_kernel): items (block of MID_ROWS output rows, block of mt token
+// tiles) x U pairs of groups of K are cut into W equal contiguous ranges, one per workgroup; an item that
+// several ranges touch has one partial sum per range, in range order.
+constexpr uint32_t MID_ROWS = 256;
+struct MidPlan {
+  uint32_t mt, Z, U, W, tot;           // Z: token blocks per row block; U: pairs of groups of K; tot = items * U
+  uint32_t T, Tp, rows, slots;         // token tiles of 32 (all, of one pass), rows of x, most slices of an item
+};
+MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual);
+uint64_t mid_ws_floats(uint32_t M, uint32_t N, uint32_t K, bool dual);
+bool mid_fits(uint32_t M, uint32_t N, uint32_t K, bool dual);
+// Range that holds unit i: ranges are [w tot / W, (w+1) tot / W).
+__host__ __device__ inline uint32_t mid_range_of(uint32_t i, uint32_t W, uint32_t tot) { return ((i + 1) * W - 1) / tot; }
+__host__ __device__ inline uint32_t mid_slices(const MidPlan& p, uint32_t item) {
+  return mid_range_of((item + 1) * p.U - 1, p.W, p.tot) - mid_range_of(item * p.U, p.W, p.tot) + 1;
+}
+hipError_t launch_block_sums(const void* x, uint32_t rows, uint32_t K, float* out, hipStream_t st);
+hipError_t launch_mid_gemm(const GemmArgs& a, float* ws, hipStream_t st);
+hipError_t launch_mid_reduce(const GemmArgs& a, const float* part, const MidPlan& mp, hipStream_t st);
 // Split-K of the int4 tile kernel when an M x N output has too few 256 x 256 tiles for the chip:
 // number of K slices (1: none) and k-tiles per slice.
 uint32_t tile_ksplit(uint32_t M, uint32_t N, uint32_t K, uint32_t* kt_per);

@@ -1,0 +1,319 @@
+// Perturbed W4A16 linear for some dozen to a few hundred tokens:
+//   Y[M,N] = X[M,K] * W_eff^T,  W_eff[n,k] = (s[n,k/128] + sigma*eps*z(row_base+n, k/128)) * (u[n,k] - zp[n,k/128])
+// (paper Eq. 4-5; zp = 8 without zero-points).  Above the few-token kernel's 64 rows per launch the weights are used
+// by several token tiles, and a 256 x 256 output tile is still mostly padding and leaves most of the chip idle.
+//
+// A workgroup of eight wavefronts owns 256 output rows (32 per wavefront) and two or four tiles of 32 tokens.  As in
+// the few-token kernel the nibbles enter the matrix unit as the exact integers 128 + u and the perturbed scale is
+// applied to a group's fp32 sums, y += s_eff * P; the weights are not rounded.  What the integers carry too much,
+// s_eff (128 + zp) X with X the block sum of the activations (delivered by the kernel that wrote them), is taken off
+// for two groups at a time by one fp32 MFMA per tile (32x32x2: its depth is the two groups), which costs no vector
+// instruction and no broadcast reads.  A token tile lies in one pass of a stacked step and takes that pass's sign.
+//
+// Everything a group needs comes by direct-to-LDS loads into a ring of three or four stages, requested two or three
+// groups ahead (swizzled on the memory side, nothing passes through registers); one barrier per group.  Inside a group
+// the instructions are dealt out behind the MFMAs by hand: unpacking behind the first tile's, a tile's rescaling
+// behind the next one's, fragment reads four ahead.  The compiler's own order needed 256 registers and spilled.
+//
+// Work is split evenly whatever the shape: items (row block, token block) x pairs of groups are cut into one
+// contiguous range per compute unit; an item that several ranges touch is summed by the reduction kernel in order.
+//
+// What bounds it: at 57 tokens per pass (4096 x 4096 .. 22016) a launch takes 16-43 us, of which about 10 us do not
+// depend on the work (start of a kernel whose code and operands come from HBM, 15-30 MB of partial sums out); a group
+// of four tiles takes 4200-5300 cycles with the matrix unit busy for 2300 and the LDS for 2700 of them.  Whole step
+// at 7B widths against two passes of the few-token kernel (up to 64 tokens) or the 256-row tile kernel (beyond):
+// 1 x 33 tokens 7.04 -> 4.63 ms, 1 x 57 7.56 -> 4.91, 2 x 40 9.45 -> 6.02, 4 x 33 9.73 -> 8.23, 4 x 48 10.1 -> 9.1.
+// Tried: one wavefront per SIMD with 64 rows each (half the LDS reads, but the accumulators move to AGPRs and every
+// rescaling then pays two register moves: 15-25 % slower); K split between two halves of a workgroup (LDS merge
+// instead of partial sums: more activation traffic, slower); activations and weights staged through registers
+// (a wait for young activation loads waits for older weight loads, and four tiles spill: 25 % slower at four tiles);
+// -(128 + zp) X as the initial accumulator (16 broadcast reads of the LDS per group: 5-8 % slower).
+#include "qzo_device.hpp"
+#include "qzo_kernels.hpp"
+#include "qzo_nibble.hpp"
+#include <algorithm>
+#include <type_traits>
+
+namespace qzo {
+
+namespace {
+
+// Global work of a launch: items (row block, token block) x pairs of groups of K, cut into W equal contiguous ranges.
+struct MidMap {
+  uint32_t U, W, tot, Z;        // pairs of groups per item, ranges, items * U, token blocks per row block
+  uint32_t T, Tp;               // token tiles of 32 rows: all, and those of one pass
+  uint32_t rows;                // rows of x and y (2 M when dual)
+};
+
+// One stage of the LDS ring holds everything that a group needs: the activation block, the weights of the
+// workgroup's rows, the block sums, scales and zero-points.
+constexpr uint32_t MID_W = MID_ROWS * 64, MID_XS = 512, MID_S = 8 * 256;
+template <int MT, bool ZP>
+struct MidLds {
+  static constexpr uint32_t X = MT * 8192, STAGE = X + MID_W + MID_XS + MID_S * (ZP ? 2 : 1);
+  static constexpr int S = MT == 4 ? 3 : 4;
+  static constexpr uint32_t BYTES = STAGE * S;
+  static constexpr int LOADS = MT + 4 + (ZP ? 1 : 0);   // load instructions per wavefront and stage
+  static_assert(BYTES <= 160 * 1024, "LDS of a compute unit");
+};
+
+#define QM_DTL(INSTR, RSRC, LDSADDR, VOFF)                                                   \
+  asm volatile("s_mov_b32 m0, %0\n\t" INSTR " %1, %2, 0 offen lds" : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC) : "memory", "m0")
+
+template <int MT, bool ZP>
+__global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp, float* __restrict__ part) {
+  typedef MidLds<MT, ZP> L;
+  constexpr int S = L::S;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const uint32_t t = threadIdx.x, lane = t & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const uint32_t lrow = lane & 31u, half = lane >> 5;     // MFMA operand: row, half of the group's inputs
+  const uint32_t K = a.K, ngrp = K >> 7;
+  const bool s_fp16 = a.s_fp16 != 0;
+  const NibbleConsts nc = nibble_constants();
+  constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  auto rsrc = [](const void* p, uint64_t bytes) {
+    return i32x4{(int)(uint32_t)(uintptr_t)p, (int)(uint32_t)((uintptr_t)p >> 32), (int)bytes, 0x00020000};
+  };
+  const i32x4 rx = rsrc(a.x, (uint64_t)mp.rows * K * 2), rw = rsrc(a.w, (uint64_t)a.N * (K >> 1));
+  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * ngrp * 2), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * ngrp);
+  const i32x4 rxs = rsrc(a.xsum, (uint64_t)mp.rows * ngrp * 4);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+
+  // what a lane reads of a stage: two chunks of its weight row, fragment j of an activation tile
+  const uint32_t wrd = L::X + wave * 2048u + lrow * 64u, wsw = (lrow >> 2) & 3u;
+  const uint32_t wrd0 = wrd + (((2 * half) ^ wsw) << 4), wrd1 = wrd + (((2 * half + 1) ^ wsw) << 4);
+  uint32_t xrd[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) xrd[j] = lrow * 256u + (((half * 8 + j) ^ (lrow & 15u)) << 4);
+
+  const uint32_t w = (mp.W & 7u) == 0 ? (blockIdx.x & 7u) * (mp.W >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+  uint32_t i0 = w * mp.tot / mp.W;
+  const uint32_t i1 = (w + 1) * mp.tot / mp.W;
+
+  while (i0 < i1) {
+    const uint32_t item = i0 / mp.U, u0 = i0 - item * mp.U, u1 = min(mp.U, u0 + (i1 - i0));
+    const uint32_t slot = w - mid_range_of(item * mp.U, mp.W, mp.tot);
+    const uint32_t rb = item / mp.Z, z = item - rb * mp.Z;
+    i0 += u1 - u0;
+    const uint32_t g0 = 2 * u0, g1 = min(ngrp, 2 * u1);
+    const uint32_t nb = rb * MID_ROWS + wave * 32;
+    const uint32_t n = min(nb + lrow, a.N - 1);             // the lane's row
+
+    // loads: activations 4 rows of 256 bytes per instruction, weights 16 rows of 64 bytes, both swizzled on the
+    // memory side (16-byte chunks; the LDS is filled in lane order)
+    auto xrow_of = [&](uint32_t row) {
+      const uint32_t ti = min(z * MT + (row >> 5), mp.T - 1), pass = ti >= mp.Tp ? 1u : 0u;
+      return pass * a.M + min((ti - pass * mp.Tp) * 32 + (row & 31u), a.M - 1);
+    };
+    uint32_t xoff[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const uint32_t row = 4 * (i * 8 + wave) + (lane >> 4);
+      xoff[i] = xrow_of(row) * K * 2 + (((lane & 15u) ^ (row & 15u)) << 4);
+    }
+    const uint32_t woff = (nb + (lane >> 2)) * (K >> 1) + ((lane & 3u) ^ ((lane >> 4) & 3u)) * 16, wstep = 16 * (K >> 1);
+    const uint32_t soff = n * ngrp;
+    const uint32_t xsoff = xrow_of(min((wave & 1u) * 64 + lane, MT * 32u - 1)) * 4u;
+    // load instruction i of group g's stage
+    auto load1 = [&](int i, uint32_t g, uint32_t stage) {
+      const uint32_t base = lds0 + stage * L::STAGE, in = g < g1 ? 0u : OUT_OF_RANGE;
+      if (i < MT)
+        QM_DTL("buffer_load_dwordx4", rx, base + (i * 8 + wave) * 1024, xoff[i] + (in + g * 256));
+      else if (i < MT + 2)
+        QM_DTL("buffer_load_dwordx4", rw, base + L::X + wave * 2048 + (i - MT) * 1024, woff + (in + g * 64 + (i - MT) * wstep));
+      else if (i == MT + 2)
+        QM_DTL("buffer_load_dword", rxs, base + L::X + MID_W + (wave & 1u) * 256, xsoff + (in + g * mp.rows * 4));
+      else if (i == MT + 3)
+        QM_DTL("buffer_load_ushort", rs, base + L::X + MID_W + MID_XS + wave * 256, soff * 2 + (in + g * 2));
+      else if (ZP && i == MT + 4)
+        QM_DTL("buffer_load_ubyte", rz, base + L::X + MID_W + MID_XS + MID_S + wave * 256, soff + (in + g));
+    };
+
+    floatx16 y[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) y[m][r] = 0.0f;
+    uint32_t zw[4];
+    float z_even = 0.0f, z_odd = 0.0f;
+    float xa[MT], bp = 0.0f, bm = 0.0f;                       // operands of the correction, see below
+#pragma unroll
+    for (int m = 0; m < MT; ++m) xa[m] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < S - 1; ++i)
+#pragma unroll
+      for (int l = 0; l < L::LOADS; ++l) load1(l, g0 + i, i);
+    uint32_t stage = 0;
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"((S - 2) * L::LOADS) : "memory");
+    __builtin_amdgcn_s_barrier();
+    // one group; d = g % 2
+    auto group = [&](uint32_t g, auto parity) {
+      constexpr int d = decltype(parity)::value;
+      const uint32_t to = stage == 0 ? S - 1 : stage - 1;     // the group before, which everyone has read
+      const unsigned char* sb = lds + stage * L::STAGE;
+      constexpr int R = 4;                  // fragments read ahead of their MFMA
+      bf16x8 wf[8], xf[R];
+      floatx16 p[2];
+      auto xread = [&](int q) {
+        xf[q % R] = *reinterpret_cast<const bf16x8*>(sb + xrd[q & 7] + (q >> 3) * 8192);
+      };
+      const u32x4 w0 = *reinterpret_cast<const u32x4*>(sb + wrd0), w1 = *reinterpret_cast<const u32x4*>(sb + wrd1);
+      const uint32_t wd[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+#pragma unroll
+      for (int q = 0; q < R; ++q) xread(q);
+      const uint32_t sbits = *reinterpret_cast<const uint32_t*>(sb + L::X + MID_W + MID_XS + wave * 256 + lane * 4);
+      const uint32_t zbits = ZP ? *reinterpret_cast<const uint32_t*>(sb + L::X + MID_W + MID_XS + MID_S + wave * 256 + lane * 4) : 8u;
+      float xs[MT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) xs[m] = *reinterpret_cast<const float*>(sb + L::X + MID_W + (m * 32 + lrow) * 4);
+      if (d == 0 && (g == g0 || (g & 7u) == 0)) {
+        const u32x4_t pw = philox4x32_10(a.row_base + n, g >> 3, 0u, 0u, a.seed_lo, a.seed_hi);
+        zw[0] = pw.x; zw[1] = pw.y; zw[2] = pw.z; zw[3] = pw.w;
+      }
+      if (d == 0) {
+        const uint32_t q = (g & 7u) >> 1;
+        normal_pair(q == 0 ? zw[0] : (q == 1 ? zw[1] : (q == 2 ? zw[2] : zw[3])), z_even, z_odd);
+      }
+      const float s0 = scale_to_f32(sbits & 0xffffu, s_fp16), zn = d ? z_odd : z_even;
+      const float sp = __builtin_fmaf(a.eps_signed, zn, s0), sm = __builtin_fmaf(-a.eps_signed, zn, s0);
+      const float cz = ZP ? -(128.0f + (float)(zbits & 0xffu)) : -136.0f;
+      // correction operands: lanes of half k hold group k of a pair
+      const bool mine = half == d;
+#pragma unroll
+      for (int m = 0; m < MT; ++m) xa[m] = mine ? xs[m] : (d == 0 ? 0.0f : xa[m]);
+      bp = mine ? sp * cz : bp;
+      bm = mine ? sm * cz : bm;
+      auto rescale = [&](int m, int r0, int cnt) {
+        const float se = (z * MT + m) >= mp.Tp ? sm : sp;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (r >= r0 && r < r0 + cnt) y[m][r] = __builtin_fmaf(se, p[m & 1][r], y[m][r]);
+      };
+      wf[0] = unpack8_natural(wd[0], nc);
+      __builtin_amdgcn_sched_barrier(0);
+      // one slot per MFMA: what else the wavefront has to do is dealt out between them
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int q = m * 8 + j;
+          const floatx16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+          p[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[q % R], wf[j], j == 0 ? zero : p[m & 1], 0, 0, 0);
+          if (q + R < MT * 8) xread(q + R);
+          if (m == 0 && j < 7) wf[j + 1] = unpack8_natural(wd[j + 1], nc);
+          if (m > 0 && j >= 1 && j <= 4) rescale(m - 1, (j - 1) * 4, 4);
+          if (q >= 2 && q - 2 < L::LOADS) load1(q - 2, g + S - 1, to);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+      for (int l = MT * 8 - 2; l < L::LOADS; ++l) load1(l, g + S - 1, to);
+      rescale(MT - 1, 0, 16);
+      stage = stage == S - 1 ? 0 : stage + 1;
+      // the next group has landed (later ones may still be on their way), and everyone has read this one
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((S - 2) * L::LOADS) : "memory");
+      __builtin_amdgcn_s_barrier();
+    };
+    for (uint32_t g = g0; g < g1; g += 2) {
+      group(g, std::integral_constant<int, 0>());
+      if (g + 1 < g1) group(g + 1, std::integral_constant<int, 1>());
+      // the integers entered as 128 + u: y -= s_eff (128 + zp) X, two groups at a time on the fp32 matrix unit
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        y[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[m], (z * MT + m) >= mp.Tp ? bm : bp, y[m], 0, 0, 0);
+    }
+
+    // partial sums of this range
+    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(part, 0, (int)0x7fffffff, 0x00020000);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const uint32_t ti = z * MT + m, pass = ti >= mp.Tp ? 1u : 0u;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const uint32_t tok = (ti - pass * mp.Tp) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        const uint32_t off = ((slot * mp.rows + pass * a.M + tok) * a.N + nb + lrow) * 4u;
+        if (ti < mp.T && tok < a.M && nb + lrow < a.N)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[m][r]), rp, (int)off, 0, 0);
+      }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");        // loads past the end still write the LDS
+}
+#undef QM_DTL
+
+// Block sums X[g][row] = sum of x[row, 128 g .. 128 g + 127]: 16 lanes a group.
+__global__ __launch_bounds__(256) void block_sums_kernel(const u32x4* __restrict__ x, uint32_t rows, uint32_t K,
+                                                         float* __restrict__ out) {
+  const uint32_t c = blockIdx.x * 256 + threadIdx.x, cpr = K >> 3;
+  const bool own = c < rows * cpr;
+  float s = own ? sum8_bf16(x[c]) : 0.0f;
+  s += __shfl_xor(s, 1, 64); s += __shfl_xor(s, 2, 64); s += __shfl_xor(s, 4, 64); s += __shfl_xor(s, 8, 64);
+  if (own && (threadIdx.x & 15u) == 0) out[(c % cpr >> 4) * rows + c / cpr] = s;
+}
+
+}  // namespace
+
+// Two token tiles per workgroup up to eleven tiles in all, four from there on: with four the workgroups read the
+// weights half as often, with two their partial sums are half as large.  Inside the 7B step at 4096 x 4096 .. 22016
+// (sum of the four linears of a layer with their reductions, two / four tiles): 4 tiles 135 / 140 us, 6 tiles
+// 167 / 179, 10 tiles 227 / 230, 12 tiles 253 / 239, 16 tiles 326 / 289.  Fewer ranges than compute units (longer
+// ranges, fewer partial sums) were slower at every size: 192 ranges +5 %, 128 +30 %.
+MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual) {
+  MidPlan p = {};
+  const uint32_t Tp = (M + 31) / 32, T = dual ? 2 * Tp : Tp;
+  p.rows = dual ? 2 * M : M; p.T = T; p.Tp = Tp;
+  p.mt = T >= 12 ? 4 : 2;
+  p.Z = (T + p.mt - 1) / p.mt;
+  p.U = ((K >> 7) + 1) / 2;
+  p.tot = ((N + MID_ROWS - 1) / MID_ROWS) * p.Z * p.U;
+  p.W = std::min(p.tot, gemm_workgroups(1u << 20, 1u << 20));     // compute units
+  const uint32_t shortest = p.tot / p.W;
+  p.slots = std::min(p.U, (p.U + shortest - 1) / shortest + 1);   // no item is touched by more ranges than that
+  return p;
+}
+uint64_t mid_ws_floats(uint32_t M, uint32_t N, uint32_t K, bool dual) {
+  const MidPlan p = mid_plan(M, N, K, dual);
+  return (uint64_t)p.slots * p.rows * N;
+}
+// 32-bit byte offsets into the operands and the partial sums, 32-bit products in the ranges' arithmetic
+bool mid_fits(uint32_t M, uint32_t N, uint32_t K, bool dual) {
+  const MidPlan p = mid_plan(M, N, K, dual);
+  return (uint64_t)p.slots * p.rows * N * 4 < (1ull << 31) && (uint64_t)p.rows * K * 2 < (1ull << 31) &&
+         ((uint64_t)N + MID_ROWS) * (K >> 1) < (1ull << 31) &&
+         ((uint64_t)N / MID_ROWS + 1) * p.Z * p.U * (p.W + 1) < (1ull << 32);
+}
+
+template <int MT, bool ZP>
+static hipError_t mid_launch(const GemmArgs& a, const MidMap& mp, float* ws, hipStream_t st) {
+  static bool ready = false;
+  constexpr uint32_t L = MidLds<MT, ZP>::BYTES;
+  if (!ready) {
+    hipError_t e = hipFuncSetAttribute((const void*)mid_gemm_kernel<MT, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize, L);
+    if (e != hipSuccess) return e;
+    ready = true;
+  }
+  mid_gemm_kernel<MT, ZP><<<mp.W, 512, L, st>>>(a, mp, ws);
+  return hipGetLastError();
+}
+template <bool ZP>
+static hipError_t mid_launch_mt(uint32_t mt, const GemmArgs& a, const MidMap& mp, float* ws, hipStream_t st) {
+  return mt == 2 ? mid_launch<2, ZP>(a, mp, ws, st) : mid_launch<4, ZP>(a, mp, ws, st);
+}
+
+hipError_t launch_block_sums(const void* x, uint32_t rows, uint32_t K, float* out, hipStream_t st) {
+  block_sums_kernel<<<(rows * (K >> 3) + 255) / 256, 256, 0, st>>>((const u32x4*)x, rows, K, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_mid_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
+  if (a.M == 0 || a.N == 0) return hipSuccess;
+  const MidPlan p = mid_plan(a.M, a.N, a.K, a.dual != 0);
+  if (!ws || !a.xsum || !mid_fits(a.M, a.N, a.K, a.dual != 0)) return hipErrorInvalidValue;
+  const MidMap mp = {p.U, p.W, p.tot, p.Z, p.T, p.Tp, p.rows};
+  hipError_t e = a.zp ? mid_launch_mt<true>(p.mt, a, mp, ws, st) : mid_launch_mt<false>(p.mt, a, mp, ws, st);
+  if (e != hipSuccess) return e;
+  return launch_mid_reduce(a, ws, p, st);
+}
+
+}  // namespace qzo

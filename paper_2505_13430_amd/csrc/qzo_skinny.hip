@@ -38,64 +38,21 @@
 // (rows [0,M) and [M,2M)).
 #include "qzo_device.hpp"
 #include "qzo_kernels.hpp"
+#include "qzo_nibble.hpp"
 
 namespace qzo {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
 constexpr int SK_ROWS = 128;      // output rows per workgroup
 constexpr int SK_WD = 8;          // groups per pass of the K loop: four rounds of two groups, all in flight
 
-// 8 nibbles of one dword -> the bf16 values 128 + u, in the order k = 0,4,1,5,2,6,3,7.
-// One bitfield insert per pair ((mask & w) | (~mask & 0x43004300)) with the two constants in
-// registers; written as "and, or" with literals the compiler spends two instructions on it.
-__device__ __forceinline__ uint32_t bias_pair(uint32_t w, uint32_t mask, uint32_t magic) {
-  uint32_t r;
-  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(mask), "v"(w), "v"(magic));
-  return r;
-}
-__device__ __forceinline__ bf16x8 unpack8_biased(uint32_t w, uint32_t mask, uint32_t magic) {
-  union { bf16x8 v; uint32_t u[4]; } r;
-  r.u[0] = bias_pair(w, mask, magic);
-  r.u[1] = bias_pair(w >> 4, mask, magic);
-  r.u[2] = bias_pair(w >> 8, mask, magic);
-  r.u[3] = bias_pair(w >> 12, mask, magic);
-  return r.v;
-}
-// 8 consecutive bf16 (4 dwords) -> the same order 0,4,1,5,2,6,3,7
-__device__ __forceinline__ u32x4 permute8(u32x4 x) {
-  u32x4 r;
-  r.x = __builtin_amdgcn_perm(x.z, x.x, 0x05040100u);    // (x0, x4): low halves of dwords 0 and 2
-  r.y = __builtin_amdgcn_perm(x.z, x.x, 0x07060302u);    // (x1, x5): high halves
-  r.z = __builtin_amdgcn_perm(x.w, x.y, 0x05040100u);    // (x2, x6)
-  r.w = __builtin_amdgcn_perm(x.w, x.y, 0x07060302u);    // (x3, x7)
-  return r;
-}
-// sum of 8 bf16 values in fp32
-__device__ __forceinline__ float sum8_bf16(u32x4 x) {
-  const uint32_t d[4] = {x.x, x.y, x.z, x.w};
-  float lo = 0.0f, hi = 0.0f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    lo += __uint_as_float(d[i] << 16);
-    hi += __uint_as_float(d[i] & 0xffff0000u);
-  }
-  return lo + hi;
-}
-
-__device__ __forceinline__ uint32_t x_lds_off(uint32_t row, uint32_t chunk) {   // 256-byte rows, 16 chunks
-  return row * 256u + ((chunk ^ (row & 15u)) << 4);
-}
-
 // One output item of the slice reduction: 4 consecutive output features f .. f+3 of token m.
 // Adds the K-slice partials in slice order and applies the epilogue; returns the sum of the squares
 // of the stored bf16 values (and their plain sum in `sum`).
+// ksplit: slices of feature f (and of the up feature NO + f with SwiGLU: ksplit_up).
 __device__ __forceinline__ float reduce_item(const GemmArgs& a, const float* __restrict__ part, uint32_t ksplit,
-                                             uint32_t m, uint32_t f, float& sum) {
+                                             uint32_t ksplit_up, uint32_t m, uint32_t f, float& sum) {
   const bool swiglu = (a.epi & EPI_SWIGLU) != 0;
   const uint32_t NO = swiglu ? a.N >> 1 : a.N;
   auto load4 = [&](uint32_t ks, uint32_t col) {
@@ -104,20 +61,18 @@ __device__ __forceinline__ float reduce_item(const GemmArgs& a, const float* __r
   // four slices' loads in flight at a time (one at a time, the loop is a chain of memory
   // latencies); the additions stay in slice order
   float v[4] = {0, 0, 0, 0}, u[4] = {0, 0, 0, 0};
-  for (uint32_t k0 = 0; k0 < ksplit; k0 += 4) {
+  const uint32_t most = swiglu ? max(ksplit, ksplit_up) : ksplit;
+  for (uint32_t k0 = 0; k0 < most; k0 += 4) {
     float4 p[4], pu[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t ks = min(k0 + i, ksplit - 1);
-      p[i] = load4(ks, f);
-      if (swiglu) pu[i] = load4(ks, NO + f);
+      p[i] = load4(min(k0 + i, ksplit - 1), f);
+      if (swiglu) pu[i] = load4(min(k0 + i, ksplit_up - 1), NO + f);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if (k0 + i < ksplit) {
-        v[0] += p[i].x; v[1] += p[i].y; v[2] += p[i].z; v[3] += p[i].w;
-        if (swiglu) { u[0] += pu[i].x; u[1] += pu[i].y; u[2] += pu[i].z; u[3] += pu[i].w; }
-      }
+      if (k0 + i < ksplit) { v[0] += p[i].x; v[1] += p[i].y; v[2] += p[i].z; v[3] += p[i].w; }
+      if (swiglu && k0 + i < ksplit_up) { u[0] += pu[i].x; u[1] += pu[i].y; u[2] += pu[i].z; u[3] += pu[i].w; }
     }
   }
   if (swiglu) {
@@ -177,9 +132,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
   const uint32_t n_own = nb + lrow;
   const uint32_t n = min(n_own, a.N - 1);                 // the row this lane feeds to the MFMA
   const bool s_fp16 = a.s_fp16 != 0;
-  const uint32_t nib_mask = 0x000f000fu;
-  uint32_t nib_magic;
-  asm volatile("v_mov_b32 %0, 0x43004300" : "=v"(nib_magic));      // kept in a vector register
+  const NibbleConsts nc = nibble_constants();
 
   // y[m][4 b + c]: weight row n, tile row 32 m + 8 b + 4 half + c
   floatx16 y[MT];
@@ -396,7 +349,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
           floatx16 pg[MT], px;                    // px: X[m,g] of tile rows 8 b + 4 half + c in every lane
 #pragma unroll
           for (int j = 0; j < 8; ++j) {           // k-step j: inputs 64 half + 8 j .. + 7 of the group
-            const bf16x8 wf = unpack8_biased(wd[j], nib_mask, nib_magic);
+            const bf16x8 wf = unpack8_biased(wd[j], nc);
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
               const bf16x8 xf = *reinterpret_cast<const bf16x8*>(xs[buf] + x_lds_off(m * 32 + lrow, half * 8 + j));
@@ -451,13 +404,26 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
 
 // Adds the K-slice partials in slice order and applies the epilogue.  A thread owns 4
 // consecutive output features of one token (of the output: [M, N], or [M, N/2] with SwiGLU).
+// MAPPED: the slices come from mid_gemm_kernel, whose ranges of work give every block of the output a number of
+// slices of its own.
+template <bool MAPPED>
 __global__ __launch_bounds__(256) void skinny_reduce_kernel(GemmArgs a, const float* __restrict__ part,
-                                                            uint32_t ksplit) {
+                                                            uint32_t ksplit, MidPlan mp) {
   const uint32_t NO = (a.epi & EPI_SWIGLU) ? a.N >> 1 : a.N;                  // output width
   const uint32_t q = blockIdx.x * 256 + threadIdx.x, per_row = NO >> 2;
   float ssq = 0.0f, sx = 0.0f;
   const bool own = q < a.M * per_row;
-  if (own) ssq = reduce_item(a, part, ksplit, q / per_row, (q % per_row) * 4, sx);
+  if (own) {
+    const uint32_t m = q / per_row, f = (q % per_row) * 4;
+    uint32_t kf = ksplit, ku = ksplit;
+    if (MAPPED) {
+      const uint32_t pass_rows = mp.T == mp.Tp ? mp.rows : mp.rows >> 1, pass = m >= pass_rows ? 1u : 0u;
+      const uint32_t z = (pass * mp.Tp + ((m - pass * pass_rows) >> 5)) / mp.mt;
+      kf = mid_slices(mp, (f / MID_ROWS) * mp.Z + z);
+      ku = (a.epi & EPI_SWIGLU) ? mid_slices(mp, ((NO + f) / MID_ROWS) * mp.Z + z) : kf;
+    }
+    ssq = reduce_item(a, part, kf, ku, m, f, sx);
+  }
   if (a.xsum_out) {
     // block sums of the output for a few-token linear that reads it: 128 features = 32 consecutive
     // threads of one token (the output width is a multiple of 128)
@@ -536,7 +502,7 @@ hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   GemmArgs r = a;                               // the reduction sees the stacked rows as one matrix
   if (a.dual) r.M = 2 * a.M;
   if (r.ldy || ((r.epi & EPI_SWIGLU) ? r.N >> 1 : r.N) % 128) r.xsum_out = nullptr;
-  skinny_reduce_kernel<<<skinny_reduce_blocks(r.M, r.N, r.epi), 256, 0, st>>>(r, ws, ks);
+  skinny_reduce_kernel<false><<<skinny_reduce_blocks(r.M, r.N, r.epi), 256, 0, st>>>(r, ws, ks, MidPlan{});
   return hipGetLastError();
 }
 
@@ -544,7 +510,15 @@ hipError_t launch_partial_reduce(const GemmArgs& a, const float* part, uint32_t 
   if (a.M == 0 || a.N == 0) return hipSuccess;
   GemmArgs r = a;
   r.xsum_out = nullptr;                         // block sums are a service of the few-token path only
-  skinny_reduce_kernel<<<skinny_reduce_blocks(a.M, a.N, a.epi), 256, 0, st>>>(r, part, ksplit);
+  skinny_reduce_kernel<false><<<skinny_reduce_blocks(a.M, a.N, a.epi), 256, 0, st>>>(r, part, ksplit, MidPlan{});
+  return hipGetLastError();
+}
+
+hipError_t launch_mid_reduce(const GemmArgs& a, const float* part, const MidPlan& mp, hipStream_t st) {
+  GemmArgs r = a;
+  r.M = mp.rows;
+  if (r.ldy || ((r.epi & EPI_SWIGLU) ? r.N >> 1 : r.N) % 128) r.xsum_out = nullptr;
+  skinny_reduce_kernel<true><<<skinny_reduce_blocks(r.M, r.N, r.epi), 256, 0, st>>>(r, part, 0, mp);
   return hipGetLastError();
 }
 

@@ -659,6 +659,35 @@ def test_real_width_one_layer_stacked_tile_step(oracle, name, asym):
     dm.close()
 
 
+MID_LLAMA = dict(arch="llama", n_layers=2, d_model=384, n_heads=3, d_ffn=640, vocab=300, max_seq=64)
+MID_OPT = dict(arch="opt", n_layers=2, d_model=384, n_heads=6, d_ffn=640, vocab=300, max_seq=64)
+MID_7B = dict(synth.SHAPES["llama-2-7b"], n_layers=1, vocab=1000)
+
+
+@pytest.mark.parametrize("base,var,batch,seq", [
+    (MID_LLAMA, False, 1, 33), (MID_LLAMA, "zp16", 1, 57), (MID_LLAMA, True, 4, 24), (MID_LLAMA, False, 3, 43),
+    (MID_LLAMA, False, 3, 61), (MID_OPT, True, 4, 48), (MID_OPT, False, 4, 64), (MID_7B, False, 1, 57),
+    (MID_7B, True, 4, 45)])
+def test_some_dozen_to_a_few_hundred_tokens(oracle, base, var, batch, seq):
+    """33 to 256 tokens per pass, both passes stacked in tiles of 32 tokens: odd numbers of groups (K = 384, 640),
+    row blocks that end inside the matrix, partly filled and missing token tiles, two and four tiles per workgroup,
+    items that one range covers and that several share.  Losses against the oracle (bf16 forward: 2e-2 as for the
+    other routes) and against two single passes on the expanded weights (bf16 noise of a mean over the tokens)."""
+    shape = dict(base, batch=batch, seq=seq)
+    om, dm = _models(oracle, shape, 1234, 4.0 if base["d_model"] < 1024 else 1.0, **_variant_args(var))
+    tok = synth.tokens(shape, 5678)
+    tokd = _dev(tok)
+    got = qb.read_step_result(dm.step(tokd, 21, 1e-3, 0.0, 100.0))       # eta = 0: scales untouched
+    want = oracle.qzo_step(om, tok, seed=21, eps=1e-3, eta=0.0, Cthr=100.0)
+    dm.set_int4_path(2)
+    single = [float(dm.forward_loss(tokd, 21, 1e-3, sign).item()) for sign in (1, -1)]
+    for k, other in zip(("loss_plus", "loss_minus"), single):
+        assert abs(got[k] - want[k]) <= 2e-2 * want[k], (k, got[k], want[k])
+        assert abs(got[k] - other) <= 5e-3 * other, (k, got[k], other)
+    assert got["loss_plus"] != got["loss_minus"]
+    dm.close()
+
+
 def test_failing_calls_enqueue_nothing(oracle):
     """Every error that the library finds itself (anything but a failing HIP call) is found before
     the first launch: outputs, workspace and scales are untouched afterwards."""
