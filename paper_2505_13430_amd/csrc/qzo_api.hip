@@ -206,16 +206,32 @@ bool mid_route(const qzo_model* m, uint64_t M1) {
 // (7B widths, 33 / 57 tokens: 3.34 / 3.65 ms a pass against 3.60 / 3.92; OPT-1.3B, 57: 1.88 against 2.22).
 bool mid_single_pass(uint64_t M1) { return M1 > SKINNY_MAX_M; }
 
+// Row at which the second pass of a stacked forward starts.
+uint64_t stacked_pass_stride(const qzo_model* m, uint64_t M1) {
+  const bool tiles_of_256 = m->cfg.quant == 3 || (M1 > SKINNY_MAX_M_DUAL && !mid_route(m, M1));
+  return tiles_of_256 ? (M1 + 255) / 256 * 256 : M1;
+}
+uint64_t widest_row(const qzo_model_config& c) {
+  return std::max<uint64_t>({3ull * c.d_model, (c.arch == 0 ? 2ull : 1ull) * c.d_ffn});
+}
+
 // Whether qzo_step runs its two perturbed passes as one forward over 2 * batch sequences.  With at
-// most 32 tokens the few-token kernel reads the int4 weights once for both.  Beyond the few-token
-// kernel's range and as long as the fused kernel serves (at most 4096 tokens per pass), a launch of
+// most 32 tokens the few-token kernel reads the int4 weights once for both, on the route above mid_gemm_kernel does.
+// Beyond and as long as the fused kernel serves (at most 4096 tokens per pass), a launch of
 // the tile kernel holds both passes' token tiles, the second pass's with -eps: twice the tiles per
 // launch for a chip that such token counts do not fill, half the launches.  The second pass starts
 // on a tile boundary (stacked_pass_stride); the rows in between are padding (zeros at the embedding,
 // never read back).
+// NormalFloat-4 from 65 tokens per pass on: one expansion reads the indices once and writes both passes' matrices
+// (4.5 bytes per weight instead of two times 2.5), the plain GEMM's tiles take their pass's.  Whole steps at 7B
+// widths, separate -> stacked: 4 x 100 tokens 25.6 -> 24.4 ms, 4 x 256 36.1 -> 34.6, 8 x 256 55.9 -> 52.4; 1 x 16 16.5 ->
+// 17.4 (two token tiles of padding), hence the limit.  The same for int4, whose fused kernel does without the
+// expansion: 1.22 of the fused kernel's time at 1024 tokens, 1.05 at 2048, 0.99 at 3072, 1.00 at 4096.
 bool passes_stacked(const qzo_model* m, uint64_t M1) {
   const qzo_model_config& c = m->cfg;
-  if (!(c.quant == 0 || c.quant == 2) || m->dense_master || c.act_order) return false;
+  if (c.quant == 1 || m->dense_master || c.act_order) return false;
+  if (c.quant == 3)
+    return M1 > SKINNY_MAX_M && M1 <= STACK_TILE_MAX_M && (stacked_pass_stride(m, M1) + M1) * widest_row(c) * 2 < (1ull << 31);
   if (M1 <= SKINNY_MAX_M_DUAL || mid_route(m, M1)) return true;
   if (M1 <= SKINNY_MAX_M || M1 > STACK_TILE_MAX_M || m->int4_path == 2) return false;
   // Stacked, the fused kernel stays ahead of expand-then-multiply for a fifth more tokens than the
@@ -225,10 +241,6 @@ bool passes_stacked(const qzo_model* m, uint64_t M1) {
     for (int i = 0; i < 4; ++i)
       if (M1 * 5 >= (uint64_t)expand_min_m_int4(m->lin[i].N, m->lin[i].K) * 6) return false;
   return true;
-}
-// Row at which the second pass of a stacked forward starts.
-uint64_t stacked_pass_stride(const qzo_model* m, uint64_t M1) {
-  return M1 <= SKINNY_MAX_M_DUAL || mid_route(m, M1) ? M1 : (M1 + 255) / 256 * 256;
 }
 
 Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
@@ -286,10 +298,12 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   // and the NormalFloat-4 format at any token count (with its perturbed block scales, fp32)
   uint64_t ex = 0, sx = 0;
   for (int i = 0; i < 4; ++i) {
+    const uint64_t bytes = (uint64_t)m->lin[i].N * m->lin[i].K * 2;
     const bool expanded = c.quant == 3 || c.act_order || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK) ||
                           (int4 && m->int4_path != 1 && !stack &&
                            (m->int4_path == 2 || M1 >= expand_min_m_int4(m->lin[i].N, m->lin[i].K)));
-    if (expanded) ex = std::max<uint64_t>(ex, (uint64_t)m->lin[i].N * m->lin[i].K * 2);
+    if (expanded) ex = std::max(ex, bytes);
+    if (c.quant == 3 && stack) ex = std::max(ex, 2 * bytes);      // both passes' matrices
   }
   if (ex && c.quant != 1) sx = m->n_scales * 4;     // every perturbed scale of the model, fp32
   w.wexp = take(ex);
@@ -315,8 +329,7 @@ qzo_status check_batch(const qzo_model* m, const void* tok, uint32_t batch, uint
     const qzo_model_config& c = m->cfg;
     const uint64_t M1 = (uint64_t)batch * seq +
                         (passes_stacked(m, (uint64_t)batch * seq) ? stacked_pass_stride(m, (uint64_t)batch * seq) : 0);
-    const uint64_t widest = std::max<uint64_t>({3ull * c.d_model, (c.arch == 0 ? 2ull : 1ull) * c.d_ffn});
-    if (M1 * widest * 2 >= (1ull << 31))
+    if (M1 * widest_row(c) * 2 >= (1ull << 31))
       return fail(QZO_ERR_SHAPE, "batch*seq too large for this model: an activation tensor would exceed 2^31 bytes");
   }
   Workspace w = carve(m, batch, seq, nullptr);
@@ -377,7 +390,8 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
   }
   if (w.se) {   // some linear takes the expansion route: one launch perturbs every scale of the model
     ProfScope ps(PK_EXPAND, 0, st);
-    QZO_HIP(launch_perturbed_scales_all(m->arena, m->plan, seed_lo, seed_hi, eps_signed, w.se, st));
+    if (n_pass == 2) QZO_HIP(launch_scale_noise_all(m->arena, m->plan, seed_lo, seed_hi, w.se, st));
+    else QZO_HIP(launch_perturbed_scales_all(m->arena, m->plan, seed_lo, seed_hi, eps_signed, w.se, st));
   }
   {
     ProfScope ps(PK_OTHER, 0, st);
@@ -459,7 +473,12 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
         return launch_bf16_gemm(g, PLAIN_GEMM_PIPE, st);
       }
       if (c.quant == 3) {
-        // NormalFloat-4: table lookup and scaling once per weight, then a plain bf16 GEMM
+        // NormalFloat-4: table lookup and scaling once per weight (stacked passes: both matrices), then a plain bf16 GEMM
+        const bool pair = n_pass == 2;
+        if (pair) {
+          g.M = M; g.dual = 0; g.pass_stride = 0;
+          g.flip_row = P; g.w_flip = (uint64_t)g.N * g.K * 2;
+        }
         const bool split = w.split && tile_ksplit(g.M, g.N, g.K, nullptr) > 1;
         int order = ((epi & EPI_SWIGLU) && !split) ? ROW_ORDER_SWIGLU : ROW_ORDER_NATURAL;
         if (epi == EPI_ROPE && !split && (dh == 64 || (dh == 128 && g.N % 256 == 0))) {   // as for int4 below
@@ -468,8 +487,10 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
           rope_fused = true;
         }
         {
-          ProfScope pe(PK_EXPAND, 2.5 * (double)g.N * g.K, st);
-          hipError_t e = launch_expand_nf4_from(g.w, w.se + layer_off + m->lin[li].s_off, g.N, g.K, order, w.wexp, st);
+          ProfScope pe(PK_EXPAND, (pair ? 4.5 : 2.5) * (double)g.N * g.K, st);
+          float* const se = w.se + layer_off + m->lin[li].s_off;
+          hipError_t e = pair ? launch_expand_nf4_pair(g.w, g.s, se, eps_signed, g.N, g.K, order, w.wexp, st)
+                              : launch_expand_nf4_from(g.w, se, g.N, g.K, order, w.wexp, st);
           if (e != hipSuccess) return e;
         }
         g.w = w.wexp; g.s = nullptr; g.skinny_ws = nullptr; g.split_ws = (split || (w.split && tile_tail_cols(g.M, g.N, g.K, g.epi))) ? w.split : nullptr;

@@ -100,6 +100,8 @@ __global__ __launch_bounds__(256) void perturbed_scales_kernel(const bf16_t* __r
 
 // The same for every scale of a model in one launch, laid out like the scale arena (the update's
 // plan: grid = (workgroups per layer, layers), a thread owns the eight scales of one counter).
+// NOISE: z itself instead, for the expansions that write both passes' matrices.
+template <bool NOISE>
 __global__ __launch_bounds__(256) void perturbed_scales_all_kernel(const bf16_t* __restrict__ arena, UpdPlan plan,
                                                                    uint32_t seed_lo, uint32_t seed_hi,
                                                                    float eps_signed, float* __restrict__ se) {
@@ -122,11 +124,17 @@ __global__ __launch_bounds__(256) void perturbed_scales_all_kernel(const bf16_t*
     // (4-byte aligned accesses: rows of 86 or 108 groups start on a dword only)
     struct a4_u32x4 { uint32_t x, y, z, w; } __attribute__((packed, aligned(4)));
     struct a4_f32x4 { float x, y, z, w; } __attribute__((packed, aligned(4)));
-    const a4_u32x4 v = *reinterpret_cast<const a4_u32x4*>(arena + base);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
     float o[8];
+    a4_u32x4 v = {0u, 0u, 0u, 0u};
+    if (!NOISE) v = *reinterpret_cast<const a4_u32x4*>(arena + base);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
+      if (NOISE) {
+        o[2 * j] = z[2 * j];
+        o[2 * j + 1] = z[2 * j + 1];
+        continue;
+      }
       o[2 * j] = __builtin_fmaf(eps_signed, z[2 * j], scale_to_f32(w[j] & 0xffffu, fp16));
       o[2 * j + 1] = __builtin_fmaf(eps_signed, z[2 * j + 1], scale_to_f32(w[j] >> 16, fp16));
     }
@@ -138,14 +146,25 @@ __global__ __launch_bounds__(256) void perturbed_scales_all_kernel(const bf16_t*
 #pragma unroll
   for (int j = 0; j < 8; ++j)
     if ((uint32_t)j < nv)
-      se[base + j] = __builtin_fmaf(eps_signed, z[j], scale_to_f32(arena[base + j], fp16));
+      se[base + j] = NOISE ? z[j] : __builtin_fmaf(eps_signed, z[j], scale_to_f32(arena[base + j], fp16));
+}
+
+
+// 8 weights of a row: value times scale, rounded once, 16 bytes
+__device__ __forceinline__ void store_scaled(const float v[8], float sc, uint4* out) {
+  *out = make_uint4(pack_bf16x2(sc * v[0], sc * v[1]), pack_bf16x2(sc * v[2], sc * v[3]),
+                    pack_bf16x2(sc * v[4], sc * v[5]), pack_bf16x2(sc * v[6], sc * v[7]));
 }
 
 // bf16 [N,K] from the indices and the perturbed scales: a thread turns one dword (eight
 // indices, k = 8c .. 8c+7, lowest nibble first) into 16 bytes; the level table sits in LDS
 // (16 words in 16 banks: any mix of indices is served without a conflict).
+// PAIR: both passes' matrices from one read of the indices (the second one N K elements further on); se holds z
+// and the perturbed scales are formed here, by the same fma.
+template <bool PAIR>
 __global__ __launch_bounds__(256) void expand_nf4_kernel(const uint32_t* __restrict__ q,
-                                                         const float* __restrict__ se, uint32_t N,
+                                                         const float* __restrict__ se,
+                                                         const bf16_t* __restrict__ s, float eps, uint32_t N,
                                                          uint32_t K, int swiglu, uint4* __restrict__ out) {
   __shared__ float lut[16];
   if (threadIdx.x < 16) lut[threadIdx.x] = NF4_LEVELS_DEV[threadIdx.x];
@@ -154,12 +173,13 @@ __global__ __launch_bounds__(256) void expand_nf4_kernel(const uint32_t* __restr
   if (kc >= nc) return;
   const uint32_t gn = expand_source_row(p, N, swiglu);
   const uint32_t w = q[(uint64_t)gn * nc + kc];
-  const float sc = se[(uint64_t)gn * (K >> 6) + (kc >> 3)];
-  uint32_t o[4];
+  const uint64_t gi = (uint64_t)gn * (K >> 6) + (kc >> 3);
+  const float sc = PAIR ? __builtin_fmaf(eps, se[gi], bf16_to_f32(s[gi])) : se[gi];
+  float v[8];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    o[j] = pack_bf16x2(sc * lut[(w >> (8 * j)) & 15u], sc * lut[(w >> (8 * j + 4)) & 15u]);
-  out[(uint64_t)p * nc + kc] = make_uint4(o[0], o[1], o[2], o[3]);
+  for (int i = 0; i < 8; ++i) v[i] = lut[(w >> (4 * i)) & 15u];
+  store_scaled(v, sc, out + (uint64_t)p * nc + kc);
+  if (PAIR) store_scaled(v, __builtin_fmaf(-eps, se[gi], bf16_to_f32(s[gi])), out + ((uint64_t)N + p) * nc + kc);
 }
 
 // int4 groups of 128 (Eq. 4-5): W = (s + sigma*eps*z)[n, k/128] * (u - zp), zp = 8 without a
@@ -220,7 +240,15 @@ hipError_t launch_perturbed_scales_all(const void* arena, const UpdPlan& plan, u
                                        float eps_signed, float* se_all, hipStream_t st) {
   dim3 grid(plan.wgs_per_layer, plan.n_layers);
   if (grid.x == 0 || grid.y == 0) return hipSuccess;
-  perturbed_scales_all_kernel<<<grid, 256, 0, st>>>((const bf16_t*)arena, plan, seed_lo, seed_hi, eps_signed, se_all);
+  perturbed_scales_all_kernel<false><<<grid, 256, 0, st>>>((const bf16_t*)arena, plan, seed_lo, seed_hi, eps_signed, se_all);
+  return hipGetLastError();
+}
+
+hipError_t launch_scale_noise_all(const void* arena, const UpdPlan& plan, uint32_t seed_lo, uint32_t seed_hi,
+                                  float* z_all, hipStream_t st) {
+  dim3 grid(plan.wgs_per_layer, plan.n_layers);
+  if (grid.x == 0 || grid.y == 0) return hipSuccess;
+  perturbed_scales_all_kernel<true><<<grid, 256, 0, st>>>((const bf16_t*)arena, plan, seed_lo, seed_hi, 0.0f, z_all);
   return hipGetLastError();
 }
 
@@ -235,8 +263,16 @@ hipError_t launch_expand_int4_from(const void* q, const float* se, const void* z
 hipError_t launch_expand_nf4_from(const void* q, const float* se, uint32_t N, uint32_t K, int swiglu,
                                   void* out_bf16, hipStream_t st) {
   if (N == 0) return hipSuccess;
-  expand_nf4_kernel<<<dim3(N, ((K >> 3) + 255) / 256), 256, 0, st>>>((const uint32_t*)q, se, N, K, swiglu,
-                                                                   (uint4*)out_bf16);
+  expand_nf4_kernel<false><<<dim3(N, ((K >> 3) + 255) / 256), 256, 0, st>>>((const uint32_t*)q, se, nullptr, 0.0f, N, K,
+                                                                          swiglu, (uint4*)out_bf16);
+  return hipGetLastError();
+}
+
+hipError_t launch_expand_nf4_pair(const void* q, const void* s_bf16, const float* z, float eps, uint32_t N, uint32_t K,
+                                  int order, void* out_bf16, hipStream_t st) {
+  if (N == 0) return hipSuccess;
+  expand_nf4_kernel<true><<<dim3(N, ((K >> 3) + 255) / 256), 256, 0, st>>>((const uint32_t*)q, z, (const bf16_t*)s_bf16,
+                                                                         eps, N, K, order, (uint4*)out_bf16);
   return hipGetLastError();
 }
 
@@ -250,8 +286,8 @@ hipError_t launch_expand_nf4(const void* q, const void* s_bf16, uint32_t N, uint
       (const bf16_t*)s_bf16, N, G, row_base, seed_lo, seed_hi, eps_signed, se_scratch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  expand_nf4_kernel<<<dim3(N, ((K >> 3) + 255) / 256), 256, 0, st>>>((const uint32_t*)q, se_scratch, N, K,
-                                                                   swiglu, (uint4*)out_bf16);
+  expand_nf4_kernel<false><<<dim3(N, ((K >> 3) + 255) / 256), 256, 0, st>>>((const uint32_t*)q, se_scratch, nullptr, 0.0f,
+                                                                          N, K, swiglu, (uint4*)out_bf16);
   return hipGetLastError();
 }
 

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   const i32x4 rx4 = {(int)(uint32_t)(uintptr_t)a.x, (int)(uint32_t)((uintptr_t)a.x >> 32),
                      (int)((uint64_t)a.M * K * 2), 0x00020000};
-  const i32x4 rw4 = {(int)(uint32_t)(uintptr_t)a.w, (int)(uint32_t)((uintptr_t)a.w >> 32),
+  i32x4 rw4 = {(int)(uint32_t)(uintptr_t)a.w, (int)(uint32_t)((uintptr_t)a.w >> 32),
                      (int)((uint64_t)a.N * K * 2), 0x00020000};
   const uint32_t lds_wave = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
                             __builtin_amdgcn_readfirstlane(wave) * 1024u;
@@ -206,7 +206,12 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
       xo[i] = (min((TM) * BM + row, a.M - 1) * K + c * 8) * 2;                               \
       if (!ROWMAP) wo[i] = (min((TN) * BN + row, a.N - 1) * K + c * 8) * 2;                  \
     }                                                                                        \
-    eps_tile = (a.flip_row && (TM) * BM >= a.flip_row) ? -a.eps_signed : a.eps_signed;       \
+    const bool second_ = a.flip_row && (TM) * BM >= a.flip_row;                              \
+    eps_tile = second_ ? -a.eps_signed : a.eps_signed;                                       \
+    if (DTL) {                         /* plain GEMM: the second pass has a matrix of its own */ \
+      const uint64_t wb_ = (uint64_t)(uintptr_t)a.w + (second_ ? a.w_flip : 0u);             \
+      rw4[0] = (int)(uint32_t)wb_; rw4[1] = (int)(uint32_t)(wb_ >> 32);                      \
+    }                                                                                        \
     if (ROWMAP) {                                                                            \
       /* fused SwiGLU: the tile's rows are 4 x (32 gate rows, 32 up rows of the same   */      \
       /* features), so a lane's two accumulators hold gate and up of one feature      */      \
@@ -772,7 +777,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
     const bool rotate = na_base < d2;            // a wavefront's 64 columns lie within one third of qkv
     auto tb_of = [&](int u) {
       const uint32_t m = m0 + wm * 128 + (u >> 1) * 32 + frow;
-      const uint32_t pos = min(m, a.M - 1) % a.rope_S;
+      const uint32_t mr = min(m, a.M - 1), pos = (mr - (mr >= a.flip_row ? a.flip_row : 0u)) % a.rope_S;
       return reinterpret_cast<const float4*>(table + (uint64_t)pos * half + idx_base + (2u * (u & 1) + fhalf) * 8u);
     };
     float4 tn[4] = {};
@@ -1102,6 +1107,7 @@ hipError_t launch_bf16_gemm(const GemmArgs& a, int pipe, hipStream_t st) {
   // the 7B step: gate/up 1088 us with the 512-thread kernel, 1130 us with the other)
   if (pipe == 2 && g.ksplit == 1 && !(g.epi & EPI_SWIGLU)) return launch_bf16_gemm_wide(g, st);
   const uint32_t wgs = gemm_workgroups(a.M, ((a.N + BN - 1) / BN) * g.ksplit * BN);
+  if (g.flip_row && pipe != 2) return hipErrorInvalidValue;    // only the direct-to-LDS kernels know two matrices
   if (pipe == 2)         // K split over workgroups: both operand tiles straight from memory into the LDS, 512 threads
     gemm_kernel<1, false, 4, 3><<<wgs, 512, LDS_BYTES + 1024, st>>>(g, ce);
   else if (pipe == 1)    // staged through registers, explicit issue order

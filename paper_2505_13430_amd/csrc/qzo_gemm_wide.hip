@@ -45,7 +45,7 @@ __global__ __launch_bounds__(256, 1) void wide_gemm_kernel(GemmArgs a) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   const i32x4 rx4 = {(int)(uint32_t)(uintptr_t)a.x, (int)(uint32_t)((uintptr_t)a.x >> 32),
                      (int)((uint64_t)a.M * K * 2), 0x00020000};
-  const i32x4 rw4 = {(int)(uint32_t)(uintptr_t)a.w, (int)(uint32_t)((uintptr_t)a.w >> 32),
+  i32x4 rw4 = {(int)(uint32_t)(uintptr_t)a.w, (int)(uint32_t)((uintptr_t)a.w >> 32),
                      (int)((uint64_t)a.N * K * 2), 0x00020000};
   const uint32_t ldy = a.ldy ? a.ldy : a.N;        // row stride of y and resid (a column block of a wider matrix)
   const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
@@ -64,6 +64,9 @@ __global__ __launch_bounds__(256, 1) void wide_gemm_kernel(GemmArgs a) {
       xo[i] = (min((TM) * BM + row, a.M - 1) * K + c * 8) * 2;                               \
       wo[i] = (min((TN) * BN + row, a.N - 1) * K + c * 8) * 2;                               \
     }                                                                                        \
+    /* stacked passes: the second one has a matrix of its own */                             \
+    const uint64_t wb_ = (uint64_t)(uintptr_t)a.w + (a.flip_row && (TM) * BM >= a.flip_row ? a.w_flip : 0u); \
+    rw4[0] = (int)(uint32_t)wb_; rw4[1] = (int)(uint32_t)(wb_ >> 32);                        \
   } while (0)
   QW_TILE_PTRS(tile_m, tile_n);
 #define QW_DTL_ONE(KT, STAGE, D)                                                             \
@@ -208,7 +211,7 @@ __global__ __launch_bounds__(256, 1) void wide_gemm_kernel(GemmArgs a) {
         const int i = u >> 2, jp = (u >> 1) & 1, bp = u & 1;
         const uint32_t wq = wn * 2u + jp;
         const uint32_t idx_base = half == 64u ? (wq & 1u) * 32u : 0u;
-        const uint32_t pos = min(mrow + i * 32, a.M - 1) % a.rope_S;
+        const uint32_t mr = min(mrow + i * 32, a.M - 1), pos = (mr - (mr >= a.flip_row ? a.flip_row : 0u)) % a.rope_S;
         return reinterpret_cast<const float4*>(table + (uint64_t)pos * half + idx_base + (2u * bp + fhalf) * 8u);
       };
       float4 tn[4];

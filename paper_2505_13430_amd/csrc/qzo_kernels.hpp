@@ -56,7 +56,9 @@ struct GemmArgs {
                         // [M,2M) -eps_signed (few-token path: M <= 32; tile path: see pass_stride)
   uint32_t pass_stride; // dual, tile path: the second pass starts at this row (a multiple of 256 >= M; x, y, resid
                         // hold pass_stride + M rows, the rows in between are padding); 0: at row M
-  uint32_t flip_row;    // set by the launcher for the tile kernel: rows from here on take -eps_signed (0: none)
+  uint32_t flip_row;    // tile kernels: rows from here on (a multiple of 256) take -eps_signed (0: none); set by the
+                        // launcher of the fused kernel, by the caller of the plain bf16 GEMM
+  uint64_t w_flip;      // plain bf16 GEMM with flip_row: bytes from w to the matrix of the second pass
   uint32_t M, N, K;
   uint32_t ldy;         // row stride of y and resid in elements when the call covers a column block of a wider
                         // matrix (0: N); plain epilogues only (bias, residual, ReLU)
@@ -144,6 +146,12 @@ hipError_t launch_expand_int4_from(const void* q, const float* se, const void* z
                                    uint32_t N, uint32_t K, int swiglu, void* out_bf16, hipStream_t st);
 hipError_t launch_expand_nf4_from(const void* q, const float* se, uint32_t N, uint32_t K, int swiglu,
                                   void* out_bf16, hipStream_t st);
+// Stacked passes (NormalFloat-4): the same launch over the model leaves z itself, and an expansion reads its linear's
+// scales s and z and writes both passes' matrices, +eps at out_bf16 and -eps N*K elements further on.
+hipError_t launch_scale_noise_all(const void* arena, const UpdPlan& plan, uint32_t seed_lo, uint32_t seed_hi,
+                                  float* z_all, hipStream_t st);
+hipError_t launch_expand_nf4_pair(const void* q, const void* s_bf16, const float* z, float eps, uint32_t N, uint32_t K,
+                                  int order, void* out_bf16, hipStream_t st);
 // Tokens per pass from which an int4 linear [N,K] is expanded first.  The expansion costs two short
 // launches (about 8 us) plus 2.5 bytes per weight at about 4.5 TB/s; the fused kernel needs about 13.6 %
 // more time than the plain GEMM on the expanded weights, a time that grows with the tokens

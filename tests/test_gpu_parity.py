@@ -462,6 +462,27 @@ def test_stacked_tile_passes_match_separate_passes(oracle, name, batch, seq):
     dm.close()
 
 
+@pytest.mark.parametrize("name,batch,seq", [("tiny", 3, 40), ("tiny_opt", 2, 64), ("long_llama", 1, 300),
+                                            ("long_ragged", 2, 300)])
+def test_nf4_stacked_passes_match_separate_passes(oracle, name, batch, seq):
+    """From 65 tokens on a NormalFloat-4 step runs both passes as one forward: one expansion writes both matrices,
+    the GEMM's token tiles take their pass's, the rotary positions of the second pass count from its first row
+    (padding: 120 -> 256, 300 -> 512, 600 -> 768).  Same tiles, same order of sums as in separate passes but for the
+    K split: within the 16-bit activations' noise of them (2e-3 as for int4), and of the oracle (2e-2)."""
+    base, _ = _case(name)
+    shape = dict(base, batch=batch, seq=seq)
+    om, dm = _models(oracle, shape, 1234, 4.0, nf4=True)
+    tok = synth.tokens(shape, 5678)
+    got = qb.read_step_result(dm.step(_dev(tok), 21, 1e-3, 0.0, 100.0))
+    want = oracle.qzo_step(om, tok, seed=21, eps=1e-3, eta=0.0, Cthr=100.0)
+    for k, sign in (("loss_plus", 1), ("loss_minus", -1)):
+        single = float(dm.forward_loss(_dev(tok), 21, 1e-3, sign).item())
+        assert abs(got[k] - single) <= 2e-3 * single, (k, got[k], single)
+        assert abs(got[k] - want[k]) <= 2e-2 * want[k], (k, got[k], want[k])
+    assert got["loss_plus"] != got["loss_minus"]
+    dm.close()
+
+
 def test_step_special_cases(oracle):
     shape = synth.SHAPES["tiny"]
     om, dm = _models(oracle, shape, 1234)
