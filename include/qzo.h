@@ -170,17 +170,18 @@ qzo_status qzo_forward_loss(qzo_model* m, const int32_t* tokens_dev, uint32_t ba
  * receives the scalars.  clip must be >= 0.  A non-finite d leaves the scales
  * untouched and sets result.status = QZO_ERR_NONFINITE.
  * With int4 weights (no joint mode, no group index per column) the two forwards run as one
- * forward over 2*batch sequences when batch*seq <= 32 (the few-token kernel then reads the
- * weights once for both passes; losses bit-identical to two qzo_forward_loss calls), and above
- * that up to the token count from which the model's linears take the expand-then-multiply
- * route (about 3200 at Llama-2-7B widths; at most 4096; never when that route is forced).
- * Up to 128 tokens per pass (192 or 256 where a layer's linears hold at most 2^28 or 2^26
- * weights) the launches work in tiles of 32 tokens, each of one pass; beyond, a launch of the
- * 256-row tile kernel holds the token tiles of both passes, the second pass's starting on a
- * tile boundary (padding rows in between).  Losses then equal two qzo_forward_loss calls within
- * the 16-bit activations' noise, the K split of a linear being a function of the number of token
- * tiles.  With a forced route (1) up to 64 tokens as above, from 65 on the 256-row tiles.
- * qzo_workspace_bytes accounts for it.
+ * forward over 2*batch sequences.  Up to 32 tokens the few-token kernel reads the weights once
+ * for both: losses bit-identical to two qzo_forward_loss calls.  Above 64, up
+ * to the token count from which the model's linears take the expand-then-multiply route (about
+ * 3200 at Llama-2-7B widths; at most 4096; never when that route is forced), a launch of the
+ * tile kernel holds the token tiles of both passes, the second pass's with -eps and starting
+ * on a 256-row tile boundary (padding rows in between); losses equal to two qzo_forward_loss
+ * calls within the 16-bit activations' noise, the K split of a linear being a function of the
+ * number of token tiles.  Zero-point models with fp16 scales (33 to 128 tokens; up to 192 or
+ * 256 where a layer's linears hold at most 2^28 or 2^26 weights) and NormalFloat-4 models (up
+ * to 384 or 512 tokens) work in tiles of 32 tokens, each of one pass, with the same agreement;
+ * NormalFloat-4 models beyond, up to 4096 tokens, in 256-row tiles on both passes' expanded
+ * matrices.  qzo_workspace_bytes accounts for it.
  */
 qzo_status qzo_step(qzo_model* m, const int32_t* tokens_dev, uint32_t batch, uint32_t seq,
                     uint64_t seed, float eps, float eta, float clip, void* workspace_dev,

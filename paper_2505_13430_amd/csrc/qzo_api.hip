@@ -184,31 +184,43 @@ void table_layout(const qzo_model_config& c, std::vector<uint64_t>& need, std::v
   b16(V * d);
 }
 
-// Token counts per pass that take mid_gemm_kernel (int4, beyond the few-token kernel's stacked range).  Its time grows
-// by tiles of 32 tokens, the tile kernel's by tiles of 256, and the wider the layer the better the tile kernel fills
-// the chip.  Whole steps, mid_gemm_kernel's time over the other route's: 7B widths 0.65 (33-96 tokens), 0.85 (132), 0.90
-// (192), 1.00 (224), 1.03 (256); 13B widths 0.66 (40), 0.73 (96), 0.98 (132), 1.2 (256); OPT-1.3B widths 0.62 (40),
-// 0.81 (132), 0.90 (256); smaller models 0.53-0.97 up to 256.  A route that the caller chose stays: 1 (fused) keeps
-// the tile kernel beyond the few-token kernel's 64 tokens.
+// Token counts per pass that take mid_gemm_kernel: NormalFloat-4, and zero-point int4 with fp16 scales beyond the
+// few-token kernel's stacked range.
+//   Its time grows by tiles of 32 tokens, the tile kernel's by tiles of 256, and the wider the layer the better the tile
+// kernel fills the chip.  Whole steps of zero-point models, mid_gemm_kernel's time over the other routes': 7B widths 0.65
+// (33-96 tokens), 0.85 (132), 0.90 (192), 1.00 (224), 1.03 (256); 13B widths 0.66 (40), 0.73 (96), 0.98 (132), 1.2
+// (256); OPT-1.3B widths 0.62 (40), 0.81 (132), 0.90 (256); smaller models 0.53-0.97 up to 256.  A route that the
+// caller chose stays: 1 (fused) keeps the tile kernel beyond the few-token kernel's 64 tokens.
+//   NormalFloat-4 has no other fused kernel; against the expansion: 7B widths 0.25 (1-16 tokens), 0.31 (57), 0.40 (96),
+// 0.50 (132-192), 0.67 (256), 0.86 (400), 0.90 (512), 0.86 (640), 0.98 (768); 13B widths 0.31 (33), 0.58 (192), 0.90
+// (400); OPT-1.3B widths 0.40 (33), 0.60 (120), 0.91 (512), 1.13 (768).
+//   int4 with a bf16 arena keeps the routes whose sums its losses have always had: another order of sums moves the losses
+// by the activations' 16-bit noise, and every step then leaves the scales whose update lies near half a bf16 step (2^-8
+// of the value) a whole step apart from an earlier run's.  (fp16 scales have an eighth of that step; NormalFloat-4's
+// are ten times larger, an update is far below half of theirs.)
 bool mid_route(const qzo_model* m, uint64_t M1) {
   const qzo_model_config& c = m->cfg;
-  if (!(c.quant == 0 || c.quant == 2) || c.act_order || M1 <= SKINNY_MAX_M_DUAL) return false;
-  if (m->int4_path == 2 || (m->int4_path == 1 && M1 > SKINNY_MAX_M)) return false;
+  const bool nf4 = c.quant == 3;
+  if (!nf4 && (c.quant != 2 || !c.scale_fp16 || c.act_order)) return false;
+  if (!nf4 && (M1 <= SKINNY_MAX_M_DUAL || m->int4_path == 2 || (m->int4_path == 1 && M1 > SKINNY_MAX_M))) return false;
   uint64_t weights = 0;
   for (int i = 0; i < 4; ++i) weights += (uint64_t)m->lin[i].N * m->lin[i].K;
-  if (M1 > (weights <= (1u << 26) ? 256u : (weights <= (1u << 28) ? 192u : 128u))) return false;
+  const uint32_t most = nf4 ? (weights <= (1u << 28) ? 512u : 384u)
+                            : (weights <= (1u << 26) ? 256u : (weights <= (1u << 28) ? 192u : 128u));
+  if (M1 > most) return false;
   for (int i = 0; i < 4; ++i)
-    if (!mid_fits((uint32_t)M1, m->lin[i].N, m->lin[i].K, true)) return false;
+    if (!mid_fits((uint32_t)M1, m->lin[i].N, m->lin[i].K, true, nf4)) return false;
   return true;
 }
 
 // One pass on its own (qzo_forward_loss, joint mode): the few-token kernel is the faster one over its whole range
 // (7B widths, 33 / 57 tokens: 3.34 / 3.65 ms a pass against 3.60 / 3.92; OPT-1.3B, 57: 1.88 against 2.22).
-bool mid_single_pass(uint64_t M1) { return M1 > SKINNY_MAX_M; }
+// NormalFloat-4 has mid_gemm_kernel only (16 tokens: 3.9 ms a pass, expanded 8.1).
+bool mid_single_pass(const qzo_model* m, uint64_t M1) { return m->cfg.quant == 3 || M1 > SKINNY_MAX_M; }
 
 // Row at which the second pass of a stacked forward starts.
 uint64_t stacked_pass_stride(const qzo_model* m, uint64_t M1) {
-  const bool tiles_of_256 = m->cfg.quant == 3 || (M1 > SKINNY_MAX_M_DUAL && !mid_route(m, M1));
+  const bool tiles_of_256 = !mid_route(m, M1) && (m->cfg.quant == 3 || M1 > SKINNY_MAX_M_DUAL);
   return tiles_of_256 ? (M1 + 255) / 256 * 256 : M1;
 }
 uint64_t widest_row(const qzo_model_config& c) {
@@ -222,16 +234,15 @@ uint64_t widest_row(const qzo_model_config& c) {
 // launch for a chip that such token counts do not fill, half the launches.  The second pass starts
 // on a tile boundary (stacked_pass_stride); the rows in between are padding (zeros at the embedding,
 // never read back).
-// NormalFloat-4 from 65 tokens per pass on: one expansion reads the indices once and writes both passes' matrices
+// NormalFloat-4 beyond mid_gemm_kernel's range: one expansion reads the indices once and writes both passes' matrices
 // (4.5 bytes per weight instead of two times 2.5), the plain GEMM's tiles take their pass's.  Whole steps at 7B
-// widths, separate -> stacked: 4 x 100 tokens 25.6 -> 24.4 ms, 4 x 256 36.1 -> 34.6, 8 x 256 55.9 -> 52.4; 1 x 16 16.5 ->
-// 17.4 (two token tiles of padding), hence the limit.  The same for int4, whose fused kernel does without the
+// widths, separate -> stacked: 4 x 256 tokens 36.1 -> 34.6 ms, 8 x 256 55.9 -> 52.4.  The same for int4, whose fused kernel does without the
 // expansion: 1.22 of the fused kernel's time at 1024 tokens, 1.05 at 2048, 0.99 at 3072, 1.00 at 4096.
 bool passes_stacked(const qzo_model* m, uint64_t M1) {
   const qzo_model_config& c = m->cfg;
   if (c.quant == 1 || m->dense_master || c.act_order) return false;
   if (c.quant == 3)
-    return M1 > SKINNY_MAX_M && M1 <= STACK_TILE_MAX_M && (stacked_pass_stride(m, M1) + M1) * widest_row(c) * 2 < (1ull << 31);
+    return mid_route(m, M1) || (M1 <= STACK_TILE_MAX_M && (stacked_pass_stride(m, M1) + M1) * widest_row(c) * 2 < (1ull << 31));
   if (M1 <= SKINNY_MAX_M_DUAL || mid_route(m, M1)) return true;
   if (M1 <= SKINNY_MAX_M || M1 > STACK_TILE_MAX_M || m->int4_path == 2) return false;
   // Stacked, the fused kernel stays ahead of expand-then-multiply for a fifth more tokens than the
@@ -280,13 +291,13 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   uint64_t mw = 0;
   if (mid)
     for (int i = 0; i < 4; ++i)
-      for (int dual = mid_single_pass(M1) ? 0 : 1; dual < (stack ? 2 : 1); ++dual)
-        mw = std::max<uint64_t>(mw, mid_ws_floats((uint32_t)M1, m->lin[i].N, m->lin[i].K, dual != 0));
+      for (int dual = mid_single_pass(m, M1) ? 0 : 1; dual < (stack ? 2 : 1); ++dual)
+        mw = std::max<uint64_t>(mw, mid_ws_floats((uint32_t)M1, m->lin[i].N, m->lin[i].K, dual != 0, c.quant == 3));
   w.mid = (float*)take(mw * 4);
   if (mw == 0) w.mid = nullptr;
   // more tokens than that but still too few output tiles for the chip: split-K partial sums
   uint64_t sp = 0;
-  if ((M1 > SKINNY_MAX_M && int4 && !mid) || c.act_order || c.quant == 3 || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK))
+  if ((M1 > SKINNY_MAX_M && int4 && !mid) || c.act_order || (c.quant == 3 && !mid) || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK))
     for (int i = 0; i < 4; ++i) {
       sp = std::max<uint64_t>(sp, tile_split_ws_floats((uint32_t)M, m->lin[i].N, m->lin[i].K));
       // a single pass (qzo_forward_loss) of a batch whose step stacks its two passes
@@ -299,11 +310,11 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   uint64_t ex = 0, sx = 0;
   for (int i = 0; i < 4; ++i) {
     const uint64_t bytes = (uint64_t)m->lin[i].N * m->lin[i].K * 2;
-    const bool expanded = c.quant == 3 || c.act_order || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK) ||
+    const bool expanded = (c.quant == 3 && !mid) || c.act_order || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK) ||
                           (int4 && m->int4_path != 1 && !stack &&
                            (m->int4_path == 2 || M1 >= expand_min_m_int4(m->lin[i].N, m->lin[i].K)));
     if (expanded) ex = std::max(ex, bytes);
-    if (c.quant == 3 && stack) ex = std::max(ex, 2 * bytes);      // both passes' matrices
+    if (c.quant == 3 && stack && !mid) ex = std::max(ex, 2 * bytes);      // both passes' matrices
   }
   if (ex && c.quant != 1) sx = m->n_scales * 4;     // every perturbed scale of the model, fp32
   w.wexp = take(ex);
@@ -416,8 +427,8 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
   (void)other;
   bool rope_fused = false;     // set by a qkv linear whose GEMM applied the rotary embedding itself
   // few-token linears take the block sums of their input from its producer
-  float* const mid_ws = n_pass == 2 || mid_single_pass(M1) ? w.mid : nullptr;
-  const bool few = mid_ws || (w.skinny && M1 <= SKINNY_MAX_M && (c.quant == 0 || c.quant == 2) && !c.act_order);
+  float* const mid_ws = n_pass == 2 || mid_single_pass(m, M1) ? w.mid : nullptr;
+  const bool few = (mid_ws && c.quant != 3) || (w.skinny && M1 <= SKINNY_MAX_M && (c.quant == 0 || c.quant == 2) && !c.act_order);
   float* const xs_a = few ? w.xs_a : nullptr;
   for (uint32_t l = 0; l < c.n_layers; ++l) {
     const qzo_buf* T = &m->T[m->first_layer_tensor + (size_t)l * m->tensors_per_layer];
@@ -448,10 +459,11 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       g.skinny_ws = mid_ws ? nullptr : w.skinny;
       g.split_ws = w.split;
       g.mid_ws = mid_ws;
+      g.nf4 = c.quant == 3;
       if (few) {     // the few-token kernel takes the block sums of its input from the kernel that wrote it
         g.xsum = (li == 0 || li == 2) ? w.xs_a : (li == 3 ? w.xs_act : nullptr);
         g.xsum_out = li == 2 ? w.xs_act : nullptr;
-        if (mid_ws && li == 1) {      // the attention output's block sums, where the norm's were
+        if (mid_ws && li == 1 && c.quant != 3) {      // the attention output's block sums, where the norm's were
           hipError_t e = launch_block_sums(x, M, g.K, w.xs_a, st);
           if (e != hipSuccess) return e;
           g.xsum = w.xs_a;
@@ -472,7 +484,7 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
         ProfScope ps(PK_W4GEMM, 2.0 * Mreal * (double)g.N * g.K, st);
         return launch_bf16_gemm(g, PLAIN_GEMM_PIPE, st);
       }
-      if (c.quant == 3) {
+      if (c.quant == 3 && !mid_ws) {
         // NormalFloat-4: table lookup and scaling once per weight (stacked passes: both matrices), then a plain bf16 GEMM
         const bool pair = n_pass == 2;
         if (pair) {

@@ -67,6 +67,7 @@ struct GemmArgs {
   float eps_signed;
   uint32_t epi;
   uint32_t s_fp16;      // int4 formats: s holds fp16 instead of bf16
+  uint32_t nf4;         // mid_gemm_kernel: w holds NormalFloat-4 indices, s bf16 [N,K/64], no block sums
   // Few-token path: block sums X[g][row] = sum of x[row, 128 g .. 128 g + 127] (fp32, [K/128][rows], rows = M or
   // 2 M when dual), delivered by the kernel that wrote x (null: the kernel sums them itself), and the same for
   // the output y of the K-slice reduction ([N_out/128][rows], N_out % 128 == 0; null: not wanted).
@@ -96,9 +97,9 @@ struct MidPlan {
   uint32_t mt, Z, U, W, tot;           // Z: token blocks per row block; U: pairs of groups of K; tot = items * U
   uint32_t T, Tp, rows, slots;         // token tiles of 32 (all, of one pass), rows of x, most slices of an item
 };
-MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual);
-uint64_t mid_ws_floats(uint32_t M, uint32_t N, uint32_t K, bool dual);
-bool mid_fits(uint32_t M, uint32_t N, uint32_t K, bool dual);
+MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4);
+uint64_t mid_ws_floats(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4);
+bool mid_fits(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4);
 // Range that holds unit i: ranges are [w tot / W, (w+1) tot / W).
 __host__ __device__ inline uint32_t mid_range_of(uint32_t i, uint32_t W, uint32_t tot) { return ((i + 1) * W - 1) / tot; }
 __host__ __device__ inline uint32_t mid_slices(const MidPlan& p, uint32_t item) {

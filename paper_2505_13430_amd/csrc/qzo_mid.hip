@@ -18,6 +18,13 @@
 // Work is split evenly whatever the shape: items (row block, token block) x pairs of groups are cut into one
 // contiguous range per compute unit; an item that several ranges touch is summed by the reduction kernel in order.
 //
+// NormalFloat-4 (FMT_NF4): indices become bf16 levels by byte permutations (33 instructions for 8 weights, see
+// unpack8_nf4), a group holds two blocks of 64 with a scale each: the k-steps 0-3 and 4-7, whose sums are rescaled
+// apart; the levels are signed, so there is no correction.  Against expand-then-multiply, which writes and reads 2
+// bytes per weight and pass: 1 x 16 tokens at 7B widths 16.6 -> 4.2 ms per step, 1 x 57 17.3 -> 5.3, 4 x 33 19.8 -> 9.9,
+// 4 x 100 25.9 -> 21.0, 8 x 64 27.3 -> 22.2.  Vector instructions bound it (about 450 per group and wavefront with
+// four tiles against 32 MFMAs).
+//
 // What bounds it: at 57 tokens per pass (4096 x 4096 .. 22016) a launch takes 16-43 us, of which about 10 us do not
 // depend on the work (start of a kernel whose code and operands come from HBM, 15-30 MB of partial sums out); a group
 // of four tiles takes 4200-5300 cycles with the matrix unit busy for 2300 and the LDS for 2700 of them.  Whole step
@@ -48,21 +55,23 @@ struct MidMap {
 // One stage of the LDS ring holds everything that a group needs: the activation block, the weights of the
 // workgroup's rows, the block sums, scales and zero-points.
 constexpr uint32_t MID_W = MID_ROWS * 64, MID_XS = 512, MID_S = 8 * 256;
-template <int MT, bool ZP>
+enum { FMT_INT4 = 0, FMT_ZP = 1, FMT_NF4 = 2 };
+template <int MT, int FMT>
 struct MidLds {
-  static constexpr uint32_t X = MT * 8192, STAGE = X + MID_W + MID_XS + MID_S * (ZP ? 2 : 1);
+  static constexpr uint32_t X = MT * 8192, STAGE = X + MID_W + MID_XS + MID_S * (FMT == FMT_ZP ? 2 : 1);
   static constexpr int S = MT == 4 ? 3 : 4;
   static constexpr uint32_t BYTES = STAGE * S;
-  static constexpr int LOADS = MT + 4 + (ZP ? 1 : 0);   // load instructions per wavefront and stage
+  static constexpr int LOADS = MT + 4 + (FMT == FMT_ZP ? 1 : FMT == FMT_NF4 ? -1 : 0);   // load instructions per wavefront and stage
   static_assert(BYTES <= 160 * 1024, "LDS of a compute unit");
 };
 
 #define QM_DTL(INSTR, RSRC, LDSADDR, VOFF)                                                   \
   asm volatile("s_mov_b32 m0, %0\n\t" INSTR " %1, %2, 0 offen lds" : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC) : "memory", "m0")
 
-template <int MT, bool ZP>
+template <int MT, int FMT>
 __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp, float* __restrict__ part) {
-  typedef MidLds<MT, ZP> L;
+  typedef MidLds<MT, FMT> L;
+  constexpr bool ZP = FMT == FMT_ZP, NF4 = FMT == FMT_NF4;
   constexpr int S = L::S;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const uint32_t t = threadIdx.x, lane = t & 63u;
@@ -71,13 +80,14 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
   const uint32_t K = a.K, ngrp = K >> 7;
   const bool s_fp16 = a.s_fp16 != 0;
   const NibbleConsts nc = nibble_constants();
+  const Nf4Consts fc = nf4_constants();
   constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   auto rsrc = [](const void* p, uint64_t bytes) {
     return i32x4{(int)(uint32_t)(uintptr_t)p, (int)(uint32_t)((uintptr_t)p >> 32), (int)bytes, 0x00020000};
   };
   const i32x4 rx = rsrc(a.x, (uint64_t)mp.rows * K * 2), rw = rsrc(a.w, (uint64_t)a.N * (K >> 1));
-  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * ngrp * 2), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * ngrp);
+  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * ngrp * (NF4 ? 4 : 2)), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * ngrp);
   const i32x4 rxs = rsrc(a.xsum, (uint64_t)mp.rows * ngrp * 4);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
 
@@ -86,7 +96,7 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
   const uint32_t wrd0 = wrd + (((2 * half) ^ wsw) << 4), wrd1 = wrd + (((2 * half + 1) ^ wsw) << 4);
   uint32_t xrd[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) xrd[j] = lrow * 256u + (((half * 8 + j) ^ (lrow & 15u)) << 4);
+  for (int j = 0; j < 8; ++j) xrd[j] = lrow * 256u + (((NF4 ? 2 * j + half : half * 8 + j) ^ (lrow & 15u)) << 4);
 
   const uint32_t w = (mp.W & 7u) == 0 ? (blockIdx.x & 7u) * (mp.W >> 3) + (blockIdx.x >> 3) : blockIdx.x;
   uint32_t i0 = w * mp.tot / mp.W;
@@ -123,9 +133,11 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
         QM_DTL("buffer_load_dwordx4", rx, base + (i * 8 + wave) * 1024, xoff[i] + (in + g * 256));
       else if (i < MT + 2)
         QM_DTL("buffer_load_dwordx4", rw, base + L::X + wave * 2048 + (i - MT) * 1024, woff + (in + g * 64 + (i - MT) * wstep));
-      else if (i == MT + 2)
+      else if (NF4 && i == MT + 2)       // the scales of the group's two blocks
+        QM_DTL("buffer_load_dword", rs, base + L::X + MID_W + MID_XS + wave * 256, soff * 4 + (in + g * 4));
+      else if (!NF4 && i == MT + 2)
         QM_DTL("buffer_load_dword", rxs, base + L::X + MID_W + (wave & 1u) * 256, xsoff + (in + g * mp.rows * 4));
-      else if (i == MT + 3)
+      else if (!NF4 && i == MT + 3)
         QM_DTL("buffer_load_ushort", rs, base + L::X + MID_W + MID_XS + wave * 256, soff * 2 + (in + g * 2));
       else if (ZP && i == MT + 4)
         QM_DTL("buffer_load_ubyte", rz, base + L::X + MID_W + MID_XS + MID_S + wave * 256, soff + (in + g));
@@ -159,39 +171,57 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
       auto xread = [&](int q) {
         xf[q % R] = *reinterpret_cast<const bf16x8*>(sb + xrd[q & 7] + (q >> 3) * 8192);
       };
-      const u32x4 w0 = *reinterpret_cast<const u32x4*>(sb + wrd0), w1 = *reinterpret_cast<const u32x4*>(sb + wrd1);
-      const uint32_t wd[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+      uint32_t wd[8];                       // the eight inputs that the lane's half feeds to k-step j
+      if (NF4) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          wd[j] = *reinterpret_cast<const uint32_t*>(sb + wrd + (((j >> 1) ^ wsw) << 4) + 8 * (j & 1) + 4 * half);
+      } else {
+        const u32x4 w0 = *reinterpret_cast<const u32x4*>(sb + wrd0), w1 = *reinterpret_cast<const u32x4*>(sb + wrd1);
+        wd[0] = w0.x; wd[1] = w0.y; wd[2] = w0.z; wd[3] = w0.w;
+        wd[4] = w1.x; wd[5] = w1.y; wd[6] = w1.z; wd[7] = w1.w;
+      }
+      auto unpack = [&](uint32_t v) { return NF4 ? unpack8_nf4(v, fc) : unpack8_natural(v, nc); };
 #pragma unroll
       for (int q = 0; q < R; ++q) xread(q);
       const uint32_t sbits = *reinterpret_cast<const uint32_t*>(sb + L::X + MID_W + MID_XS + wave * 256 + lane * 4);
       const uint32_t zbits = ZP ? *reinterpret_cast<const uint32_t*>(sb + L::X + MID_W + MID_XS + MID_S + wave * 256 + lane * 4) : 8u;
       float xs[MT];
 #pragma unroll
-      for (int m = 0; m < MT; ++m) xs[m] = *reinterpret_cast<const float*>(sb + L::X + MID_W + (m * 32 + lrow) * 4);
-      if (d == 0 && (g == g0 || (g & 7u) == 0)) {
-        const u32x4_t pw = philox4x32_10(a.row_base + n, g >> 3, 0u, 0u, a.seed_lo, a.seed_hi);
+      for (int m = 0; m < MT; ++m) xs[m] = NF4 ? 0.0f : *reinterpret_cast<const float*>(sb + L::X + MID_W + (m * 32 + lrow) * 4);
+      // noise: a counter serves eight scales, a word two: two groups, or the two blocks of one NormalFloat-4 group
+      const uint32_t pair = NF4 ? g : g >> 1;
+      if ((NF4 || d == 0) && (g == g0 || (pair & 3u) == 0)) {
+        const u32x4_t pw = philox4x32_10(a.row_base + n, pair >> 2, 0u, 0u, a.seed_lo, a.seed_hi);
         zw[0] = pw.x; zw[1] = pw.y; zw[2] = pw.z; zw[3] = pw.w;
       }
-      if (d == 0) {
-        const uint32_t q = (g & 7u) >> 1;
+      if (NF4 || d == 0) {
+        const uint32_t q = pair & 3u;
         normal_pair(q == 0 ? zw[0] : (q == 1 ? zw[1] : (q == 2 ? zw[2] : zw[3])), z_even, z_odd);
       }
-      const float s0 = scale_to_f32(sbits & 0xffffu, s_fp16), zn = d ? z_odd : z_even;
-      const float sp = __builtin_fmaf(a.eps_signed, zn, s0), sm = __builtin_fmaf(-a.eps_signed, zn, s0);
+      float sp[2], sm[2];                   // perturbed scales of the two passes (NormalFloat-4: of two blocks)
+#pragma unroll
+      for (int h = 0; h < (NF4 ? 2 : 1); ++h) {
+        const float s0 = scale_to_f32(h ? sbits >> 16 : sbits & 0xffffu, s_fp16), zn = (NF4 ? h : d) ? z_odd : z_even;
+        sp[h] = __builtin_fmaf(a.eps_signed, zn, s0);
+        sm[h] = __builtin_fmaf(-a.eps_signed, zn, s0);
+        if (NF4) { sp[h] *= 1.0f / NF4_LEVEL_FACTOR; sm[h] *= 1.0f / NF4_LEVEL_FACTOR; }
+      }
       const float cz = ZP ? -(128.0f + (float)(zbits & 0xffu)) : -136.0f;
       // correction operands: lanes of half k hold group k of a pair
       const bool mine = half == d;
 #pragma unroll
       for (int m = 0; m < MT; ++m) xa[m] = mine ? xs[m] : (d == 0 ? 0.0f : xa[m]);
-      bp = mine ? sp * cz : bp;
-      bm = mine ? sm * cz : bm;
-      auto rescale = [&](int m, int r0, int cnt) {
-        const float se = (z * MT + m) >= mp.Tp ? sm : sp;
+      bp = mine ? sp[0] * cz : bp;
+      bm = mine ? sm[0] * cz : bm;
+      // p[b]: sums of tile m, b = m % 2; of block b of the tile for NormalFloat-4
+      auto rescale = [&](int m, int b, int r0, int cnt) {
+        const float se = (z * MT + m) >= mp.Tp ? sm[NF4 ? b : 0] : sp[NF4 ? b : 0];
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (r >= r0 && r < r0 + cnt) y[m][r] = __builtin_fmaf(se, p[m & 1][r], y[m][r]);
+          if (r >= r0 && r < r0 + cnt) y[m][r] = __builtin_fmaf(se, p[b][r], y[m][r]);
       };
-      wf[0] = unpack8_natural(wd[0], nc);
+      wf[0] = unpack(wd[0]);
       __builtin_amdgcn_sched_barrier(0);
       // one slot per MFMA: what else the wavefront has to do is dealt out between them
 #pragma unroll
@@ -200,16 +230,20 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
         for (int j = 0; j < 8; ++j) {
           const int q = m * 8 + j;
           const floatx16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-          p[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[q % R], wf[j], j == 0 ? zero : p[m & 1], 0, 0, 0);
+          const int b = NF4 ? j >> 2 : m & 1;
+          const bool first = NF4 ? (j & 3) == 0 : j == 0;
+          p[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[q % R], wf[j], first ? zero : p[b], 0, 0, 0);
           if (q + R < MT * 8) xread(q + R);
-          if (m == 0 && j < 7) wf[j + 1] = unpack8_natural(wd[j + 1], nc);
-          if (m > 0 && j >= 1 && j <= 4) rescale(m - 1, (j - 1) * 4, 4);
+          if (m == 0 && j < 7) wf[j + 1] = unpack(wd[j + 1]);
+          if (!NF4 && m > 0 && j >= 1 && j <= 4) rescale(m - 1, (m - 1) & 1, (j - 1) * 4, 4);
+          if (NF4 && m > 0 && (j == 1 || j == 2)) rescale(m - 1, 1, (j - 1) * 8, 8);
+          if (NF4 && (j == 5 || j == 6)) rescale(m, 0, (j - 5) * 8, 8);
           if (q >= 2 && q - 2 < L::LOADS) load1(q - 2, g + S - 1, to);
           __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
       for (int l = MT * 8 - 2; l < L::LOADS; ++l) load1(l, g + S - 1, to);
-      rescale(MT - 1, 0, 16);
+      rescale(MT - 1, (MT - 1) & 1, 0, 16);
       stage = stage == S - 1 ? 0 : stage + 1;
       // the next group has landed (later ones may still be on their way), and everyone has read this one
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((S - 2) * L::LOADS) : "memory");
@@ -219,6 +253,7 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
       group(g, std::integral_constant<int, 0>());
       if (g + 1 < g1) group(g + 1, std::integral_constant<int, 1>());
       // the integers entered as 128 + u: y -= s_eff (128 + zp) X, two groups at a time on the fp32 matrix unit
+      if (!NF4)
 #pragma unroll
       for (int m = 0; m < MT; ++m)
         y[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[m], (z * MT + m) >= mp.Tp ? bm : bp, y[m], 0, 0, 0);
@@ -258,12 +293,14 @@ __global__ __launch_bounds__(256) void block_sums_kernel(const u32x4* __restrict
 // weights half as often, with two their partial sums are half as large.  Inside the 7B step at 4096 x 4096 .. 22016
 // (sum of the four linears of a layer with their reductions, two / four tiles): 4 tiles 135 / 140 us, 6 tiles
 // 167 / 179, 10 tiles 227 / 230, 12 tiles 253 / 239, 16 tiles 326 / 289.  Fewer ranges than compute units (longer
-// ranges, fewer partial sums) were slower at every size: 192 ranges +5 %, 128 +30 %.
-MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual) {
+// ranges, fewer partial sums) were slower at every size: 192 ranges +5 %, 128 +30 %.  NormalFloat-4, whose unpacking
+// costs four times as much, takes four from four tiles on (7B step with two / four: 4 tiles 5.57 / 5.16 ms, 8 tiles
+// 8.93 / 7.61; OPT-1.3B: 4 tiles 2.30 / 2.44, 8 tiles 2.98 / 2.98).
+MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4) {
   MidPlan p = {};
   const uint32_t Tp = (M + 31) / 32, T = dual ? 2 * Tp : Tp;
   p.rows = dual ? 2 * M : M; p.T = T; p.Tp = Tp;
-  p.mt = T >= 12 ? 4 : 2;
+  p.mt = T >= (nf4 ? 4u : 12u) ? 4 : 2;
   p.Z = (T + p.mt - 1) / p.mt;
   p.U = ((K >> 7) + 1) / 2;
   p.tot = ((N + MID_ROWS - 1) / MID_ROWS) * p.Z * p.U;
@@ -272,33 +309,33 @@ MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual) {
   p.slots = std::min(p.U, (p.U + shortest - 1) / shortest + 1);   // no item is touched by more ranges than that
   return p;
 }
-uint64_t mid_ws_floats(uint32_t M, uint32_t N, uint32_t K, bool dual) {
-  const MidPlan p = mid_plan(M, N, K, dual);
+uint64_t mid_ws_floats(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4) {
+  const MidPlan p = mid_plan(M, N, K, dual, nf4);
   return (uint64_t)p.slots * p.rows * N;
 }
 // 32-bit byte offsets into the operands and the partial sums, 32-bit products in the ranges' arithmetic
-bool mid_fits(uint32_t M, uint32_t N, uint32_t K, bool dual) {
-  const MidPlan p = mid_plan(M, N, K, dual);
+bool mid_fits(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4) {
+  const MidPlan p = mid_plan(M, N, K, dual, nf4);
   return (uint64_t)p.slots * p.rows * N * 4 < (1ull << 31) && (uint64_t)p.rows * K * 2 < (1ull << 31) &&
          ((uint64_t)N + MID_ROWS) * (K >> 1) < (1ull << 31) &&
          ((uint64_t)N / MID_ROWS + 1) * p.Z * p.U * (p.W + 1) < (1ull << 32);
 }
 
-template <int MT, bool ZP>
+template <int MT, int FMT>
 static hipError_t mid_launch(const GemmArgs& a, const MidMap& mp, float* ws, hipStream_t st) {
   static bool ready = false;
-  constexpr uint32_t L = MidLds<MT, ZP>::BYTES;
+  constexpr uint32_t L = MidLds<MT, FMT>::BYTES;
   if (!ready) {
-    hipError_t e = hipFuncSetAttribute((const void*)mid_gemm_kernel<MT, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize, L);
+    hipError_t e = hipFuncSetAttribute((const void*)mid_gemm_kernel<MT, FMT>, hipFuncAttributeMaxDynamicSharedMemorySize, L);
     if (e != hipSuccess) return e;
     ready = true;
   }
-  mid_gemm_kernel<MT, ZP><<<mp.W, 512, L, st>>>(a, mp, ws);
+  mid_gemm_kernel<MT, FMT><<<mp.W, 512, L, st>>>(a, mp, ws);
   return hipGetLastError();
 }
-template <bool ZP>
+template <int FMT>
 static hipError_t mid_launch_mt(uint32_t mt, const GemmArgs& a, const MidMap& mp, float* ws, hipStream_t st) {
-  return mt == 2 ? mid_launch<2, ZP>(a, mp, ws, st) : mid_launch<4, ZP>(a, mp, ws, st);
+  return mt == 2 ? mid_launch<2, FMT>(a, mp, ws, st) : mid_launch<4, FMT>(a, mp, ws, st);
 }
 
 hipError_t launch_block_sums(const void* x, uint32_t rows, uint32_t K, float* out, hipStream_t st) {
@@ -308,10 +345,11 @@ hipError_t launch_block_sums(const void* x, uint32_t rows, uint32_t K, float* ou
 
 hipError_t launch_mid_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
-  const MidPlan p = mid_plan(a.M, a.N, a.K, a.dual != 0);
-  if (!ws || !a.xsum || !mid_fits(a.M, a.N, a.K, a.dual != 0)) return hipErrorInvalidValue;
+  const MidPlan p = mid_plan(a.M, a.N, a.K, a.dual != 0, a.nf4 != 0);
+  if (!ws || (!a.xsum && !a.nf4) || !mid_fits(a.M, a.N, a.K, a.dual != 0, a.nf4 != 0)) return hipErrorInvalidValue;
   const MidMap mp = {p.U, p.W, p.tot, p.Z, p.T, p.Tp, p.rows};
-  hipError_t e = a.zp ? mid_launch_mt<true>(p.mt, a, mp, ws, st) : mid_launch_mt<false>(p.mt, a, mp, ws, st);
+  hipError_t e = a.nf4 ? mid_launch_mt<FMT_NF4>(p.mt, a, mp, ws, st)
+               : a.zp ? mid_launch_mt<FMT_ZP>(p.mt, a, mp, ws, st) : mid_launch_mt<FMT_INT4>(p.mt, a, mp, ws, st);
   if (e != hipSuccess) return e;
   return launch_mid_reduce(a, ws, p, st);
 }
