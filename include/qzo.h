@@ -170,8 +170,8 @@ qzo_status qzo_forward_loss(qzo_model* m, const int32_t* tokens_dev, uint32_t ba
  * receives the scalars.  clip must be >= 0.  A non-finite d leaves the scales
  * untouched and sets result.status = QZO_ERR_NONFINITE.
  * With int4 weights (no joint mode, no group index per column) the two forwards run as one
- * forward over 2*batch sequences.  Up to 32 tokens the few-token kernel reads the weights once
- * for both: losses bit-identical to two qzo_forward_loss calls.  Above 64, up
+ * forward over 2*batch sequences.  Up to 64 tokens the few-token kernel serves both (up to 32
+ * it reads the weights once): losses bit-identical to two qzo_forward_loss calls.  Beyond, up
  * to the token count from which the model's linears take the expand-then-multiply route (about
  * 3200 at Llama-2-7B widths; at most 4096; never when that route is forced), a launch of the
  * tile kernel holds the token tiles of both passes, the second pass's with -eps and starting

@@ -220,7 +220,7 @@ bool mid_single_pass(const qzo_model* m, uint64_t M1) { return m->cfg.quant == 3
 
 // Row at which the second pass of a stacked forward starts.
 uint64_t stacked_pass_stride(const qzo_model* m, uint64_t M1) {
-  const bool tiles_of_256 = !mid_route(m, M1) && (m->cfg.quant == 3 || M1 > SKINNY_MAX_M_DUAL);
+  const bool tiles_of_256 = !mid_route(m, M1) && (m->cfg.quant == 3 || M1 > SKINNY_MAX_M);
   return tiles_of_256 ? (M1 + 255) / 256 * 256 : M1;
 }
 uint64_t widest_row(const qzo_model_config& c) {
@@ -228,7 +228,9 @@ uint64_t widest_row(const qzo_model_config& c) {
 }
 
 // Whether qzo_step runs its two perturbed passes as one forward over 2 * batch sequences.  With at
-// most 32 tokens the few-token kernel reads the int4 weights once for both, on the route above mid_gemm_kernel does.
+// most 32 tokens the few-token kernel reads the int4 weights once for both, with up to 64 its launches hold a
+// workgroup of either pass (half the launches, bit-identical to separate passes); on the route above mid_gemm_kernel
+// serves both.
 // Beyond and as long as the fused kernel serves (at most 4096 tokens per pass), a launch of
 // the tile kernel holds both passes' token tiles, the second pass's with -eps: twice the tiles per
 // launch for a chip that such token counts do not fill, half the launches.  The second pass starts
@@ -244,7 +246,8 @@ bool passes_stacked(const qzo_model* m, uint64_t M1) {
   if (c.quant == 3)
     return mid_route(m, M1) || (M1 <= STACK_TILE_MAX_M && (stacked_pass_stride(m, M1) + M1) * widest_row(c) * 2 < (1ull << 31));
   if (M1 <= SKINNY_MAX_M_DUAL || mid_route(m, M1)) return true;
-  if (M1 <= SKINNY_MAX_M || M1 > STACK_TILE_MAX_M || m->int4_path == 2) return false;
+  if (M1 > STACK_TILE_MAX_M || m->int4_path == 2) return false;
+  if (M1 <= SKINNY_MAX_M) return true;
   // Stacked, the fused kernel stays ahead of expand-then-multiply for a fifth more tokens than the
   // break-even of separate passes (7B widths: 72.2 against 74.9 ms per step at 2560 tokens, 83.8
   // against 85.0 at 3072, 103.5 against 100.1 at 4096).

@@ -128,7 +128,15 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
   const uint32_t lr = lane >> 3, lc = lane & 7u;          // loads: row within an instruction's 8 rows, 16-byte chunk
   const uint32_t K = a.K, ngrp = K >> 7;
   const uint32_t g0 = blockIdx.y * groups_per_split, g1 = min(g0 + groups_per_split, ngrp);   // g0 is even
-  const uint32_t nb = blockIdx.x * SK_ROWS + wave * 32;   // the wavefront's first row
+  // both passes in one launch, a workgroup each (33 to 64 tokens per pass): eight consecutive workgroups of one pass,
+  // then the same row blocks of the other, so that the two that read the same weights sit on the same XCD
+  const bool both = !DUAL && a.dual;
+  const uint32_t pass = both ? (blockIdx.x >> 3) & 1u : 0u;
+  const uint32_t blk = both ? (blockIdx.x >> 4) * 8 + (blockIdx.x & 7u) : blockIdx.x;
+  if (both && blk * SK_ROWS >= a.N) return;
+  const uint32_t row0 = pass * a.M, rows_all = (DUAL || both) ? 2 * a.M : a.M;
+  const float eps_signed = pass ? -a.eps_signed : a.eps_signed;
+  const uint32_t nb = blk * SK_ROWS + wave * 32;          // the wavefront's first row
   const uint32_t n_own = nb + lrow;
   const uint32_t n = min(n_own, a.N - 1);                 // the row this lane feeds to the MFMA
   const bool s_fp16 = a.s_fp16 != 0;
@@ -148,7 +156,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
     // counts the loads issued after it and nothing more.
     constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<void*>(a.x), 0, (int)((uint64_t)(DUAL ? 2 * a.M : a.M) * K * 2), 0x00020000);
+        const_cast<void*>(a.x), 0, (int)((uint64_t)rows_all * K * 2), 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void*>(a.w), 0, (int)((uint64_t)a.N * (K >> 1)), 0x00020000);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
@@ -170,7 +178,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
       const uint32_t c = t + 256u * i, row = c >> 4, ch = c & 15u;
-      const uint32_t xrow = DUAL ? (row / TPP) * a.M + min(row % TPP, a.M - 1) : min(row, a.M - 1);
+      const uint32_t xrow = DUAL ? (row / TPP) * a.M + min(row % TPP, a.M - 1) : row0 + min(row, a.M - 1);
       xoff[i] = xrow * K * 2 + ch * 16;
     }
     // The counter of outstanding loads retires in issue order: waiting for a load waits for every
@@ -255,7 +263,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
   } while (0)
 
     // XIN: element e = t + 256 i of a pass is (group e / (32 MT), tile row e % (32 MT)); X is [K/128][rows]
-    const uint32_t xrows = DUAL ? 2 * a.M : a.M;
+    const uint32_t xrows = rows_all;
     const __amdgpu_buffer_rsrc_t rxs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float*>(XIN ? a.xsum : (const float*)a.x), 0, (int)((uint64_t)xrows * ngrp * 4), 0x00020000);
     uint32_t xin_off[MT];
@@ -263,7 +271,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
       const uint32_t e = t + 256u * i, row = e % (MT * 32u);
-      const uint32_t xrow = DUAL ? (row / TPP) * a.M + min(row % TPP, a.M - 1) : min(row, a.M - 1);
+      const uint32_t xrow = DUAL ? (row / TPP) * a.M + min(row % TPP, a.M - 1) : row0 + min(row, a.M - 1);
       xin_off[i] = ((e / (MT * 32u)) * xrows + xrow) * 4u;
       xin_next[i] = 0.0f;
     }
@@ -338,8 +346,8 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
           const uint32_t sw = (d >> 1) == 0 ? sv.x : ((d >> 1) == 1 ? sv.y : ((d >> 1) == 2 ? sv.z : sv.w));
           const float zz = (g & 1u) ? z_odd : z_even;
           const float s0 = scale_to_f32((d & 1) ? sw >> 16 : sw & 0xffffu, s_fp16);
-          const float se_p = __builtin_fmaf(a.eps_signed, zz, s0);
-          const float se_m = __builtin_fmaf(-a.eps_signed, zz, s0);
+          const float se_p = __builtin_fmaf(eps_signed, zz, s0);
+          const float se_m = __builtin_fmaf(-eps_signed, zz, s0);
           const float cz = ZP ? -(128.0f + (float)((zv[d >> 2] >> (8 * (d & 3))) & 0xffu)) : -136.0f;
           // this lane's 64 nibbles of the group: chunks 4 (d % 2) + 2 half and the next of row lrow
           const uint32_t c0 = 4 * (d & 1) + 2 * half;
@@ -384,7 +392,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
 #undef QZO_SK_XINLOAD
 
     // partial sums of this slice
-    const uint32_t rows = DUAL ? 2 * a.M : a.M;
+    const uint32_t rows = rows_all;
     const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
         part, 0, (int)((uint64_t)gridDim.y * rows * a.N * 4), 0x00020000);
     if (n_own < a.N) {
@@ -394,7 +402,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
         for (int r = 0; r < 16; ++r) {
           const uint32_t tr = 32 * m + 8 * (r >> 2) + 4 * half + (r & 3);      // tile row
           const uint32_t tok = DUAL ? tr % TPP : tr;
-          const uint32_t orow = DUAL ? (tr / TPP) * a.M + tok : tok;
+          const uint32_t orow = DUAL ? (tr / TPP) * a.M + tok : row0 + tok;
           const uint32_t off = ((blockIdx.y * rows + orow) * a.N + n_own) * 4u;
           if (tok < a.M) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[m][r]), rp, (int)off, 0, 0);
         }
@@ -480,14 +488,17 @@ static void skinny_launch(const GemmArgs& a, dim3 grid, float* ws, uint32_t per,
 }
 hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
-  if (a.M > SKINNY_MAX_M || (a.dual && a.M > SKINNY_MAX_M_DUAL) || !ws) return hipErrorInvalidValue;
+  if (a.M > SKINNY_MAX_M || !ws) return hipErrorInvalidValue;
   // 32-bit byte offsets into the weights, the activations and the partial sums
   if ((uint64_t)a.N * (a.K >> 1) >= (1ull << 31) || (uint64_t)2 * SKINNY_MAX_M * a.K * 2 >= (1ull << 31) ||
       skinny_ws_floats(a.dual ? 2 * a.M : a.M, a.N, a.K) * 4 >= (1ull << 31))
     return hipErrorInvalidValue;
   const uint32_t ks = skinny_ksplit(a.N, a.K), ngrp = a.K >> 7, per = (ngrp + ks - 1) / ks;
   dim3 grid((a.N + SK_ROWS - 1) / SK_ROWS, ks);
-  if (a.dual) {
+  if (a.dual && a.M > SKINNY_MAX_M_DUAL) {        // a workgroup per pass
+    grid.x = (grid.x + 7) / 8 * 16;
+    skinny_launch<2, false, false>(a, grid, ws, per, st);
+  } else if (a.dual) {
     if (a.M <= 16) skinny_launch<1, true, true>(a, grid, ws, per, st);
     else skinny_launch<2, true, false>(a, grid, ws, per, st);
   } else if (a.M <= 16) {

@@ -417,6 +417,21 @@ def test_step_matches_oracle(oracle, name):
     dm.close()
 
 
+@pytest.mark.parametrize("name,batch,seq", [("tiny", 1, 33), ("tiny_opt", 3, 19), ("tiny+zp", 1, 64)])
+def test_stacked_workgroups_of_either_pass_equal_separate_passes(oracle, name, batch, seq):
+    """33 to 64 tokens per pass: a launch of the few-token kernel holds workgroups of both passes, each with the
+    arithmetic of a launch of its own: losses bit-identical to two separate forward passes."""
+    base, asym = _case(name)
+    shape = dict(base, batch=batch, seq=seq)
+    om, dm = _models(oracle, shape, 1234, 4.0, **_variant_args(asym))
+    tokd = _dev(synth.tokens(shape, 5678))
+    res = qb.read_step_result(dm.step(tokd, 21, 1e-3, 0.0, 100.0))       # eta = 0: scales untouched
+    lp = float(dm.forward_loss(tokd, 21, 1e-3, 1).item())
+    lm = float(dm.forward_loss(tokd, 21, 1e-3, -1).item())
+    assert res["loss_plus"] == lp and res["loss_minus"] == lm and lp != lm
+    dm.close()
+
+
 @pytest.mark.parametrize("name", ["tiny", "tiny_opt", "tiny+zp", "tiny+zp16"])
 def test_stacked_passes_equal_separate_passes(oracle, name):
     """With at most 32 tokens qzo_step runs both perturbed passes as one stacked forward (the
