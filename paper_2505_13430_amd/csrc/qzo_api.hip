@@ -433,6 +433,16 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
   float* const mid_ws = n_pass == 2 || mid_single_pass(m, M1) ? w.mid : nullptr;
   const bool few = (mid_ws && c.quant != 3) || (w.skinny && M1 <= SKINNY_MAX_M && (c.quant == 0 || c.quant == 2) && !c.act_order);
   float* const xs_a = few ? w.xs_a : nullptr;
+  // the norm that follows a linear into the residual stream: taken over by the linear's slice reduction where it has one
+  NextNorm nn = {};
+  auto norm = [&](const void* gain, const void* nbias, float* xs) {
+    if (nn.done) { nn.done = false; return hipSuccess; }
+    return nbias ? launch_layernorm(w.h, gain, nbias, M, d, c.norm_eps, w.a, st, xs)
+                 : launch_rmsnorm(w.h, gain, M, d, c.norm_eps, w.a, st, xs);
+  };
+  auto before = [&](const void* gain, const void* nbias, float* xs) {
+    nn = {gain, nbias, c.norm_eps, w.a, xs, false};
+  };
   for (uint32_t l = 0; l < c.n_layers; ++l) {
     const qzo_buf* T = &m->T[m->first_layer_tensor + (size_t)l * m->tensors_per_layer];
     const uint64_t layer_off = (uint64_t)l * m->scales_per_layer;
@@ -462,6 +472,7 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       g.skinny_ws = mid_ws ? nullptr : w.skinny;
       g.split_ws = w.split;
       g.mid_ws = mid_ws;
+      g.next = li == 1 || li == 3 ? &nn : nullptr;
       g.nf4 = c.quant == 3;
       if (few) {     // the few-token kernel takes the block sums of its input from the kernel that wrote it
         g.xsum = (li == 0 || li == 2) ? w.xs_a : (li == 3 ? w.xs_act : nullptr);
@@ -572,6 +583,9 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       ProfScope ps(PK_W4GEMM, 2.0 * Mreal * (double)g.N * g.K, st);
       return launch_codebook_gemm(g, st);
     };
+    // the next layer's first tensors are its first norm's, behind the last layer the final norm's
+    const bool last = l + 1 == c.n_layers;
+    auto after_layer = [&](size_t k) { return T[m->tensors_per_layer + k].ptr_dev; };
     if (llama && c.quant == 1) {
       // attn_norm, codes/cb qkv, codes/cb o, ffn_norm, codes/cb gate+up, codes/cb down
       QZO_HIP(launch_rmsnorm(w.h, T[0].ptr_dev, M, d, c.norm_eps, w.a, st));
@@ -585,35 +599,33 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       QZO_HIP(cgemm(3, w.act, T[8].ptr_dev, T[9].ptr_dev, w.h, w.h, EPI_RESIDUAL));
     } else if (llama) {
       // attn_norm, wqkv, wo, ffn_norm, wgu, wdown (symmetric-table positions)
-      QZO_HIP(launch_rmsnorm(w.h, ti(0), M, d, c.norm_eps, w.a, st, xs_a));
+      QZO_HIP(norm(ti(0), nullptr, xs_a));
       rope_fused = false;
       QZO_HIP(gemm(0, w.a, nullptr, nullptr, w.qkv, EPI_ROPE));
       if (!rope_fused && !rope_in_attention) QZO_HIP(launch_rope(w.qkv, w.rope, M, seq, P, d, H, st));
       QZO_HIP(attention(rope_fused || !rope_in_attention));
+      before(ti(3), nullptr, xs_a);
       QZO_HIP(gemm(1, w.att, nullptr, w.h, w.h, EPI_RESIDUAL));
-      QZO_HIP(launch_rmsnorm(w.h, ti(3), M, d, c.norm_eps, w.a, st, xs_a));
+      QZO_HIP(norm(ti(3), nullptr, xs_a));
       QZO_HIP(gemm(2, w.a, nullptr, nullptr, w.act, EPI_SWIGLU));
+      before(after_layer(0), nullptr, last ? nullptr : xs_a);
       QZO_HIP(gemm(3, w.act, nullptr, w.h, w.h, EPI_RESIDUAL));
     } else {
       // ln1_g, ln1_b, wqkv, bqkv, wo, bo, ln2_g, ln2_b, wfc1, bfc1, wfc2, bfc2 (symmetric-table positions)
-      QZO_HIP(launch_layernorm(w.h, ti(0), ti(1), M, d, c.norm_eps, w.a, st, xs_a));
+      QZO_HIP(norm(ti(0), ti(1), xs_a));
       QZO_HIP(gemm(0, w.a, ti(3), nullptr, w.qkv, EPI_BIAS));
       QZO_HIP(attention(true));
+      before(ti(6), ti(7), xs_a);
       QZO_HIP(gemm(1, w.att, ti(5), w.h, w.h, EPI_BIAS | EPI_RESIDUAL));
-      QZO_HIP(launch_layernorm(w.h, ti(6), ti(7), M, d, c.norm_eps, w.a, st, xs_a));
+      QZO_HIP(norm(ti(6), ti(7), xs_a));
       QZO_HIP(gemm(2, w.a, ti(9), nullptr, w.ff, EPI_BIAS | EPI_RELU));
+      before(after_layer(0), after_layer(1), last ? nullptr : xs_a);
       QZO_HIP(gemm(3, w.ff, ti(11), w.h, w.h, EPI_BIAS | EPI_RESIDUAL));
     }
   }
   const size_t tail = m->first_layer_tensor + (size_t)c.n_layers * m->tensors_per_layer;
-  const void* lm_head;
-  if (llama) {
-    QZO_HIP(launch_rmsnorm(w.h, m->T[tail].ptr_dev, M, d, c.norm_eps, w.a, st));
-    lm_head = m->T[tail + 1].ptr_dev;
-  } else {
-    QZO_HIP(launch_layernorm(w.h, m->T[tail].ptr_dev, m->T[tail + 1].ptr_dev, M, d, c.norm_eps, w.a, st));
-    lm_head = m->T[tail + 2].ptr_dev;
-  }
+  QZO_HIP(norm(m->T[tail].ptr_dev, llama ? nullptr : m->T[tail + 1].ptr_dev, nullptr));
+  const void* lm_head = m->T[tail + (llama ? 1 : 2)].ptr_dev;
   if (hidden_out)
     QZO_HIP(hipMemcpyAsync(hidden_out, w.a, (size_t)M * d * 2, hipMemcpyDeviceToDevice, st));
   CeArgs ce = {};

@@ -991,6 +991,7 @@ constexpr int W4_PIPE = 2;
 static GemmArgs column_block(const GemmArgs& a, uint32_t first, uint32_t count, int w_bits, bool codes_per_scale_group) {
   (void)codes_per_scale_group;
   GemmArgs s = a;
+  s.next = nullptr;                              // a column block does not complete rows
   const uint32_t ld = a.ldy ? a.ldy : a.N;
   s.N = count; s.ldy = ld;
   s.w = (const char*)a.w + (uint64_t)first * a.K * w_bits / 8;

@@ -36,6 +36,13 @@ enum : uint32_t {
                        // of W must be in ROW_ORDER_ROPE128 order
 };
 
+struct NextNorm {
+  const void *gain, *bias;     // bias: LayerNorm, null: RMSNorm
+  float eps;
+  void* out;                   // bf16 [rows, N]
+  float* xsum;                 // nullable: block sums of out, [N/128][rows]
+  bool done;                   // set by the launcher that took it over
+};
 struct GemmArgs {
   const void* x;        // bf16 [M,K]
   const void* w;        // packed int4 [N,K/2] (W4) or bf16 [N,K] (dense)
@@ -73,6 +80,8 @@ struct GemmArgs {
   // the output y of the K-slice reduction ([N_out/128][rows], N_out % 128 == 0; null: not wanted).
   const float* xsum;
   float* xsum_out;
+  // The norm that reads y next (null: none wanted): a slice reduction norms the rows it completes (NextNorm::done).
+  struct NextNorm* next;
 };
 hipError_t launch_w4a16_gemm(const GemmArgs& a, hipStream_t st);
 // Order of the rows of an expanded (bf16) weight matrix: natural; the fused-SwiGLU consumer's tile order;

@@ -39,6 +39,8 @@
 #include "qzo_device.hpp"
 #include "qzo_kernels.hpp"
 #include "qzo_nibble.hpp"
+#include "qzo_norm.hpp"
+#include <algorithm>
 
 namespace qzo {
 
@@ -52,7 +54,8 @@ constexpr int SK_WD = 8;          // groups per pass of the K loop: four rounds 
 // of the stored bf16 values (and their plain sum in `sum`).
 // ksplit: slices of feature f (and of the up feature NO + f with SwiGLU: ksplit_up).
 __device__ __forceinline__ float reduce_item(const GemmArgs& a, const float* __restrict__ part, uint32_t ksplit,
-                                             uint32_t ksplit_up, uint32_t m, uint32_t f, float& sum) {
+                                             uint32_t ksplit_up, uint32_t m, uint32_t f, float& sum,
+                                             uint2* packed = nullptr) {
   const bool swiglu = (a.epi & EPI_SWIGLU) != 0;
   const uint32_t NO = swiglu ? a.N >> 1 : a.N;
   auto load4 = [&](uint32_t ks, uint32_t col) {
@@ -99,6 +102,7 @@ __device__ __forceinline__ float reduce_item(const GemmArgs& a, const float* __r
   out.x = pack_bf16x2(v[0], v[1]);
   out.y = pack_bf16x2(v[2], v[3]);
   *reinterpret_cast<uint2*>((bf16_t*)a.y + o) = out;
+  if (packed) *packed = out;
   const float q0 = __uint_as_float(out.x << 16), q1 = __uint_as_float(out.x & 0xffff0000u);
   const float q2 = __uint_as_float(out.y << 16), q3 = __uint_as_float(out.y & 0xffff0000u);
   sum = (q0 + q2) + (q1 + q3);
@@ -410,6 +414,13 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
   }
 }
 
+// Slices of row m, feature f when the partial sums come from mid_gemm_kernel.
+__device__ __forceinline__ uint32_t slices_of(const MidPlan& mp, uint32_t m, uint32_t f) {
+  const uint32_t pass_rows = mp.T == mp.Tp ? mp.rows : mp.rows >> 1, pass = m >= pass_rows ? 1u : 0u;
+  const uint32_t z = (pass * mp.Tp + ((m - pass * pass_rows) >> 5)) / mp.mt;
+  return mid_slices(mp, (f / MID_ROWS) * mp.Z + z);
+}
+
 // Adds the K-slice partials in slice order and applies the epilogue.  A thread owns 4
 // consecutive output features of one token (of the output: [M, N], or [M, N/2] with SwiGLU).
 // MAPPED: the slices come from mid_gemm_kernel, whose ranges of work give every block of the output a number of
@@ -423,13 +434,8 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(GemmArgs a, const fl
   const bool own = q < a.M * per_row;
   if (own) {
     const uint32_t m = q / per_row, f = (q % per_row) * 4;
-    uint32_t kf = ksplit, ku = ksplit;
-    if (MAPPED) {
-      const uint32_t pass_rows = mp.T == mp.Tp ? mp.rows : mp.rows >> 1, pass = m >= pass_rows ? 1u : 0u;
-      const uint32_t z = (pass * mp.Tp + ((m - pass * pass_rows) >> 5)) / mp.mt;
-      kf = mid_slices(mp, (f / MID_ROWS) * mp.Z + z);
-      ku = (a.epi & EPI_SWIGLU) ? mid_slices(mp, ((NO + f) / MID_ROWS) * mp.Z + z) : kf;
-    }
+    const uint32_t kf = MAPPED ? slices_of(mp, m, f) : ksplit;
+    const uint32_t ku = MAPPED && (a.epi & EPI_SWIGLU) ? slices_of(mp, m, NO + f) : kf;
     ssq = reduce_item(a, part, kf, ku, m, f, sx);
   }
   if (a.xsum_out) {
@@ -446,6 +452,49 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(GemmArgs a, const fl
     __syncthreads();
     if (threadIdx.x == 0) a.partials[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
   }
+}
+
+// The same for a linear without SwiGLU whose output h is normed next: a workgroup of up to 1024 threads completes a row,
+// keeps it in the LDS and norms it (the norm kernel's arithmetic, bit for bit), so that one launch with its fixed cost
+// of 4-5 us between weights that fill every cache does the work of two.  N <= 8192.
+// Whole steps, two launches -> one: 7B widths 1 x 16 tokens 2.89 -> 2.82 ms, 1 x 32 3.74 -> 3.62, 1 x 57 4.96 -> 4.87,
+// 4 x 33 (two split-K linears a layer) 9.24 -> 9.09; OPT-1.3B 1 x 16 1.57 -> 1.50.  Up to 512 rows: with 2048 the two
+// launches are bound by their bytes and a row of 2048 features leaves too few loads in flight (OPT-1.3B 16 x 64: +2.8 %).  Rows that take more than one item per thread
+// want a few hundred workgroups (13B widths: 388 rows of 5120 features -1.5 %, 32 rows +0.7 %).
+template <bool LAYERNORM, bool MAPPED>
+__global__ __launch_bounds__(1024) void reduce_norm_kernel(GemmArgs a, const float* __restrict__ part, uint32_t ksplit,
+                                                           MidPlan mp, NextNorm nn) {
+  __shared__ __attribute__((aligned(16))) uint2 row[2048];
+  __shared__ float red[4];
+  const uint32_t m = blockIdx.x;
+  for (uint32_t f = threadIdx.x * 4; f < a.N; f += blockDim.x * 4) {
+    float sum;
+    const uint32_t kf = MAPPED ? slices_of(mp, m, f) : ksplit;
+    (void)reduce_item(a, part, kf, kf, m, f, sum, row + (f >> 2));
+  }
+  __syncthreads();
+  auto chunk = [&](int i, uint32_t) { return reinterpret_cast<const uint4*>(row)[(threadIdx.x & 255u) + 256u * i]; };
+  norm_row<LAYERNORM, true>(chunk, (const bf16_t*)nn.gain, (const bf16_t*)nn.bias, a.N, nn.eps,
+                            (bf16_t*)nn.out + (uint64_t)m * a.N, nn.xsum, m, gridDim.x, red);
+}
+
+// Slice reduction of a.M rows, with the norm that reads its output where the caller named one.
+template <bool MAPPED>
+hipError_t launch_reduce(const GemmArgs& r, const float* part, uint32_t ksplit, const MidPlan& mp, hipStream_t st) {
+  if (r.next && !(r.epi & (EPI_SWIGLU | EPI_SUMSQ)) && !r.ldy && !r.xsum_out && r.N <= 8192 && r.N % 8 == 0 &&
+      r.M <= 512 && (r.N <= 4096 || r.M >= 256)) {
+    NextNorm nn = *r.next;
+    // whole wavefronts, an equal number of features each; the norm itself wants 256 threads
+    const uint32_t items = r.N / 4, per = (items + 1023) / 1024;
+    const uint32_t threads = std::max(256u, ((items + per - 1) / per + 63) / 64 * 64);
+    if (r.N % 128) nn.xsum = nullptr;
+    if (nn.bias) reduce_norm_kernel<true, MAPPED><<<r.M, threads, 0, st>>>(r, part, ksplit, mp, nn);
+    else reduce_norm_kernel<false, MAPPED><<<r.M, threads, 0, st>>>(r, part, ksplit, mp, nn);
+    r.next->done = true;
+  } else {
+    skinny_reduce_kernel<MAPPED><<<skinny_reduce_blocks(r.M, r.N, r.epi), 256, 0, st>>>(r, part, ksplit, mp);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -513,24 +562,21 @@ hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   GemmArgs r = a;                               // the reduction sees the stacked rows as one matrix
   if (a.dual) r.M = 2 * a.M;
   if (r.ldy || ((r.epi & EPI_SWIGLU) ? r.N >> 1 : r.N) % 128) r.xsum_out = nullptr;
-  skinny_reduce_kernel<false><<<skinny_reduce_blocks(r.M, r.N, r.epi), 256, 0, st>>>(r, ws, ks, MidPlan{});
-  return hipGetLastError();
+  return launch_reduce<false>(r, ws, ks, MidPlan{}, st);
 }
 
 hipError_t launch_partial_reduce(const GemmArgs& a, const float* part, uint32_t ksplit, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
   GemmArgs r = a;
   r.xsum_out = nullptr;                         // block sums are a service of the few-token path only
-  skinny_reduce_kernel<false><<<skinny_reduce_blocks(a.M, a.N, a.epi), 256, 0, st>>>(r, part, ksplit, MidPlan{});
-  return hipGetLastError();
+  return launch_reduce<false>(r, part, ksplit, MidPlan{}, st);
 }
 
 hipError_t launch_mid_reduce(const GemmArgs& a, const float* part, const MidPlan& mp, hipStream_t st) {
   GemmArgs r = a;
   r.M = mp.rows;
   if (r.ldy || ((r.epi & EPI_SWIGLU) ? r.N >> 1 : r.N) % 128) r.xsum_out = nullptr;
-  skinny_reduce_kernel<true><<<skinny_reduce_blocks(r.M, r.N, r.epi), 256, 0, st>>>(r, part, 0, mp);
-  return hipGetLastError();
+  return launch_reduce<true>(r, part, 0, mp, st);
 }
 
 }  // namespace qzo
