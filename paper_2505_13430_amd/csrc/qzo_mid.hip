@@ -1,7 +1,8 @@
-// Perturbed W4A16 linear for some dozen to a few hundred tokens:
+// Perturbed 4-bit linear for up to a few hundred tokens, zero-point int4 and NormalFloat-4:
 //   Y[M,N] = X[M,K] * W_eff^T,  W_eff[n,k] = (s[n,k/128] + sigma*eps*z(row_base+n, k/128)) * (u[n,k] - zp[n,k/128])
-// (paper Eq. 4-5; zp = 8 without zero-points).  Above the few-token kernel's 64 rows per launch the weights are used
-// by several token tiles, and a 256 x 256 output tile is still mostly padding and leaves most of the chip idle.
+// (paper Eq. 4-5), or (s[n,k/64] + sigma*eps*z(row_base+n, k/64)) * level[u[n,k]].  Above the few-token kernel's rows
+// the weights are used by several token tiles, and a 256 x 256 output tile is still mostly padding and leaves most
+// of the chip idle.
 //
 // A workgroup of eight wavefronts owns 256 output rows (32 per wavefront) and two or four tiles of 32 tokens.  As in
 // the few-token kernel the nibbles enter the matrix unit as the exact integers 128 + u and the perturbed scale is
@@ -9,6 +10,7 @@
 // s_eff (128 + zp) X with X the block sum of the activations (delivered by the kernel that wrote them), is taken off
 // for two groups at a time by one fp32 MFMA per tile (32x32x2: its depth is the two groups), which costs no vector
 // instruction and no broadcast reads.  A token tile lies in one pass of a stacked step and takes that pass's sign.
+// Hidden states of one layer against 64 bits: 7.8e-3 (the bf16 weight tile of the 256-row kernel) -> 6.4e-3.
 //
 // Everything a group needs comes by direct-to-LDS loads into a ring of three or four stages, requested two or three
 // groups ahead (swizzled on the memory side, nothing passes through registers); one barrier per group.  Inside a group
@@ -18,18 +20,19 @@
 // Work is split evenly whatever the shape: items (row block, token block) x pairs of groups are cut into one
 // contiguous range per compute unit; an item that several ranges touch is summed by the reduction kernel in order.
 //
-// NormalFloat-4 (FMT_NF4): indices become bf16 levels by byte permutations (33 instructions for 8 weights, see
-// unpack8_nf4), a group holds two blocks of 64 with a scale each: the k-steps 0-3 and 4-7, whose sums are rescaled
-// apart; the levels are signed, so there is no correction.  Against expand-then-multiply, which writes and reads 2
-// bytes per weight and pass: 1 x 16 tokens at 7B widths 16.6 -> 4.2 ms per step, 1 x 57 17.3 -> 5.3, 4 x 33 19.8 -> 9.9,
-// 4 x 100 25.9 -> 21.0, 8 x 64 27.3 -> 22.2.  Vector instructions bound it (about 450 per group and wavefront with
-// four tiles against 32 MFMAs).
+// NormalFloat-4: indices become bf16 levels by byte permutations (33 instructions for 8 weights, see unpack8_nf4), a
+// group holds two blocks of 64 with a scale each: the k-steps 0-3 and 4-7, whose sums are rescaled apart; the levels
+// are signed, so there is no correction.  Against expand-then-multiply, which writes and reads 2 bytes per weight and
+// pass: 1 x 16 tokens at 7B widths 16.6 -> 4.2 ms per step, 1 x 57 17.3 -> 5.3, 4 x 33 19.8 -> 9.9, 4 x 100 25.7 -> 21.0,
+// 8 x 64 27.3 -> 22.2.  Vector instructions bound it (about 450 per group and wavefront with four tiles against 32
+// MFMAs).  Hidden states against 64 bits: 7.8e-3 -> 6.8e-3.
 //
-// What bounds it: at 57 tokens per pass (4096 x 4096 .. 22016) a launch takes 16-43 us, of which about 10 us do not
-// depend on the work (start of a kernel whose code and operands come from HBM, 15-30 MB of partial sums out); a group
-// of four tiles takes 4200-5300 cycles with the matrix unit busy for 2300 and the LDS for 2700 of them.  Whole step
-// at 7B widths against two passes of the few-token kernel (up to 64 tokens) or the 256-row tile kernel (beyond):
-// 1 x 33 tokens 7.04 -> 4.63 ms, 1 x 57 7.56 -> 4.91, 2 x 40 9.45 -> 6.02, 4 x 33 9.73 -> 8.23, 4 x 48 10.1 -> 9.1.
+// What bounds the integer format: at 57 tokens per pass (4096 x 4096 .. 22016) a launch takes 16-43 us, of which about
+// 10 us do not depend on the work (start of a kernel whose code and operands come from HBM, 15-30 MB of partial sums
+// out); a group of four tiles takes 4200-5300 cycles with the matrix unit busy for 2300 and the LDS for 2700 of them.
+// Whole steps of zero-point models at 7B widths against two passes of the few-token kernel (up to 64 tokens) or the
+// 256-row tile kernel (beyond): 1 x 33 tokens 7.24 -> 4.70 ms, 1 x 57 7.74 -> 5.00, 2 x 40 9.75 -> 6.11, 4 x 33 9.90 -> 8.37,
+// 4 x 48 10.2 -> 9.1.
 // Tried: one wavefront per SIMD with 64 rows each (half the LDS reads, but the accumulators move to AGPRs and every
 // rescaling then pays two register moves: 15-25 % slower); K split between two halves of a workgroup (LDS merge
 // instead of partial sums: more activation traffic, slower); activations and weights staged through registers
@@ -55,23 +58,21 @@ struct MidMap {
 // One stage of the LDS ring holds everything that a group needs: the activation block, the weights of the
 // workgroup's rows, the block sums, scales and zero-points.
 constexpr uint32_t MID_W = MID_ROWS * 64, MID_XS = 512, MID_S = 8 * 256;
-enum { FMT_INT4 = 0, FMT_ZP = 1, FMT_NF4 = 2 };
-template <int MT, int FMT>
+template <int MT, bool NF4>
 struct MidLds {
-  static constexpr uint32_t X = MT * 8192, STAGE = X + MID_W + MID_XS + MID_S * (FMT == FMT_ZP ? 2 : 1);
+  static constexpr uint32_t X = MT * 8192, STAGE = X + MID_W + MID_XS + MID_S * (NF4 ? 1 : 2);
   static constexpr int S = MT == 4 ? 3 : 4;
   static constexpr uint32_t BYTES = STAGE * S;
-  static constexpr int LOADS = MT + 4 + (FMT == FMT_ZP ? 1 : FMT == FMT_NF4 ? -1 : 0);   // load instructions per wavefront and stage
+  static constexpr int LOADS = MT + (NF4 ? 3 : 5);   // load instructions per wavefront and stage
   static_assert(BYTES <= 160 * 1024, "LDS of a compute unit");
 };
 
 #define QM_DTL(INSTR, RSRC, LDSADDR, VOFF)                                                   \
   asm volatile("s_mov_b32 m0, %0\n\t" INSTR " %1, %2, 0 offen lds" : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC) : "memory", "m0")
 
-template <int MT, int FMT>
+template <int MT, bool NF4>
 __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp, float* __restrict__ part) {
-  typedef MidLds<MT, FMT> L;
-  constexpr bool ZP = FMT == FMT_ZP, NF4 = FMT == FMT_NF4;
+  typedef MidLds<MT, NF4> L;
   constexpr int S = L::S;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const uint32_t t = threadIdx.x, lane = t & 63u;
@@ -87,7 +88,7 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
     return i32x4{(int)(uint32_t)(uintptr_t)p, (int)(uint32_t)((uintptr_t)p >> 32), (int)bytes, 0x00020000};
   };
   const i32x4 rx = rsrc(a.x, (uint64_t)mp.rows * K * 2), rw = rsrc(a.w, (uint64_t)a.N * (K >> 1));
-  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * ngrp * (NF4 ? 4 : 2)), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * ngrp);
+  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * ngrp * (NF4 ? 4 : 2)), rz = rsrc(NF4 ? a.s : a.zp, (uint64_t)a.N * ngrp);
   const i32x4 rxs = rsrc(a.xsum, (uint64_t)mp.rows * ngrp * 4);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
 
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
         QM_DTL("buffer_load_dword", rxs, base + L::X + MID_W + (wave & 1u) * 256, xsoff + (in + g * mp.rows * 4));
       else if (!NF4 && i == MT + 3)
         QM_DTL("buffer_load_ushort", rs, base + L::X + MID_W + MID_XS + wave * 256, soff * 2 + (in + g * 2));
-      else if (ZP && i == MT + 4)
+      else if (!NF4 && i == MT + 4)
         QM_DTL("buffer_load_ubyte", rz, base + L::X + MID_W + MID_XS + MID_S + wave * 256, soff + (in + g));
     };
 
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
 #pragma unroll
       for (int q = 0; q < R; ++q) xread(q);
       const uint32_t sbits = *reinterpret_cast<const uint32_t*>(sb + L::X + MID_W + MID_XS + wave * 256 + lane * 4);
-      const uint32_t zbits = ZP ? *reinterpret_cast<const uint32_t*>(sb + L::X + MID_W + MID_XS + MID_S + wave * 256 + lane * 4) : 8u;
+      const uint32_t zbits = !NF4 ? *reinterpret_cast<const uint32_t*>(sb + L::X + MID_W + MID_XS + MID_S + wave * 256 + lane * 4) : 0u;
       float xs[MT];
 #pragma unroll
       for (int m = 0; m < MT; ++m) xs[m] = NF4 ? 0.0f : *reinterpret_cast<const float*>(sb + L::X + MID_W + (m * 32 + lrow) * 4);
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
         sm[h] = __builtin_fmaf(-a.eps_signed, zn, s0);
         if (NF4) { sp[h] *= 1.0f / NF4_LEVEL_FACTOR; sm[h] *= 1.0f / NF4_LEVEL_FACTOR; }
       }
-      const float cz = ZP ? -(128.0f + (float)(zbits & 0xffu)) : -136.0f;
+      const float cz = -(128.0f + (float)(zbits & 0xffu));
       // correction operands: lanes of half k hold group k of a pair
       const bool mine = half == d;
 #pragma unroll
@@ -321,21 +322,21 @@ bool mid_fits(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4) {
          ((uint64_t)N / MID_ROWS + 1) * p.Z * p.U * (p.W + 1) < (1ull << 32);
 }
 
-template <int MT, int FMT>
+template <int MT, bool NF4>
 static hipError_t mid_launch(const GemmArgs& a, const MidMap& mp, float* ws, hipStream_t st) {
   static bool ready = false;
-  constexpr uint32_t L = MidLds<MT, FMT>::BYTES;
+  constexpr uint32_t L = MidLds<MT, NF4>::BYTES;
   if (!ready) {
-    hipError_t e = hipFuncSetAttribute((const void*)mid_gemm_kernel<MT, FMT>, hipFuncAttributeMaxDynamicSharedMemorySize, L);
+    hipError_t e = hipFuncSetAttribute((const void*)mid_gemm_kernel<MT, NF4>, hipFuncAttributeMaxDynamicSharedMemorySize, L);
     if (e != hipSuccess) return e;
     ready = true;
   }
-  mid_gemm_kernel<MT, FMT><<<mp.W, 512, L, st>>>(a, mp, ws);
+  mid_gemm_kernel<MT, NF4><<<mp.W, 512, L, st>>>(a, mp, ws);
   return hipGetLastError();
 }
-template <int FMT>
+template <bool NF4>
 static hipError_t mid_launch_mt(uint32_t mt, const GemmArgs& a, const MidMap& mp, float* ws, hipStream_t st) {
-  return mt == 2 ? mid_launch<2, FMT>(a, mp, ws, st) : mid_launch<4, FMT>(a, mp, ws, st);
+  return mt == 2 ? mid_launch<2, NF4>(a, mp, ws, st) : mid_launch<4, NF4>(a, mp, ws, st);
 }
 
 hipError_t launch_block_sums(const void* x, uint32_t rows, uint32_t K, float* out, hipStream_t st) {
@@ -346,10 +347,9 @@ hipError_t launch_block_sums(const void* x, uint32_t rows, uint32_t K, float* ou
 hipError_t launch_mid_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
   const MidPlan p = mid_plan(a.M, a.N, a.K, a.dual != 0, a.nf4 != 0);
-  if (!ws || (!a.xsum && !a.nf4) || !mid_fits(a.M, a.N, a.K, a.dual != 0, a.nf4 != 0)) return hipErrorInvalidValue;
+  if (!ws || (!a.nf4 && (!a.xsum || !a.zp)) || !mid_fits(a.M, a.N, a.K, a.dual != 0, a.nf4 != 0)) return hipErrorInvalidValue;
   const MidMap mp = {p.U, p.W, p.tot, p.Z, p.T, p.Tp, p.rows};
-  hipError_t e = a.nf4 ? mid_launch_mt<FMT_NF4>(p.mt, a, mp, ws, st)
-               : a.zp ? mid_launch_mt<FMT_ZP>(p.mt, a, mp, ws, st) : mid_launch_mt<FMT_INT4>(p.mt, a, mp, ws, st);
+  hipError_t e = a.nf4 ? mid_launch_mt<true>(p.mt, a, mp, ws, st) : mid_launch_mt<false>(p.mt, a, mp, ws, st);
   if (e != hipSuccess) return e;
   return launch_mid_reduce(a, ws, p, st);
 }
