@@ -6,6 +6,7 @@
 // by HBM: about 2.3 bytes per weight (codes or nibbles in, bf16 out).
 #include "qzo_device.hpp"
 #include "qzo_kernels.hpp"
+#include "qzo_nibble.hpp"
 
 namespace qzo {
 
@@ -72,13 +73,6 @@ hipError_t launch_expand_codebook(const void* codes, const void* cb, const void*
 }
 
 // ---- NormalFloat-4 blocks (Sec. 4.3's quantizer): W = (s + sigma*eps*z)[n, k/64] * level[u] ----
-// The 16 levels of the published NormalFloat-4 code book (normal quantiles scaled to [-1, 1]).
-__device__ const float NF4_LEVELS_DEV[16] = {
-    -1.0f, -0.6961928009986877f, -0.5250730514526367f, -0.39491748809814453f,
-    -0.28444138169288635f, -0.18477343022823334f, -0.09105003625154495f, 0.0f,
-    0.07958029955625534f, 0.16093020141124725f, 0.24611230194568634f, 0.33791524171829224f,
-    0.44070982933044434f, 0.5626170039176941f, 0.7229568362236023f, 1.0f};
-
 // Perturbed block scales of one linear as fp32 [N, G]: s + (sigma*eps) z, one fma each.  A thread
 // owns the eight scales of one Philox counter (row, 8 gb .. 8 gb + 7), as the update does.
 __global__ __launch_bounds__(256) void perturbed_scales_kernel(const bf16_t* __restrict__ s, uint32_t N,

@@ -101,14 +101,31 @@ hipError_t launch_partial_reduce(const GemmArgs& a, const float* part, uint32_t 
 // Some dozen to a few hundred tokens per pass (mid_gemm_kernel): items (block of MID_ROWS output rows, block of mt token
 // tiles) x U pairs of groups of K are cut into W equal contiguous ranges, one per workgroup; an item that
 // several ranges touch has one partial sum per range, in range order.
+// The token tiles of both passes are counted through, and a place of a token block holds one of them; a NormalFloat-4
+// block that would hold tiles of both passes (Tp % mt != 0) has half of its places for either (both = 1), so that which
+// pass a place belongs to is known when its kernel is compiled.  Either way ceil(T / mt) blocks.
 constexpr uint32_t MID_ROWS = 256;
 struct MidPlan {
   uint32_t mt, Z, U, W, tot;           // Z: token blocks per row block; U: pairs of groups of K; tot = items * U
   uint32_t T, Tp, rows, slots;         // token tiles of 32 (all, of one pass), rows of x, most slices of an item
+  uint32_t both;
 };
 MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4);
 uint64_t mid_ws_floats(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4);
 bool mid_fits(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4);
+struct MidTile { uint32_t pass, tile, valid; };      // tile: within its pass
+// Place m of token block z.
+__host__ __device__ inline MidTile mid_tile(const MidPlan& p, uint32_t z, uint32_t m) {
+  if (p.both) {
+    const uint32_t half = p.mt >> 1, pass = m >= half ? 1u : 0u, tile = z * half + m - pass * half;
+    return {pass, tile, tile < p.Tp ? 1u : 0u};
+  }
+  const uint32_t ti = z * p.mt + m, pass = ti >= p.Tp ? 1u : 0u;
+  return {pass, ti - pass * p.Tp, ti < p.T ? 1u : 0u};
+}
+__host__ __device__ inline uint32_t mid_block_of(const MidPlan& p, uint32_t pass, uint32_t tile) {
+  return p.both ? tile / (p.mt >> 1) : (pass * p.Tp + tile) / p.mt;
+}
 // Range that holds unit i: ranges are [w tot / W, (w+1) tot / W).
 __host__ __device__ inline uint32_t mid_range_of(uint32_t i, uint32_t W, uint32_t tot) { return ((i + 1) * W - 1) / tot; }
 __host__ __device__ inline uint32_t mid_slices(const MidPlan& p, uint32_t item) {

@@ -6,7 +6,7 @@
 //
 // A workgroup of eight wavefronts owns 256 output rows (32 per wavefront) and two or four tiles of 32 tokens.  As in
 // the few-token kernel the nibbles enter the matrix unit as the exact integers 128 + u and the perturbed scale is
-// applied to a group's fp32 sums, y += s_eff * P; the weights are not rounded.  What the integers carry too much,
+// applied to a group's fp32 sums, y += s_eff * P; the int4 weights are not rounded.  What the integers carry too much,
 // s_eff (128 + zp) X with X the block sum of the activations (delivered by the kernel that wrote them), is taken off
 // for two groups at a time by one fp32 MFMA per tile (32x32x2: its depth is the two groups), which costs no vector
 // instruction and no broadcast reads.  A token tile lies in one pass of a stacked step and takes that pass's sign.
@@ -20,12 +20,16 @@
 // Work is split evenly whatever the shape: items (row block, token block) x pairs of groups are cut into one
 // contiguous range per compute unit; an item that several ranges touch is summed by the reduction kernel in order.
 //
-// NormalFloat-4: indices become bf16 levels by byte permutations (33 instructions for 8 weights, see unpack8_nf4), a
-// group holds two blocks of 64 with a scale each: the k-steps 0-3 and 4-7, whose sums are rescaled apart; the levels
-// are signed, so there is no correction.  Against expand-then-multiply, which writes and reads 2 bytes per weight and
-// pass: 1 x 16 tokens at 7B widths 16.6 -> 4.2 ms per step, 1 x 57 17.3 -> 5.3, 4 x 33 19.8 -> 9.9, 4 x 100 25.7 -> 21.0,
-// 8 x 64 27.3 -> 22.2.  Vector instructions bound it (about 450 per group and wavefront with four tiles against 32
-// MFMAs).  Hidden states against 64 bits: 7.8e-3 -> 6.8e-3.
+// NormalFloat-4: the weights that enter the matrix unit are those of the expanded matrix, (s + sigma*eps*z) * level
+// rounded once (hidden states equal to four digits).  The 16 products of a block are formed once per row and looked up
+// by byte permutations (nf4_table, unpack8_nf4); a lane's half of a group's inputs is one block, so a lane holds one
+// table per pass.  The sums need no rescaling and no correction.  A token block holds tiles of one pass, or half of
+// its places for either (BOTH: a second table, and a second lookup behind the same selectors): about 310 or 470 vector
+// instructions per group and wavefront with four tiles against 32 MFMAs, which bound it.
+// Against expand-then-multiply, which writes and reads 2 bytes per weight and pass: 1 x 16 tokens at 7B widths
+// 16.5 -> 4.2 ms per step, 1 x 57 17.1 -> 5.6, 4 x 33 19.7 -> 10.4, 4 x 64 23.8 -> 11.6, 4 x 100 25.8 -> 21.7,
+// 8 x 64 27.2 -> 20.5.  Blocks of either kind in one launch (BOTH for the remainder only): 6-13 % slower, the second
+// copy of the loop is more cold code per launch.
 //
 // What bounds the integer format: at 57 tokens per pass (4096 x 4096 .. 22016) a launch takes 16-43 us, of which about
 // 10 us do not depend on the work (start of a kernel whose code and operands come from HBM, 15-30 MB of partial sums
@@ -48,13 +52,6 @@ namespace qzo {
 
 namespace {
 
-// Global work of a launch: items (row block, token block) x pairs of groups of K, cut into W equal contiguous ranges.
-struct MidMap {
-  uint32_t U, W, tot, Z;        // pairs of groups per item, ranges, items * U, token blocks per row block
-  uint32_t T, Tp;               // token tiles of 32 rows: all, and those of one pass
-  uint32_t rows;                // rows of x and y (2 M when dual)
-};
-
 // One stage of the LDS ring holds everything that a group needs: the activation block, the weights of the
 // workgroup's rows, the block sums, scales and zero-points.
 constexpr uint32_t MID_W = MID_ROWS * 64, MID_XS = 512, MID_S = 8 * 256;
@@ -70,8 +67,10 @@ struct MidLds {
 #define QM_DTL(INSTR, RSRC, LDSADDR, VOFF)                                                   \
   asm volatile("s_mov_b32 m0, %0\n\t" INSTR " %1, %2, 0 offen lds" : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC) : "memory", "m0")
 
-template <int MT, bool NF4>
-__global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp, float* __restrict__ part) {
+// BOTH: NormalFloat-4, every token block holds tiles of both passes.
+template <int MT, bool NF4, bool BOTH>
+__global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidPlan mp, float* __restrict__ part) {
+  mp.mt = MT; mp.both = BOTH ? 1u : 0u;            // known here
   typedef MidLds<MT, NF4> L;
   constexpr int S = L::S;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -81,7 +80,6 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
   const uint32_t K = a.K, ngrp = K >> 7;
   const bool s_fp16 = a.s_fp16 != 0;
   const NibbleConsts nc = nibble_constants();
-  const Nf4Consts fc = nf4_constants();
   constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   auto rsrc = [](const void* p, uint64_t bytes) {
@@ -97,7 +95,7 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
   const uint32_t wrd0 = wrd + (((2 * half) ^ wsw) << 4), wrd1 = wrd + (((2 * half + 1) ^ wsw) << 4);
   uint32_t xrd[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) xrd[j] = lrow * 256u + (((NF4 ? 2 * j + half : half * 8 + j) ^ (lrow & 15u)) << 4);
+  for (int j = 0; j < 8; ++j) xrd[j] = lrow * 256u + ((half * 8 + j) ^ (lrow & 15u)) * 16u;
 
   const uint32_t w = (mp.W & 7u) == 0 ? (blockIdx.x & 7u) * (mp.W >> 3) + (blockIdx.x >> 3) : blockIdx.x;
   uint32_t i0 = w * mp.tot / mp.W;
@@ -114,9 +112,9 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
 
     // loads: activations 4 rows of 256 bytes per instruction, weights 16 rows of 64 bytes, both swizzled on the
     // memory side (16-byte chunks; the LDS is filled in lane order)
-    auto xrow_of = [&](uint32_t row) {
-      const uint32_t ti = min(z * MT + (row >> 5), mp.T - 1), pass = ti >= mp.Tp ? 1u : 0u;
-      return pass * a.M + min((ti - pass * mp.Tp) * 32 + (row & 31u), a.M - 1);
+    auto xrow_of = [&](uint32_t row) {             // (places without a tile: some row that exists)
+      const MidTile k = mid_tile(mp, z, row >> 5);
+      return min(k.pass, mp.T == mp.Tp ? 0u : 1u) * a.M + min(k.tile * 32 + (row & 31u), a.M - 1);
     };
     uint32_t xoff[MT];
 #pragma unroll
@@ -161,28 +159,23 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
     uint32_t stage = 0;
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"((S - 2) * L::LOADS) : "memory");
     __builtin_amdgcn_s_barrier();
-    // one group; d = g % 2
+    // one group; integers: d = g % 2
     auto group = [&](uint32_t g, auto parity) {
       constexpr int d = decltype(parity)::value;
       const uint32_t to = stage == 0 ? S - 1 : stage - 1;     // the group before, which everyone has read
       const unsigned char* sb = lds + stage * L::STAGE;
       constexpr int R = 4;                  // fragments read ahead of their MFMA
-      bf16x8 wf[8], xf[R];
+      bf16x8 wf[8], wb[BOTH ? 8 : 1], xf[R];      // wb: the second pass's weights
       floatx16 p[2];
       auto xread = [&](int q) {
         xf[q % R] = *reinterpret_cast<const bf16x8*>(sb + xrd[q & 7] + (q >> 3) * 8192);
       };
       uint32_t wd[8];                       // the eight inputs that the lane's half feeds to k-step j
-      if (NF4) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          wd[j] = *reinterpret_cast<const uint32_t*>(sb + wrd + (((j >> 1) ^ wsw) << 4) + 8 * (j & 1) + 4 * half);
-      } else {
+      {
         const u32x4 w0 = *reinterpret_cast<const u32x4*>(sb + wrd0), w1 = *reinterpret_cast<const u32x4*>(sb + wrd1);
         wd[0] = w0.x; wd[1] = w0.y; wd[2] = w0.z; wd[3] = w0.w;
         wd[4] = w1.x; wd[5] = w1.y; wd[6] = w1.z; wd[7] = w1.w;
       }
-      auto unpack = [&](uint32_t v) { return NF4 ? unpack8_nf4(v, fc) : unpack8_natural(v, nc); };
 #pragma unroll
       for (int q = 0; q < R; ++q) xread(q);
       const uint32_t sbits = *reinterpret_cast<const uint32_t*>(sb + L::X + MID_W + MID_XS + wave * 256 + lane * 4);
@@ -200,29 +193,36 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
         const uint32_t q = pair & 3u;
         normal_pair(q == 0 ? zw[0] : (q == 1 ? zw[1] : (q == 2 ? zw[2] : zw[3])), z_even, z_odd);
       }
-      float sp[2], sm[2];                   // perturbed scales of the two passes (NormalFloat-4: of two blocks)
-#pragma unroll
-      for (int h = 0; h < (NF4 ? 2 : 1); ++h) {
-        const float s0 = scale_to_f32(h ? sbits >> 16 : sbits & 0xffffu, s_fp16), zn = (NF4 ? h : d) ? z_odd : z_even;
-        sp[h] = __builtin_fmaf(a.eps_signed, zn, s0);
-        sm[h] = __builtin_fmaf(-a.eps_signed, zn, s0);
-        if (NF4) { sp[h] *= 1.0f / NF4_LEVEL_FACTOR; sm[h] *= 1.0f / NF4_LEVEL_FACTOR; }
-      }
+      // perturbed scales of the two passes; for NormalFloat-4 those of the block that the lane's inputs lie in, and
+      // without BOTH the first one is that of the token block's pass
+      const bool second = NF4 && !BOTH && mid_tile(mp, z, 0).pass != 0;
+      const float s0 = scale_to_f32(NF4 && half ? sbits >> 16 : sbits & 0xffffu, s_fp16);
+      const float zn = (NF4 ? half != 0 : d != 0) ? z_odd : z_even;
+      const float sp = __builtin_fmaf(second ? -a.eps_signed : a.eps_signed, zn, s0);
+      const float sm = __builtin_fmaf(-a.eps_signed, zn, s0);
+      Nf4Table tp, tm;
+      if constexpr (NF4) tp = nf4_table(sp);
+      if constexpr (BOTH) tm = nf4_table(sm);
+      auto unpack = [&](int j) {
+        if constexpr (NF4) wf[j] = unpack8_nf4(wd[j], tp);
+        else wf[j] = unpack8_natural(wd[j], nc);
+        if constexpr (BOTH) wb[j] = unpack8_nf4(wd[j], tm);
+      };
       const float cz = -(128.0f + (float)(zbits & 0xffu));
       // correction operands: lanes of half k hold group k of a pair
       const bool mine = half == d;
 #pragma unroll
       for (int m = 0; m < MT; ++m) xa[m] = mine ? xs[m] : (d == 0 ? 0.0f : xa[m]);
-      bp = mine ? sp[0] * cz : bp;
-      bm = mine ? sm[0] * cz : bm;
-      // p[b]: sums of tile m, b = m % 2; of block b of the tile for NormalFloat-4
-      auto rescale = [&](int m, int b, int r0, int cnt) {
-        const float se = (z * MT + m) >= mp.Tp ? sm[NF4 ? b : 0] : sp[NF4 ? b : 0];
+      bp = mine ? sp * cz : bp;
+      bm = mine ? sm * cz : bm;
+      // p[m % 2]: sums of tile m
+      auto rescale = [&](int m, int r0, int cnt) {
+        const float se = (z * MT + m) >= mp.Tp ? sm : sp;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (r >= r0 && r < r0 + cnt) y[m][r] = __builtin_fmaf(se, p[b][r], y[m][r]);
+          if (r >= r0 && r < r0 + cnt) y[m][r] = __builtin_fmaf(se, p[m & 1][r], y[m][r]);
       };
-      wf[0] = unpack(wd[0]);
+      unpack(0);
       __builtin_amdgcn_sched_barrier(0);
       // one slot per MFMA: what else the wavefront has to do is dealt out between them
 #pragma unroll
@@ -231,30 +231,28 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
         for (int j = 0; j < 8; ++j) {
           const int q = m * 8 + j;
           const floatx16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-          const int b = NF4 ? j >> 2 : m & 1;
-          const bool first = NF4 ? (j & 3) == 0 : j == 0;
-          p[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[q % R], wf[j], first ? zero : p[b], 0, 0, 0);
+          if constexpr (NF4) y[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[q % R], BOTH && m >= MT / 2 ? wb[BOTH ? j : 0] : wf[j], y[m], 0, 0, 0);
+          else p[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[q % R], wf[j], j == 0 ? zero : p[m & 1], 0, 0, 0);
           if (q + R < MT * 8) xread(q + R);
-          if (m == 0 && j < 7) wf[j + 1] = unpack(wd[j + 1]);
-          if (!NF4 && m > 0 && j >= 1 && j <= 4) rescale(m - 1, (m - 1) & 1, (j - 1) * 4, 4);
-          if (NF4 && m > 0 && (j == 1 || j == 2)) rescale(m - 1, 1, (j - 1) * 8, 8);
-          if (NF4 && (j == 5 || j == 6)) rescale(m, 0, (j - 5) * 8, 8);
+          if (m == 0 && j < 7) unpack(j + 1);
+          if (!NF4 && m > 0 && j >= 1 && j <= 4) rescale(m - 1, (j - 1) * 4, 4);
           if (q >= 2 && q - 2 < L::LOADS) load1(q - 2, g + S - 1, to);
           __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
       for (int l = MT * 8 - 2; l < L::LOADS; ++l) load1(l, g + S - 1, to);
-      rescale(MT - 1, (MT - 1) & 1, 0, 16);
+      if (!NF4) rescale(MT - 1, 0, 16);
       stage = stage == S - 1 ? 0 : stage + 1;
       // the next group has landed (later ones may still be on their way), and everyone has read this one
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((S - 2) * L::LOADS) : "memory");
       __builtin_amdgcn_s_barrier();
     };
-    for (uint32_t g = g0; g < g1; g += 2) {
+    if constexpr (NF4) {
+      for (uint32_t g = g0; g < g1; ++g) group(g, std::integral_constant<int, 0>());
+    } else for (uint32_t g = g0; g < g1; g += 2) {
       group(g, std::integral_constant<int, 0>());
       if (g + 1 < g1) group(g + 1, std::integral_constant<int, 1>());
       // the integers entered as 128 + u: y -= s_eff (128 + zp) X, two groups at a time on the fp32 matrix unit
-      if (!NF4)
 #pragma unroll
       for (int m = 0; m < MT; ++m)
         y[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[m], (z * MT + m) >= mp.Tp ? bm : bp, y[m], 0, 0, 0);
@@ -264,12 +262,12 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidMap mp,
     const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(part, 0, (int)0x7fffffff, 0x00020000);
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
-      const uint32_t ti = z * MT + m, pass = ti >= mp.Tp ? 1u : 0u;
+      const MidTile k = mid_tile(mp, z, m);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const uint32_t tok = (ti - pass * mp.Tp) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        const uint32_t off = ((slot * mp.rows + pass * a.M + tok) * a.N + nb + lrow) * 4u;
-        if (ti < mp.T && tok < a.M && nb + lrow < a.N)
+        const uint32_t tok = k.tile * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        const uint32_t off = ((slot * mp.rows + k.pass * a.M + tok) * a.N + nb + lrow) * 4u;
+        if (k.valid && tok < a.M && nb + lrow < a.N)
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[m][r]), rp, (int)off, 0, 0);
       }
     }
@@ -295,14 +293,15 @@ __global__ __launch_bounds__(256) void block_sums_kernel(const u32x4* __restrict
 // (sum of the four linears of a layer with their reductions, two / four tiles): 4 tiles 135 / 140 us, 6 tiles
 // 167 / 179, 10 tiles 227 / 230, 12 tiles 253 / 239, 16 tiles 326 / 289.  Fewer ranges than compute units (longer
 // ranges, fewer partial sums) were slower at every size: 192 ranges +5 %, 128 +30 %.  NormalFloat-4, whose unpacking
-// costs four times as much, takes four from four tiles on (7B step with two / four: 4 tiles 5.57 / 5.16 ms, 8 tiles
-// 8.93 / 7.61; OPT-1.3B: 4 tiles 2.30 / 2.44, 8 tiles 2.98 / 2.98).
+// costs three times as much, takes four from four tiles on (steps with two / four: 7B widths 6 tiles 2.11 / 2.01 ms for
+// eight layers, 16 tiles 3.77 / 3.00; OPT-1.3B 6 tiles 1.08 / 1.06, 16 tiles 1.49 / 1.36).
 MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4) {
   MidPlan p = {};
   const uint32_t Tp = (M + 31) / 32, T = dual ? 2 * Tp : Tp;
   p.rows = dual ? 2 * M : M; p.T = T; p.Tp = Tp;
   p.mt = T >= (nf4 ? 4u : 12u) ? 4 : 2;
   p.Z = (T + p.mt - 1) / p.mt;
+  p.both = nf4 && dual && Tp % p.mt != 0;
   p.U = ((K >> 7) + 1) / 2;
   p.tot = ((N + MID_ROWS - 1) / MID_ROWS) * p.Z * p.U;
   p.W = std::min(p.tot, gemm_workgroups(1u << 20, 1u << 20));     // compute units
@@ -322,21 +321,21 @@ bool mid_fits(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4) {
          ((uint64_t)N / MID_ROWS + 1) * p.Z * p.U * (p.W + 1) < (1ull << 32);
 }
 
-template <int MT, bool NF4>
-static hipError_t mid_launch(const GemmArgs& a, const MidMap& mp, float* ws, hipStream_t st) {
+template <int MT, bool NF4, bool BOTH>
+static hipError_t mid_launch(const GemmArgs& a, const MidPlan& mp, float* ws, hipStream_t st) {
   static bool ready = false;
   constexpr uint32_t L = MidLds<MT, NF4>::BYTES;
   if (!ready) {
-    hipError_t e = hipFuncSetAttribute((const void*)mid_gemm_kernel<MT, NF4>, hipFuncAttributeMaxDynamicSharedMemorySize, L);
+    hipError_t e = hipFuncSetAttribute((const void*)mid_gemm_kernel<MT, NF4, BOTH>, hipFuncAttributeMaxDynamicSharedMemorySize, L);
     if (e != hipSuccess) return e;
     ready = true;
   }
-  mid_gemm_kernel<MT, NF4><<<mp.W, 512, L, st>>>(a, mp, ws);
+  mid_gemm_kernel<MT, NF4, BOTH><<<mp.W, 512, L, st>>>(a, mp, ws);
   return hipGetLastError();
 }
-template <bool NF4>
-static hipError_t mid_launch_mt(uint32_t mt, const GemmArgs& a, const MidMap& mp, float* ws, hipStream_t st) {
-  return mt == 2 ? mid_launch<2, NF4>(a, mp, ws, st) : mid_launch<4, NF4>(a, mp, ws, st);
+template <bool NF4, bool BOTH>
+static hipError_t mid_launch_mt(const GemmArgs& a, const MidPlan& mp, float* ws, hipStream_t st) {
+  return mp.mt == 2 ? mid_launch<2, NF4, BOTH>(a, mp, ws, st) : mid_launch<4, NF4, BOTH>(a, mp, ws, st);
 }
 
 hipError_t launch_block_sums(const void* x, uint32_t rows, uint32_t K, float* out, hipStream_t st) {
@@ -348,8 +347,8 @@ hipError_t launch_mid_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
   const MidPlan p = mid_plan(a.M, a.N, a.K, a.dual != 0, a.nf4 != 0);
   if (!ws || (!a.nf4 && (!a.xsum || !a.zp)) || !mid_fits(a.M, a.N, a.K, a.dual != 0, a.nf4 != 0)) return hipErrorInvalidValue;
-  const MidMap mp = {p.U, p.W, p.tot, p.Z, p.T, p.Tp, p.rows};
-  hipError_t e = a.nf4 ? mid_launch_mt<true>(p.mt, a, mp, ws, st) : mid_launch_mt<false>(p.mt, a, mp, ws, st);
+  hipError_t e = !a.nf4 ? mid_launch_mt<false, false>(a, p, ws, st)
+                        : (p.both ? mid_launch_mt<true, true>(a, p, ws, st) : mid_launch_mt<true, false>(a, p, ws, st));
   if (e != hipSuccess) return e;
   return launch_mid_reduce(a, ws, p, st);
 }

@@ -39,32 +39,50 @@ __device__ __forceinline__ bf16x8 unpack8_natural(uint32_t w, NibbleConsts c) {
   r.u[3] = (__builtin_amdgcn_perm(o, w, 0x0c070c03u) & c.mask) | c.magic;
   return r.v;
 }
-// NormalFloat-4: 8 indices of one dword -> c * level in bf16, natural order (33 instructions: the two bytes of the 16
-// levels are looked up for four indices at a time, eight entries per byte permutation, the half of the table chosen
-// by bit 3).  The common factor c = 1 + 3580/8192, taken off again from the block's scale, is the one whose 16 products
-// lie closest to bf16 numbers: 2-norm error of the level table 6.3e-4 (c = 1: 1.06e-3; products scale * level rounded
-// to bf16, as the expanded matrix holds them: 1.6e-3).
-constexpr float NF4_LEVEL_FACTOR = 1.0f + 3580.0f / 8192.0f;
-struct Nf4Consts { uint32_t lo[4], hi[4]; };
-__device__ __forceinline__ Nf4Consts nf4_constants() {
-  return {{0x114180b8u, 0x000688d1u, 0xf9b56deau, 0xb8854f22u}, {0xbfbfbfbfu, 0x00bebebeu, 0x3e3e3e3du, 0x3f3f3f3fu}};
+// The 16 levels of the published NormalFloat-4 code book (normal quantiles scaled to [-1, 1]).
+__device__ const float NF4_LEVELS_DEV[16] = {
+    -1.0f, -0.6961928009986877f, -0.5250730514526367f, -0.39491748809814453f,
+    -0.28444138169288635f, -0.18477343022823334f, -0.09105003625154495f, 0.0f,
+    0.07958029955625534f, 0.16093020141124725f, 0.24611230194568634f, 0.33791524171829224f,
+    0.44070982933044434f, 0.5626170039176941f, 0.7229568362236023f, 1.0f};
+
+// NormalFloat-4 weights of one block as MFMA operands: the 16 products scale * level, each rounded once to bf16 as the
+// expanded matrix holds them, as byte tables (32 instructions per block); then 8 indices of one dword -> 8 products in
+// natural order by byte permutations (26 instructions, 16 for a second table: the two bytes of the products are looked
+// up for four indices at a time, eight entries per permutation, the half of the table chosen by bit 3).
+// Levels rounded on their own, with the scale applied to the sums, need no table per block and pass, but a level's
+// rounding is the same in every weight that has it: over activations of one sign the errors add up instead of averaging
+// out (silu(g) g of 2048 / 8192 features: 9.6e-3 / 1.7e-2 in the hidden states, rounded products 6.4e-3 / 6.3e-3).
+struct Nf4Table { uint32_t lo[4], hi[4]; };
+__device__ __forceinline__ Nf4Table nf4_table(float s) {
+  Nf4Table t;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t a = pack_bf16x2(s * NF4_LEVELS_DEV[4 * q], s * NF4_LEVELS_DEV[4 * q + 1]);
+    const uint32_t b = pack_bf16x2(s * NF4_LEVELS_DEV[4 * q + 2], s * NF4_LEVELS_DEV[4 * q + 3]);
+    t.lo[q] = __builtin_amdgcn_perm(b, a, 0x06040200u);
+    t.hi[q] = __builtin_amdgcn_perm(b, a, 0x07050301u);
+  }
+  return t;
 }
-__device__ __forceinline__ void nf4_bytes(uint32_t x, const Nf4Consts& c, uint32_t& lo, uint32_t& hi) {
-  const uint32_t sel = x & 0x07070707u, m = x & 0x08080808u, upper = (m << 5) - (m >> 3);    // 0xff where bit 3 is set
-  lo = (__builtin_amdgcn_perm(c.lo[3], c.lo[2], sel) & upper) | (__builtin_amdgcn_perm(c.lo[1], c.lo[0], sel) & ~upper);
-  hi = (__builtin_amdgcn_perm(c.hi[3], c.hi[2], sel) & upper) | (__builtin_amdgcn_perm(c.hi[1], c.hi[0], sel) & ~upper);
+// Four indices: entry within a half of the table, and 0xff where bit 3 is set (permutation selectors 8 .. 11 return the
+// top bit of a source's byte 1 or 3, eight times).
+struct Nf4Select { uint32_t sel, upper; };
+__device__ __forceinline__ uint32_t nf4_bytes(const uint32_t (&t)[4], Nf4Select s) {
+  return (__builtin_amdgcn_perm(t[3], t[2], s.sel) & s.upper) | (__builtin_amdgcn_perm(t[1], t[0], s.sel) & ~s.upper);
 }
-__device__ __forceinline__ bf16x8 unpack8_nf4(uint32_t w, const Nf4Consts& c) {
-  uint32_t el, eh, ol, oh;                                // even and odd indices
-  nf4_bytes(w & 0x0f0f0f0fu, c, el, eh);
-  nf4_bytes((w >> 4) & 0x0f0f0f0fu, c, ol, oh);
-  const uint32_t e0 = __builtin_amdgcn_perm(eh, el, 0x05010400u), e1 = __builtin_amdgcn_perm(eh, el, 0x07030602u);
-  const uint32_t o0 = __builtin_amdgcn_perm(oh, ol, 0x05010400u), o1 = __builtin_amdgcn_perm(oh, ol, 0x07030602u);
+__device__ __forceinline__ bf16x8 unpack8_nf4(uint32_t w, const Nf4Table& t) {
+  const uint32_t o = w >> 4;
+  const Nf4Select a = {__builtin_amdgcn_perm(o, w, 0x06020400u) & 0x07070707u,           // indices 0, 1, 4, 5
+                       __builtin_amdgcn_perm(w << 8, w << 12, 0x0b090a08u)};
+  const Nf4Select b = {__builtin_amdgcn_perm(o, w, 0x07030501u) & 0x07070707u,           // indices 2, 3, 6, 7
+                       __builtin_amdgcn_perm(w, w << 4, 0x0b090a08u)};
+  const uint32_t al = nf4_bytes(t.lo, a), ah = nf4_bytes(t.hi, a), bl = nf4_bytes(t.lo, b), bh = nf4_bytes(t.hi, b);
   union { bf16x8 v; uint32_t u[4]; } r;
-  r.u[0] = __builtin_amdgcn_perm(o0, e0, 0x05040100u);
-  r.u[1] = __builtin_amdgcn_perm(o0, e0, 0x07060302u);
-  r.u[2] = __builtin_amdgcn_perm(o1, e1, 0x05040100u);
-  r.u[3] = __builtin_amdgcn_perm(o1, e1, 0x07060302u);
+  r.u[0] = __builtin_amdgcn_perm(ah, al, 0x05010400u);
+  r.u[1] = __builtin_amdgcn_perm(bh, bl, 0x05010400u);
+  r.u[2] = __builtin_amdgcn_perm(ah, al, 0x07030602u);
+  r.u[3] = __builtin_amdgcn_perm(bh, bl, 0x07030602u);
   return r.v;
 }
 // 8 consecutive bf16 (4 dwords) -> the same order 0,4,1,5,2,6,3,7

@@ -417,8 +417,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
 // Slices of row m, feature f when the partial sums come from mid_gemm_kernel.
 __device__ __forceinline__ uint32_t slices_of(const MidPlan& mp, uint32_t m, uint32_t f) {
   const uint32_t pass_rows = mp.T == mp.Tp ? mp.rows : mp.rows >> 1, pass = m >= pass_rows ? 1u : 0u;
-  const uint32_t z = (pass * mp.Tp + ((m - pass * pass_rows) >> 5)) / mp.mt;
-  return mid_slices(mp, (f / MID_ROWS) * mp.Z + z);
+  return mid_slices(mp, (f / MID_ROWS) * mp.Z + mid_block_of(mp, pass, (m - pass * pass_rows) >> 5));
 }
 
 // Adds the K-slice partials in slice order and applies the epilogue.  A thread owns 4

@@ -727,6 +727,62 @@ def test_some_dozen_to_a_few_hundred_tokens(oracle, base, var, batch, seq):
     dm.close()
 
 
+def _step_hidden(dm, tok, seed, eps, stride=None):
+    """Final hidden states [B*S, d] of both passes of a stacked step (eta = 0), read from where the lm_head takes them:
+    the second tensor of the workspace.  stride: row at which the second pass starts (its first row, or a tile's)."""
+    B, S = tok.shape
+    d, M1 = dm.shape["d_model"], B * S
+    stride = stride or M1
+    res = qb.read_step_result(dm.step(tok, seed, eps, 0.0, 100.0))
+    nbytes = (stride + M1) * d * 2
+    off = (nbytes + 255) // 256 * 256
+    h = dm._ws[off:off + nbytes].clone().view(torch.bfloat16).view(stride + M1, d).float().cpu().numpy().astype(np.float64)
+    return res, (h[:M1], h[stride:])
+
+
+def _hidden(dm, tok, seed, eps, sign):
+    B, S = tok.shape
+    hid = torch.zeros((B * S, dm.shape["d_model"]), dtype=torch.bfloat16, device=DEV)
+    loss = torch.zeros(1, dtype=torch.float32, device=DEV)
+    qb.qzo_debug_forward(dm.handle, tok, seed, eps, sign, dm.workspace(B, S), loss, hid)
+    return hid.float().cpu().numpy().astype(np.float64)
+
+
+def _rms(a):
+    return math.sqrt((a ** 2).mean())
+
+
+@pytest.mark.parametrize("base,F,batch,seq", [(MID_LLAMA, 2048, 1, 57), (MID_LLAMA, 640, 1, 7), (MID_LLAMA, 640, 4, 24),
+                                              (MID_OPT, 640, 3, 43), (MID_OPT, 2048, 8, 63)])
+def test_nf4_weights_are_the_same_at_any_token_count(oracle, base, F, batch, seq):
+    """NormalFloat-4 weights are (s + sigma eps z) * level rounded once, whatever the route.  The hidden states of a few
+    sequences (unpacked in the GEMM; both passes in a token block, a pass each, two and four tiles a block) against
+    those of the same sequences inside a batch of more than 512 tokens (expanded matrix).  Activations of one sign into
+    the last linear (ReLU; SwiGLU with equal gate and up weights, so silu(g) g), where weights rounded in any way
+    that is the same in all weights of an index are off by several times the bound: its 2048 errors add up instead of
+    averaging out."""
+    shape = dict(base, n_layers=1, d_ffn=F, batch=-(-513 // seq), seq=seq)
+    table = synth.tensor_table(shape, 1234)
+    if shape["arch"] == "llama":
+        table = [(n, k, np.concatenate([a[:F], a[:F]]) if a.shape == (2 * F, shape["d_model"]) else a) for n, k, a in table]
+    om = oracle.build_model(shape, table, nf4=True)
+    dm = DeviceModel.from_host(dict(shape, quant=om.quant, group=om.group), om.tensors, om.scales, DEV)
+    tok = synth.tokens(shape, 5678)
+    many, few = _dev(tok), _dev(tok[:batch])
+    _, both = _step_hidden(dm, few, 9, 2e-2)
+    M1 = batch * seq
+    want = [_hidden(dm, many, 9, 2e-2, sign)[:M1] for sign in (1, -1)]
+    for sign, h, w, other in ((1, both[0], want[0], want[1]), (-1, both[1], want[1], want[0])):
+        print(shape["arch"], F, M1, sign, "apart %.2e" % (_rms(h - w) / _rms(w)), "passes apart %.2e" % (_rms(w - other) / _rms(w)))
+        # the same products in another order of fp32 sums: what is left are 16-bit activations that fall to the other
+        # side of a rounding
+        assert _rms(h - w) <= 2.5e-3 * _rms(w)
+        assert _rms(h - other) > 10 * _rms(h - w)
+        single = _hidden(dm, few, 9, 2e-2, sign)
+        assert _rms(single - w) <= 2.5e-3 * _rms(w)
+    dm.close()
+
+
 def test_failing_calls_enqueue_nothing(oracle):
     """Every error that the library finds itself (anything but a failing HIP call) is found before
     the first launch: outputs, workspace and scales are untouched afterwards."""
