@@ -181,7 +181,8 @@ qzo_status qzo_forward_loss(qzo_model* m, const int32_t* tokens_dev, uint32_t ba
  * 256 where a layer's linears hold at most 2^28 or 2^26 weights) and NormalFloat-4 models (up
  * to 384 or 512 tokens) work in tiles of 32 tokens, each of one pass, with the same agreement;
  * NormalFloat-4 models beyond, up to 4096 tokens, in 256-row tiles on both passes' expanded
- * matrices.  qzo_workspace_bytes accounts for it.
+ * matrices where that is estimated to be faster than two forwards (the workspace then holds both
+ * matrices of a linear).  qzo_workspace_bytes accounts for it.
  */
 qzo_status qzo_step(qzo_model* m, const int32_t* tokens_dev, uint32_t batch, uint32_t seq,
                     uint64_t seed, float eps, float eta, float clip, void* workspace_dev,

@@ -227,6 +227,30 @@ uint64_t widest_row(const qzo_model_config& c) {
   return std::max<uint64_t>({3ull * c.d_model, (c.arch == 0 ? 2ull : 1ull) * c.d_ffn});
 }
 
+// NormalFloat-4 beyond mid_gemm_kernel's range: one expansion can read the indices once and write both passes' matrices
+// (4.5 bytes per weight instead of two times 2.5), the plain GEMM's tiles take their pass's.  That halves the launches,
+// and twice the tiles leave fewer compute units idle in a launch's last round; but it takes K slices away from launches
+// that filled the chip with them, and two matrices of a wide linear (180 MB each at 7B widths) no longer stay in the
+// last-level cache between expansion and product.  Steps, separate -> stacked: OPT-1.3B 513 .. 4096 tokens 0.69-0.90 of
+// the time; 7B widths 1024 tokens 0.95, 1536 0.93, but 513 1.05, 1152 1.06, 3584 1.05; 13B widths 1280 0.89, 1792
+// 1.07; 4096 x 16384 (OPT) 520 1.16.  Hence an estimate: what the launches save against 0.35 us per million weights of a
+// layer and 10 us.  Of 164 measured pairs of shape and token count it stacks six that are slower that way (by at most
+// 6 %) and leaves three apart that are faster stacked (by at most 5 %).
+//   The same for int4, whose fused kernel does without the expansion: 1.22 of the fused kernel's time at 1024 tokens, 1.05 at
+// 2048, 0.99 at 3072, 1.00 at 4096.
+bool nf4_stack_pays(const qzo_model* m, uint64_t M1) {
+  const bool llama = m->cfg.arch == 0;
+  const uint32_t epi[4] = {llama ? EPI_ROPE : EPI_BIAS, EPI_RESIDUAL, llama ? EPI_SWIGLU : EPI_BIAS | EPI_RELU, EPI_RESIDUAL};
+  const uint32_t rows = (uint32_t)(stacked_pass_stride(m, M1) + M1);
+  double gain = 0.0, weights = 0.0;
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t N = m->lin[i].N, K = m->lin[i].K;
+    gain += 2.0 * bf16_gemm_estimate((uint32_t)M1, N, K, epi[i]) - bf16_gemm_estimate(rows, N, K, epi[i]);
+    weights += (double)N * K;
+  }
+  return gain > 10.0 + 0.35e-6 * weights;
+}
+
 // Whether qzo_step runs its two perturbed passes as one forward over 2 * batch sequences.  With at
 // most 32 tokens the few-token kernel reads the int4 weights once for both, with up to 64 its launches hold a
 // workgroup of either pass (half the launches, bit-identical to separate passes); on the route above mid_gemm_kernel
@@ -236,15 +260,13 @@ uint64_t widest_row(const qzo_model_config& c) {
 // launch for a chip that such token counts do not fill, half the launches.  The second pass starts
 // on a tile boundary (stacked_pass_stride); the rows in between are padding (zeros at the embedding,
 // never read back).
-// NormalFloat-4 beyond mid_gemm_kernel's range: one expansion reads the indices once and writes both passes' matrices
-// (4.5 bytes per weight instead of two times 2.5), the plain GEMM's tiles take their pass's.  Whole steps at 7B
-// widths, separate -> stacked: 4 x 256 tokens 36.1 -> 34.6 ms, 8 x 256 55.9 -> 52.4.  The same for int4, whose fused kernel does without the
-// expansion: 1.22 of the fused kernel's time at 1024 tokens, 1.05 at 2048, 0.99 at 3072, 1.00 at 4096.
+// NormalFloat-4 beyond mid_gemm_kernel's range (up to 4096 tokens, too): where nf4_stack_pays.
 bool passes_stacked(const qzo_model* m, uint64_t M1) {
   const qzo_model_config& c = m->cfg;
   if (c.quant == 1 || m->dense_master || c.act_order) return false;
   if (c.quant == 3)
-    return mid_route(m, M1) || (M1 <= STACK_TILE_MAX_M && (stacked_pass_stride(m, M1) + M1) * widest_row(c) * 2 < (1ull << 31));
+    return mid_route(m, M1) || (M1 <= STACK_TILE_MAX_M && (stacked_pass_stride(m, M1) + M1) * widest_row(c) * 2 < (1ull << 31) &&
+                                nf4_stack_pays(m, M1));
   if (M1 <= SKINNY_MAX_M_DUAL || mid_route(m, M1)) return true;
   if (M1 > STACK_TILE_MAX_M || m->int4_path == 2) return false;
   if (M1 <= SKINNY_MAX_M) return true;

@@ -61,6 +61,19 @@ uint32_t tile_tail_cols(uint32_t M, uint32_t N, uint32_t K, uint32_t epi) {
   if (tail * 2 > cus || tile_ksplit(M, N - n1 * BN, K, nullptr) < 2 || K / BK < 16) return 0;
   return n1 * BN;
 }
+// What a compute unit that takes part in every round goes through: 0.9 us per k-tile of a full chip, 2.2 us per million
+// elements of K slices written and added up (both fitted to differences of whole NormalFloat-4 steps, see
+// nf4_stack_pays).
+double bf16_gemm_estimate(uint32_t M, uint32_t N, uint32_t K, uint32_t epi) {
+  const uint32_t cus = gemm_workgroups(1u << 20, 1u << 20), n1 = tile_tail_cols(M, N, K, epi);
+  auto part = [&](uint32_t n, bool split) {
+    uint32_t per = K / BK;
+    const uint64_t ks = split ? tile_ksplit(M, n, K, &per) : 1u;
+    const uint64_t tiles = (uint64_t)((M + BM - 1) / BM) * ((n + BN - 1) / BN) * ks;
+    return 0.9 * (double)((tiles + cus - 1) / cus * per) + (ks > 1 ? 2.2e-6 * (double)(ks * M * n) : 0.0);
+  };
+  return n1 ? part(n1, false) + part(N - n1, true) : part(N, true);
+}
 uint64_t tile_split_ws_floats(uint32_t M, uint32_t N, uint32_t K) {
   const uint32_t ks = tile_ksplit(M, N, K, nullptr);
   if (ks > 1) return (uint64_t)ks * M * N;

@@ -141,6 +141,8 @@ uint32_t tile_ksplit(uint32_t M, uint32_t N, uint32_t K, uint32_t* kt_per);
 // tile_tail_cols(...) columns (whole rounds, ordinary launch) and the rest (at most half a round of tiles,
 // cut along K so that they fill the chip); 0: no split.  Plain epilogues only.
 uint32_t tile_tail_cols(uint32_t M, uint32_t N, uint32_t K, uint32_t epi);
+// Estimated time (us) of launch_bf16_gemm with split_ws given: see there.
+double bf16_gemm_estimate(uint32_t M, uint32_t N, uint32_t K, uint32_t epi);
 uint64_t tile_split_ws_floats(uint32_t M, uint32_t N, uint32_t K);
 // w = uint16 codes [N,K/8]; cb and s as above; N % 8 == 0, K % 128 == 0.
 hipError_t launch_codebook_gemm(const GemmArgs& a, hipStream_t st);

@@ -95,6 +95,70 @@ def test_dense_count_is_the_16_bit_part_of_the_table(oracle, name):
         assert O.dense_master(m).size == want
 
 
+class _Unbacked:
+    """A tensor that host-only calls can be handed: an aligned address nothing reads, and a size in elements."""
+    is_cuda = True
+
+    def __init__(self, numel, element_size):
+        self._n, self._e = numel, element_size
+
+    def is_contiguous(self):
+        return True
+
+    def data_ptr(self):
+        return 1 << 20
+
+    def numel(self):
+        return self._n
+
+    def element_size(self):
+        return self._e
+
+
+def _host_model(shape):
+    """A model handle without device memory (creating one is host work only): the int4 / NormalFloat-4 tables."""
+    d, F, V = shape["d_model"], shape["d_ffn"], shape["vocab"]
+    llama = shape["arch"] == "llama"
+
+    def b16(n):
+        return [_Unbacked(n, 2)]
+
+    def weight(N, K):
+        return [_Unbacked(N * K // 2, 1)] + ([_Unbacked(N * K // 128, 1)] if shape.get("quant") == 2 else [])
+
+    table = b16(V * d) + ([] if llama else b16(shape["max_seq"] * d))
+    for _ in range(shape["n_layers"]):
+        if llama:
+            table += b16(d) + weight(3 * d, d) + weight(d, d) + b16(d) + weight(2 * F, d) + weight(d, F)
+        else:
+            table += (b16(d) * 2 + weight(3 * d, d) + b16(3 * d) + weight(d, d) + b16(d) + b16(d) * 2 + weight(F, d) + b16(F) +
+                      weight(d, F) + b16(d))
+    table += b16(d) + ([] if llama else b16(d)) + b16(V * d)
+    return qb.qzo_model_create(shape, table, _Unbacked(qb.qzo_model_scale_count(shape), 2))
+
+
+@pytest.mark.parametrize("name,batch,seq,stacked", [
+    # separate passes are the faster ones (time of the stacked step over theirs in brackets)
+    ("llama-2-7b", 9, 57, False), ("llama-2-7b", 9, 128, False), ("llama-2-7b", 7, 512, False),      # 1.05, 1.06, 1.05
+    ("llama-2-13b", 7, 256, False), ("opt-6.7b", 8, 65, False),                                     # 1.07, 1.16
+    ("llama-2-7b", 6, 256, True), ("llama-2-13b", 5, 256, True),                                   # 0.93, 0.89
+    ("opt-1.3b", 9, 64, True), ("opt-1.3b", 16, 256, True)])                                       # 0.73, 0.90
+def test_nf4_passes_are_stacked_where_it_pays(name, batch, seq, stacked):
+    """A NormalFloat-4 step beyond 512 tokens: both passes' expanded matrices lie in the workspace, or one."""
+    shape = dict(synth.SHAPES["opt-1.3b"], d_model=4096, n_heads=32, d_ffn=16384) if name == "opt-6.7b" else synth.SHAPES[name]
+    shape = dict(shape, n_layers=1, max_seq=512, quant=3, group=64)
+    m = _host_model(shape)
+    d, F, M1 = shape["d_model"], shape["d_ffn"], batch * seq
+    widest = max(3 * d * d, (2 if shape["arch"] == "llama" else 1) * F * d)
+    # activations of one pass; K-slice sums are at most one 256 x 256 fp32 tile per compute unit
+    rows = M1 * (12 * d + 2 * F + 32 * -(-shape["vocab"] // 256)) + 4 * qb.qzo_model_scale_count(shape)
+    extra = qb.qzo_workspace_bytes(m, batch, seq) - rows
+    assert (extra > 4 * widest) == stacked, (extra / widest)
+    if not stacked:
+        assert extra < 2 * widest + 256 * 256 * 256 * 4 + (4 << 20)
+    qb.qzo_model_destroy(m)
+
+
 def test_scratch_sizes_and_mode_switches():
     assert qb.qzo_nf4_scratch_bytes(512, 1024) >= 512 * 1024 * 2 + 512 * 16 * 4
     assert qb.qzo_int4_scratch_bytes(512, 1024) >= 512 * 1024 * 2 + 512 * 8 * 4
