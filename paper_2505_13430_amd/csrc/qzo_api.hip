@@ -233,9 +233,10 @@ uint64_t widest_row(const qzo_model_config& c) {
 // that filled the chip with them, and two matrices of a wide linear (180 MB each at 7B widths) no longer stay in the
 // last-level cache between expansion and product.  Steps, separate -> stacked: OPT-1.3B 513 .. 4096 tokens 0.69-0.90 of
 // the time; 7B widths 1024 tokens 0.95, 1536 0.93, but 513 1.05, 1152 1.06, 3584 1.05; 13B widths 1280 0.89, 1792
-// 1.07; 4096 x 16384 (OPT) 520 1.16.  Hence an estimate: what the launches save against 0.35 us per million weights of a
-// layer and 10 us.  Of 164 measured pairs of shape and token count it stacks six that are slower that way (by at most
-// 6 %) and leaves three apart that are faster stacked (by at most 5 %).
+// 1.07; 4096 x 16384 (OPT) 520 1.16.  Hence an estimate: what the launches save against 0.4 us per million weights of a
+// layer (no constant part: a small model, bound by its launches, always stacks).  Of 164 measured pairs of shape and
+// token count it stacks eight that are slower that way (by 0.7-5.8 %) and leaves four apart that are faster stacked (by
+// 1.0-5.4 %).
 //   The same for int4, whose fused kernel does without the expansion: 1.22 of the fused kernel's time at 1024 tokens, 1.05 at
 // 2048, 0.99 at 3072, 1.00 at 4096.
 bool nf4_stack_pays(const qzo_model* m, uint64_t M1) {
@@ -248,7 +249,7 @@ bool nf4_stack_pays(const qzo_model* m, uint64_t M1) {
     gain += 2.0 * bf16_gemm_estimate((uint32_t)M1, N, K, epi[i]) - bf16_gemm_estimate(rows, N, K, epi[i]);
     weights += (double)N * K;
   }
-  return gain > 10.0 + 0.35e-6 * weights;
+  return gain > 0.4e-6 * weights;
 }
 
 // Whether qzo_step runs its two perturbed passes as one forward over 2 * batch sequences.  With at
