@@ -270,7 +270,11 @@ bool passes_stacked(const qzo_model* m, uint64_t M1) {
                                 nf4_stack_pays(m, M1));
   if (M1 <= SKINNY_MAX_M_DUAL || mid_route(m, M1)) return true;
   if (M1 > STACK_TILE_MAX_M || m->int4_path == 2) return false;
-  if (M1 <= SKINNY_MAX_M) return true;
+  if (M1 <= SKINNY_MAX_M) {      // linears of millions of rows: the partial sums of both passes may be too large where one's fit
+    for (int i = 0; i < 4; ++i)
+      if (!skinny_fits(2 * (uint32_t)M1, m->lin[i].N, m->lin[i].K)) return false;
+    return true;
+  }
   // Stacked, the fused kernel stays ahead of expand-then-multiply for a fifth more tokens than the
   // break-even of separate passes (7B widths: 72.2 against 74.9 ms per step at 2560 tokens, 83.8
   // against 85.0 at 3072, 103.5 against 100.1 at 4096).

@@ -93,7 +93,8 @@ constexpr uint32_t SKINNY_MAX_M = 64;
 constexpr uint32_t STACK_TILE_MAX_M = 4096;  // tile kernel: the two passes share a launch up to this many tokens per pass
 constexpr uint32_t SKINNY_MAX_M_DUAL = 32;   // per sign, when both perturbed passes share one launch
 uint32_t skinny_ksplit(uint32_t N, uint32_t K);
-uint64_t skinny_ws_floats(uint32_t M, uint32_t N, uint32_t K);
+uint64_t skinny_ws_floats(uint32_t rows, uint32_t N, uint32_t K);      // rows = M, or 2 M in dual mode
+bool skinny_fits(uint32_t rows, uint32_t N, uint32_t K);
 uint32_t skinny_reduce_blocks(uint32_t M, uint32_t N, uint32_t epi);   // EPI_SUMSQ partial count
 hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st);
 // Adds K-slice partial sums part[slice][M][N] in slice order and applies a's epilogue.

@@ -513,6 +513,11 @@ uint32_t skinny_ksplit(uint32_t N, uint32_t K) {
 uint64_t skinny_ws_floats(uint32_t rows, uint32_t N, uint32_t K) {     // rows = M, or 2 M in dual mode
   return (uint64_t)skinny_ksplit(N, K) * rows * N;
 }
+// 32-bit byte offsets into the weights, the activations and the partial sums
+bool skinny_fits(uint32_t rows, uint32_t N, uint32_t K) {
+  return (uint64_t)N * (K >> 1) < (1ull << 31) && (uint64_t)2 * SKINNY_MAX_M * K * 2 < (1ull << 31) &&
+         skinny_ws_floats(rows, N, K) * 4 < (1ull << 31);
+}
 uint32_t skinny_reduce_blocks(uint32_t M, uint32_t N, uint32_t epi) {
   const uint32_t NO = (epi & EPI_SWIGLU) ? N >> 1 : N;
   return (uint32_t)(((uint64_t)M * (NO >> 2) + 255) / 256);
@@ -537,10 +542,7 @@ static void skinny_launch(const GemmArgs& a, dim3 grid, float* ws, uint32_t per,
 hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
   if (a.M > SKINNY_MAX_M || !ws) return hipErrorInvalidValue;
-  // 32-bit byte offsets into the weights, the activations and the partial sums
-  if ((uint64_t)a.N * (a.K >> 1) >= (1ull << 31) || (uint64_t)2 * SKINNY_MAX_M * a.K * 2 >= (1ull << 31) ||
-      skinny_ws_floats(a.dual ? 2 * a.M : a.M, a.N, a.K) * 4 >= (1ull << 31))
-    return hipErrorInvalidValue;
+  if (!skinny_fits(a.dual ? 2 * a.M : a.M, a.N, a.K)) return hipErrorInvalidValue;
   const uint32_t ks = skinny_ksplit(a.N, a.K), ngrp = a.K >> 7, per = (ngrp + ks - 1) / ks;
   dim3 grid((a.N + SK_ROWS - 1) / SK_ROWS, ks);
   if (a.dual && a.M > SKINNY_MAX_M_DUAL) {        // a workgroup per pass

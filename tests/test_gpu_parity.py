@@ -432,6 +432,19 @@ def test_stacked_workgroups_of_either_pass_equal_separate_passes(oracle, name, b
     dm.close()
 
 
+def test_few_token_step_of_a_layer_with_millions_of_rows():
+    """64 tokens through a gate/up linear of 2^22 rows: the partial sums of both passes would need 2^31 bytes, those of one
+    pass half of that, so the step runs two forwards: bit-identical to forward_loss."""
+    shape = dict(synth.SHAPES["tiny"], n_layers=1, d_model=128, n_heads=1, d_ffn=1 << 21, vocab=300, max_seq=64)
+    dm = DeviceModel.synthetic(shape, 5, DEV)
+    tok = torch.randint(0, 300, (1, 64), device=DEV, dtype=torch.int32)
+    res = qb.read_step_result(dm.step(tok, 21, 1e-3, 0.0, 100.0))
+    lp = float(dm.forward_loss(tok, 21, 1e-3, 1).item())
+    lm = float(dm.forward_loss(tok, 21, 1e-3, -1).item())
+    assert res["status"] == 0 and res["loss_plus"] == lp and res["loss_minus"] == lm and lp != lm
+    dm.close()
+
+
 @pytest.mark.parametrize("name", ["tiny", "tiny_opt", "tiny+zp", "tiny+zp16"])
 def test_stacked_passes_equal_separate_passes(oracle, name):
     """With at most 32 tokens qzo_step runs both perturbed passes as one stacked forward (the

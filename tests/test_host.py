@@ -159,6 +159,18 @@ def test_nf4_passes_are_stacked_where_it_pays(name, batch, seq, stacked):
     qb.qzo_model_destroy(m)
 
 
+def test_few_token_passes_are_stacked_only_where_their_sums_fit():
+    """33 to 64 int4 tokens: with millions of output rows the partial sums of both passes exceed the kernels' 32-bit
+    offsets while those of one pass do not; such a step runs two forwards (its workspace holds 64 rows at 64 tokens
+    as at the 32 whose passes are always stacked, not 128)."""
+    for F, both in ((1 << 21, False), (1 << 16, True)):
+        shape = dict(synth.SHAPES["tiny"], n_layers=1, d_model=128, n_heads=1, d_ffn=F, max_seq=64)
+        m = _host_model(shape)
+        ratio = qb.qzo_workspace_bytes(m, 1, 64) / qb.qzo_workspace_bytes(m, 1, 32)
+        assert (ratio > 1.9) == both and (ratio < 1.1) == (not both), (F, ratio)
+        qb.qzo_model_destroy(m)
+
+
 def test_scratch_sizes_and_mode_switches():
     assert qb.qzo_nf4_scratch_bytes(512, 1024) >= 512 * 1024 * 2 + 512 * 16 * 4
     assert qb.qzo_int4_scratch_bytes(512, 1024) >= 512 * 1024 * 2 + 512 * 8 * 4
