@@ -316,8 +316,9 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
       sk = std::max<uint64_t>(sk, skinny_ws_floats((uint32_t)(mid ? M1 : M), m->lin[i].N, m->lin[i].K));
   w.skinny = (float*)take(sk * 4);
   if (sk == 0) w.skinny = nullptr;
-  w.xs_a = sk || mid ? (float*)take((d / 128) * M * 4) : nullptr;
-  w.xs_act = sk || mid ? (float*)take((F / 128) * M * 4) : nullptr;
+  const bool sums = sk || (mid && int4);        // NormalFloat-4 needs none
+  w.xs_a = sums ? (float*)take((d / 128) * M * 4) : nullptr;
+  w.xs_act = sums ? (float*)take((F / 128) * M * 4) : nullptr;
   uint64_t mw = 0;
   if (mid)
     for (int i = 0; i < 4; ++i)

@@ -159,6 +159,18 @@ def test_nf4_passes_are_stacked_where_it_pays(name, batch, seq, stacked):
     qb.qzo_model_destroy(m)
 
 
+def test_nf4_workspace_holds_no_block_sums():
+    """Up to 512 tokens a NormalFloat-4 workspace is activations, cross-entropy partials, the rotary table and K-slice sums,
+    nothing for block sums (which only integer codes need)."""
+    shape = dict(synth.SHAPES["tiny"], n_layers=1, d_model=128, n_heads=1, d_ffn=128 * 256, vocab=256, max_seq=64, quant=3, group=64)
+    m = _host_model(shape)
+    d, F, rows = 128, 128 * 256, 2 * 64                # both passes of 64 tokens
+    # the largest sums: gate and up (2F rows, one group each: never cut)
+    want = rows * (12 * d + 2 * F + 4 * 8 + 8) + 256 + 64 * 64 * 8 + 4 * rows * 2 * F
+    assert qb.qzo_workspace_bytes(m, 1, 64) == want
+    qb.qzo_model_destroy(m)
+
+
 def test_few_token_passes_are_stacked_only_where_their_sums_fit():
     """33 to 64 int4 tokens: with millions of output rows the partial sums of both passes exceed the kernels' 32-bit
     offsets while those of one pass do not; such a step runs two forwards (its workspace holds 64 rows at 64 tokens
