@@ -234,12 +234,13 @@ uint64_t widest_row(const qzo_model_config& c) {
 // last-level cache between expansion and product.  Steps, separate -> stacked: OPT-1.3B 513 .. 4096 tokens 0.69-0.90 of
 // the time; 7B widths 1024 tokens 0.95, 1536 0.93, but 513 1.05, 1152 1.06, 3584 1.05; 13B widths 1280 0.89, 1792
 // 1.07; 4096 x 16384 (OPT) 520 1.16.  Hence an estimate: what the launches save against 0.4 us per million weights of a
-// layer (no constant part: a small model, bound by its launches, always stacks).  Of 164 measured pairs of shape and
-// token count it stacks eight that are slower that way (by 0.7-5.8 %) and leaves four apart that are faster stacked (by
-// 1.0-5.4 %).
+// layer (no constant part: a small model, bound by its launches, always stacks).  Of 200 measured pairs of shape and
+// token count it stacks ten that are slower that way (by 0.7-5.8 %) and leaves nine apart that are faster stacked (by
+// 1.0-5.4 %).  385 to 512 tokens of the layers that leave mid_gemm_kernel there: 0.87-0.94 of the time at all sizes.
 //   The same for int4, whose fused kernel does without the expansion: 1.22 of the fused kernel's time at 1024 tokens, 1.05 at
 // 2048, 0.99 at 3072, 1.00 at 4096.
 bool nf4_stack_pays(const qzo_model* m, uint64_t M1) {
+  if (M1 <= 512) return true;
   const bool llama = m->cfg.arch == 0;
   const uint32_t epi[4] = {llama ? EPI_ROPE : EPI_BIAS, EPI_RESIDUAL, llama ? EPI_SWIGLU : EPI_BIAS | EPI_RELU, EPI_RESIDUAL};
   const uint32_t rows = (uint32_t)(stacked_pass_stride(m, M1) + M1);

@@ -141,6 +141,7 @@ def _host_model(shape):
     # separate passes are the faster ones (time of the stacked step over theirs in brackets)
     ("llama-2-7b", 9, 57, False), ("llama-2-7b", 9, 128, False), ("llama-2-7b", 7, 512, False),      # 1.05, 1.06, 1.05
     ("llama-2-13b", 7, 256, False), ("opt-6.7b", 8, 65, False),                                     # 1.07, 1.16
+    ("llama-2-13b", 8, 60, True),                                                                  # 0.89
     ("llama-2-7b", 6, 256, True), ("llama-2-13b", 5, 256, True),                                   # 0.93, 0.89
     ("opt-1.3b", 9, 64, True), ("opt-1.3b", 16, 256, True)])                                       # 0.73, 0.90
 def test_nf4_passes_are_stacked_where_it_pays(name, batch, seq, stacked):
