@@ -293,18 +293,22 @@ __global__ __launch_bounds__(256) void block_sums_kernel(const u32x4* __restrict
 // (sum of the four linears of a layer with their reductions, two / four tiles): 4 tiles 135 / 140 us, 6 tiles
 // 167 / 179, 10 tiles 227 / 230, 12 tiles 253 / 239, 16 tiles 326 / 289.  Fewer ranges than compute units (longer
 // ranges, fewer partial sums) were slower at every size: 192 ranges +5 %, 128 +30 %.  NormalFloat-4, whose unpacking
-// costs three times as much, takes four from four tiles on (steps with two / four: 7B widths 6 tiles 2.11 / 2.01 ms for
-// eight layers, 16 tiles 3.77 / 3.00; OPT-1.3B 6 tiles 1.08 / 1.06, 16 tiles 1.49 / 1.36).
+// costs three times as much, takes four from four tiles on, as long as that leaves every compute unit two pairs of
+// groups (steps with four / two: 7B widths 6 tiles 2.04 / 2.15 ms for eight layers, 16 tiles 3.07 / 3.73; d_model 1024
+// 4 tiles 0.368 / 0.323 for four layers, 10 tiles 0.436 / 0.405; the smallest model of the tests 0.165 / 0.140).  With
+// the limit, per linear, against four throughout: OPT-1.3B 4 tiles 0.97, 10 tiles 1.02, 16 tiles 0.99; a limit of one
+// pair: the same but for 7B and 13B widths at 4 tiles (1.00 against 0.98).
 MidPlan mid_plan(uint32_t M, uint32_t N, uint32_t K, bool dual, bool nf4) {
   MidPlan p = {};
   const uint32_t Tp = (M + 31) / 32, T = dual ? 2 * Tp : Tp;
   p.rows = dual ? 2 * M : M; p.T = T; p.Tp = Tp;
-  p.mt = T >= (nf4 ? 4u : 12u) ? 4 : 2;
+  p.U = ((K >> 7) + 1) / 2;
+  const uint32_t blocks = (N + MID_ROWS - 1) / MID_ROWS, cus = gemm_workgroups(1u << 20, 1u << 20);
+  p.mt = T >= (nf4 ? 4u : 12u) && (!nf4 || blocks * ((T + 3) / 4) * p.U >= 2 * cus) ? 4 : 2;
   p.Z = (T + p.mt - 1) / p.mt;
   p.both = nf4 && dual && Tp % p.mt != 0;
-  p.U = ((K >> 7) + 1) / 2;
-  p.tot = ((N + MID_ROWS - 1) / MID_ROWS) * p.Z * p.U;
-  p.W = std::min(p.tot, gemm_workgroups(1u << 20, 1u << 20));     // compute units
+  p.tot = blocks * p.Z * p.U;
+  p.W = std::min(p.tot, cus);
   const uint32_t shortest = p.tot / p.W;
   p.slots = std::min(p.U, (p.U + shortest - 1) / shortest + 1);   // no item is touched by more ranges than that
   return p;
