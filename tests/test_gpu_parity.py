@@ -312,6 +312,49 @@ FEW = {"few_llama": dict(synth.SHAPES["tiny"], batch=1, seq=24),        # 24 tok
        "few_opt": dict(synth.SHAPES["tiny_opt"], batch=2, seq=32)}      # 64 tokens: two token tiles
 
 
+def _step_hidden(dm, tok, seed, eps, stride=None):
+    """Final hidden states [B*S, d] of both passes of a stacked step (eta = 0), read from where the lm_head takes them:
+    the second tensor of the workspace.  stride: row at which the second pass starts (its first row, or a tile's)."""
+    B, S = tok.shape
+    d, M1 = dm.shape["d_model"], B * S
+    stride = stride or M1
+    res = qb.read_step_result(dm.step(tok, seed, eps, 0.0, 100.0))
+    nbytes = (stride + M1) * d * 2
+    off = (nbytes + 255) // 256 * 256
+    h = dm._ws[off:off + nbytes].clone().view(torch.bfloat16).view(stride + M1, d).float().cpu().numpy().astype(np.float64)
+    return res, (h[:M1], h[stride:])
+
+
+def _hidden(dm, tok, seed, eps, sign):
+    B, S = tok.shape
+    hid = torch.zeros((B * S, dm.shape["d_model"]), dtype=torch.bfloat16, device=DEV)
+    loss = torch.zeros(1, dtype=torch.float32, device=DEV)
+    qb.qzo_debug_forward(dm.handle, tok, seed, eps, sign, dm.workspace(B, S), loss, hid)
+    return hid.float().cpu().numpy().astype(np.float64)
+
+
+def _rms(a):
+    return math.sqrt((a ** 2).mean())
+
+
+def _hidden_bounds(oracle, om, tok, se):
+    """Reference hidden states [B*S, d] and what a device result may be off them, root mean square and largest: see
+    test_forward_matches_oracle."""
+    _, ref = oracle.forward_loss(om, se, tok, act_bf16=True, want_hidden=True)
+    _, exact = oracle.forward_loss(om, se, tok, act_bf16=False, want_hidden=True)
+    ref, exact = (np.asarray(a).reshape(tok.size, -1) for a in (ref, exact))
+    rms = _rms(ref)
+    return ref, 2 * _rms(exact - ref) + 2e-3 * rms, 3 * np.abs(exact - ref).max() + 2e-2 * rms
+
+
+def _check_both_passes(oracle, om, tok, seed, eps, both):
+    """Each pass's hidden states against the oracle's for its own sign, element by element, and far from the other's."""
+    want = [_hidden_bounds(oracle, om, tok, oracle.perturbed_scales(om, seed, sign * np.float32(eps))) for sign in (1, -1)]
+    for h, (ref, rms_bound, max_bound), (other, _, _) in ((both[0], want[0], want[1]), (both[1], want[1], want[0])):
+        assert _rms(h - ref) <= rms_bound and np.abs(h - ref).max() <= max_bound, (_rms(h - ref), rms_bound, np.abs(h - ref).max(), max_bound)
+        assert _rms(h - other) > 5 * _rms(h - ref), (_rms(h - other), _rms(h - ref))
+
+
 @pytest.mark.parametrize("name,gain", [("tiny", 1.0), ("tiny_opt", 1.0), ("tiny", 4.0), ("tiny_opt", 4.0),
                                        ("sharp", 4.0), ("few_llama", 4.0), ("few_opt", 4.0),
                                        ("tiny+zp", 4.0), ("tiny_opt+zp", 4.0), ("sharp+zp", 4.0),
@@ -508,6 +551,42 @@ def test_nf4_stacked_passes_match_separate_passes(oracle, name, batch, seq):
         assert abs(got[k] - single) <= 2e-3 * single, (k, got[k], single)
         assert abs(got[k] - want[k]) <= 2e-2 * want[k], (k, got[k], want[k])
     assert got["loss_plus"] != got["loss_minus"]
+    # the losses of the two signs are closer than those bounds; their hidden states at a larger eps are not
+    _, both = _step_hidden(dm, _dev(tok), 21, 1e-2, -(-tok.size // 256) * 256)
+    _check_both_passes(oracle, om, tok, 21, 1e-2, both)
+    # what is left in the workspace: the last linear's two matrices, bit for bit those of a single expansion with either
+    # sign (the row table of the rotary embedding, the noise of every scale and the matrices end the workspace)
+    d, F, llama = shape["d_model"], shape["d_ffn"], shape["arch"] == "llama"
+    up = lambda n: -(-n // 256) * 256
+    wide = max(3 * d * d, (2 if llama else 1) * F * d)
+    tail = (up(seq * (d // shape["n_heads"] // 2) * 8) if llama else 0) + up(dm.scales.numel() * 4) + up(4 * wide)
+    pair = dm._ws[dm._ws.numel() - tail:][:4 * d * F].view(torch.bfloat16).view(2, d, F)
+    rows = 4 * d + (2 if llama else 1) * F
+    w = torch.empty(d, F, dtype=torch.bfloat16, device=DEV)
+    scratch = torch.empty(d, F // 64, dtype=torch.float32, device=DEV)
+    q = dm.tensors[-3] if llama else dm.tensors[-5]
+    for i, sign in enumerate((1, -1)):
+        qb.qzo_nf4_expand(q, dm.scales[-d * (F // 64):].view(d, F // 64), (shape["n_layers"] - 1) * (rows + d) + rows, 21, 1e-2, sign, scratch, w)
+        assert torch.equal(pair[i].view(torch.int16), w.view(torch.int16))
+    dm.close()
+
+
+def test_nf4_stacked_passes_with_a_column_tail_match_separate_passes():
+    """4096 NormalFloat-4 tokens at d_model 1024: the 32 x 12 tiles of the stacked qkv linear are one and a half rounds of the
+    chip, so its last columns are cut along K, from both passes' matrices; a single pass (16 x 12 tiles) has no such
+    tail.  Hidden states of each pass against the single pass of its sign: the same matrices, sums in another order;
+    bounded by what half the batch, whose linears cut K differently again, moves a single pass by (twice that)."""
+    shape = dict(synth.SHAPES["opt-1.3b"], n_layers=1, d_model=1024, n_heads=16, d_ffn=4096, vocab=600, max_seq=512)
+    dm = DeviceModel.synthetic(shape, 5, DEV, nf4=True)
+    dm.scales.mul_(0.3)                       # attention logits of a few units, not of dozens: see the test of the weights
+    tok = torch.from_numpy(synth.tokens(dict(shape, batch=8, seq=512), 5678)).to(DEV)
+    _, both = _step_hidden(dm, tok, 9, 6e-3, 4096)
+    want = [_hidden(dm, tok, 9, 6e-3, sign) for sign in (1, -1)]
+    order = _rms(_hidden(dm, tok[:4].contiguous(), 9, 6e-3, 1) - want[0][:2048])
+    for h, w, other in ((both[0], want[0], want[1]), (both[1], want[1], want[0])):
+        print("apart", _rms(h - w), "order", order, "passes apart", _rms(w - other))
+        assert 0 < _rms(h - w) <= 2 * order and np.abs(h - w).max() <= 0.1 * np.abs(w).max()
+        assert _rms(h - other) > 20 * _rms(h - w)
     dm.close()
 
 
@@ -725,13 +804,16 @@ def test_some_dozen_to_a_few_hundred_tokens(oracle, base, var, batch, seq):
     row blocks that end inside the matrix, partly filled and missing token tiles, two and four tiles per workgroup,
     items that one range covers and that several share.  Losses against the oracle (bf16 forward: 2e-2 as for the
     other routes) and against two single passes on the expanded weights (bf16 noise of a mean over the tokens; NormalFloat-4: the same
-    kernel on one pass)."""
+    kernel on one pass).  The hidden states of both passes against the oracle's, element by element (the mean losses of
+    the two signs are closer than the bounds on them, and a few wrong rows vanish in a mean)."""
     shape = dict(base, batch=batch, seq=seq)
     om, dm = _models(oracle, shape, 1234, 4.0 if base["d_model"] < 1024 else 1.0, **_variant_args(var))
     tok = synth.tokens(shape, 5678)
     tokd = _dev(tok)
     got = qb.read_step_result(dm.step(tokd, 21, 1e-3, 0.0, 100.0))       # eta = 0: scales untouched
     want = oracle.qzo_step(om, tok, seed=21, eps=1e-3, eta=0.0, Cthr=100.0)
+    _, both = _step_hidden(dm, tokd, 21, 1e-2)
+    _check_both_passes(oracle, om, tok, 21, 1e-2, both)
     if var != "nf4":
         dm.set_int4_path(2)
     single = [float(dm.forward_loss(tokd, 21, 1e-3, sign).item()) for sign in (1, -1)]
@@ -740,31 +822,6 @@ def test_some_dozen_to_a_few_hundred_tokens(oracle, base, var, batch, seq):
         assert abs(got[k] - other) <= 5e-3 * other, (k, got[k], other)
     assert got["loss_plus"] != got["loss_minus"]
     dm.close()
-
-
-def _step_hidden(dm, tok, seed, eps, stride=None):
-    """Final hidden states [B*S, d] of both passes of a stacked step (eta = 0), read from where the lm_head takes them:
-    the second tensor of the workspace.  stride: row at which the second pass starts (its first row, or a tile's)."""
-    B, S = tok.shape
-    d, M1 = dm.shape["d_model"], B * S
-    stride = stride or M1
-    res = qb.read_step_result(dm.step(tok, seed, eps, 0.0, 100.0))
-    nbytes = (stride + M1) * d * 2
-    off = (nbytes + 255) // 256 * 256
-    h = dm._ws[off:off + nbytes].clone().view(torch.bfloat16).view(stride + M1, d).float().cpu().numpy().astype(np.float64)
-    return res, (h[:M1], h[stride:])
-
-
-def _hidden(dm, tok, seed, eps, sign):
-    B, S = tok.shape
-    hid = torch.zeros((B * S, dm.shape["d_model"]), dtype=torch.bfloat16, device=DEV)
-    loss = torch.zeros(1, dtype=torch.float32, device=DEV)
-    qb.qzo_debug_forward(dm.handle, tok, seed, eps, sign, dm.workspace(B, S), loss, hid)
-    return hid.float().cpu().numpy().astype(np.float64)
-
-
-def _rms(a):
-    return math.sqrt((a ** 2).mean())
 
 
 @pytest.mark.parametrize("base,F,batch,seq", [(MID_LLAMA, 2048, 1, 57), (MID_LLAMA, 640, 1, 7), (MID_LLAMA, 640, 4, 24),
