@@ -426,6 +426,17 @@ qzo_status qzo_model_set_int4_path(qzo_model* m, int mode);
 qzo_status qzo_debug_bf16_gemm(const void* x_dev, const void* w_dev, uint32_t M, uint32_t N, uint32_t K,
                                int pipe, void* y_dev, void* stream);
 
+/* Inspection: the end of a K-split linear into the residual stream.  part_dev fp32 [slices, M, N]; the slices are added
+ * in order, bias_dev (bf16 [N], nullable) and resid_dev (bf16 [M,N]) added, y_dev bf16 [M,N] written (it may be
+ * resid_dev), and the norm that follows it in the model, RMSNorm with gain_dev bf16 [N] or, with norm_bias_dev given,
+ * LayerNorm, written to out_dev bf16 [M,N] with the block sums of its output to xsum_dev (fp32 [N/128][M], nullable).
+ * joined = 0: as two launches; 1: as the models do, in one launch where their rule says so (*joined_out, host, tells).
+ * N a multiple of 128, slices >= 1, slices*M*N below 2^31 elements, pointers 16-byte aligned. */
+qzo_status qzo_debug_reduce_norm(const float* part_dev, uint32_t slices, uint32_t M, uint32_t N, const void* bias_dev,
+                                 const void* resid_dev, const void* gain_dev, const void* norm_bias_dev, float eps,
+                                 int joined, void* y_dev, void* out_dev, float* xsum_dev, uint32_t* joined_out,
+                                 void* stream);
+
 /* Measurement aid, not part of the method: one 512-thread workgroup per compute unit, each
  * wavefront issuing iters x 16 v_mfma_f32_32x32x16_bf16 (32768 flop each) on register operands
  * that are all zero (random_operands = 0) or pseudo-random bf16 values, with no memory traffic.

@@ -30,7 +30,7 @@ EXPORTS = [
     "qzo_nf4_expand", "qzo_nf4_scratch_bytes", "qzo_nf4_gemm",
     "qzo_codebook_scratch_bytes", "qzo_codebook_gemm", "qzo_apply_update_channel",
     "qzo_debug_philox", "qzo_debug_normal_pairs", "qzo_debug_normals", "qzo_debug_dequant", "qzo_debug_dequant_zp",
-    "qzo_debug_forward", "qzo_debug_bf16_gemm", "qzo_debug_mfma_rate",
+    "qzo_debug_forward", "qzo_debug_bf16_gemm", "qzo_debug_reduce_norm", "qzo_debug_mfma_rate",
     "qzo_profile_begin", "qzo_profile_collect", "qzo_profile_stride",
     "qzo_last_error",
 ]
@@ -344,6 +344,16 @@ def qzo_debug_bf16_gemm(x, w, y, pipe=2, stream=None):
     N = w.shape[0]
     _check(lib().qzo_debug_bf16_gemm(_ptr(x), _ptr(w), C.c_uint32(M), C.c_uint32(N), C.c_uint32(K),
                                      C.c_int(pipe), _ptr(y), _stream(stream)))
+
+
+def qzo_debug_reduce_norm(part, bias, resid, gain, norm_bias, eps, joined, y, out, xsum=None, stream=None) -> bool:
+    """Returns whether the reduction and the norm ran as one launch."""
+    slices, M, N = part.shape
+    done = C.c_uint32(0)
+    _check(lib().qzo_debug_reduce_norm(_ptr(part), C.c_uint32(slices), C.c_uint32(M), C.c_uint32(N), _ptr(bias),
+                                       _ptr(resid), _ptr(gain), _ptr(norm_bias), C.c_float(eps), C.c_int(int(joined)),
+                                       _ptr(y), _ptr(out), _ptr(xsum), C.byref(done), _stream(stream)))
+    return bool(done.value)
 
 
 def qzo_debug_dequant_zp(q, s, zp, row_base, seed, eps, sign, w_eff, group=128, stream=None):

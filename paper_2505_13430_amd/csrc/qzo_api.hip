@@ -1283,6 +1283,30 @@ qzo_status qzo_debug_bf16_gemm(const void* x_dev, const void* w_dev, uint32_t M,
   return QZO_OK;
 }
 
+qzo_status qzo_debug_reduce_norm(const float* part_dev, uint32_t slices, uint32_t M, uint32_t N, const void* bias_dev,
+                                 const void* resid_dev, const void* gain_dev, const void* norm_bias_dev, float eps,
+                                 int joined, void* y_dev, void* out_dev, float* xsum_dev, uint32_t* joined_out,
+                                 void* stream) {
+  if (!part_dev || !resid_dev || !gain_dev || !y_dev || !out_dev || !joined_out) return fail(QZO_ERR_ARG, "null pointer");
+  if (!aligned16(part_dev) || !aligned16(bias_dev) || !aligned16(resid_dev) || !aligned16(gain_dev) ||
+      !aligned16(norm_bias_dev) || !aligned16(y_dev) || !aligned16(out_dev) || !aligned16(xsum_dev))
+    return fail(QZO_ERR_ALIGN, "device pointer not 16-byte aligned");
+  if (M == 0 || N == 0 || N % 128 || slices == 0 || (uint64_t)slices * M * N >= (1ull << 31))
+    return fail(QZO_ERR_SHAPE, "need M >= 1, N a positive multiple of 128, slices >= 1, slices*M*N below 2^31");
+  hipStream_t st = (hipStream_t)stream;
+  NextNorm nn = {gain_dev, norm_bias_dev, eps, out_dev, xsum_dev, false};
+  GemmArgs g = {};
+  g.bias = bias_dev; g.resid = resid_dev; g.y = y_dev; g.M = M; g.N = N;
+  g.epi = EPI_RESIDUAL | (bias_dev ? EPI_BIAS : 0u);
+  g.next = joined ? &nn : nullptr;
+  QZO_HIP(launch_partial_reduce(g, part_dev, slices, st));
+  *joined_out = nn.done ? 1u : 0u;
+  if (!nn.done)
+    QZO_HIP(norm_bias_dev ? launch_layernorm(y_dev, gain_dev, norm_bias_dev, M, N, eps, out_dev, st, xsum_dev)
+                          : launch_rmsnorm(y_dev, gain_dev, M, N, eps, out_dev, st, xsum_dev));
+  return QZO_OK;
+}
+
 qzo_status qzo_apply_update_channel(void* c_dev, uint32_t n_rows, uint32_t row_base, uint64_t seed,
                                     float eta, float d_clipped, void* stream) {
   if (!c_dev) return fail(QZO_ERR_ARG, "c_dev is null");

@@ -867,6 +867,49 @@ def test_nf4_weights_are_the_same_at_any_token_count(oracle, base, F, batch, seq
     dm.close()
 
 
+@pytest.mark.parametrize("layernorm", [False, True])
+@pytest.mark.parametrize("M,N,slices", [(1, 128, 1), (2, 384, 3), (33, 2048, 5), (128, 4096, 4), (512, 4096, 2),
+                                        # more than one item of four features per thread
+                                        (256, 4224, 3), (300, 5120, 3), (256, 8192, 2), (512, 8064, 2)])
+def test_reduction_and_norm_in_one_launch_equal_two(M, N, slices, layernorm):
+    """Same partial sums through the joined launch and through the reduction and the norm kernel: the residual stream, the
+    norm's output and its block sums, bit for bit, the residual stream updated in place."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(M * N + slices)
+
+    def rand(*sz):
+        return torch.randn(*sz, generator=gen, device=DEV)
+
+    part = rand(slices, M, N)
+    h0, gain = rand(M, N).to(torch.bfloat16), (rand(N) + 1).to(torch.bfloat16)
+    bias, nbias = (rand(N).to(torch.bfloat16), rand(N).to(torch.bfloat16)) if layernorm else (None, None)
+    got = []
+    for joined in (False, True):
+        h = h0.clone()
+        out, xsum = torch.zeros_like(h), torch.zeros(N // 128, M, device=DEV)
+        assert qb.qzo_debug_reduce_norm(part, bias, h, gain, nbias, 1e-5, joined, h, out, xsum) == joined
+        got.append((h, out, xsum))
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
+                           b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32))
+    # and they are what they should be (bf16 outputs of fp32 sums)
+    want = h0.double() + part.double().sum(0) + (bias.double() if layernorm else 0)
+    assert (got[1][0].double() - want).abs().max() <= 2 ** -8 * want.abs().max()
+    x = got[1][0].double()
+    x = x - x.mean(1, keepdim=True) if layernorm else x
+    y = x / (x.pow(2).mean(1, keepdim=True) + 1e-5).sqrt() * gain.double() + (nbias.double() if layernorm else 0)
+    assert ((got[1][1].double() - y).abs() <= 2 ** -8 * y.abs() + 1e-5).all()
+    assert torch.allclose(got[1][2].t().double(), got[1][1].double().view(M, N // 128, 128).sum(2), atol=1e-3)
+
+
+@pytest.mark.parametrize("M,N", [(513, 4096), (255, 4224), (300, 8320)])
+def test_reduction_and_norm_stay_two_launches_outside_the_rule(M, N):
+    h, part = torch.zeros(M, N, dtype=torch.bfloat16, device=DEV), torch.ones(2, M, N, device=DEV)
+    gain, out = torch.ones(N, dtype=torch.bfloat16, device=DEV), torch.zeros(M, N, dtype=torch.bfloat16, device=DEV)
+    assert not qb.qzo_debug_reduce_norm(part, None, h, gain, None, 0.0, True, h, out)
+    assert (h == 2).all() and (out == 1).all()
+
+
 def test_failing_calls_enqueue_nothing(oracle):
     """Every error that the library finds itself (anything but a failing HIP call) is found before
     the first launch: outputs, workspace and scales are untouched afterwards."""
