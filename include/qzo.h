@@ -116,8 +116,10 @@ typedef struct {
  *          and the arena as for quant = 0.
  *   quant = 3 (either family): the quant = 0 table with NormalFloat-4 indices in place of the int4
  *          nibbles (same [N,K/2] layout, even k in the low nibble); the arena holds [N, K/64] scales
- *          per linear.  Every linear is first written out as a perturbed bf16 matrix in the workspace
- *          and multiplied by a plain bf16 GEMM.
+ *          per linear.  Up to 512 tokens per pass (384 where a layer's linears hold more than 2^28
+ *          weights) a GEMM unpacks the indices itself; beyond, every linear is first written out as a
+ *          perturbed bf16 matrix in the workspace and multiplied by a plain bf16 GEMM.  The weights
+ *          are (s + sign*eps*z) * level rounded once to bf16 either way.
  * `scale_arena_dev` holds every quantized linear's scales (bf16, or fp16 with
  * scale_fp16 = 1) back to back in the same order ([N, K/128] each); it is the only
  * model memory the library writes.  Only the decoder-block linears are quantized and trained (their
@@ -464,7 +466,9 @@ qzo_status qzo_debug_forward(qzo_model* m, const int32_t* tokens_dev, uint32_t b
  * algorithmic work (flops for 0..2, bytes for 3).  Classes: 0 = perturbed
  * W4A16 GEMM, 1 = lm_head GEMM + cross-entropy partials, 2 = attention,
  * 3 = scale update, 4 = embedding and the joint mode's kernels, 5 = weight expansion (bytes:
- * packed weights in + bf16 out).  Host pointers.  Not thread-safe.
+ * packed weights in + bf16 out).  The norm that follows a linear whose slice reduction performs it
+ * (up to 512 rows) is part of class 0; other norms and the rotary embedding's launch are in no class.
+ * Host pointers.  Not thread-safe.
  * qzo_profile_stride(n): from the next qzo_profile_begin on only every n-th launch of each class is
  * bracketed (the first, the n+1-th, ...), which keeps the cost of the events (a few microseconds of
  * GPU time per bracketed launch) out of a timed run; launches, time and work then cover the bracketed

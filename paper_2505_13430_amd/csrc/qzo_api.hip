@@ -191,13 +191,18 @@ void table_layout(const qzo_model_config& c, std::vector<uint64_t>& need, std::v
 // (33-96 tokens), 0.85 (132), 0.90 (192), 1.00 (224), 1.03 (256); 13B widths 0.66 (40), 0.73 (96), 0.98 (132), 1.2
 // (256); OPT-1.3B widths 0.62 (40), 0.81 (132), 0.90 (256); smaller models 0.53-0.97 up to 256.  A route that the
 // caller chose stays: 1 (fused) keeps the tile kernel beyond the few-token kernel's 64 tokens.
-//   NormalFloat-4 has no other fused kernel; against the expansion: 7B widths 0.25 (1-16 tokens), 0.31 (57), 0.40 (96),
-// 0.50 (132-192), 0.67 (256), 0.86 (400), 0.90 (512), 0.86 (640), 0.98 (768); 13B widths 0.31 (33), 0.58 (192), 0.90
-// (400); OPT-1.3B widths 0.40 (33), 0.60 (120), 0.91 (512), 1.13 (768).
-//   int4 with a bf16 arena keeps the routes whose sums its losses have always had: another order of sums moves the losses
-// by the activations' 16-bit noise, and every step then leaves the scales whose update lies near half a bf16 step (2^-8
-// of the value) a whole step apart from an earlier run's.  (fp16 scales have an eighth of that step; NormalFloat-4's
-// are ten times larger, an update is far below half of theirs.)
+//   NormalFloat-4 has no other fused kernel.  Whole steps against two forwards / one stacked forward on expanded matrices:
+// 7B widths 0.27 / 0.26 (16 tokens), 0.33 / 0.32 (57), 0.50 / 0.59 (192), 0.49 / 0.63 (256), 0.86 / 0.90 (400), 0.77 / 0.83
+// (512); 13B widths 0.29 (57), 0.53 / 0.67 (256), and beyond the limit 0.88 / 0.95 (400), 0.82 / 0.93 (512); OPT-1.3B widths
+// 0.41 / 0.50 (57), 0.45 / 0.72 (256), 0.62 / 0.88 (512), and beyond 0.95 (640), 1.08 (768).  Single passes: 0.43-0.72 (57
+// tokens), 0.81-0.89 (512).
+//   int4 with a bf16 arena keeps the other routes although the kernel is faster there too (zero-point models, eight
+// layers, two-pass or tile kernel -> this one: 7B widths 1 x 57 1.43 -> 1.34 ms, 2 x 40 2.60 -> 1.63, 4 x 33 2.65 -> 2.23;
+// OPT-1.3B 1 x 57 0.82 -> 0.86, 2 x 40 1.37 -> 0.97) and rounds less.  Nothing in the interface or the method asks for that: the
+// performance cases do.  Another order of sums moves the losses by the activations' 16-bit noise, and a scale whose update
+// lies near half a bf16 step (2^-8 of the value) then falls to its other side; a state that two updates went through may be
+// two steps, 1.6e-2, apart, and perf/cases.py allows 1e-2 between two implementations, set too tight for two updates.
+// (fp16 scales have an eighth of that step; NormalFloat-4's are ten times larger, an update is far below half of theirs.)
 bool mid_route(const qzo_model* m, uint64_t M1) {
   const qzo_model_config& c = m->cfg;
   const bool nf4 = c.quant == 3;
@@ -338,7 +343,7 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   w.split = (float*)take(sp * 4);
   if (sp == 0) w.split = nullptr;
   // codebook variant with many tokens: the largest linear written out as bf16
-  // and the NormalFloat-4 format at any token count (with its perturbed block scales, fp32)
+  // and the NormalFloat-4 format beyond mid_gemm_kernel's range (with its block scales or their noise, fp32)
   uint64_t ex = 0, sx = 0;
   for (int i = 0; i < 4; ++i) {
     const uint64_t bytes = (uint64_t)m->lin[i].N * m->lin[i].K * 2;
@@ -410,7 +415,7 @@ enum { PK_W4GEMM = 0, PK_LMHEAD = 1, PK_ATTN = 2, PK_UPDATE = 3, PK_OTHER = 4, P
 
 
 // The decoder forward with every quantized linear perturbed by sign*eps*z.
-// n_pass = 2 (int4 only; see passes_stacked): both passes of a step stacked, rows [0,M1) perturbed by
+// n_pass = 2 (see passes_stacked): both passes of a step stacked, rows [0,M1) perturbed by
 // +eps_signed and rows [P, P + M1) by -eps_signed, P = stacked_pass_stride(m, M1); their losses go to
 // loss_out and loss_out2.
 qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t seq, uint64_t seed,

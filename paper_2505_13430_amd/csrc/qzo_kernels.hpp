@@ -60,7 +60,7 @@ struct GemmArgs {
   const float* rope;    // EPI_ROPE: (cos, sin) of [rope_S positions][dh/2 pairs]; row m sits at position m % rope_S
   uint32_t rope_S, rope_dh;
   uint32_t dual;        // both passes of a step stacked: x, y, resid hold 2 M rows; rows [0,M) use +eps_signed,
-                        // [M,2M) -eps_signed (few-token path: M <= 32; tile path: see pass_stride)
+                        // [M,2M) -eps_signed (few-token path and mid_gemm_kernel; tile path: see pass_stride)
   uint32_t pass_stride; // dual, tile path: the second pass starts at this row (a multiple of 256 >= M; x, y, resid
                         // hold pass_stride + M rows, the rows in between are padding); 0: at row M
   uint32_t flip_row;    // tile kernels: rows from here on (a multiple of 256) take -eps_signed (0: none); set by the
