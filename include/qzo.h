@@ -179,8 +179,8 @@ qzo_status qzo_forward_loss(qzo_model* m, const int32_t* tokens_dev, uint32_t ba
  * tile kernel holds the token tiles of both passes, the second pass's with -eps and starting
  * on a 256-row tile boundary (padding rows in between); losses equal to two qzo_forward_loss
  * calls within the 16-bit activations' noise, the K split of a linear being a function of the
- * number of token tiles.  Zero-point models with fp16 scales (33 to 128 tokens; up to 192 or
- * 256 where a layer's linears hold at most 2^28 or 2^26 weights) and NormalFloat-4 models (up
+ * number of token tiles.  Zero-point models with fp16 scales (33 to 128 tokens, up to 192 where a
+ * layer's linears hold at most 2^28 weights; 65 to 256 where they hold at most 2^26) and NormalFloat-4 models (up
  * to 384 or 512 tokens) work in tiles of 32 tokens, each of one pass, with the same agreement;
  * NormalFloat-4 models beyond, up to 4096 tokens, in 256-row tiles on both passes' expanded
  * matrices where that is estimated to be faster than two forwards (the workspace then holds both

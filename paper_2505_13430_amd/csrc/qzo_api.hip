@@ -187,10 +187,12 @@ void table_layout(const qzo_model_config& c, std::vector<uint64_t>& need, std::v
 // Token counts per pass that take mid_gemm_kernel: NormalFloat-4, and zero-point int4 with fp16 scales beyond the
 // few-token kernel's stacked range.
 //   Its time grows by tiles of 32 tokens, the tile kernel's by tiles of 256, and the wider the layer the better the tile
-// kernel fills the chip.  Whole steps of zero-point models, mid_gemm_kernel's time over the other routes': 7B widths 0.65
-// (33-96 tokens), 0.85 (132), 0.90 (192), 1.00 (224), 1.03 (256); 13B widths 0.66 (40), 0.73 (96), 0.98 (132), 1.2
-// (256); OPT-1.3B widths 0.62 (40), 0.81 (132), 0.90 (256); smaller models 0.53-0.97 up to 256.  A route that the
-// caller chose stays: 1 (fused) keeps the tile kernel beyond the few-token kernel's 64 tokens.
+// kernel fills the chip.  Whole steps of zero-point models, mid_gemm_kernel's time over the tile kernel's: 7B widths 0.65
+// (96 tokens), 0.85 (132), 0.90 (192), 1.00 (224), 1.03 (256); 13B widths 0.73 (96), 0.98 (132), 1.2 (256); OPT-1.3B widths
+// 0.81 (132), 0.90 (256); smaller models 0.53-0.97 up to 256.  Up to 64 tokens, over the few-token kernel's with a workgroup
+// per pass: 7B widths 0.91-0.94, 13B 0.88-0.89, 2560 x 10240 and 3072 x 8192 0.93-0.96, but OPT-1.3B 1.01-1.04, 2048 x 5632
+// 1.05-1.07, smaller models 0.97-1.02: there the few-token kernel stays, whose losses are those of two separate passes.
+// A route that the caller chose stays: 1 (fused) keeps the tile kernel beyond the few-token kernel's 64 tokens.
 //   NormalFloat-4 has no other fused kernel.  Whole steps against two forwards / one stacked forward on expanded matrices:
 // 7B widths 0.27 / 0.26 (16 tokens), 0.33 / 0.32 (57), 0.50 / 0.59 (192), 0.49 / 0.63 (256), 0.86 / 0.90 (400), 0.77 / 0.83
 // (512); 13B widths 0.29 (57), 0.53 / 0.67 (256), and beyond the limit 0.88 / 0.95 (400), 0.82 / 0.93 (512); OPT-1.3B widths
@@ -210,6 +212,7 @@ bool mid_route(const qzo_model* m, uint64_t M1) {
   if (!nf4 && (M1 <= SKINNY_MAX_M_DUAL || m->int4_path == 2 || (m->int4_path == 1 && M1 > SKINNY_MAX_M))) return false;
   uint64_t weights = 0;
   for (int i = 0; i < 4; ++i) weights += (uint64_t)m->lin[i].N * m->lin[i].K;
+  if (!nf4 && M1 <= SKINNY_MAX_M && weights <= (1u << 26)) return false;
   const uint32_t most = nf4 ? (weights <= (1u << 28) ? 512u : 384u)
                             : (weights <= (1u << 26) ? 256u : (weights <= (1u << 28) ? 192u : 128u));
   if (M1 > most) return false;

@@ -460,7 +460,8 @@ def test_step_matches_oracle(oracle, name):
     dm.close()
 
 
-@pytest.mark.parametrize("name,batch,seq", [("tiny", 1, 33), ("tiny_opt", 3, 19), ("tiny+zp", 1, 64)])
+@pytest.mark.parametrize("name,batch,seq", [("tiny", 1, 33), ("tiny_opt", 3, 19), ("tiny+zp", 1, 64),
+                                            ("tiny+zp16", 1, 57)])
 def test_stacked_workgroups_of_either_pass_equal_separate_passes(oracle, name, batch, seq):
     """33 to 64 tokens per pass: a launch of the few-token kernel holds workgroups of both passes, each with the
     arithmetic of a launch of its own: losses bit-identical to two separate forward passes."""
@@ -795,12 +796,13 @@ MID_7B = dict(synth.SHAPES["llama-2-7b"], n_layers=1, vocab=1000)
 
 
 @pytest.mark.parametrize("base,var,batch,seq", [
-    (MID_LLAMA, "zp16", 1, 33), (MID_OPT, "zp16", 1, 57), (MID_LLAMA, "zp16", 4, 24), (MID_LLAMA, "zp16", 3, 43),
+    (MID_LLAMA, "zp16", 1, 33), (MID_OPT, "zp16", 1, 57), (MID_OPT, "zp16", 2, 33), (MID_LLAMA, "zp16", 4, 24), (MID_LLAMA, "zp16", 3, 43),
     (MID_LLAMA, "zp16", 3, 61), (MID_OPT, "zp16", 4, 48), (MID_OPT, "zp16", 4, 64), (MID_7B, "zp16", 1, 57),
     (MID_7B, "zp16", 4, 45), (MID_LLAMA, "nf4", 1, 7), (MID_OPT, "nf4", 1, 57), (MID_LLAMA, "nf4", 3, 43),
     (MID_OPT, "nf4", 8, 63), (MID_7B, "nf4", 3, 45)])
 def test_some_dozen_to_a_few_hundred_tokens(oracle, base, var, batch, seq):
-    """Zero-points with fp16 scales, 33 to 256 tokens per pass (NormalFloat-4: 1 to 512), both passes stacked in tiles of 32 tokens: odd numbers of groups (K = 384, 640),
+    """Zero-points with fp16 scales, 33 (in narrow layers 65; below, the few-token kernel) to 256 tokens per pass
+    (NormalFloat-4: 1 to 512), both passes stacked in tiles of 32 tokens: odd numbers of groups (K = 384, 640),
     row blocks that end inside the matrix, partly filled and missing token tiles, two and four tiles per workgroup,
     items that one range covers and that several share.  Losses against the oracle (bf16 forward: 2e-2 as for the
     other routes) and against two single passes on the expanded weights (bf16 noise of a mean over the tokens; NormalFloat-4: the same
