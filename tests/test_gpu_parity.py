@@ -791,7 +791,7 @@ def test_real_width_one_layer_stacked_tile_step(oracle, name, asym):
 MID_LLAMA = dict(arch="llama", n_layers=2, d_model=384, n_heads=3, d_ffn=640, vocab=300, max_seq=64)
 MID_OPT = dict(arch="opt", n_layers=2, d_model=384, n_heads=6, d_ffn=640, vocab=300, max_seq=64)
 WIDE_OPT = dict(synth.SHAPES["opt-1.3b"], vocab=600)
-WIDE_LLAMA = dict(arch="llama", d_model=2048, n_heads=16, vocab=600, max_seq=64)
+WIDE_LLAMA = dict(arch="llama", d_model=2176, n_heads=17, vocab=600, max_seq=64)      # 17 and 45 groups, 8.5 and 25.5 row blocks
 MID_7B = dict(synth.SHAPES["llama-2-7b"], n_layers=1, vocab=1000)
 
 
@@ -829,7 +829,7 @@ def test_some_dozen_to_a_few_hundred_tokens(oracle, base, var, batch, seq):
 @pytest.mark.parametrize("base,F,batch,seq", [(MID_LLAMA, 2048, 1, 57), (MID_LLAMA, 640, 1, 7), (MID_LLAMA, 640, 4, 24),
                                               (MID_OPT, 640, 3, 43), (MID_OPT, 2048, 8, 63),
                                               # wide enough for four tiles a block: passes apart, and both in a block
-                                              (WIDE_OPT, 8192, 4, 60), (WIDE_OPT, 8192, 4, 50), (WIDE_LLAMA, 5632, 5, 51)])
+                                              (WIDE_OPT, 8192, 4, 60), (WIDE_OPT, 8192, 4, 50), (WIDE_LLAMA, 5760, 5, 51), (WIDE_LLAMA, 5760, 4, 60)])
 def test_nf4_weights_are_the_same_at_any_token_count(oracle, base, F, batch, seq):
     """NormalFloat-4 weights are (s + sigma eps z) * level rounded once, whatever the route.  The hidden states of a few
     sequences (unpacked in the GEMM; both passes in a token block, a pass each, two and four tiles a block) against
