@@ -235,8 +235,10 @@ qzo_status qzo_model_apply_update(qzo_model* m, uint64_t seed, float eta, float 
  * the bf16-rounded outputs.  Requires group == 128, K % 128 == 0, N % 8 == 0.
  * scratch_dev: qzo_linear_scratch_bytes(M, N, K, sumsq_dev != NULL) bytes of caller-owned
  * device memory, 256-byte aligned (may be NULL when that size is 0), contents undefined
- * afterwards; calls that share a scratch buffer must not overlap.  It holds the per-tile
- * partial sums of sum y^2 and the K-slice partial sums of the two paths below.
+ * afterwards; calls that share a scratch buffer must not overlap.  It holds the
+ * partial sums of sum y^2 and the K-slice partial sums of the two paths below.  (Where the partial sums are all there is,
+ * up to 256 floats, one per 256 x 256 output tile, rounded up to 256 bytes, are accepted too: the outputs are the same,
+ * small calls take longer.)
  * With M <= 64 the call takes the few-token path (the paper's batch-1 memory
  * profile and short-prompt batches, Sec. 4.3): the int4 weights are streamed once and
  * enter the matrix unit as integer codes, each 128-wide group's sum is scaled by the

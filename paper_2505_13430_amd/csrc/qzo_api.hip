@@ -952,18 +952,25 @@ qzo_status qzo_apply_update(void* s_dev, uint32_t n_rows, uint32_t G, uint32_t r
   return QZO_OK;
 }
 
-// Scratch of a single perturbed linear: [per-tile sums of y^2][K-slice partial sums], each part
-// rounded up to 256 bytes.
-struct LinearScratch { uint32_t tiles; uint64_t part_floats; uint64_t part_off, total; bool skinny, split; };
+// Scratch of a single perturbed linear: [partial sums of y^2][K-slice partial sums], each part rounded up to 256 bytes.
+// total: what a call needs, with one sum per 256 x 256 tile; best: with one per workgroup of the tile height that is
+// fastest (lower tiles, more of them), which a call uses where its scratch has that room.
+struct LinearScratch { uint32_t parts, best_parts; uint64_t part_floats; uint64_t part_off, total, best; bool skinny, split; };
 static LinearScratch linear_scratch(uint32_t M, uint32_t N, uint32_t K, bool with_sumsq) {
   LinearScratch ls = {};
   if (M == 0 || N == 0) return ls;
   ls.skinny = M <= SKINNY_MAX_M;
   ls.split = !ls.skinny && tile_ksplit(M, N, K, nullptr) > 1;     // too few tiles for the chip
-  ls.tiles = (ls.skinny || ls.split) ? skinny_reduce_blocks(M, N, 0) : ((M + 255) / 256) * ((N + 255) / 256);
+  ls.parts = (ls.skinny || ls.split) ? skinny_reduce_blocks(M, N, 0) : ((M + 255) / 256) * ((N + 255) / 256);
   ls.part_floats = ls.skinny ? skinny_ws_floats(M, N, K) : (ls.split ? tile_split_ws_floats(M, N, K) : 0);
-  ls.part_off = with_sumsq ? up256((uint64_t)ls.tiles * 4) : 0;
+  ls.part_off = with_sumsq ? up256((uint64_t)ls.parts * 4) : 0;
   ls.total = ls.part_off + up256(ls.part_floats * 4);
+  ls.best = ls.total; ls.best_parts = ls.parts;
+  if (!ls.skinny && !ls.split && with_sumsq) {
+    ls.best_parts = std::max(ls.parts, w4_plan(M, 0, N, K, 1, 0, 0).wgs);
+    ls.best = up256((uint64_t)ls.best_parts * 4);
+    ls.parts = (uint32_t)(ls.total / 4);
+  }
   return ls;
 }
 
@@ -984,11 +991,11 @@ static qzo_status linear_check(const void* x_dev, const void* q_dev, const void*
   return QZO_OK;
 }
 
-// The launches of a single perturbed linear; scratch (ls.total bytes) is known to be large enough.
+// The launches of a single perturbed linear; scratch (scratch_bytes >= ls.total) is known to be large enough.
 static qzo_status dequant_gemm_run(const void* x_dev, const void* q_dev, const void* s_dev, const void* zp_dev,
                                    uint32_t scale_fp16, uint32_t row_base, uint32_t M, uint32_t N, uint32_t K, uint64_t seed,
                                    float eps, int sign, void* y_dev, float* sumsq_dev, void* scratch,
-                                   const LinearScratch& ls, hipStream_t st) {
+                                   uint64_t scratch_bytes, const LinearScratch& ls, hipStream_t st) {
   if (M == 0 || N == 0) {
     if (sumsq_dev) QZO_HIP(launch_sum_partials(nullptr, 0, sumsq_dev, st));
     return QZO_OK;
@@ -1005,9 +1012,12 @@ static qzo_status dequant_gemm_run(const void* x_dev, const void* q_dev, const v
   if (sumsq_dev) {
     g.epi = EPI_SUMSQ;
     g.partials = (float*)scratch;
+    g.n_partials = scratch_bytes >= ls.best ? ls.best_parts : ls.parts;
   }
   QZO_HIP(launch_w4a16_gemm(g, st));
-  if (sumsq_dev) QZO_HIP(launch_sum_partials((const float*)scratch, ls.tiles, sumsq_dev, st));
+  // one sum per block of the slice reduction, or per workgroup of the tile kernel
+  const uint32_t sums = (ls.skinny || ls.split) ? ls.parts : w4_plan(M, 0, N, K, 1, 0, g.n_partials).wgs;
+  if (sumsq_dev) QZO_HIP(launch_sum_partials((const float*)scratch, sums, sumsq_dev, st));
   return QZO_OK;
 }
 
@@ -1025,13 +1035,13 @@ static qzo_status dequant_gemm(const void* x_dev, const void* q_dev, const void*
     if (scratch_bytes < ls.total) return fail(QZO_ERR_WORKSPACE, "scratch too small: see qzo_linear_scratch_bytes");
   }
   return dequant_gemm_run(x_dev, q_dev, s_dev, zp_dev, scale_fp16, row_base, M, N, K, seed, eps, sign, y_dev,
-                          sumsq_dev, scratch_dev, ls, (hipStream_t)stream);
+                          sumsq_dev, scratch_dev, scratch_bytes, ls, (hipStream_t)stream);
 }
 
 qzo_status qzo_linear_scratch_bytes(uint32_t M, uint32_t N, uint32_t K, int with_sumsq, uint64_t* out) {
   if (!out) return fail(QZO_ERR_ARG, "out is null");
   if (K == 0 || K % 128) return fail(QZO_ERR_SHAPE, "K must be a positive multiple of 128");
-  *out = linear_scratch(M, N, K, with_sumsq != 0).total;
+  *out = linear_scratch(M, N, K, with_sumsq != 0).best;
   return QZO_OK;
 }
 
@@ -1081,7 +1091,7 @@ qzo_status qzo_dequant_gemm_static(const void* x_dev, const void* q_dev, const v
   }
   // nothing in the scratch has to start at zero: every partial sum that is read was written by this call
   return dequant_gemm_run(x_dev, q_dev, s_dev, nullptr, 0u, row_base, M, N, K, seed, eps, sign, y_dev, sumsq_dev,
-                          ptr, ls, (hipStream_t)stream);
+                          ptr, STATIC_SCRATCH_BYTES, ls, (hipStream_t)stream);
 }
 
 qzo_status qzo_dequant_gemm_zp(const void* x_dev, const void* q_dev, const void* s_dev,

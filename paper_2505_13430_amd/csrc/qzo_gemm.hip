@@ -1,18 +1,12 @@
-// W4A16 group-dequant GEMM with the Q-SPSA perturbation fused into the weight
-// tile (paper Eq. 4-5): Y[M,N] = X[M,K] * W_eff^T,
-//   W_eff[n,k] = (s[n,k/128] + sigma*eps*z(row_base+n, k/128)) * wbar[n,k],
-// bf16 MFMA (v_mfma_f32_32x32x16_bf16) with fp32 accumulation, for gfx950.
-// The same tiling serves the dense bf16 lm_head GEMM whose epilogue folds the
-// cross-entropy partial reductions instead of writing logits.
+// Tile GEMM on operands that need no unpacking (expanded bf16 weights, lm_head) or a gather (codebook), for gfx950:
+// bf16 MFMA (v_mfma_f32_32x32x16_bf16) with fp32 accumulation.  Also the int4 launcher: which route a perturbed W4A16
+// linear takes, K slices, column tails.  (The int4 kernel itself: qzo_w4.hip.)
 //
 // Tiling: 256x256 output tile per workgroup, BK = 64, eight wavefronts in a
 // 2 (M) x 4 (N) arrangement, each owning 128x64 = 4x2 MFMA tiles.  Both
 // operands are K-contiguous in LDS (128 B per row, 16-byte chunks XOR-swizzled
 // by row pair so that 16 lanes of a fragment read hit all 64 banks), double
-// buffered.  int4 weights are unpacked, scaled by the perturbed scale and
-// rounded to bf16 once per workgroup while being written to LDS; the noise z is
-// regenerated per row every eight groups from the Philox counter (row, g/8)
-// and never touches memory.
+// buffered.
 //
 // The weight tile is the MFMA's first operand and the activation tile its
 // second, so a lane of the result owns one token and four consecutive output
@@ -82,37 +76,6 @@ uint64_t tile_split_ws_floats(uint32_t M, uint32_t N, uint32_t K) {
   return 0;
 }
 
-// 8 nibbles of one dword -> 8 bf16 of (nibble-8)*se, in k order.  A byte holding
-// a nibble u (0..15) read as an fp8 E4M3 pattern is exactly u * 2^-9, so one
-// v_cvt_pk_f32_fp8 turns two nibbles into floats; fma(u 2^-9, 512 se, -8 se)
-// is (u-8)*se with a single rounding, the same bits as se * float(u-8).
-// With zero-points (ZP) the two parameters are the scale se and the negated zero-point:
-// fma(u 2^-9, 512, -zp) is the integer u - zp exactly and its product with se is rounded
-// once, the same bits as se * float(u - zp).
-template <bool ZP = false>
-__device__ __forceinline__ uint4 dequant8(uint32_t w, float se512, float m8se) {
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  const uint32_t lo = w & 0x0f0f0f0fu, hi = (w >> 4) & 0x0f0f0f0fu;
-  const f2 l01 = __builtin_amdgcn_cvt_pk_f32_fp8(lo, false);   // nibbles 0, 2
-  const f2 l23 = __builtin_amdgcn_cvt_pk_f32_fp8(lo, true);    // nibbles 4, 6
-  const f2 h01 = __builtin_amdgcn_cvt_pk_f32_fp8(hi, false);   // nibbles 1, 3
-  const f2 h23 = __builtin_amdgcn_cvt_pk_f32_fp8(hi, true);    // nibbles 5, 7
-  float e0, e1, e2, e3, e4, e5, e6, e7;
-  if (ZP) {
-    e0 = __builtin_fmaf(l01.x, 512.0f, m8se) * se512; e1 = __builtin_fmaf(h01.x, 512.0f, m8se) * se512;
-    e2 = __builtin_fmaf(l01.y, 512.0f, m8se) * se512; e3 = __builtin_fmaf(h01.y, 512.0f, m8se) * se512;
-    e4 = __builtin_fmaf(l23.x, 512.0f, m8se) * se512; e5 = __builtin_fmaf(h23.x, 512.0f, m8se) * se512;
-    e6 = __builtin_fmaf(l23.y, 512.0f, m8se) * se512; e7 = __builtin_fmaf(h23.y, 512.0f, m8se) * se512;
-  } else {
-    e0 = __builtin_fmaf(l01.x, se512, m8se); e1 = __builtin_fmaf(h01.x, se512, m8se);
-    e2 = __builtin_fmaf(l01.y, se512, m8se); e3 = __builtin_fmaf(h01.y, se512, m8se);
-    e4 = __builtin_fmaf(l23.x, se512, m8se); e5 = __builtin_fmaf(h23.x, se512, m8se);
-    e6 = __builtin_fmaf(l23.y, se512, m8se); e7 = __builtin_fmaf(h23.y, se512, m8se);
-  }
-  return make_uint4(pack_bf16x2(e0, e1), pack_bf16x2(e2, e3), pack_bf16x2(e4, e5),
-                    pack_bf16x2(e6, e7));
-}
-
 // 8 fp16 values -> 8 bf16 (round-to-nearest-even), same order.
 __device__ __forceinline__ uint4 half8_to_bf16(uint32_t __attribute__((ext_vector_type(4))) h) {
   typedef _Float16 h2 __attribute__((ext_vector_type(2)));
@@ -131,35 +94,30 @@ struct CeEpilogue {
 
 // NWN = wavefronts along N (2 along M): 4 -> 512 threads, each wavefront 128x64;
 // 2 -> 256 threads (one wavefront per SIMD, twice the registers), each 128x128.
-// QM = weight format: 0 int4 + per-group scales (perturbed in the weight tile), 1 plain bf16,
-// 2 codebook (one 16-bit code per 8 weights into an fp16 [65536,8] codebook, gathered into the
+// QM = weight format: 1 plain bf16, 2 codebook (one 16-bit code per 8 weights into an fp16 [65536,8] codebook, gathered into the
 // weight tile; the perturbed per-output-channel scale multiplies the accumulators).
 // PIPE = how a k-tile's instructions are ordered: 0 left to the compiler, 1 one interleaved
-// stream per wavefront with an explicit issue order, 2 alternating phases (see QZO_PP_TILE).
-// ZP (int4 only) = asymmetric groups: a.zp holds one zero-point byte per (row, group).
-template <int QM, bool CE, int NWN, int PIPE, bool ZP = false>
+// stream per wavefront with an explicit issue order, 3 direct-to-LDS staging.
+template <int QM, bool CE, int NWN, int PIPE>
 __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilogue ce) {
-  static_assert(!ZP || QM == 0, "zero-points belong to the int4 format");
-  constexpr bool W4 = QM == 0, CB = QM == 2, ROWMAP = W4 || CB;
-  constexpr bool SCHED = PIPE == 1, PP = PIPE == 2;
+  constexpr bool CB = QM == 2;
+  constexpr bool SCHED = PIPE == 1;
   // PIPE == 3 (plain bf16 weights): both operand tiles go from memory straight into the LDS
   // (buffer loads with the lds modifier); no staging registers, no LDS store instructions
   constexpr bool DTL = PIPE == 3;
   static_assert(!DTL || QM == 1, "direct-to-LDS staging is written for plain bf16 weights");
   static_assert(!CB || NWN == 4, "codebook staging is written for 512 threads");
-  static_assert(!PP || (NWN == 4 && W4), "the phase schedule is written for int4 weights, 512 threads");
   constexpr int THREADS = 128 * NWN;
   constexpr int TJ = 8 / NWN;                 // 32-wide feature tiles per wavefront
   constexpr int NA = 2048 / THREADS;          // 16-byte chunks of a 256x64 bf16 tile per thread
   constexpr int RSTEP = THREADS / 8;          // rows between a thread's consecutive chunks
-  constexpr int TPR = THREADS / 256;          // W4: threads per weight row
-  constexpr int NBQ = 2 / TPR;                // W4: 16-byte loads (32 nibbles) per thread
-  constexpr int NBC = 4 * NBQ;                // W4: bf16 chunks written per thread
+  constexpr int TPR = THREADS / 256;          // codebook: threads per weight row
+  constexpr int NBC = 8 / TPR;                // codebook: bf16 chunks written per thread
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  // Split-K (int4 and plain bf16 weights; a.ksplit > 1): a workgroup's unit of work is one K slice of an output tile,
+  // Split-K (plain bf16 weights; a.ksplit > 1): a workgroup's unit of work is one K slice of an output tile,
   // a.kt_per k-tiles (a multiple of 4, so slices start on an even group) from k-tile kt0 on; its
   // fp32 accumulators go to a.split_ws[slice][M][N] and a second kernel adds the slices.
-  constexpr bool SPLITK = (W4 || QM == 1) && !CE;
+  constexpr bool SPLITK = QM == 1 && !CE;
   const uint32_t ksplit = SPLITK ? max(a.ksplit, 1u) : 1u;
   const uint32_t real_tiles_n = (a.N + BN - 1) / BN;
   TileWalk walk = tile_walk_init(a.M, a.N, ksplit);
@@ -177,19 +135,14 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
   // tile, and the k advance is a scalar offset.
   // A (and dense B): 2048 16-byte chunks per tile, 4 per thread; 8 consecutive
   // threads cover one 128-byte row segment.
-  // W4: thread = (row t/2, half t%2): 16 bytes = 32 nibbles = 4 chunks.
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(a.x), 0, (int)((uint64_t)a.M * K * 2), 0x00020000);
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(a.w), 0,
-      (int)(W4 ? (uint64_t)a.N * (K >> 1) : (CB ? (uint64_t)a.N * (K >> 2) : (uint64_t)a.N * K * 2)),
+      (int)(CB ? (uint64_t)a.N * (K >> 2) : (uint64_t)a.N * K * 2),
       0x00020000);
   const __amdgpu_buffer_rsrc_t rcb = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(CB ? a.cb : a.x), 0, CB ? (65536 * 16) : 16, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void*>(W4 ? a.s : a.x), 0, (int)(W4 ? (uint64_t)a.N * (K >> 7) * 2 : 16), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void*>(ZP ? a.zp : a.x), 0, (int)(ZP ? (uint64_t)a.N * (K >> 7) : 16), 0x00020000);
   // Direct-to-LDS: a wavefront's load instruction fills 1 KB of LDS in lane order (8 rows of
   // 128 bytes), so the XOR swizzle is applied on the memory side: the lane that fills position
   // p of row r fetches chunk p ^ swizzle(r).
@@ -200,13 +153,12 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
                      (int)((uint64_t)a.N * K * 2), 0x00020000};
   const uint32_t lds_wave = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
                             __builtin_amdgcn_readfirstlane(wave) * 1024u;
-  uint32_t xo[NA], wo[NA], so = 0, gn_w4 = 0;
-  float eps_tile = a.eps_signed;      // stacked passes: token tiles from row a.flip_row on take -eps
+  uint32_t xo[NA], wo[NA];
   const uint32_t brow = t / TPR, bpart = t % TPR;
   // LDS offsets: rows t/8 + RSTEP i share their swizzle, so chunk i is a_lds + i * RSTEP rows.
   const uint32_t a_lds = lds_off(t >> 3, t & 7u);
-  uint32_t b_lds[ROWMAP ? NBC : 1];
-  if (ROWMAP) {
+  uint32_t b_lds[CB ? NBC : 1];
+  if (CB) {
 #pragma unroll
     for (int c = 0; c < NBC; ++c) b_lds[c] = lds_off(brow, bpart * NBC + c);
   }
@@ -217,45 +169,32 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
       const uint32_t row = (t >> 3) + RSTEP * i;                                             \
       const uint32_t c = DTL ? ((t & 7u) ^ ((row >> 1) & 7u)) : (t & 7u);                    \
       xo[i] = (min((TM) * BM + row, a.M - 1) * K + c * 8) * 2;                               \
-      if (!ROWMAP) wo[i] = (min((TN) * BN + row, a.N - 1) * K + c * 8) * 2;                  \
+      if (!CB) wo[i] = (min((TN) * BN + row, a.N - 1) * K + c * 8) * 2;                  \
     }                                                                                        \
-    const bool second_ = a.flip_row && (TM) * BM >= a.flip_row;                              \
-    eps_tile = second_ ? -a.eps_signed : a.eps_signed;                                       \
-    if (DTL) {                         /* plain GEMM: the second pass has a matrix of its own */ \
+    if (DTL) {                         /* stacked passes: the second one has a matrix of its own */ \
+      const bool second_ = a.flip_row && (TM) * BM >= a.flip_row;                            \
       const uint64_t wb_ = (uint64_t)(uintptr_t)a.w + (second_ ? a.w_flip : 0u);             \
       rw4[0] = (int)(uint32_t)wb_; rw4[1] = (int)(uint32_t)(wb_ >> 32);                      \
     }                                                                                        \
-    if (ROWMAP) {                                                                            \
+    if (CB) {                                                                                \
       /* fused SwiGLU: the tile's rows are 4 x (32 gate rows, 32 up rows of the same   */      \
       /* features), so a lane's two accumulators hold gate and up of one feature      */      \
-      gn_w4 = (a.epi & EPI_SWIGLU)                                                           \
+      const uint32_t gn_ = (a.epi & EPI_SWIGLU)                                              \
                   ? ((brow >> 5) & 1u) * (a.N >> 1) + (TN) * 128u + (brow >> 6) * 32u + (brow & 31u) \
                   : min((TN) * BN + brow, a.N - 1);                                          \
-      wo[0] = W4 ? gn_w4 * (K >> 1) + bpart * 16 : gn_w4 * (K >> 2) + bpart * 8;             \
-      so = gn_w4 * (K >> 7) * 2;                                                             \
+      wo[0] = gn_ * (K >> 2) + bpart * 8;                                                    \
     }                                                                                        \
-    if (SPLITK && kt0) { /* this slice's first k-tile: 128 B of activations, 32 B of nibbles, half a group */ \
+    if (SPLITK && kt0) {                                    /* this slice's first k-tile */  \
       _Pragma("unroll") for (int i = 0; i < NA; ++i) xo[i] += kt0 * (BK * 2);                \
-      if (W4) {                                                                              \
-        wo[0] += kt0 * (BK / 2);                                                             \
-        so += (kt0 >> 1) * 2;                                                                \
-      } else {                                                                               \
-        _Pragma("unroll") for (int i = 0; i < NA; ++i) wo[i] += kt0 * (BK * 2);              \
-      }                                                                                      \
+      _Pragma("unroll") for (int i = 0; i < NA; ++i) wo[i] += kt0 * (BK * 2);                \
     }                                                                                        \
   } while (0)
   QZO_TILE_PTRS(tile_m, tile_n);
 
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  u32x4 ra[NA], rb[W4 ? NBQ : NA];
+  u32x4 ra[NA], rb[NA];
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-  u32x4 rbp[2];                      // phase schedule: weight quads of the next two tiles
   u32x2 rq = {0, 0};                 // codebook: the four codes of the next weight chunk
-  uint32_t zw[4] = {0, 0, 0, 0};     // Philox words of the current 8 groups
-  float z_odd = 0.0f;                // second variate of the current pair
-  float se512 = 0.0f, m8se = 0.0f;
-  bf16_t s_next = 0;
-  uint8_t z_next = 8;
 
   // LDS: A stage 0 | A stage 1 | B stage 0 | B stage 1, 32 KB each.  The k-loop is
   // unrolled by two so the stage is a compile-time constant and every LDS address is
@@ -273,10 +212,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
   } while (0)
 #define QZO_GLOAD_B(KT)                                                                      \
   do {                                                                                       \
-    if (W4) {                                                                                \
-      _Pragma("unroll") for (int q = 0; q < NBQ; ++q) rb[q] = __builtin_amdgcn_raw_buffer_load_b128( \
-          rw, (int)wo[0] + q * 16, (int)((KT) * (BK / 2)), 0);                               \
-    } else if (CB) { /* gather the 8-vectors of the codes read one tile earlier */           \
+    if (CB) { /* gather the 8-vectors of the codes read one tile earlier */                  \
       rb[0] = __builtin_amdgcn_raw_buffer_load_b128(rcb, (int)((rq.x & 0xffffu) << 4), 0, 0); \
       rb[1] = __builtin_amdgcn_raw_buffer_load_b128(rcb, (int)((rq.x >> 16) << 4), 0, 0);    \
       rb[2] = __builtin_amdgcn_raw_buffer_load_b128(rcb, (int)((rq.y & 0xffffu) << 4), 0, 0); \
@@ -319,38 +255,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
     __syncthreads();                                                                         \
   } while (0)
 
-// New perturbed scale for group G_ (every two k-tiles): s + (sigma*eps)*z as one
-// fp32 fma.  One Philox counter (row, G_/8) serves 8 groups; its four words are
-// kept and each word's Box-Muller pair is evaluated when its even group starts.
-// The stored scale itself was requested a tile earlier (QZO_SCALE_PREFETCH), ahead
-// of that tile's operand loads: memory returns in order, so a scale requested here
-// would make the wavefront wait for every operand load issued before it.
-#define QZO_SCALE_PREFETCH(G_)                                                               \
-  do {                                                                                       \
-    const uint32_t gp_ = min((uint32_t)(G_), (nkt >> 1) - 1u);                               \
-    s_next = (bf16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)so, (int)(gp_ * 2u), 0);  \
-    if (ZP) z_next = __builtin_amdgcn_raw_buffer_load_b8(rz, (int)(so >> 1), (int)gp_, 0);   \
-  } while (0)
-#define QZO_NEW_GROUP(G_)                                                                    \
-  do {                                                                                       \
-    const uint32_t g_ = (G_) + (kt0 >> 1);      /* group index within the row */             \
-    if ((g_ & 7u) == 0u || (G_) == 0u) {        /* a slice may start inside a counter */     \
-      const u32x4_t pw_ = philox4x32_10(a.row_base + gn_w4, g_ >> 3, 0u, 0u, a.seed_lo, a.seed_hi); \
-      zw[0] = pw_.x; zw[1] = pw_.y; zw[2] = pw_.z; zw[3] = pw_.w;                            \
-    }                                                                                        \
-    float zz_ = z_odd;                                                                       \
-    if ((g_ & 1u) == 0u) {                                                                   \
-      const uint32_t p_ = (g_ & 7u) >> 1;                                                    \
-      const uint32_t w_ = p_ == 0 ? zw[0] : (p_ == 1 ? zw[1] : (p_ == 2 ? zw[2] : zw[3]));   \
-      normal_pair(w_, zz_, z_odd);                                                           \
-    }                                                                                        \
-    const float se_ = __builtin_fmaf(eps_tile, zz_, scale_to_f32(s_next, a.s_fp16 != 0));    \
-    se512 = ZP ? se_ : 512.0f * se_;                  /* ZP: the scale itself          */    \
-    m8se = ZP ? -(float)z_next : -8.0f * se_;         /* ZP: the negated zero-point    */    \
-  } while (0)
-
-// Registers -> LDS stage STAGE (compile-time); the int4 tile is unpacked, scaled
-// by the perturbed scale and rounded to bf16 on the way.
+// Registers -> LDS stage STAGE (compile-time).
 #define QZO_LSTORE_A(STAGE)                                                                  \
   do {                                                                                       \
     _Pragma("unroll") for (int i = 0; i < NA; ++i) *reinterpret_cast<u32x4*>(                \
@@ -358,14 +263,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
   } while (0)
 #define QZO_LSTORE_B(STAGE)                                                                  \
   do {                                                                                       \
-    if (W4) {                                                                                \
-      _Pragma("unroll") for (int q = 0; q < NBQ; ++q) {                                      \
-        *reinterpret_cast<uint4*>(lds_b + b_lds[4 * q + 0] + (STAGE) * TILE_BYTES) = dequant8<ZP>(rb[q].x, se512, m8se); \
-        *reinterpret_cast<uint4*>(lds_b + b_lds[4 * q + 1] + (STAGE) * TILE_BYTES) = dequant8<ZP>(rb[q].y, se512, m8se); \
-        *reinterpret_cast<uint4*>(lds_b + b_lds[4 * q + 2] + (STAGE) * TILE_BYTES) = dequant8<ZP>(rb[q].z, se512, m8se); \
-        *reinterpret_cast<uint4*>(lds_b + b_lds[4 * q + 3] + (STAGE) * TILE_BYTES) = dequant8<ZP>(rb[q].w, se512, m8se); \
-      }                                                                                      \
-    } else if (CB) {                                                                         \
+    if (CB) {                                                                                \
       _Pragma("unroll") for (int q = 0; q < 4; ++q) *reinterpret_cast<uint4*>(               \
           lds_b + b_lds[q] + (STAGE) * TILE_BYTES) = half8_to_bf16(rb[q]);                   \
     } else {                                                                                 \
@@ -431,7 +329,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
 // slower than LDS loads, the LDS executes in order and the barrier must wait for
 // them, so they may neither bunch up in front of the fragment loads nor sit at
 // the end), and the global loads go behind the last k-step's MFMAs.
-#define QZO_TILE(STAGE, HOLD, STORE_STAGE, NEXT_KT, PREF_G)                                  \
+#define QZO_TILE(STAGE, HOLD, STORE_STAGE, NEXT_KT)                                  \
   do {                                                                                       \
     QZO_FRAGS(0, 0, STAGE);                                                                  \
     if (HOLD) QZO_MFMAS(1); /* k-step 3 of the previous tile */                              \
@@ -442,7 +340,6 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
     QZO_FRAGS(1, 3, STAGE);                                                                  \
     if ((STORE_STAGE) >= 0) {                                                                \
       QZO_LSTORE((STORE_STAGE) & 1);                                                         \
-      if (W4 && (int)(PREF_G) >= 0) QZO_SCALE_PREFETCH(PREF_G);                              \
       QZO_GLOAD(NEXT_KT);                                                                    \
     }                                                                                        \
     QZO_MFMAS(0);                                                                            \
@@ -495,93 +392,12 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
     QZO_DTL_LANDED();                                                                        \
   } while (0)
 
-// Phase schedule (int4 weights).  Wavefronts w and w + 4 share a SIMD.  A k-tile is cut
-// into two halves of two k-steps; for each half a wavefront runs a memory phase and then a
-// matrix phase of sixteen MFMAs whose operands are all in registers.  Phases are separated
-// by workgroup barriers and wavefronts 4..7 run one phase behind wavefronts 0..3, so on
-// every SIMD one wavefront feeds the matrix pipe while the other uses the LDS and the
-// vector ALU.  With t the current tile (LDS stage t & 1):
-//   memory A: 12 fragment reads (k-steps 0,1); while they are served, convert dwords 0,1
-//             of tile t+1's weight quad; store them and activation chunks 0,1 of tile t+1
-//   matrix A: 16 MFMAs; request activation chunks 0,1 of tile t+2 (and a scale)
-//   memory B: 12 fragment reads (k-steps 2,3); convert and store dwords 2,3 and chunks
-//             2,3 of tile t+1; then, before an even tile t+2, the scale of its group
-//   matrix B: 16 MFMAs; request chunks 2,3 of tile t+2 and the weight quad of tile t+3
-// Stage hazards: tile t+1 is written to the other stage during tile t's first three
-// phases, after the barrier that ends the last fragment read of tile t-1 and before the
-// barrier that precedes the first read of tile t+1 by the other half of the wavefronts.
-#define QZO_PHASE_SYNC()                                                                     \
-  do {                                                                                       \
-    __builtin_amdgcn_sched_barrier(0);                                                       \
-    __syncthreads();                                                                         \
-    __builtin_amdgcn_sched_barrier(0);                                                       \
-  } while (0)
-#define QZO_PP_LOAD_B(KT, PAR)                                                               \
-  rbp[PAR] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)wo[0], (int)((KT) * (BK / 2)), 0)
-#define QZO_PP_LOAD_A(KT, I0)                                                                \
-  do {                                                                                       \
-    ra[I0] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)xo[I0], (int)((KT) * (BK * 2)), 0); \
-    ra[(I0) + 1] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)xo[(I0) + 1], (int)((KT) * (BK * 2)), 0); \
-  } while (0)
-/* half H (0, 1) of the staging of one tile: two weight dwords and two activation chunks */ \
-
-#define QZO_PP_STAGE_HALF(PAR, STAGE, H)                                                     \
-  do {                                                                                       \
-    const uint4 c0_ = dequant8<ZP>((H) ? rbp[PAR].z : rbp[PAR].x, se512, m8se);                  \
-    const uint4 c1_ = dequant8<ZP>((H) ? rbp[PAR].w : rbp[PAR].y, se512, m8se);                  \
-    *reinterpret_cast<uint4*>(lds_b + b_lds[2 * (H)] + (STAGE) * TILE_BYTES) = c0_;          \
-    *reinterpret_cast<uint4*>(lds_b + b_lds[2 * (H) + 1] + (STAGE) * TILE_BYTES) = c1_;      \
-    *reinterpret_cast<u32x4*>(lds_a + a_lds + ((2 * (H)) * RSTEP * 128 + (STAGE) * TILE_BYTES)) = ra[2 * (H)]; \
-    *reinterpret_cast<u32x4*>(lds_a + a_lds + ((2 * (H) + 1) * RSTEP * 128 + (STAGE) * TILE_BYTES)) = ra[2 * (H) + 1]; \
-  } while (0)
-#define QZO_PP_MFMAS()                                                                       \
-  do {                                                                                       \
-    QZO_MFMAS(0);                                                                            \
-    QZO_MFMAS(1);                                                                            \
-  } while (0)
-#define QZO_PP_TILE(STAGE, STORE_STAGE, NEXT_KT, NEXT_B_KT, NEW_G, PREF_G)                   \
-  do {                                                                                       \
-    QZO_FRAGS(0, 0, STAGE);                                                                  \
-    QZO_FRAGS(1, 1, STAGE);                                                                  \
-    __builtin_amdgcn_sched_barrier(0);                                                       \
-    if ((STORE_STAGE) >= 0) QZO_PP_STAGE_HALF((STORE_STAGE) & 1, (STORE_STAGE) & 1, 0);      \
-    QZO_PHASE_SYNC();                                                                        \
-    __builtin_amdgcn_s_setprio(1);                                                           \
-    QZO_PP_MFMAS();                                                                          \
-    if ((STORE_STAGE) >= 0) {                                                                \
-      if ((int)(PREF_G) >= 0) QZO_SCALE_PREFETCH(PREF_G);                                    \
-      QZO_PP_LOAD_A(NEXT_KT, 0);                                                             \
-    }                                                                                        \
-    __builtin_amdgcn_s_setprio(0);                                                           \
-    QZO_PHASE_SYNC();                                                                        \
-    QZO_FRAGS(0, 2, STAGE);                                                                  \
-    QZO_FRAGS(1, 3, STAGE);                                                                  \
-    __builtin_amdgcn_sched_barrier(0);                                                       \
-    if ((STORE_STAGE) >= 0) {                                                                \
-      QZO_PP_STAGE_HALF((STORE_STAGE) & 1, (STORE_STAGE) & 1, 1);                            \
-      if ((int)(NEW_G) >= 0) QZO_NEW_GROUP((uint32_t)(NEW_G));                               \
-    }                                                                                        \
-    QZO_PHASE_SYNC();                                                                        \
-    __builtin_amdgcn_s_setprio(1);                                                           \
-    QZO_PP_MFMAS();                                                                          \
-    if ((STORE_STAGE) >= 0) {                                                                \
-      QZO_PP_LOAD_A(NEXT_KT, 2);                                                             \
-      QZO_PP_LOAD_B(NEXT_B_KT, (STORE_STAGE) & 1);                                           \
-    }                                                                                        \
-    __builtin_amdgcn_s_setprio(0);                                                           \
-    QZO_PHASE_SYNC();                                                                        \
-  } while (0)
-  const bool late_group = PP && __builtin_amdgcn_readfirstlane(wave) >= 4u;
-
   // K is a multiple of 128, so the number of k-tiles is even.  Tile kt lives in
   // LDS stage kt & 1; during tile kt the registers loaded one tile earlier (tile
   // kt+1) go to the other stage and tile kt+2 is requested from memory.
   uint32_t nkt = (SPLITK && ksplit > 1) ? min(a.kt_per, K / BK - kt0) : K / BK, last = nkt - 1;
   if (CB) QZO_CODES(0u);
-  if (PP) {
-    QZO_GLOAD_A(0);
-    QZO_PP_LOAD_B(0u, 0);
-  } else if (DTL) {
+  if (DTL) {
     QZO_DTL(0u, 0);
     QZO_DTL(1u, 1);
   } else {
@@ -594,18 +410,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
     for (int j = 0; j < TJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-  if (W4) {
-    QZO_SCALE_PREFETCH(0u);
-    QZO_NEW_GROUP(0u);
-    QZO_SCALE_PREFETCH(1u);
-  }
-  if (PP) {
-    QZO_PP_STAGE_HALF(0, 0, 0);
-    QZO_PP_STAGE_HALF(0, 0, 1);
-    QZO_GLOAD_A(1u);
-    QZO_PP_LOAD_B(1u, 1);
-    QZO_PP_LOAD_B(min(2u, last), 0);
-  } else if (!DTL) {
+  if (!DTL) {
     QZO_LSTORE(0);
     QZO_GLOAD(1u);
   }
@@ -620,18 +425,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
   } else {
     __syncthreads();
   }
-  if (PP) {
-    if (late_group) QZO_PHASE_SYNC();
-    /* tile t stores tile t+1, requests activations of t+2 and weights of t+3; an even   */
-    /* tile ends its staging with the scale of the group that tile t+2 starts            */
-    QZO_PP_TILE(0, 1, min(2u, last), min(3u, last), 1, -1);
-    for (uint32_t kt = 1; kt + 1 < nkt; kt += 2) {
-      QZO_PP_TILE(1, 0, min(kt + 2, last), min(kt + 3, last), -1, (kt + 3) >> 1);
-      QZO_PP_TILE(0, 1, min(kt + 3, last), min(kt + 4, last), (kt + 3) >> 1, -1);
-    }
-    QZO_PP_TILE(1, -1, 0u, 0u, -1, -1);
-    if (!late_group) QZO_PHASE_SYNC();
-  } else if (DTL) {
+  if (DTL) {
     QZO_TILE_D(0, false, -1);                 /* tiles 0 and 1 were requested ahead of the loop */
     for (uint32_t kt = 1; kt + 1 < nkt; kt += 2) {
       QZO_TILE_D(1, true, (int)(kt + 1));
@@ -640,16 +434,15 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
     QZO_TILE_D(1, true, -1);
     QZO_MFMAS(1);
   } else {
-  QZO_TILE(0, false, 1, min(2u, last), -1);
+  QZO_TILE(0, false, 1, min(2u, last));
   __syncthreads();
   for (uint32_t kt = 1; kt + 1 < nkt; kt += 2) {
-    if (W4) QZO_NEW_GROUP((kt + 1) >> 1);
-    QZO_TILE(1, true, 0, min(kt + 2, last), -1);
+    QZO_TILE(1, true, 0, min(kt + 2, last));
     __syncthreads();
-    QZO_TILE(0, true, 1, min(kt + 3, last), (kt + 3) >> 1);
+    QZO_TILE(0, true, 1, min(kt + 3, last));
     __syncthreads();
   }
-  QZO_TILE(1, true, -1, 0u, -1);
+  QZO_TILE(1, true, -1, 0u);
   QZO_MFMAS(1);
   }
 
@@ -670,10 +463,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
     }
     QZO_TILE_PTRS(tile_m, tile_n);
     if (CB) QZO_CODES(0u);
-    if (PP) {
-      QZO_GLOAD_A(0);
-      QZO_PP_LOAD_B(0u, 0);
-    } else if (DTL) {       /* every wavefront is past the barrier that ends the last k-tile */
+    if (DTL) {       /* every wavefront is past the barrier that ends the last k-tile */
       QZO_DTL(0u, 0);
       QZO_DTL(1u, 1);
     } else {
@@ -774,7 +564,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
       }
     }
     trail_stores = TRAIL ? 8 : 0;
-  } else if (!CE && TJ == 2 && !W4 && !CB && (a.epi & EPI_ROPE)) {
+  } else if (!CE && TJ == 2 && !CB && (a.epi & EPI_ROPE)) {
     // qkv [M, 3d] with the rotary embedding on its q and k thirds.  The wavefront's two 32-wide
     // feature tiles hold feature i and feature i + dh/2 of a head for the same token (heads of 64:
     // the natural order; heads of 128: the rows of W were written in ROW_ORDER_ROPE128), so a lane
@@ -968,12 +758,6 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
 #undef QZO_DTL_PART
 #undef QZO_DTL16
 #undef QZO_DTL_LANDED
-#undef QZO_PP_TILE
-#undef QZO_PP_LOAD_A
-#undef QZO_PP_LOAD_B
-#undef QZO_PP_STAGE_HALF
-#undef QZO_PP_MFMAS
-#undef QZO_PHASE_SYNC
 #undef QZO_LSTORE_A
 #undef QZO_LSTORE_B
 #undef QZO_GLOAD_A
@@ -981,8 +765,6 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
 #undef QZO_MFMAS
 #undef QZO_FRAGS
 #undef QZO_LSTORE
-#undef QZO_NEW_GROUP
-#undef QZO_SCALE_PREFETCH
 #undef QZO_GLOAD
 #undef QZO_CODES
 #undef QZO_TILE_PTRS
@@ -992,17 +774,9 @@ static hipError_t set_lds_attr(const void* fn) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
 }
 
-// Launch configuration of the perturbed W4A16 GEMM.  Measured on MI355X at the
-// Llama-2-7B layer shapes (M = 8192): 4 wavefronts along N (512 threads, two per
-// SIMD) with the explicit issue order is the fastest; 2 along N (256 threads, one
-// per SIMD, 128x128 per wavefront) is about 10 % slower.
-constexpr int W4_NWN = 4;
-constexpr int W4_PIPE = 2;
-
 // Columns [n1, N) of a GEMM as a call of its own: weights, scales, zero-points, bias, output and residual
 // advanced, the noise rows offset; y and resid keep the full matrix's row stride.
-static GemmArgs column_block(const GemmArgs& a, uint32_t first, uint32_t count, int w_bits, bool codes_per_scale_group) {
-  (void)codes_per_scale_group;
+static GemmArgs column_block(const GemmArgs& a, uint32_t first, uint32_t count, int w_bits) {
   GemmArgs s = a;
   s.next = nullptr;                              // a column block does not complete rows
   const uint32_t ld = a.ldy ? a.ldy : a.N;
@@ -1020,13 +794,6 @@ static GemmArgs column_block(const GemmArgs& a, uint32_t first, uint32_t count, 
 }
 
 hipError_t launch_w4a16_gemm(const GemmArgs& a0, hipStream_t st) {
-  static bool ready = false;
-  if (!ready) {
-    hipError_t e = set_lds_attr((const void*)gemm_kernel<0, false, W4_NWN, W4_PIPE>);
-    if (e == hipSuccess) e = set_lds_attr((const void*)gemm_kernel<0, false, W4_NWN, W4_PIPE, true>);
-    if (e != hipSuccess) return e;
-    ready = true;
-  }
   if (a0.M == 0 || a0.N == 0) return hipSuccess;
   if (a0.M <= SKINNY_MAX_M && a0.skinny_ws) return launch_skinny_gemm(a0, a0.skinny_ws, st);
   if (a0.mid_ws) return launch_mid_gemm(a0, a0.mid_ws, st);
@@ -1044,26 +811,21 @@ hipError_t launch_w4a16_gemm(const GemmArgs& a0, hipStream_t st) {
     // a little more than whole rounds of tiles: the whole rounds as they are, the rest cut along K
     const uint32_t n1 = tile_tail_cols(a.M, a.N, a.K, a.epi);
     if (n1) {
-      GemmArgs h = column_block(a, 0, n1, 4, false), t = column_block(a, n1, a.N - n1, 4, false);
+      GemmArgs h = column_block(a, 0, n1, 4), t = column_block(a, n1, a.N - n1, 4);
       h.split_ws = nullptr;
       hipError_t e = launch_w4a16_gemm(h, st);
       return e != hipSuccess ? e : launch_w4a16_gemm(t, st);
     }
   }
-  CeEpilogue ce = {nullptr, nullptr, nullptr, 1, 1, 1};
   GemmArgs g = a;
-  g.ksplit = 1;
-  g.kt_per = a.K / BK;
-  if (a.split_ws) g.ksplit = tile_ksplit(a.M, a.N, a.K, &g.kt_per);
-  if (g.ksplit > 1) g.epi = 0;       // natural row order, fp32 partial sums; the reduction applies a.epi
-  const uint32_t wgs = gemm_workgroups(a.M, ((a.N + BN - 1) / BN) * g.ksplit * BN);
-  if (a.zp)
-    gemm_kernel<0, false, W4_NWN, W4_PIPE, true><<<wgs, 128 * W4_NWN, LDS_BYTES, st>>>(g, ce);
-  else
-    gemm_kernel<0, false, W4_NWN, W4_PIPE><<<wgs, 128 * W4_NWN, LDS_BYTES, st>>>(g, ce);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || g.ksplit == 1) return e;
-  return launch_partial_reduce(a, a.split_ws, g.ksplit, st);
+  uint32_t ksplit = 1, kt_per = a.K / BK;
+  if (a.split_ws) ksplit = tile_ksplit(a.M, a.N, a.K, &kt_per);
+  if (ksplit > 1) g.epi = 0;         // natural row order, fp32 partial sums; the reduction applies a.epi
+  if (a.flip_row) g.M = a.M - a.flip_row;
+  hipError_t e = launch_w4_tiles(g, w4_plan(g.M, a.flip_row, a.N, a.K, ksplit, kt_per, g.epi & EPI_SUMSQ ? a.n_partials : 0u), st);
+  if (e != hipSuccess || ksplit == 1) return e;
+  if (a.flip_row) { a.skip_row = g.M; a.skip = a.flip_row - g.M; }      // padding rows have no sums
+  return launch_partial_reduce(a, a.split_ws, ksplit, st);
 }
 
 hipError_t launch_codebook_gemm(const GemmArgs& a, hipStream_t st) {
@@ -1104,7 +866,7 @@ hipError_t launch_bf16_gemm(const GemmArgs& a, int pipe, hipStream_t st) {
     // a little more than whole rounds of tiles: the whole rounds as they are, the rest cut along K
     const uint32_t n1 = tile_tail_cols(a.M, a.N, a.K, a.epi);
     if (n1) {
-      GemmArgs h = column_block(a, 0, n1, 16, false), t = column_block(a, n1, a.N - n1, 16, false);
+      GemmArgs h = column_block(a, 0, n1, 16), t = column_block(a, n1, a.N - n1, 16);
       h.split_ws = nullptr;
       hipError_t e = launch_bf16_gemm(h, pipe, st);
       return e != hipSuccess ? e : launch_bf16_gemm(t, pipe, st);

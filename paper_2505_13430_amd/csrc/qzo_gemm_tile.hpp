@@ -25,18 +25,21 @@ constexpr uint32_t WALK_M = 4;
 struct TileWalk {
   uint32_t tiles_m, tiles_n, total, per, xcd, slot, stride;
 };
-// With K slices (split-K) the walk runs over feature-tiles x slices: entry tn of the walk is feature
-// tile tn % real_tiles_n, slice tn / real_tiles_n.
-__device__ __forceinline__ TileWalk tile_walk_init(uint32_t M, uint32_t N, uint32_t ksplit = 1) {
+__device__ __forceinline__ TileWalk tile_walk_of(uint32_t tiles_m, uint32_t tiles_n) {
   TileWalk w;
-  w.tiles_m = (M + BM - 1) / BM;
-  w.tiles_n = ((N + BN - 1) / BN) * ksplit;
+  w.tiles_m = tiles_m;
+  w.tiles_n = tiles_n;
   w.total = w.tiles_m * w.tiles_n;
   w.per = (w.total + 7) >> 3;
   w.xcd = blockIdx.x & 7u;
   w.slot = blockIdx.x >> 3;
   w.stride = gridDim.x >> 3;
   return w;
+}
+// With K slices (split-K) the walk runs over feature-tiles x slices: entry tn of the walk is feature
+// tile tn % real_tiles_n, slice tn / real_tiles_n.
+__device__ __forceinline__ TileWalk tile_walk_init(uint32_t M, uint32_t N, uint32_t ksplit = 1) {
+  return tile_walk_of((M + BM - 1) / BM, ((N + BN - 1) / BN) * ksplit);
 }
 // Tile of the walk's current slot; false when the walk is over.
 __device__ __forceinline__ bool tile_walk_get(const TileWalk& w, uint32_t& tm, uint32_t& tn) {

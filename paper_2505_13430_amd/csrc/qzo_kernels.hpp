@@ -53,6 +53,7 @@ struct GemmArgs {
   const void* resid;    // bf16 [M,N] or null
   void* y;              // bf16 [M,N]
   float* partials;      // EPI_SUMSQ: one float per workgroup
+  uint32_t n_partials;  // EPI_SUMSQ, fused int4 kernel: how many of them there is room for
   float* skinny_ws;     // fp32 scratch of skinny_ws_floats(rows, N, K) floats: enables the few-token path (M <= 64)
   float* mid_ws;        // fp32 scratch of mid_ws_floats(M, N, K, dual) floats: enables mid_gemm_kernel
   float* split_ws;      // fp32 scratch of tile_split_ws_floats(M, N, K) floats: enables split-K of the int4 tile kernel
@@ -63,9 +64,10 @@ struct GemmArgs {
                         // [M,2M) -eps_signed (few-token path and mid_gemm_kernel; tile path: see pass_stride)
   uint32_t pass_stride; // dual, tile path: the second pass starts at this row (a multiple of 256 >= M; x, y, resid
                         // hold pass_stride + M rows, the rows in between are padding); 0: at row M
-  uint32_t flip_row;    // tile kernels: rows from here on (a multiple of 256) take -eps_signed (0: none); set by the
-                        // launcher of the fused kernel, by the caller of the plain bf16 GEMM
+  uint32_t flip_row;    // tile kernels: first row of the second pass (0: one pass), whose rows take -eps_signed; set by
+                        // the launcher of the fused kernel, by the caller of the plain bf16 GEMM (a multiple of 256)
   uint64_t w_flip;      // plain bf16 GEMM with flip_row: bytes from w to the matrix of the second pass
+  uint32_t skip_row, skip;   // slice reduction: rows skip_row .. skip_row + skip - 1 are padding and have no partial sums
   uint32_t M, N, K;
   uint32_t ldy;         // row stride of y and resid in elements when the call covers a column block of a wider
                         // matrix (0: N); plain epilogues only (bias, residual, ReLU)
@@ -84,6 +86,17 @@ struct GemmArgs {
   struct NextNorm* next;
 };
 hipError_t launch_w4a16_gemm(const GemmArgs& a, hipStream_t st);
+// Output tiles of the fused kernel: 32 mt tokens x 256 features, each in one pass of a stacked step; units of work are
+// (output tile, K slice of kt_per k-tiles).  M: tokens of a pass; second_row: first row of the second pass (0: one pass).
+struct W4Plan {
+  uint32_t mt, tiles_m, tiles_per_pass, tiles_n, ksplit, kt_per;
+  uint32_t second_row, rows;         // rows: of x, y and resid
+  uint32_t wgs;                      // persistent workgroups
+};
+// most_parts (0: no limit): room for one partial sum of squares per workgroup; never refused when it holds one per
+// 256 x 256 tile, rounded up to a multiple of 8.
+W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t ksplit, uint32_t kt_per, uint32_t most_parts);
+hipError_t launch_w4_tiles(const GemmArgs& a, const W4Plan& p, hipStream_t st);
 // Order of the rows of an expanded (bf16) weight matrix: natural; the fused-SwiGLU consumer's tile order;
 // the fused-RoPE consumer's order for heads of 128 features (within every 256 rows, so that a lane of the
 // GEMM holds feature i and feature i + 64 of a head).

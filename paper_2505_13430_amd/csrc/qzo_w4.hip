@@ -1,0 +1,556 @@
+// W4A16 group-dequant GEMM with the Q-SPSA perturbation fused into the weight operand (paper Eq. 4-5):
+//   Y[M,N] = X[M,K] * W_eff^T,  W_eff[n,k] = (s[n,k/128] + sigma*eps*z(row_base+n, k/128)) * (u[n,k] - zp),
+// bf16 MFMA (v_mfma_f32_32x32x16_bf16) with fp32 accumulation; a weight is formed in fp32 and rounded to bf16 once.
+//
+// A workgroup of four wavefronts, one per SIMD, owns 32 MT tokens x 256 features (MT = 1 .. 8), a wavefront all its
+// tokens and 64 of the features: 2 MT accumulator tiles, in AGPRs from MT = 5 on.  A wavefront unpacks the weights that
+// it multiplies, in registers, one k-step ahead of the MFMAs: they pass through the LDS as nibbles (8 KB a k-tile, read
+// by their wavefront only, no barrier), not as 32 KB of bf16 that eight wavefronts stored and fetched between barriers.
+// What the LDS carries per k-tile of 256 x 256 outputs falls from 256 to 170 KB, and no weight is converted twice.
+// Everything comes from memory by direct-to-LDS loads (swizzled on the memory side): activations into a ring of three
+// stages, two k-tiles ahead, weights and scales into two slots of a group each, two k-tiles ahead.  One barrier per
+// k-tile, in front of its last k-step, whose operands are in registers by then.
+// A lone wavefront issues an instruction every four cycles, so an MFMA of 32 cycles leaves seven places: fragment reads,
+// loads and the conversion (eight pieces per dword) are dealt out behind the MFMAs in source order, held by scheduling
+// fences.  With the conversion in four pieces behind every other MFMA, all loads at the head of a k-tile and the next
+// k-step's conversion sunk behind the noise's branch by the compiler a k-tile took 1.73 us, as it stands 1.58.
+//
+// The noise is drawn by one lane per row (64 rows, 64 lanes): a Philox counter serves eight groups, a Box-Muller pair
+// two, one exchange between the wavefront's halves hands the perturbed scales to both.
+//
+// Per k-tile at MT = 8 on a full chip, against the kernel this one replaces (eight wavefronts in alternating phases,
+// weight tile in the LDS), same board: 1.79 -> 1.58 us (1203 -> 1358 TFLOP/s), with zero-points 1.95 -> 1.64.  The MFMAs
+// are 1.15 us of that at the clock the board grants on such data.  Timing-only variants (board with 1.69): loads not
+// issued 1.59; noise left out -0.02 to -0.05; fragment reads left out -0.08.
+// Lower tiles serve the sizes whose rounds of 256-token tiles are badly filled (w4_plan): steps at 7B widths, before ->
+// after: 4 x 33 tokens 9.5 -> 6.9 ms, 8 x 200 with zero-points 45.9 -> 39.6, 16 x 64 28.6 -> 25.8; OPT-1.3B 16 x 256
+// 22.1 -> 20.6; one linear 2048 x 11008 x 4096, both signs, 0.439 -> 0.336; the tests' smallest model 0.180 -> 0.119.
+// Outputs are the same bit for bit whatever MT: every one sums the same k-steps in the same order.
+#include "qzo_gemm_tile.hpp"
+#include <algorithm>
+#include <type_traits>
+
+namespace qzo {
+
+namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// LDS: three stages of activations (a k-tile of 32 MT rows of 128 bytes), two slots of packed weights (a group of 256
+// rows: 64 bytes each) with their scales and zero-points (a dword each).
+template <int MT, bool ZP>
+struct W4Lds {
+  static constexpr uint32_t X = MT * 4096u, W0 = 3 * X, W = 256 * 64, S = 256 * 4, SLOT = W + S * (ZP ? 2 : 1);
+  static constexpr uint32_t RED = W0 + 2 * SLOT, BYTES = RED + 64;
+  static constexpr int NW = ZP ? 6 : 5;            // load instructions per wavefront for a group's weights
+  static_assert(BYTES <= 160 * 1024, "LDS of a compute unit");
+};
+
+#define Q4_DTL(INSTR, RSRC, LDSADDR, VOFF, SOFF)                                             \
+  asm volatile("s_mov_b32 m0, %0\n\t" INSTR " %1, %2, %3 offen lds"                          \
+               : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC), "s"(SOFF) : "memory", "m0")
+
+#define Q4_INLINE __attribute__((always_inline))
+template <int V>
+using Int = std::integral_constant<int, V>;
+
+template <int MT, bool ZP>
+__global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
+  typedef W4Lds<MT, ZP> L;
+  constexpr int SLOTS = 2 * MT;                    // MFMAs of a k-step
+  constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const uint32_t t = threadIdx.x, lane = t & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const uint32_t lrow = lane & 31u, half = lane >> 5;
+  const uint32_t K = a.K, G = K >> 7;
+  const bool swiglu = (a.epi & EPI_SWIGLU) != 0, s_fp16 = a.s_fp16 != 0;
+  TileWalk walk = tile_walk_of(p.tiles_m, p.tiles_n * p.ksplit);
+  uint32_t tile_m, tile_n;
+  if (!tile_walk_get(walk, tile_m, tile_n)) {
+    if ((a.epi & EPI_SUMSQ) && threadIdx.x == 0) a.partials[blockIdx.x] = 0.0f;
+    return;
+  }
+
+  auto rsrc = [](const void* q, uint64_t bytes) {
+    return i32x4{(int)(uint32_t)(uintptr_t)q, (int)(uint32_t)((uintptr_t)q >> 32), (int)bytes, 0x00020000};
+  };
+  const uint32_t rows_all = p.rows;
+  const i32x4 rx = rsrc(a.x, (uint64_t)rows_all * K * 2), rw = rsrc(a.w, (uint64_t)a.N * (K >> 1));
+  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * G * 2), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * G);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+
+  // a unit of work: K slice kslice of output tile (tile_m, tile_n), k-tiles kt0 .. kt0 + 2 ng - 1
+  uint32_t kslice, kt0, ng, row0, row_last, noise_row, pass;
+  uint32_t xo[MT], wo[4], so;
+  float eps;
+  auto point = [&]() Q4_INLINE {
+    kslice = tile_n / p.tiles_n;
+    tile_n -= kslice * p.tiles_n;
+    kt0 = kslice * p.kt_per;
+    ng = min(p.kt_per, K / BK - kt0) >> 1;
+    pass = tile_m >= p.tiles_per_pass ? 1u : 0u;
+    row0 = pass * p.second_row + (tile_m - pass * p.tiles_per_pass) * (32 * MT);
+    row_last = pass * p.second_row + a.M - 1;
+    eps = pass ? -a.eps_signed : a.eps_signed;
+    // fused SwiGLU: a wavefront's rows are 32 gate rows and the 32 up rows of the same features
+    auto wrow = [&](uint32_t r) Q4_INLINE {
+      return swiglu ? ((r >> 5) & 1u) * (a.N >> 1) + tile_n * 128u + (r >> 6) * 32u + (r & 31u)
+                    : min(tile_n * 256u + r, a.N - 1);
+    };
+    // a load instruction fills 1 KB of LDS in lane order: 8 rows of 128 bytes of activations, 16 rows of 64 bytes of
+    // weights; the swizzles of their 16-byte chunks are applied on the memory side
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const uint32_t row = 8 * (4 * i + wave) + (lane >> 3);
+      xo[i] = min(row0 + row, row_last) * K * 2 + (((lane & 7u) ^ ((row >> 1) & 7u)) << 4) + kt0 * (BK * 2);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      wo[q] = wrow(wave * 64 + 16 * q + (lane >> 2)) * (K >> 1) + (((lane & 3u) ^ ((lane >> 4) & 3u)) << 4) + kt0 * (BK / 2);
+    const uint32_t own = wrow(wave * 64 + lane);
+    so = own * G + (kt0 >> 1);
+    noise_row = a.row_base + own;
+  };
+  auto load_x = [&](int i, uint32_t kt, uint32_t stage) Q4_INLINE {
+    Q4_DTL("buffer_load_dwordx4", rx, lds0 + stage + (4 * i + wave) * 1024, xo[i], kt * (BK * 2));
+  };
+  auto load_w = [&](int q, uint32_t g, uint32_t slot) Q4_INLINE {
+    const uint32_t base = lds0 + L::W0 + slot;
+    if (q < 4) Q4_DTL("buffer_load_dwordx4", rw, base + wave * 4096 + q * 1024, wo[q], g * 64);
+    else if (q == 4) Q4_DTL("buffer_load_ushort", rs, base + L::W + wave * 256, so * 2, g * 2);
+    else Q4_DTL("buffer_load_ubyte", rz, base + L::W + L::S + wave * 256, so, g);
+  };
+  auto request_first = [&]() Q4_INLINE {       // groups 0 and 1, k-tiles 0 and 1, in the order the k-loop goes on with
+#pragma unroll
+    for (int q = 0; q < L::NW; ++q) load_w(q, 0u, 0u);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) load_x(i, 0u, 0u);
+    if (ng < 2) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) wo[q] = OUT_OF_RANGE;
+      so = OUT_OF_RANGE >> 1;
+    }
+#pragma unroll
+    for (int q = 0; q < L::NW; ++q) load_w(q, 1u, L::SLOT);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) load_x(i, 1u, L::X);
+    if (ng < 2) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) xo[i] = OUT_OF_RANGE;
+    }
+  };
+
+  // fragment addresses: activations: row lrow (+ 32 i), chunk of k-step ks; weights: row lrow (+ 32 j), the dwords of
+  // chunk c that hold the eight inputs of the lane's half of k-steps 2 c and 2 c + 1
+  uint32_t xrd[4], wrd[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) xrd[ks] = lrow * 128u + (((uint32_t)(ks * 2 + half) ^ ((lrow >> 1) & 7u)) << 4);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) wrd[c] = L::W0 + wave * 4096 + lrow * 64u + (((uint32_t)c ^ ((lrow >> 2) & 3u)) << 4) + half * 4;
+
+  floatx16 acc[MT][2];
+  bf16x8 fx[2][MT], fw[2][2];
+  uint32_t raw[2][8];                               // nibbles of the group: [feature tile][k-step of the group]
+  float se[2], m8[2];                               // per feature tile: operands of the conversion
+  float z_even = 0.0f, z_odd = 0.0f;
+  uint32_t zw0 = 0, zw1 = 0, zw2 = 0, zw3 = 0, sbits = 0, zbits = 0;
+  const floatx16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+
+  auto read_raw = [&](int c, uint32_t slot) Q4_INLINE {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t* q = reinterpret_cast<const uint32_t*>(lds + (wrd[c] + slot) + j * 2048);
+      raw[j][2 * c] = q[0];
+      raw[j][2 * c + 1] = q[2];
+    }
+  };
+  auto read_scale = [&](uint32_t slot) Q4_INLINE {
+    sbits = *reinterpret_cast<const uint32_t*>(lds + L::W0 + slot + L::W + wave * 256 + lane * 4);
+    if (ZP) zbits = *reinterpret_cast<const uint32_t*>(lds + L::W0 + slot + L::W + L::S + wave * 256 + lane * 4);
+  };
+  // noise of the lane's own row, group g of the row
+  auto noise = [&](uint32_t g, bool first) Q4_INLINE {
+    if (first || (g & 7u) == 0) {
+      const u32x4_t w = philox4x32_10(noise_row, g >> 3, 0u, 0u, a.seed_lo, a.seed_hi);
+      zw0 = w.x; zw1 = w.y; zw2 = w.z; zw3 = w.w;
+    }
+    if ((g & 1u) == 0) {
+      const uint32_t q = (g & 7u) >> 1;
+      const uint32_t w0 = zw0, w1 = zw1, w2 = zw2, w3 = zw3;
+      float even, odd;
+      normal_pair(q == 0 ? w0 : (q == 1 ? w1 : (q == 2 ? w2 : w3)), even, odd);
+      z_even = even; z_odd = odd;
+    }
+  };
+  // the lane's row is row lane of the wavefront's 64: one exchange between the halves gives every lane its two tiles'
+  auto new_scale = [&](uint32_t g) Q4_INLINE {
+    const float even = z_even, odd = z_odd;
+    const float s = __builtin_fmaf(eps, (g & 1u) ? odd : even, scale_to_f32(sbits & 0xffffu, s_fp16));
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    const float s0 = __uint_as_float(r[0]), s1 = __uint_as_float(r[1]);
+    if (ZP) {
+      const float nz = -(float)(zbits & 0xffu);
+      const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(nz), __float_as_uint(nz), false, false);
+      se[0] = s0; se[1] = s1;
+      m8[0] = __uint_as_float(q[0]); m8[1] = __uint_as_float(q[1]);
+    } else {
+      se[0] = 512.0f * s0; se[1] = 512.0f * s1;
+      m8[0] = -8.0f * s0; m8[1] = -8.0f * s1;
+    }
+  };
+  // Conversion of a dword of nibbles in eight pieces.  A byte holding a nibble u read as an fp8 E4M3 pattern is exactly
+  // u * 2^-9: fma(u 2^-9, 512 se, -8 se) is (u-8)*se with one rounding; with zero-points fma(u 2^-9, 512, -zp) is the
+  // integer u - zp and its product with se is rounded once.
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  union Frag { bf16x8 v; uint32_t u[4]; };
+  f2 cl, ch;
+  uint32_t clo, chi;
+  float ce0, ce1;
+  Frag cf;
+  auto weight = [&](float u, int j) Q4_INLINE {
+    return ZP ? __builtin_fmaf(u, 512.0f, m8[j]) * se[j] : __builtin_fmaf(u, se[j], m8[j]);
+  };
+  auto convert = [&](int buf, int piece, int kk) Q4_INLINE {
+    const int j = piece >> 3;
+    switch (piece & 7) {
+      case 0: clo = raw[j][kk] & 0x0f0f0f0fu; chi = (raw[j][kk] >> 4) & 0x0f0f0f0fu; break;
+      case 1: cl = __builtin_amdgcn_cvt_pk_f32_fp8(clo, false); ch = __builtin_amdgcn_cvt_pk_f32_fp8(chi, false); break;
+      case 2: ce0 = weight(cl.x, j); ce1 = weight(ch.x, j); break;
+      case 3: cf.u[0] = pack_bf16x2(ce0, ce1); ce0 = weight(cl.y, j); ce1 = weight(ch.y, j); break;
+      case 4: cf.u[1] = pack_bf16x2(ce0, ce1); cl = __builtin_amdgcn_cvt_pk_f32_fp8(clo, true); break;
+      case 5: ch = __builtin_amdgcn_cvt_pk_f32_fp8(chi, true); ce0 = weight(cl.x, j); ce1 = weight(ch.x, j); break;
+      case 6: cf.u[2] = pack_bf16x2(ce0, ce1); ce0 = weight(cl.y, j); ce1 = weight(ch.y, j); break;
+      default: cf.u[3] = pack_bf16x2(ce0, ce1); fw[buf][j] = cf.v;
+    }
+  };
+  auto read_x = [&](int buf, int i, int ks, uint32_t stage) Q4_INLINE {
+    fx[buf][i] = *reinterpret_cast<const bf16x8*>(lds + (xrd[ks] + stage) + i * 4096);
+  };
+
+  uint32_t st_cur = 0, st_next = L::X, st_load = 2 * L::X;      // stages of k-tiles t, t + 1, t + 2
+  // k-step S of k-tile D of a group: its MFMAs with, dealt out between them, the fragment reads and the conversion for
+  // the next k-step, and a share of the loads: from the barrier before step 3 of a k-tile to the next barrier those of
+  // the k-tile after the next one and, once per group, of the weights of the group after the next one.
+  constexpr int ODD = 1;
+  auto loads = [&](auto E_, int first, int count, uint32_t g, uint32_t slot, uint32_t stage) Q4_INLINE {
+    constexpr int E = decltype(E_)::value;          // k-tile of its group that the loads are issued for
+#pragma unroll
+    for (int n = 0; n < MT + L::NW; ++n)
+      if (n >= first && n < first + count) {
+        if (E == ODD && n < L::NW) load_w(n, g + 2, slot);
+        else if (n < MT + (E == ODD ? L::NW : 0)) load_x(n - (E == ODD ? L::NW : 0), 2 * g + E + 2, stage);
+      }
+  };
+  auto step = [&](auto S_, auto D_, auto FIRST_, uint32_t g, uint32_t slot) Q4_INLINE {
+    constexpr int S = decltype(S_)::value, D = decltype(D_)::value;
+    constexpr bool FIRST = decltype(FIRST_)::value != 0;
+    constexpr int buf = S & 1, nb = buf ^ 1, ks = (S + 1) & 3, kk = (D * 4 + S + 1) & 7;
+    // load slots: steps 3, 0, 1, 2 in this order; E: the k-tile whose list they belong to
+    constexpr int E = S == 3 ? D ^ 1 : D, NL = MT + (E ? L::NW : 0), Q = (S + 1) & 3;
+    const uint32_t stage = S == 3 ? st_next : st_cur, lg = S == 3 && D ? g + 1 : g;
+#pragma unroll
+    for (int m = 0; m < SLOTS; ++m) {
+      const int i = m >> 1, j = m & 1;
+      if (FIRST) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[buf][j], fx[buf][i], zero16, 0, 0, 0);
+      else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[buf][j], fx[buf][i], acc[i][j], 0, 0, 0);
+      // S = 2: denser, the barrier that follows waits for them
+      if (S == 2 ? m < MT : (m & 1) == 0) read_x(nb, S == 2 ? m : m >> 1, ks, stage);
+      const int l0 = (Q * SLOTS + m) * NL / (4 * SLOTS), l1 = (Q * SLOTS + m + 1) * NL / (4 * SLOTS);
+      loads(Int<E>(), l0, l1 - l0, lg, slot, S == 3 ? st_cur : st_load);
+#pragma unroll
+      for (int c = m * 16 / SLOTS; c < (m + 1) * 16 / SLOTS; ++c) convert(nb, c, kk);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // keeps the conversion here (single uses behind a branch would be moved there, with no MFMA to hide behind)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      u32x4 pin = __builtin_bit_cast(u32x4, fw[nb][j]);
+      asm volatile("" : "+v"(pin));
+      fw[nb][j] = __builtin_bit_cast(bf16x8, pin);
+    }
+  };
+  auto sync = [&](auto LEFT_) Q4_INLINE {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(decltype(LEFT_)::value) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto next_stage = [&]() Q4_INLINE {
+    const uint32_t o = st_cur;
+    st_cur = st_next; st_next = st_load; st_load = o;
+  };
+  auto group = [&](uint32_t g, auto FIRST_) Q4_INLINE {
+    const uint32_t slot = (g & 1u) ? L::SLOT : 0u, other = L::SLOT - slot, gb = (kt0 >> 1) + g;
+    if (g + 2 >= ng) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) wo[q] = OUT_OF_RANGE;
+      so = OUT_OF_RANGE >> 1;
+    }
+    read_raw(2, slot); read_raw(3, slot);
+    step(Int<0>(), Int<0>(), FIRST_, g, slot);
+    step(Int<1>(), Int<0>(), Int<0>(), g, slot);
+    noise(gb + 1, false);
+    __builtin_amdgcn_sched_barrier(0);
+    step(Int<2>(), Int<0>(), Int<0>(), g, slot);
+    sync(Int<MT>());
+    step(Int<3>(), Int<0>(), Int<0>(), g, slot);
+    next_stage();
+    read_raw(0, other); read_raw(1, other); read_scale(other);
+    step(Int<0>(), Int<1>(), Int<0>(), g, slot);
+    step(Int<1>(), Int<1>(), Int<0>(), g, slot);
+    step(Int<2>(), Int<1>(), Int<0>(), g, slot);
+    sync(Int<MT + L::NW>());
+    new_scale(gb + 1);
+    if (g + 2 >= ng) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) xo[i] = OUT_OF_RANGE;
+    }
+    step(Int<3>(), Int<1>(), Int<0>(), g, slot);
+    next_stage();
+  };
+
+  // output rows and features of a lane: token row0 + 32 i + lrow, features 8 b + 4 half + c of feature tile j; after
+  // QZO swap of two register groups a lane owns eight consecutive features
+  const uint32_t ldy = a.ldy ? a.ldy : a.N, NO = swiglu ? a.N >> 1 : a.N;
+  const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
+      a.y, 0, (int)(((uint64_t)(rows_all - 1) * (swiglu ? NO : ldy) + NO) * 2), 0x00020000);
+  float ssq = 0.0f;                                 // of all units of the workgroup
+  uint32_t stores = 0;                              // stores of the last epilogue, issued behind the next unit's loads
+
+  point();
+  request_first();
+  for (;;) {
+    // first group's weights and first k-tile have landed; k-tile 1, group 1 and the epilogue's stores may not have
+    if (stores == 4 * MT) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(std::min(63, MT + L::NW + 4 * MT)) : "memory");
+    else if (stores == 2 * MT) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(MT + L::NW + 2 * MT) : "memory");
+    else if (stores) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(MT + L::NW) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    st_cur = 0; st_next = L::X; st_load = 2 * L::X;
+    read_raw(0, 0u); read_raw(1, 0u); read_scale(0u);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) read_x(0, i, 0, 0u);
+    noise(kt0 >> 1, true);
+    new_scale(kt0 >> 1);
+#pragma unroll
+    for (int c = 0; c < 16; ++c) convert(0, c, 0);
+    loads(Int<0>(), 0, MT / 4, 0u, 0u, st_load);
+    __builtin_amdgcn_sched_barrier(0);
+    group(0u, Int<1>());
+    for (uint32_t g = 1; g < ng; ++g) group(g, Int<0>());
+
+    const uint32_t m0 = row0 + lrow, m_last = row_last, n0 = tile_n * 256u + wave * 64u, slice = kslice;
+    const uint32_t done_n = tile_n;
+    walk.slot += walk.stride;
+    const bool more = tile_walk_get(walk, tile_m, tile_n);
+    if (more) {                 // every wavefront is past the barrier that ended the last k-tile
+      point();
+      request_first();
+    }
+    asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+// accumulators are read out one piece at a time (left to itself the compiler copies all of them to vector registers)
+#define Q4_ACC(I, J, R, DST)                                                                 \
+  do {                                                                                       \
+    if constexpr (MT >= 5) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(DST) : "a"(acc[I][J][R])); \
+    else DST = acc[I][J][R];                                                                 \
+  } while (0)
+#define Q4_SWAP8(LO, HI)                                                                     \
+  do {                                                                                       \
+    _Pragma("unroll") for (int c_ = 0; c_ < 4; ++c_) {                                       \
+      const auto r_ = __builtin_amdgcn_permlane32_swap(__float_as_uint((LO)[c_]),            \
+                                                       __float_as_uint((HI)[c_]), false, false); \
+      (LO)[c_] = __uint_as_float(r_[0]);                                                     \
+      (HI)[c_] = __uint_as_float(r_[1]);                                                     \
+    }                                                                                        \
+  } while (0)
+    if (p.ksplit > 1) {
+      // this slice's fp32 sums, [slice][rows][N]; the epilogue proper runs in the reduction
+      float* part = a.split_ws + (uint64_t)slice * rows_all * a.N;
+#pragma unroll
+      for (int u = 0; u < 4 * MT; ++u) {
+        const int i = u >> 2, j = (u >> 1) & 1, bp = u & 1;
+        float v[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) Q4_ACC(i, j, 4 * (2 * bp + h) + c, v[h][c]);
+        Q4_SWAP8(v[0], v[1]);
+        const uint32_t m = m0 + i * 32, n = n0 + j * 32 + (2u * bp + half) * 8u;
+        if (m <= m_last && n < a.N) {
+          float4* dst = reinterpret_cast<float4*>(part + (uint64_t)m * a.N + n);
+          dst[0] = make_float4(v[0][0], v[0][1], v[0][2], v[0][3]);
+          dst[1] = make_float4(v[1][0], v[1][1], v[1][2], v[1][3]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      stores = 1;
+    } else if (swiglu) {
+      // y[m, f] = silu(gate) * up, f = 128 tile_n + 32 wave + 8 b + 4 half + c; y is [rows, N/2]
+#pragma unroll
+      for (int u = 0; u < 2 * MT; ++u) {
+        const int i = u >> 1, bp = u & 1;
+        float v[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            float gt, up;
+            Q4_ACC(i, 0, 4 * (2 * bp + h) + c, gt);
+            Q4_ACC(i, 1, 4 * (2 * bp + h) + c, up);
+            v[h][c] = gt * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * gt)) * up;
+          }
+        Q4_SWAP8(v[0], v[1]);
+        const uint32_t m = m0 + i * 32, f = done_n * 128u + wave * 32u + (2u * bp + half) * 8u;
+        const u32x4 out = {pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3]),
+                           pack_bf16x2(v[1][0], v[1][1]), pack_bf16x2(v[1][2], v[1][3])};
+        __builtin_amdgcn_raw_buffer_store_b128(out, ry, (int)(m <= m_last ? (m * NO + f) * 2u : OUT_OF_RANGE), 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      stores = 2 * MT;
+    } else {
+      const bf16_t* bias = (const bf16_t*)a.bias;
+      const bool with_resid = (a.epi & EPI_RESIDUAL) != 0;
+      const __amdgpu_buffer_rsrc_t rr_ = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<void*>(with_resid ? a.resid : a.y), 0, (int)(((uint64_t)(rows_all - 1) * ldy + a.N) * 2), 0x00020000);
+      auto at = [&](int u) Q4_INLINE {
+        const uint32_t m = m0 + (u >> 2) * 32, n = n0 + ((u >> 1) & 1) * 32 + (2u * (u & 1) + half) * 8u;
+        return m <= m_last && n < a.N ? (m * ldy + n) * 2u : OUT_OF_RANGE;
+      };
+      u32x4 rn = {0, 0, 0, 0};
+      if (with_resid) rn = __builtin_amdgcn_raw_buffer_load_b128(rr_, (int)at(0), 0, 0);
+#pragma unroll
+      for (int u = 0; u < 4 * MT; ++u) {
+        const int i = u >> 2, j = (u >> 1) & 1, bp = u & 1;
+        const u32x4 rr = rn;
+        if (with_resid && u + 1 < 4 * MT) rn = __builtin_amdgcn_raw_buffer_load_b128(rr_, (int)at(u + 1), 0, 0);
+        float v[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) Q4_ACC(i, j, 4 * (2 * bp + h) + c, v[h][c]);
+        Q4_SWAP8(v[0], v[1]);
+        const uint32_t o = at(u), n = n0 + j * 32 + (2u * bp + half) * 8u;
+        if (a.epi & EPI_BIAS) {
+          const uint4 bb = *reinterpret_cast<const uint4*>(bias + min(n, a.N - 8));
+          v[0][0] += __uint_as_float(bb.x << 16); v[0][1] += __uint_as_float(bb.x & 0xffff0000u);
+          v[0][2] += __uint_as_float(bb.y << 16); v[0][3] += __uint_as_float(bb.y & 0xffff0000u);
+          v[1][0] += __uint_as_float(bb.z << 16); v[1][1] += __uint_as_float(bb.z & 0xffff0000u);
+          v[1][2] += __uint_as_float(bb.w << 16); v[1][3] += __uint_as_float(bb.w & 0xffff0000u);
+        }
+        if (with_resid) {
+          v[0][0] += __uint_as_float(rr.x << 16); v[0][1] += __uint_as_float(rr.x & 0xffff0000u);
+          v[0][2] += __uint_as_float(rr.y << 16); v[0][3] += __uint_as_float(rr.y & 0xffff0000u);
+          v[1][0] += __uint_as_float(rr.z << 16); v[1][1] += __uint_as_float(rr.z & 0xffff0000u);
+          v[1][2] += __uint_as_float(rr.w << 16); v[1][3] += __uint_as_float(rr.w & 0xffff0000u);
+        }
+        if (a.epi & EPI_RELU) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[h][c] = fmaxf(v[h][c], 0.0f);
+        }
+        const u32x4 out = {pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3]),
+                           pack_bf16x2(v[1][0], v[1][1]), pack_bf16x2(v[1][2], v[1][3])};
+        __builtin_amdgcn_raw_buffer_store_b128(out, ry, (int)o, 0, 0);
+        if ((a.epi & EPI_SUMSQ) && o != OUT_OF_RANGE) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float q0 = __uint_as_float(out[q] << 16), q1 = __uint_as_float(out[q] & 0xffff0000u);
+            ssq = __builtin_fmaf(q0, q0, ssq);
+            ssq = __builtin_fmaf(q1, q1, ssq);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      stores = 4 * MT;
+    }
+#undef Q4_SWAP8
+#undef Q4_ACC
+    if (!more) break;
+  }
+  if (a.epi & EPI_SUMSQ) {
+    float* red = reinterpret_cast<float*>(lds + L::RED);      // behind the stages
+    ssq = wave_sum(ssq);
+    if (lane == 0) red[wave] = ssq;
+    __syncthreads();
+    if (t == 0) a.partials[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+  }
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");         // loads past the end still write the LDS
+}
+#undef Q4_DTL
+
+// The LDS limits of all instantiations are set together: a size that is captured into a graph may be the first of its
+// tile height.
+template <int MT>
+hipError_t w4_prepare() {
+  hipError_t e = hipFuncSetAttribute((const void*)w4_gemm_kernel<MT, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     W4Lds<MT, false>::BYTES);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)w4_gemm_kernel<MT, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            W4Lds<MT, true>::BYTES);
+  if constexpr (MT > 1) return e != hipSuccess ? e : w4_prepare<MT - 1>();
+  return e;
+}
+template <int MT>
+void w4_launch(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
+  if (a.zp) w4_gemm_kernel<MT, true><<<p.wgs, 256, W4Lds<MT, true>::BYTES, st>>>(a, p);
+  else w4_gemm_kernel<MT, false><<<p.wgs, 256, W4Lds<MT, false>::BYTES, st>>>(a, p);
+}
+
+}  // namespace
+
+// Height of the output tiles: the one whose rounds of units take the least time.  A round lasts as long as one unit,
+// K_TILE us per k-tile on a full chip and 1.5 + 0.9 mt us around the k-loop (repeated launches, N = 8192, K from 2048 to
+// 16384, one round each); the matrix unit alone accounts for 0.13 us per tile of 32 tokens, what does not shrink with the
+// tile is the conversion of its 256 weight rows.
+W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t ksplit, uint32_t kt_per,
+               uint32_t most_parts) {
+  static const double K_TILE[9] = {0, 0.58, 0.71, 0.83, 0.95, 1.11, 1.26, 1.42, 1.58};
+  const uint32_t cus = gemm_workgroups(1u << 20, 1u << 20);
+  W4Plan best = {};
+  double best_time = 0.0;
+  for (uint32_t mt = 8; mt > 0; --mt) {
+    W4Plan p = {};
+    p.mt = mt;
+    p.ksplit = ksplit; p.kt_per = ksplit > 1 ? kt_per : K / BK;
+    p.second_row = second_row; p.rows = second_row ? second_row + M : M;
+    p.tiles_n = (N + BN - 1) / BN;
+    p.tiles_per_pass = (M + 32 * mt - 1) / (32 * mt);
+    p.tiles_m = second_row ? 2 * p.tiles_per_pass : p.tiles_per_pass;
+    const uint64_t places = ((uint64_t)p.tiles_m * p.tiles_n * ksplit + 7) / 8 * 8;     // an equal share for every XCD
+    p.wgs = (uint32_t)std::min<uint64_t>(places, cus);
+    if (most_parts && p.wgs > most_parts && mt < 8) continue;
+    const double time = (double)((places + cus - 1) / cus) * (p.kt_per * K_TILE[mt] + 1.5 + 0.9 * mt);
+    if (mt == 8 || time < 0.98 * best_time) { best = p; best_time = time; }
+  }
+  return best;
+}
+
+hipError_t launch_w4_tiles(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
+  static bool ready = false;
+  if (!ready) {
+    hipError_t e = w4_prepare<8>();
+    if (e != hipSuccess) return e;
+    ready = true;
+  }
+  if ((a.epi & EPI_SUMSQ) && p.wgs > a.n_partials) return hipErrorInvalidValue;
+  switch (p.mt) {
+    case 1: w4_launch<1>(a, p, st); break;
+    case 2: w4_launch<2>(a, p, st); break;
+    case 3: w4_launch<3>(a, p, st); break;
+    case 4: w4_launch<4>(a, p, st); break;
+    case 5: w4_launch<5>(a, p, st); break;
+    case 6: w4_launch<6>(a, p, st); break;
+    case 7: w4_launch<7>(a, p, st); break;
+    case 8: w4_launch<8>(a, p, st); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace qzo

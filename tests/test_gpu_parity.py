@@ -1495,6 +1495,37 @@ def test_activation_reordering_matrix_bit_exact_and_linear(oracle, M, N, K):
         assert torch.equal(y, y2)
 
 
+@pytest.mark.parametrize("zp", [False, True])
+@pytest.mark.parametrize("M,N,K", [(144, 8, 256), (129, 13520, 384), (257, 13216, 384), (389, 13096, 128),
+                                   (641, 10792, 128), (645, 13304, 256), (774, 13120, 256), (899, 13296, 128),
+                                   (2049, 11016, 256)])
+def test_fused_linear_of_every_tile_height(M, N, K, zp):
+    """The fused kernel at sizes whose rule picks tiles of 32, 64, .. 256 tokens (one each, then several tiles per
+    workgroup), last tiles ragged in tokens and features: bit for bit the expanded weights through the plain GEMM."""
+    rng = np.random.default_rng(M + N)
+    G = K // 128
+    x = _dev(rng.standard_normal((M, K), dtype=np.float32), torch.bfloat16)
+    q = _dev(rng.integers(0, 256, (N, K // 2), dtype=np.uint8))
+    s = _dev(rng.uniform(0.002, 0.02, (N, G)).astype(np.float32), torch.bfloat16)
+    z = _dev(rng.integers(0, 16, (N, G), dtype=np.uint8)) if zp else None
+    want = torch.zeros((M, N), dtype=torch.bfloat16, device=DEV)
+    scratch = torch.empty(qb.qzo_int4_scratch_bytes(N, K), dtype=torch.uint8, device=DEV)
+    qb.qzo_int4_gemm_expanded(x, q, s, z, None, 11, 31, 1e-3, -1, want, scratch)
+    guard = torch.full(((M + 32) * N,), 7.0, dtype=torch.bfloat16, device=DEV)
+    y, ssq = guard[:M * N].view(M, N), torch.zeros(1, dtype=torch.float32, device=DEV)
+    args = (x, q, s) + ((z,) if zp else ()) + (11, 31, 1e-3, -1, y, ssq)
+    (qb.qzo_dequant_gemm_zp if zp else qb.qzo_dequant_gemm)(*args)
+    assert torch.equal(y, want)
+    assert bool((guard[M * N:] == 7.0).all())
+    ref = float((want.double() ** 2).sum())          # fp32 sums of up to 2000 terms a lane (2^-24 sqrt(2000) each), then 256
+    assert abs(float(ssq) - ref) <= 1e-4 * ref
+    # room for one partial sum per 256 x 256 tile only
+    least = (-(-M // 256) * -(-N // 256) * 4 + 255) // 256 * 256
+    y.zero_(), ssq.zero_()
+    (qb.qzo_dequant_gemm_zp if zp else qb.qzo_dequant_gemm)(*args, scratch=torch.empty(least, dtype=torch.uint8, device=DEV))
+    assert torch.equal(y, want) and abs(float(ssq) - ref) <= 1e-4 * ref
+
+
 @pytest.mark.parametrize("name", ["tiny", "few_llama"])
 def test_step_replays_from_a_captured_graph(oracle, name):
     """qzo_step allocates nothing and never synchronises, so after one eager call (which sets the
