@@ -451,7 +451,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
   // overlaps the next tile's main loop.
   const uint32_t m0 = tile_m * BM, n0 = tile_n * BN;
   const uint32_t done_m = tile_m, done_n = tile_n, done_slice = kslice;
-  walk.slot += walk.stride;
+  tile_walk_next(walk);
   const bool more = tile_walk_get(walk, tile_m, tile_n);
   if (more) {
     if (SPLITK && ksplit > 1) {

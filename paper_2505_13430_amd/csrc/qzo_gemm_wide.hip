@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256, 1) void wide_gemm_kernel(GemmArgs a) {
 
     const uint32_t m0 = tile_m * BM, n0 = tile_n * BN;
     const uint32_t done_m = tile_m, done_n = tile_n;
-    walk.slot += walk.stride;
+    tile_walk_next(walk);
     const bool more = tile_walk_get(walk, tile_m, tile_n);
     if (more) {             /* every wavefront is past the barrier that ended the last k-tile */
       QW_TILE_PTRS(tile_m, tile_n);

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   uint32_t xo[MT], wo[4], so;
   float eps;
   auto point = [&]() Q4_INLINE {
-    kslice = tile_n / p.tiles_n;
+    kslice = p.ksplit > 1 ? tile_n / p.tiles_n : 0u;
     tile_n -= kslice * p.tiles_n;
     kt0 = kslice * p.kt_per;
     ng = min(p.kt_per, K / BK - kt0) >> 1;
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
     else if (q == 4) Q4_DTL("buffer_load_ushort", rs, base + L::W + wave * 256, so * 2, g * 2);
     else Q4_DTL("buffer_load_ubyte", rz, base + L::W + L::S + wave * 256, so, g);
   };
-  auto request_first = [&]() Q4_INLINE {       // groups 0 and 1, k-tiles 0 and 1, in the order the k-loop goes on with
+  auto request_first = [&]() Q4_INLINE {       // groups 0 and 1, k-tiles 0, 1 and 2, in the order the k-loop goes on with
 #pragma unroll
     for (int q = 0; q < L::NW; ++q) load_w(q, 0u, 0u);
 #pragma unroll
@@ -140,6 +140,8 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
 #pragma unroll
       for (int i = 0; i < MT; ++i) xo[i] = OUT_OF_RANGE;
     }
+#pragma unroll
+    for (int i = 0; i < MT; ++i) load_x(i, 2u, 2 * L::X);
   };
 
   // fragment addresses: activations: row lrow (+ 32 i), chunk of k-step ks; weights: row lrow (+ 32 j), the dwords of
@@ -243,9 +245,10 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
         else if (n < MT + (E == ODD ? L::NW : 0)) load_x(n - (E == ODD ? L::NW : 0), 2 * g + E + 2, stage);
       }
   };
-  auto step = [&](auto S_, auto D_, auto FIRST_, uint32_t g, uint32_t slot) Q4_INLINE {
+  // START: the unit's first group: its accumulators start from zero, its third k-tile is on its way already.
+  auto step = [&](auto S_, auto D_, auto START_, uint32_t g, uint32_t slot) Q4_INLINE {
     constexpr int S = decltype(S_)::value, D = decltype(D_)::value;
-    constexpr bool FIRST = decltype(FIRST_)::value != 0;
+    constexpr bool START = decltype(START_)::value != 0, FIRST = START && D == 0 && S == 0;
     constexpr int buf = S & 1, nb = buf ^ 1, ks = (S + 1) & 3, kk = (D * 4 + S + 1) & 7;
     // load slots: steps 3, 0, 1, 2 in this order; E: the k-tile whose list they belong to
     constexpr int E = S == 3 ? D ^ 1 : D, NL = MT + (E ? L::NW : 0), Q = (S + 1) & 3;
@@ -258,7 +261,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       // S = 2: denser, the barrier that follows waits for them
       if (S == 2 ? m < MT : (m & 1) == 0) read_x(nb, S == 2 ? m : m >> 1, ks, stage);
       const int l0 = (Q * SLOTS + m) * NL / (4 * SLOTS), l1 = (Q * SLOTS + m + 1) * NL / (4 * SLOTS);
-      loads(Int<E>(), l0, l1 - l0, lg, slot, S == 3 ? st_cur : st_load);
+      if (!(START && D == 0 && S < 3)) loads(Int<E>(), l0, l1 - l0, lg, slot, S == 3 ? st_cur : st_load);
 #pragma unroll
       for (int c = m * 16 / SLOTS; c < (m + 1) * 16 / SLOTS; ++c) convert(nb, c, kk);
       __builtin_amdgcn_sched_barrier(0);
@@ -271,8 +274,17 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       fw[nb][j] = __builtin_bit_cast(bf16x8, pin);
     }
   };
-  auto sync = [&](auto LEFT_) Q4_INLINE {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(decltype(LEFT_)::value) : "memory");
+  // Ends a k-tile: all but the LEFT loads issued last have landed, as far as this wavefront's go, and everyone is past
+  // its fragment reads.  In a unit's first group the stores of the epilogue before may be among the youngest.
+  uint32_t stores = 0;                              // of the last epilogue, issued behind the unit's first loads
+  auto sync = [&](auto LEFT_, auto START_) Q4_INLINE {
+    constexpr int LEFT = decltype(LEFT_)::value;
+    if (decltype(START_)::value && stores == 4 * MT)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(std::min(63, LEFT + 4 * MT)) : "memory");
+    else if (decltype(START_)::value && stores == 2 * MT)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(std::min(63, LEFT + 2 * MT)) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(LEFT) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -281,7 +293,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
     const uint32_t o = st_cur;
     st_cur = st_next; st_next = st_load; st_load = o;
   };
-  auto group = [&](uint32_t g, auto FIRST_) Q4_INLINE {
+  auto group = [&](uint32_t g, auto START_) Q4_INLINE {
     const uint32_t slot = (g & 1u) ? L::SLOT : 0u, other = L::SLOT - slot, gb = (kt0 >> 1) + g;
     if (g + 2 >= ng) {
 #pragma unroll
@@ -289,25 +301,25 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       so = OUT_OF_RANGE >> 1;
     }
     read_raw(2, slot); read_raw(3, slot);
-    step(Int<0>(), Int<0>(), FIRST_, g, slot);
-    step(Int<1>(), Int<0>(), Int<0>(), g, slot);
+    step(Int<0>(), Int<0>(), START_, g, slot);
+    step(Int<1>(), Int<0>(), START_, g, slot);
     noise(gb + 1, false);
     __builtin_amdgcn_sched_barrier(0);
-    step(Int<2>(), Int<0>(), Int<0>(), g, slot);
-    sync(Int<MT>());
-    step(Int<3>(), Int<0>(), Int<0>(), g, slot);
+    step(Int<2>(), Int<0>(), START_, g, slot);
+    sync(Int<MT>(), START_);
+    step(Int<3>(), Int<0>(), START_, g, slot);
     next_stage();
     read_raw(0, other); read_raw(1, other); read_scale(other);
-    step(Int<0>(), Int<1>(), Int<0>(), g, slot);
-    step(Int<1>(), Int<1>(), Int<0>(), g, slot);
-    step(Int<2>(), Int<1>(), Int<0>(), g, slot);
-    sync(Int<MT + L::NW>());
+    step(Int<0>(), Int<1>(), START_, g, slot);
+    step(Int<1>(), Int<1>(), START_, g, slot);
+    step(Int<2>(), Int<1>(), START_, g, slot);
+    sync(Int<MT + L::NW>(), START_);
     new_scale(gb + 1);
     if (g + 2 >= ng) {
 #pragma unroll
       for (int i = 0; i < MT; ++i) xo[i] = OUT_OF_RANGE;
     }
-    step(Int<3>(), Int<1>(), Int<0>(), g, slot);
+    step(Int<3>(), Int<1>(), START_, g, slot);
     next_stage();
   };
 
@@ -317,19 +329,11 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
       a.y, 0, (int)(((uint64_t)(rows_all - 1) * (swiglu ? NO : ldy) + NO) * 2), 0x00020000);
   float ssq = 0.0f;                                 // of all units of the workgroup
-  uint32_t stores = 0;                              // stores of the last epilogue, issued behind the next unit's loads
 
   point();
   request_first();
   for (;;) {
-    // first group's weights and first k-tile have landed; k-tile 1, group 1 and the epilogue's stores may not have
-    if (stores == 4 * MT) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(std::min(63, MT + L::NW + 4 * MT)) : "memory");
-    else if (stores == 2 * MT) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(MT + L::NW + 2 * MT) : "memory");
-    else if (stores) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(MT + L::NW) : "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
+    sync(Int<2 * MT + L::NW>(), Int<1>());          // the first group's weights and the first k-tile have landed
     st_cur = 0; st_next = L::X; st_load = 2 * L::X;
     read_raw(0, 0u); read_raw(1, 0u); read_scale(0u);
 #pragma unroll
@@ -338,14 +342,13 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
     new_scale(kt0 >> 1);
 #pragma unroll
     for (int c = 0; c < 16; ++c) convert(0, c, 0);
-    loads(Int<0>(), 0, MT / 4, 0u, 0u, st_load);
     __builtin_amdgcn_sched_barrier(0);
     group(0u, Int<1>());
     for (uint32_t g = 1; g < ng; ++g) group(g, Int<0>());
 
     const uint32_t m0 = row0 + lrow, m_last = row_last, n0 = tile_n * 256u + wave * 64u, slice = kslice;
     const uint32_t done_n = tile_n;
-    walk.slot += walk.stride;
+    tile_walk_next(walk);
     const bool more = tile_walk_get(walk, tile_m, tile_n);
     if (more) {                 // every wavefront is past the barrier that ended the last k-tile
       point();
@@ -356,7 +359,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
 // accumulators are read out one piece at a time (left to itself the compiler copies all of them to vector registers)
 #define Q4_ACC(I, J, R, DST)                                                                 \
   do {                                                                                       \
-    if constexpr (MT >= 5) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(DST) : "a"(acc[I][J][R])); \
+    if constexpr (MT >= 5) asm("v_accvgpr_read_b32 %0, %1" : "=v"(DST) : "a"(acc[I][J][R])); \
     else DST = acc[I][J][R];                                                                 \
   } while (0)
 #define Q4_SWAP8(LO, HI)                                                                     \
@@ -386,7 +389,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
           dst[0] = make_float4(v[0][0], v[0][1], v[0][2], v[0][3]);
           dst[1] = make_float4(v[1][0], v[1][1], v[1][2], v[1][3]);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        if (u & 1) __builtin_amdgcn_sched_barrier(0);
       }
       stores = 1;
     } else if (swiglu) {
@@ -409,44 +412,51 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
         const u32x4 out = {pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3]),
                            pack_bf16x2(v[1][0], v[1][1]), pack_bf16x2(v[1][2], v[1][3])};
         __builtin_amdgcn_raw_buffer_store_b128(out, ry, (int)(m <= m_last ? (m * NO + f) * 2u : OUT_OF_RANGE), 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
+        if (u & 1) __builtin_amdgcn_sched_barrier(0);
       }
       stores = 2 * MT;
     } else {
-      const bf16_t* bias = (const bf16_t*)a.bias;
-      const bool with_resid = (a.epi & EPI_RESIDUAL) != 0;
+      const bool with_resid = (a.epi & EPI_RESIDUAL) != 0, with_bias = (a.epi & EPI_BIAS) != 0;
       const __amdgpu_buffer_rsrc_t rr_ = __builtin_amdgcn_make_buffer_rsrc(
           const_cast<void*>(with_resid ? a.resid : a.y), 0, (int)(((uint64_t)(rows_all - 1) * ldy + a.N) * 2), 0x00020000);
       auto at = [&](int u) Q4_INLINE {
         const uint32_t m = m0 + (u >> 2) * 32, n = n0 + ((u >> 1) & 1) * 32 + (2u * (u & 1) + half) * 8u;
         return m <= m_last && n < a.N ? (m * ldy + n) * 2u : OUT_OF_RANGE;
       };
-      u32x4 rn = {0, 0, 0, 0};
-      if (with_resid) rn = __builtin_amdgcn_raw_buffer_load_b128(rr_, (int)at(0), 0, 0);
+      // residuals are requested AHEAD pieces before they are used: a few memory latencies per tile, not one per piece
+      constexpr int AHEAD = 12;
+      u32x4 rr[AHEAD];
+      uint4 bb[4];
+      if (with_resid) {
+#pragma unroll
+        for (int u = 0; u < AHEAD && u < 4 * MT; ++u) rr[u] = __builtin_amdgcn_raw_buffer_load_b128(rr_, (int)at(u), 0, 0);
+      }
+      if (with_bias) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          bb[c] = *reinterpret_cast<const uint4*>((const bf16_t*)a.bias + min(n0 + (c >> 1) * 32 + (2u * (c & 1) + half) * 8u, a.N - 8));
+      }
+      auto add8 = [&](float (&v)[2][4], u32x4 w) Q4_INLINE {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          v[q >> 1][2 * (q & 1)] += __uint_as_float(w[q] << 16);
+          v[q >> 1][2 * (q & 1) + 1] += __uint_as_float(w[q] & 0xffff0000u);
+        }
+      };
 #pragma unroll
       for (int u = 0; u < 4 * MT; ++u) {
         const int i = u >> 2, j = (u >> 1) & 1, bp = u & 1;
-        const u32x4 rr = rn;
-        if (with_resid && u + 1 < 4 * MT) rn = __builtin_amdgcn_raw_buffer_load_b128(rr_, (int)at(u + 1), 0, 0);
         float v[2][4];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
           for (int c = 0; c < 4; ++c) Q4_ACC(i, j, 4 * (2 * bp + h) + c, v[h][c]);
         Q4_SWAP8(v[0], v[1]);
-        const uint32_t o = at(u), n = n0 + j * 32 + (2u * bp + half) * 8u;
-        if (a.epi & EPI_BIAS) {
-          const uint4 bb = *reinterpret_cast<const uint4*>(bias + min(n, a.N - 8));
-          v[0][0] += __uint_as_float(bb.x << 16); v[0][1] += __uint_as_float(bb.x & 0xffff0000u);
-          v[0][2] += __uint_as_float(bb.y << 16); v[0][3] += __uint_as_float(bb.y & 0xffff0000u);
-          v[1][0] += __uint_as_float(bb.z << 16); v[1][1] += __uint_as_float(bb.z & 0xffff0000u);
-          v[1][2] += __uint_as_float(bb.w << 16); v[1][3] += __uint_as_float(bb.w & 0xffff0000u);
-        }
+        const uint32_t o = at(u);
+        if (with_bias) add8(v, u32x4{bb[u & 3].x, bb[u & 3].y, bb[u & 3].z, bb[u & 3].w});
         if (with_resid) {
-          v[0][0] += __uint_as_float(rr.x << 16); v[0][1] += __uint_as_float(rr.x & 0xffff0000u);
-          v[0][2] += __uint_as_float(rr.y << 16); v[0][3] += __uint_as_float(rr.y & 0xffff0000u);
-          v[1][0] += __uint_as_float(rr.z << 16); v[1][1] += __uint_as_float(rr.z & 0xffff0000u);
-          v[1][2] += __uint_as_float(rr.w << 16); v[1][3] += __uint_as_float(rr.w & 0xffff0000u);
+          add8(v, rr[u % AHEAD]);
+          if (u + AHEAD < 4 * MT) rr[u % AHEAD] = __builtin_amdgcn_raw_buffer_load_b128(rr_, (int)at(u + AHEAD), 0, 0);
         }
         if (a.epi & EPI_RELU) {
 #pragma unroll
@@ -465,7 +475,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
             ssq = __builtin_fmaf(q1, q1, ssq);
           }
         }
-        __builtin_amdgcn_sched_barrier(0);
+        if (u & 1) __builtin_amdgcn_sched_barrier(0);
       }
       stores = 4 * MT;
     }
