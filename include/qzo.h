@@ -140,9 +140,9 @@ qzo_status qzo_model_destroy(qzo_model* m);
 qzo_status qzo_model_scale_count(const qzo_model_config* cfg, uint64_t* out);
 
 /* Bytes of device workspace qzo_forward_loss / qzo_step need for (batch, seq): activations,
- * cross-entropy partials, the RoPE angle table, K-slice partial sums, and for the
- * expand-then-multiply route (see qzo_model_set_int4_path) one linear's perturbed weights in
- * bf16 plus every perturbed scale of the model in fp32.  Depends on the model's int4 route and
+ * cross-entropy partials, the RoPE angle table, K-slice partial sums, and where a linear is expanded
+ * first (int4 on request, see qzo_model_set_int4_path; group index per column, codebook, NormalFloat-4 with many
+ * tokens) one linear's perturbed weights in bf16 plus every perturbed scale of the model in fp32.  Depends on the model's int4 route and
  * on joint mode: query it after setting those. */
 qzo_status qzo_workspace_bytes(const qzo_model* m, uint32_t batch, uint32_t seq, uint64_t* out);
 
@@ -150,9 +150,8 @@ qzo_status qzo_workspace_bytes(const qzo_model* m, uint32_t batch, uint32_t seq,
  * One perturbed forward pass: L((Delta + sign*eps*z) (.) theta-bar; B) of Eq. 5,
  * next-token cross-entropy averaged over the batch*(seq-1) predicted positions.
  * The stored scales are not modified: the perturbed scale s + sign*eps*z is one fp32
- * fma (the functional form of PERTURB_SCALES in Algorithm 1), formed inside the GEMM's
- * weight tile on the fused route.  On the expand-then-multiply route (the default from a
- * few thousand tokens per pass on, see qzo_model_set_int4_path) a pass first writes the
+ * fma (the functional form of PERTURB_SCALES in Algorithm 1), formed inside the GEMM.  Where a linear is
+ * expanded first (on request, see qzo_model_set_int4_path) a pass writes the
  * perturbed scales of the whole model (fp32) and then, linear by linear, the perturbed
  * weights (bf16) into the workspace, where they live until the next linear / pass
  * overwrites them; z itself is never written anywhere.
@@ -413,11 +412,10 @@ qzo_status qzo_int4_gemm_expanded(const void* x_dev, const void* q_dev, const vo
                                   float eps, int sign, void* y_dev, void* scratch_dev,
                                   uint64_t scratch_bytes, void* stream);
 
-/* How a model's int4 linears (quant 0 and 2) run.  mode 0 (default): by size; a linear [N,K] with at
- * least 2300 + 3.3e10 / (N K) tokens in a pass (2950 for 12288 x 4096) has its perturbed weights first
- * written out as a bf16 matrix in the workspace (same bits as the fused kernel's weight tile) and multiplied
- * by the plain bf16 GEMM, with fewer the fused dequantizing GEMM runs (below the break-even an expansion
- * costs more than the fused kernel's extra work).  mode 1: always the fused kernel.  mode 2: always expand-then-multiply.
+/* How a model's int4 linears (quant 0 and 2) run.  mode 0 (default): the fused dequantizing GEMM at every token count;
+ * up to some 3000-4096 tokens a step runs its two passes as one forward.  mode 1: the same, stacked up to 4096 tokens
+ * whatever the linears.  mode 2: expand-then-multiply: the perturbed weights of a linear are first written out as a bf16
+ * matrix in the workspace (same bits as the weights that the fused kernel forms) and multiplied by the plain bf16 GEMM.
  * A field of the model; call it before qzo_workspace_bytes (the workspace layout depends on it).
  * QZO_ERR_ARG for another mode, QZO_ERR_UNSUPPORTED for a model whose format is not int4. */
 qzo_status qzo_model_set_int4_path(qzo_model* m, int mode);

@@ -68,8 +68,8 @@ struct qzo_model {
   uint32_t rows_per_layer;
   UpdPlan plan;
   uint32_t tensors_per_layer, first_layer_tensor;
-  // int4 linears: 0 = expand-then-multiply from expand_min_m_int4(N, K) tokens on, 1 = always the
-  // fused kernel, 2 = always expand-then-multiply
+  // int4 linears: 0 = by size, 1 = the fused kernel with its passes stacked up to STACK_TILE_MAX_M tokens, 2 = always
+  // expand-then-multiply
   int int4_path = 0;
   // joint SPSA on the un-quantized parameters (off until qzo_model_enable_joint)
   float* dense_master = nullptr;       // caller-owned fp32 [n_dense]
@@ -265,7 +265,7 @@ bool nf4_stack_pays(const qzo_model* m, uint64_t M1) {
 // most 32 tokens the few-token kernel reads the int4 weights once for both, with up to 64 its launches hold a
 // workgroup of either pass (half the launches, bit-identical to separate passes); on the route above mid_gemm_kernel
 // serves both.
-// Beyond and as long as the fused kernel serves (at most 4096 tokens per pass), a launch of
+// Beyond (at most 4096 tokens per pass), a launch of
 // the tile kernel holds both passes' token tiles, the second pass's with -eps: twice the tiles per
 // launch for a chip that such token counts do not fill, half the launches.  The second pass starts
 // on a tile boundary (stacked_pass_stride); the rows in between are padding (zeros at the embedding,
@@ -284,12 +284,20 @@ bool passes_stacked(const qzo_model* m, uint64_t M1) {
       if (!skinny_fits(2 * (uint32_t)M1, m->lin[i].N, m->lin[i].K)) return false;
     return true;
   }
-  // Stacked, the fused kernel stays ahead of expand-then-multiply for a fifth more tokens than the
-  // break-even of separate passes (7B widths: 72.2 against 74.9 ms per step at 2560 tokens, 83.8
-  // against 85.0 at 3072, 103.5 against 100.1 at 4096).
-  if (m->int4_path == 0)
-    for (int i = 0; i < 4; ++i)
-      if (M1 * 5 >= (uint64_t)expand_min_m_int4(m->lin[i].N, m->lin[i].K) * 6) return false;
+  // Up to a fifth beyond whole_k_min_m always; from there on where the same linears are cut along K either way, namely
+  // none, so that the sums (and losses) are those of two forwards.  Stacked over separate there: 7B widths 3240 tokens
+  // 0.96, 3360 0.99, 3600 0.99, 4096 0.96; 13B widths 3072 0.99.
+  if (m->int4_path == 0) {
+    const uint64_t rows = stacked_pass_stride(m, M1) + M1;
+    bool beyond = false, cut = rows * widest_row(c) * 2 >= (1ull << 31);
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t N = m->lin[i].N, K = m->lin[i].K;
+      beyond = beyond || M1 * 5 >= (uint64_t)whole_k_min_m(N, K) * 6;
+      for (uint32_t r : {(uint32_t)M1, (uint32_t)rows})
+        cut = cut || tile_ksplit(r, N, K, nullptr) > 1 || tile_tail_cols(r, N, K, c.arch == 0 && i == 2 ? EPI_SWIGLU : 0);
+    }
+    if (beyond && cut) return false;
+  }
   return true;
 }
 
@@ -351,8 +359,7 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   for (int i = 0; i < 4; ++i) {
     const uint64_t bytes = (uint64_t)m->lin[i].N * m->lin[i].K * 2;
     const bool expanded = (c.quant == 3 && !mid) || c.act_order || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK) ||
-                          (int4 && m->int4_path != 1 && !stack &&
-                           (m->int4_path == 2 || M1 >= expand_min_m_int4(m->lin[i].N, m->lin[i].K)));
+                          (int4 && m->int4_path == 2 && !stack);
     if (expanded) ex = std::max(ex, bytes);
     if (c.quant == 3 && stack && !mid) ex = std::max(ex, 2 * bytes);      // both passes' matrices
   }
@@ -560,9 +567,8 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
         ProfScope ps(PK_W4GEMM, 2.0 * Mreal * (double)g.N * g.K, st);
         return launch_bf16_gemm(g, PLAIN_GEMM_PIPE, st);
       }
-      if (w.wexp && m->int4_path != 1 && n_pass == 1 &&
-          (m->int4_path == 2 || M >= expand_min_m_int4(g.N, g.K))) {
-        // many tokens: write the perturbed matrix out once, then a plain bf16 GEMM.  The rotary embedding
+      if (w.wexp) {
+        // the caller's choice: write the perturbed matrix out once, then a plain bf16 GEMM.  The rotary embedding
         // of a qkv linear rides on that GEMM's epilogue (heads of 64 or 128; with 128 the matrix is
         // written in the row order that puts feature i and i + 64 of a head into one lane).
         int order = (epi & EPI_SWIGLU) ? ROW_ORDER_SWIGLU : ROW_ORDER_NATURAL;
@@ -583,6 +589,17 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
         g.split_ws = (g.epi & (EPI_SWIGLU | EPI_ROPE)) ? nullptr : w.split;
         ProfScope ps(PK_W4GEMM, 2.0 * Mreal * (double)g.N * g.K, st);
         return launch_bf16_gemm(g, PLAIN_GEMM_PIPE, st);
+      }
+      if (M1 > SKINNY_MAX_M && !mid_ws && (epi & (EPI_ROPE | EPI_SWIGLU))) {
+        // Tile kernel: the rotary embedding rides on its epilogue (sequences too long for the attention kernel's own)
+        // where the linear is not cut along K.  A pass of whole_k_min_m tokens or more never cuts these linears.
+        const bool whole = m->int4_path == 0 && M >= whole_k_min_m(g.N, g.K) && !passes_stacked(m, M1);
+        if (whole) g.split_ws = nullptr;
+        const bool cut = g.split_ws && (tile_ksplit(M, g.N, g.K, nullptr) > 1 || tile_tail_cols(M, g.N, g.K, g.epi));
+        if (epi == EPI_ROPE && (whole || !rope_in_attention) && !cut && (dh == 64 || g.N % 256 == 0)) {
+          g.epi = EPI_ROPE; g.rope = w.rope; g.rope_S = seq; g.rope_dh = dh;
+          rope_fused = true;
+        }
       }
       ProfScope ps(PK_W4GEMM, 2.0 * Mreal * (double)g.N * g.K, st);
       return launch_w4a16_gemm(g, st);

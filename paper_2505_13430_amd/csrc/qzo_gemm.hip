@@ -820,6 +820,7 @@ hipError_t launch_w4a16_gemm(const GemmArgs& a0, hipStream_t st) {
   GemmArgs g = a;
   uint32_t ksplit = 1, kt_per = a.K / BK;
   if (a.split_ws) ksplit = tile_ksplit(a.M, a.N, a.K, &kt_per);
+  if (ksplit > 1 && (a.epi & EPI_ROPE)) return hipErrorInvalidValue;     // the reduction knows no rotary embedding
   if (ksplit > 1) g.epi = 0;         // natural row order, fp32 partial sums; the reduction applies a.epi
   if (a.flip_row) g.M = a.M - a.flip_row;
   hipError_t e = launch_w4_tiles(g, w4_plan(g.M, a.flip_row, a.N, a.K, ksplit, kt_per, g.epi & EPI_SUMSQ ? a.n_partials : 0u), st);

@@ -31,9 +31,9 @@ enum : uint32_t {
   EPI_RELU = 4u,
   EPI_SUMSQ = 8u,      // per-workgroup sum of bf16(y)^2 into partials
   EPI_SWIGLU = 16u,    // W is [gate rows | up rows] (N = 2F): y[M,F] = silu(gate) * up
-  EPI_ROPE = 32u,      // plain bf16 GEMM only: y is qkv [M, 3d] of heads of 64 or 128 features; the rotary embedding
+  EPI_ROPE = 32u,      // not where K is split: y is qkv [M, 3d] of heads of 64 or 128 features; the rotary embedding
                        // is applied to the q and k thirds on the way out (rope, rope_S); with heads of 128 the rows
-                       // of W must be in ROW_ORDER_ROPE128 order
+                       // of an expanded W must be in ROW_ORDER_ROPE128 order (the fused kernel takes them so by itself)
 };
 
 struct NextNorm {
@@ -195,18 +195,14 @@ hipError_t launch_scale_noise_all(const void* arena, const UpdPlan& plan, uint32
                                   float* z_all, hipStream_t st);
 hipError_t launch_expand_nf4_pair(const void* q, const void* s_bf16, const float* z, float eps, uint32_t N, uint32_t K,
                                   int order, void* out_bf16, hipStream_t st);
-// Tokens per pass from which an int4 linear [N,K] is expanded first.  The expansion costs two short
-// launches (about 8 us) plus 2.5 bytes per weight at about 4.5 TB/s; the fused kernel needs about 13.6 %
-// more time than the plain GEMM on the expanded weights, a time that grows with the tokens
-// (2 M N K flop at about 1.3 PFLOP/s).  Setting the two equal gives M = a + b / (N K) with a near
-// 2700 and b near 4e10; fitted to the measurements (Llama-2-7B widths: a tie at 2560 tokens, the
-// expansion 3 % ahead at 3072; 13B widths: 4.5 % ahead at 4096; OPT-1.3B widths, d = 2048: 7 % behind
-// at 4096) a = 2300, b = 3.3e10.
-// The codebook format is always expanded inside a model: its fused kernel is 45 % slower than the
-// plain GEMM and cannot split K.
-inline uint32_t expand_min_m_int4(uint32_t N, uint32_t K) {
+// Tokens from which a forward of its own (passes not stacked) never cuts K of an int4 qkv or gate/up linear [N,K], whose
+// epilogues (rotary embedding, SwiGLU) then ride on the tile kernel.  The line is where the chip is filled without K
+// slices; at 7B widths 2800-2960 tokens, 10 to 12 token tiles.
+inline uint32_t whole_k_min_m(uint32_t N, uint32_t K) {
   return 2300u + (uint32_t)(3.3e10 / ((double)N * (double)K));
 }
+// The codebook format is always expanded inside a model: its fused kernel is 45 % slower than the
+// plain GEMM and cannot split K.
 constexpr uint32_t EXPAND_MIN_M_CODEBOOK = 1;
 hipError_t launch_channel_update(void* c_fp16, uint32_t n, uint32_t row_base, uint32_t seed_lo,
                                  uint32_t seed_hi, float eta, float d_clipped,

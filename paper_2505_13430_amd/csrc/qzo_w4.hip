@@ -65,7 +65,8 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const uint32_t lrow = lane & 31u, half = lane >> 5;
   const uint32_t K = a.K, G = K >> 7;
-  const bool swiglu = (a.epi & EPI_SWIGLU) != 0, s_fp16 = a.s_fp16 != 0;
+  const bool swiglu = (a.epi & EPI_SWIGLU) != 0, rope = (a.epi & EPI_ROPE) != 0, s_fp16 = a.s_fp16 != 0;
+  const bool rope128 = rope && a.rope_dh == 128;
   TileWalk walk = tile_walk_of(p.tiles_m, p.tiles_n * p.ksplit);
   uint32_t tile_m, tile_n;
   if (!tile_walk_get(walk, tile_m, tile_n)) {
@@ -94,8 +95,10 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
     row0 = pass * p.second_row + (tile_m - pass * p.tiles_per_pass) * (32 * MT);
     row_last = pass * p.second_row + a.M - 1;
     eps = pass ? -a.eps_signed : a.eps_signed;
-    // fused SwiGLU: a wavefront's rows are 32 gate rows and the 32 up rows of the same features
+    // fused SwiGLU: a wavefront's rows are 32 gate rows and the 32 up rows of the same features; rotary embedding of
+    // heads of 128 (N % 256 == 0): 32 features and their partners 64 further on
     auto wrow = [&](uint32_t r) Q4_INLINE {
+      if (rope128) return tile_n * 256u + (r >> 7) * 128u + ((r >> 6) & 1u) * 32u + ((r >> 5) & 1u) * 64u + (r & 31u);
       return swiglu ? ((r >> 5) & 1u) * (a.N >> 1) + tile_n * 128u + (r >> 6) * 32u + (r & 31u)
                     : min(tile_n * 256u + r, a.N - 1);
     };
@@ -415,6 +418,69 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
         if (u & 1) __builtin_amdgcn_sched_barrier(0);
       }
       stores = 2 * MT;
+    } else if (rope) {
+      // qkv [rows, 3d] with the rotary embedding on its q and k thirds: the wavefront's two feature tiles hold feature f
+      // and feature f + dh/2 of a head for the same token.  An output is rounded to bf16 first (what a separate pass
+      // would read), rotated in fp32 at its position and rounded again.
+      const uint32_t hd = a.rope_dh >> 1;
+      const uint32_t na = (rope128 ? done_n * 256u + (wave >> 1) * 128u + (wave & 1u) * 32u : n0) + half * 8u;
+      const bool rotate = na < (a.N / 3u) * 2u;            // a wavefront's columns lie within one third of qkv
+      const float2* table = reinterpret_cast<const float2*>(a.rope) + (rope128 ? (wave & 1u) * 32u : 0u) + half * 8u;
+      const uint32_t pass_row0 = m0 >= p.second_row ? p.second_row : 0u;
+      // the (cos, sin) values of a step are requested AHEAD steps before they are used
+      auto table_of = [&](int u) Q4_INLINE {
+        const uint32_t pos = (min(m0 + (u >> 1) * 32, m_last) - pass_row0) % a.rope_S;
+        return reinterpret_cast<const float4*>(table + (uint64_t)pos * hd + (u & 1) * 16u);
+      };
+      constexpr int AHEAD = 4;
+      float4 tn[AHEAD][4] = {};
+      if (rotate) {
+#pragma unroll
+        for (int u = 0; u < AHEAD && u < 2 * MT; ++u)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) tn[u][q] = table_of(u)[q];
+      }
+#pragma unroll
+      for (int u = 0; u < 2 * MT; ++u) {
+        const int i = u >> 1, bp = u & 1;
+        float4 cs[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cs[q] = tn[u % AHEAD][q];
+        if (rotate && u + AHEAD < 2 * MT) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) tn[u % AHEAD][q] = table_of(u + AHEAD)[q];
+        }
+        float va[2][4], vb[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            Q4_ACC(i, 0, 4 * (2 * bp + h) + c, va[h][c]);
+            Q4_ACC(i, 1, 4 * (2 * bp + h) + c, vb[h][c]);
+          }
+        Q4_SWAP8(va[0], va[1]);
+        Q4_SWAP8(vb[0], vb[1]);
+        u32x4 oa = {pack_bf16x2(va[0][0], va[0][1]), pack_bf16x2(va[0][2], va[0][3]),
+                    pack_bf16x2(va[1][0], va[1][1]), pack_bf16x2(va[1][2], va[1][3])};
+        u32x4 ob = {pack_bf16x2(vb[0][0], vb[0][1]), pack_bf16x2(vb[0][2], vb[0][3]),
+                    pack_bf16x2(vb[1][0], vb[1][1]), pack_bf16x2(vb[1][2], vb[1][3])};
+        if (rotate) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {                    // cs[q]: (cos, sin) of pairs 2 q and 2 q + 1
+            const float a0 = __uint_as_float(oa[q] << 16), a1 = __uint_as_float(oa[q] & 0xffff0000u);
+            const float b0 = __uint_as_float(ob[q] << 16), b1 = __uint_as_float(ob[q] & 0xffff0000u);
+            oa[q] = pack_bf16x2(a0 * cs[q].x - b0 * cs[q].y, a1 * cs[q].z - b1 * cs[q].w);
+            ob[q] = pack_bf16x2(b0 * cs[q].x + a0 * cs[q].y, b1 * cs[q].z + a1 * cs[q].w);
+          }
+        }
+        const uint32_t m = m0 + i * 32, n = na + bp * 16u;
+        const bool inside = m <= m_last && n < a.N;
+        const uint32_t o = (m * a.N + n) * 2u;
+        __builtin_amdgcn_raw_buffer_store_b128(oa, ry, (int)(inside ? o : OUT_OF_RANGE), 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(ob, ry, (int)(inside ? o + hd * 2u : OUT_OF_RANGE), 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      stores = 4 * MT;
     } else {
       const bool with_resid = (a.epi & EPI_RESIDUAL) != 0, with_bias = (a.epi & EPI_BIAS) != 0;
       const __amdgpu_buffer_rsrc_t rr_ = __builtin_amdgcn_make_buffer_rsrc(
