@@ -374,9 +374,10 @@ qzo_status qzo_debug_dequant_zp(const void* q_dev, const void* s_dev, const void
  *   z as for qzo_dequant_gemm: counter (row_base + n, g/8), stream 0.
  * qzo_nf4_expand writes the perturbed scales (se_dev, fp32 [N, K/64], one fma each) and the perturbed
  * matrix (w_dev, bf16 [N,K], the fp32 product se * level rounded to nearest even).
- * qzo_nf4_gemm does the same into scratch_dev (qzo_nf4_scratch_bytes(N, K) bytes, 256-byte aligned,
- * contents undefined afterwards) and then Y = X W^T with the plain bf16 GEMM: x_dev bf16 [M,K],
- * y_dev bf16 [M,N].  The table lookup is done once per weight and pass, not once per token tile.
+ * qzo_nf4_gemm: Y = X W^T with that matrix, x_dev bf16 [M,K], y_dev bf16 [M,N]; scratch_dev: qzo_nf4_scratch_bytes(N, K)
+ * bytes, 256-byte aligned, contents undefined afterwards.  With a few thousand tokens the matrix is written there and
+ * multiplied by the plain bf16 GEMM; with fewer its weights are formed inside the fused kernel (the same bits; K may be
+ * cut into slices whose fp32 sums are added in order).
  * block must be 64, K a positive multiple of 128, N a multiple of 8, pointers 16-byte aligned.
  */
 qzo_status qzo_nf4_expand(const void* q_dev, const void* s_dev, uint32_t row_base, uint32_t N,

@@ -184,6 +184,29 @@ void table_layout(const qzo_model_config& c, std::vector<uint64_t>& need, std::v
   b16(V * d);
 }
 
+uint64_t layer_weights(const qzo_model* m) {
+  uint64_t weights = 0;
+  for (int i = 0; i < 4; ++i) weights += (uint64_t)m->lin[i].N * m->lin[i].K;
+  return weights;
+}
+// NormalFloat-4 without expansion, up to this many tokens per pass.
+uint32_t nf4_fused_most(const qzo_model* m) { return layer_weights(m) <= (1u << 28) ? 512u : 384u; }
+
+// NormalFloat-4 in the tile kernel (w4_gemm_kernel): wide layers beyond 64 tokens per pass.  A weight is looked up once per
+// tile of up to 256 tokens, by mid_gemm_kernel once per 64 or 128, but that one cuts K as finely as the chip is wide.
+// Steps, tile kernel over mid_gemm_kernel: 7B widths 64 tokens 1.12, 65 0.90, 96 0.91, 128 1.03, 132 0.80, 192 0.86, 256 0.88,
+// 400 0.72, 512 0.83; 13B widths 64 1.11, 96 0.82, 128 0.96, 256 0.76, 384 0.78; narrower layers (2048 x 8192 and less) 0.93-1.18.
+bool nf4_tile_route(const qzo_model* m, uint64_t M1) {
+  if (m->cfg.quant != 3 || M1 <= 64 || M1 > nf4_fused_most(m)) return false;
+  const uint64_t weights = layer_weights(m);
+  if (weights <= (1u << 26) || (weights <= (1u << 28) && M1 > 96 && M1 <= 128)) return false;
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t N = m->lin[i].N, K = m->lin[i].K;
+    if (((M1 + 255) / 256 * 256 + M1) * std::max(N, K) * 2 >= (1ull << 31) || N * K / 2 >= (1ull << 31)) return false;
+  }
+  return true;
+}
+
 // Token counts per pass that take mid_gemm_kernel: NormalFloat-4, and zero-point int4 with fp16 scales beyond the
 // few-token kernel's stacked range.
 //   Its time grows by tiles of 32 tokens, the tile kernel's by tiles of 256, and the wider the layer the better the tile
@@ -208,12 +231,12 @@ void table_layout(const qzo_model_config& c, std::vector<uint64_t>& need, std::v
 bool mid_route(const qzo_model* m, uint64_t M1) {
   const qzo_model_config& c = m->cfg;
   const bool nf4 = c.quant == 3;
+  if (nf4_tile_route(m, M1)) return false;
   if (!nf4 && (c.quant != 2 || !c.scale_fp16 || c.act_order)) return false;
   if (!nf4 && (M1 <= SKINNY_MAX_M_DUAL || m->int4_path == 2 || (m->int4_path == 1 && M1 > SKINNY_MAX_M))) return false;
-  uint64_t weights = 0;
-  for (int i = 0; i < 4; ++i) weights += (uint64_t)m->lin[i].N * m->lin[i].K;
+  const uint64_t weights = layer_weights(m);
   if (!nf4 && M1 <= SKINNY_MAX_M && weights <= (1u << 26)) return false;
-  const uint32_t most = nf4 ? (weights <= (1u << 28) ? 512u : 384u)
+  const uint32_t most = nf4 ? nf4_fused_most(m)
                             : (weights <= (1u << 26) ? 256u : (weights <= (1u << 28) ? 192u : 128u));
   if (M1 > most) return false;
   for (int i = 0; i < 4; ++i)
@@ -226,9 +249,11 @@ bool mid_route(const qzo_model* m, uint64_t M1) {
 // NormalFloat-4 has mid_gemm_kernel only (16 tokens: 3.9 ms a pass, expanded 8.1).
 bool mid_single_pass(const qzo_model* m, uint64_t M1) { return m->cfg.quant == 3 || M1 > SKINNY_MAX_M; }
 
-// Row at which the second pass of a stacked forward starts.
+// Row at which the second pass of a stacked forward starts: behind the first one's, on a multiple of 256 where the plain
+// GEMM's token tiles take their pass's expanded matrix (the rows in between are padding: zeros at the embedding, never
+// read back).
 uint64_t stacked_pass_stride(const qzo_model* m, uint64_t M1) {
-  const bool tiles_of_256 = !mid_route(m, M1) && (m->cfg.quant == 3 || M1 > SKINNY_MAX_M);
+  const bool tiles_of_256 = m->cfg.quant == 3 && !mid_route(m, M1) && !nf4_tile_route(m, M1);
   return tiles_of_256 ? (M1 + 255) / 256 * 256 : M1;
 }
 uint64_t widest_row(const qzo_model_config& c) {
@@ -267,15 +292,13 @@ bool nf4_stack_pays(const qzo_model* m, uint64_t M1) {
 // serves both.
 // Beyond (at most 4096 tokens per pass), a launch of
 // the tile kernel holds both passes' token tiles, the second pass's with -eps: twice the tiles per
-// launch for a chip that such token counts do not fill, half the launches.  The second pass starts
-// on a tile boundary (stacked_pass_stride); the rows in between are padding (zeros at the embedding,
-// never read back).
+// launch for a chip that such token counts do not fill, half the launches.
 // NormalFloat-4 beyond mid_gemm_kernel's range (up to 4096 tokens, too): where nf4_stack_pays.
 bool passes_stacked(const qzo_model* m, uint64_t M1) {
   const qzo_model_config& c = m->cfg;
   if (c.quant == 1 || m->dense_master || c.act_order) return false;
   if (c.quant == 3)
-    return mid_route(m, M1) || (M1 <= STACK_TILE_MAX_M && (stacked_pass_stride(m, M1) + M1) * widest_row(c) * 2 < (1ull << 31) &&
+    return mid_route(m, M1) || nf4_tile_route(m, M1) || (M1 <= STACK_TILE_MAX_M && (stacked_pass_stride(m, M1) + M1) * widest_row(c) * 2 < (1ull << 31) &&
                                 nf4_stack_pays(m, M1));
   if (M1 <= SKINNY_MAX_M_DUAL || mid_route(m, M1)) return true;
   if (M1 > STACK_TILE_MAX_M || m->int4_path == 2) return false;
@@ -288,7 +311,7 @@ bool passes_stacked(const qzo_model* m, uint64_t M1) {
   // none, so that the sums (and losses) are those of two forwards.  Stacked over separate there: 7B widths 3240 tokens
   // 0.96, 3360 0.99, 3600 0.99, 4096 0.96; 13B widths 3072 0.99.
   if (m->int4_path == 0) {
-    const uint64_t rows = stacked_pass_stride(m, M1) + M1;
+    const uint64_t rows = stacked_cut_rows((uint32_t)M1);
     bool beyond = false, cut = rows * widest_row(c) * 2 >= (1ull << 31);
     for (int i = 0; i < 4; ++i) {
       const uint32_t N = m->lin[i].N, K = m->lin[i].K;
@@ -327,7 +350,7 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   w.losses = (float*)take(256);
   // few-token path of the int4 GEMM: fp32 partial sums of the K slices of the largest linear
   uint64_t sk = 0;
-  const bool mid = mid_route(m, M1);
+  const bool mid = mid_route(m, M1), nf4_expanded = c.quant == 3 && !mid && !nf4_tile_route(m, M1);
   if (M1 <= SKINNY_MAX_M && int4 && !c.act_order)
     for (int i = 0; i < 4; ++i)
       sk = std::max<uint64_t>(sk, skinny_ws_floats((uint32_t)(mid ? M1 : M), m->lin[i].N, m->lin[i].K));
@@ -347,7 +370,7 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   uint64_t sp = 0;
   if ((M1 > SKINNY_MAX_M && int4 && !mid) || c.act_order || (c.quant == 3 && !mid) || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK))
     for (int i = 0; i < 4; ++i) {
-      sp = std::max<uint64_t>(sp, tile_split_ws_floats((uint32_t)M, m->lin[i].N, m->lin[i].K));
+      sp = std::max<uint64_t>(sp, tile_split_ws_floats(stack ? stacked_cut_rows((uint32_t)M1) : (uint32_t)M, m->lin[i].N, m->lin[i].K));
       // a single pass (qzo_forward_loss) of a batch whose step stacks its two passes
       if (stack) sp = std::max<uint64_t>(sp, tile_split_ws_floats((uint32_t)M1, m->lin[i].N, m->lin[i].K));
     }
@@ -358,10 +381,10 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   uint64_t ex = 0, sx = 0;
   for (int i = 0; i < 4; ++i) {
     const uint64_t bytes = (uint64_t)m->lin[i].N * m->lin[i].K * 2;
-    const bool expanded = (c.quant == 3 && !mid) || c.act_order || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK) ||
+    const bool expanded = nf4_expanded || c.act_order || (c.quant == 1 && M1 >= EXPAND_MIN_M_CODEBOOK) ||
                           (int4 && m->int4_path == 2 && !stack);
     if (expanded) ex = std::max(ex, bytes);
-    if (c.quant == 3 && stack && !mid) ex = std::max(ex, 2 * bytes);      // both passes' matrices
+    if (nf4_expanded && stack) ex = std::max(ex, 2 * bytes);      // both passes' matrices
   }
   if (ex && c.quant != 1) sx = m->n_scales * 4;     // every perturbed scale of the model, fp32
   w.wexp = take(ex);
@@ -385,9 +408,9 @@ qzo_status check_batch(const qzo_model* m, const void* tok, uint32_t batch, uint
     // the kernels address every operand with 32-bit byte offsets: tokens x widest tensor row, in
     // bf16, must stay below 2^31 bytes (stacked passes count twice)
     const qzo_model_config& c = m->cfg;
-    const uint64_t M1 = (uint64_t)batch * seq +
-                        (passes_stacked(m, (uint64_t)batch * seq) ? stacked_pass_stride(m, (uint64_t)batch * seq) : 0);
-    if (M1 * widest_row(c) * 2 >= (1ull << 31))
+    const uint64_t M1 = (uint64_t)batch * seq, rows = !passes_stacked(m, M1) ? M1 : (c.quant != 3 && M1 <= SKINNY_MAX_M) || mid_route(m, M1) ? 2 * M1
+                                                      : stacked_cut_rows((uint32_t)M1);
+    if (rows * widest_row(c) * 2 >= (1ull << 31))
       return fail(QZO_ERR_SHAPE, "batch*seq too large for this model: an activation tensor would exceed 2^31 bytes");
   }
   Workspace w = carve(m, batch, seq, nullptr);
@@ -508,7 +531,6 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       g.bias = bias; g.resid = resid; g.y = y;
       g.M = M1; g.N = m->lin[li].N; g.K = m->lin[li].K;
       g.dual = n_pass == 2;
-      g.pass_stride = n_pass == 2 ? P : 0;
       g.row_base = l * m->rows_per_layer + m->lin[li].row_base;
       g.seed_lo = seed_lo; g.seed_hi = seed_hi; g.eps_signed = eps_signed;
       g.epi = epi & ~EPI_ROPE;                // a request: only the plain GEMM of the int4 expansion route serves it
@@ -542,11 +564,11 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
         ProfScope ps(PK_W4GEMM, 2.0 * Mreal * (double)g.N * g.K, st);
         return launch_bf16_gemm(g, PLAIN_GEMM_PIPE, st);
       }
-      if (c.quant == 3 && !mid_ws) {
+      if (c.quant == 3 && w.wexp) {
         // NormalFloat-4: table lookup and scaling once per weight (stacked passes: both matrices), then a plain bf16 GEMM
         const bool pair = n_pass == 2;
         if (pair) {
-          g.M = M; g.dual = 0; g.pass_stride = 0;
+          g.M = M; g.dual = 0;
           g.flip_row = P; g.w_flip = (uint64_t)g.N * g.K * 2;
         }
         const bool split = w.split && tile_ksplit(g.M, g.N, g.K, nullptr) > 1;
@@ -595,7 +617,8 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
         // where the linear is not cut along K.  A pass of whole_k_min_m tokens or more never cuts these linears.
         const bool whole = m->int4_path == 0 && M >= whole_k_min_m(g.N, g.K) && !passes_stacked(m, M1);
         if (whole) g.split_ws = nullptr;
-        const bool cut = g.split_ws && (tile_ksplit(M, g.N, g.K, nullptr) > 1 || tile_tail_cols(M, g.N, g.K, g.epi));
+        const uint32_t r = n_pass == 2 ? stacked_cut_rows(M1) : M1;
+        const bool cut = g.split_ws && (tile_ksplit(r, g.N, g.K, nullptr) > 1 || tile_tail_cols(r, g.N, g.K, g.epi));
         if (epi == EPI_ROPE && (whole || !rope_in_attention) && !cut && (dh == 64 || g.N % 256 == 0)) {
           g.epi = EPI_ROPE; g.rope = w.rope; g.rope_S = seq; g.rope_dh = dh;
           rope_fused = true;
@@ -1271,6 +1294,12 @@ qzo_status qzo_nf4_scratch_bytes(uint32_t N, uint32_t K, uint64_t* out) {
   return QZO_OK;
 }
 
+// A single linear is expanded first from this many tokens on, unless it is small.  Fused over expanded: 11008 x 4096 16 tokens
+// 0.24, 256 0.50, 1024 0.96, 2048 0.99, 3072 0.98, 4096 1.10; 4096 x 11008 16 0.11, 1024 0.52, 2048 0.84, 3072 1.04; 4096 x 4096
+// 1024 0.77, 2048 0.88, 3072 1.00, 8192 1.12; 22016 x 4096 1024 0.85, 2048 0.96, 3072 1.03; 8192 x 512 and 1024 x 1024 4096 tokens
+// 0.76 and 0.63, 8192 0.43 and 0.73.
+constexpr uint32_t NF4_LINEAR_EXPAND_MIN_M = 2816;
+constexpr uint64_t NF4_LINEAR_NEVER_EXPAND = 1ull << 23;
 qzo_status qzo_nf4_gemm(const void* x_dev, const void* q_dev, const void* s_dev, uint32_t row_base,
                         uint32_t M, uint32_t N, uint32_t K, uint32_t block, uint64_t seed, float eps,
                         int sign, void* y_dev, void* scratch_dev, uint64_t scratch_bytes, void* stream) {
@@ -1285,12 +1314,26 @@ qzo_status qzo_nf4_gemm(const void* x_dev, const void* q_dev, const void* s_dev,
   if (!bf16_gemm_fits(M, N, K)) return fail(QZO_ERR_SHAPE, "an operand exceeds 2^31 bytes");
   if (M == 0 || N == 0) return QZO_OK;
   hipStream_t s = (hipStream_t)stream;
+  GemmArgs g = {};
+  g.x = x_dev; g.y = y_dev; g.M = M; g.N = N; g.K = K;
+  if (M < NF4_LINEAR_EXPAND_MIN_M || (uint64_t)N * K <= NF4_LINEAR_NEVER_EXPAND) {
+    g.nf4 = 1; g.w = q_dev; g.s = s_dev; g.row_base = row_base;
+    g.seed_lo = (uint32_t)seed; g.seed_hi = (uint32_t)(seed >> 32); g.eps_signed = sign > 0 ? eps : -eps;
+    // K slices, where the expansion's place holds the partial sums of two or more
+    const uint64_t room = need / ((uint64_t)M * N * 4);
+    const bool tail = tile_ksplit(M, N, K, nullptr) < 2;
+    if (room >= 2 && (!tail || tile_split_ws_floats(M, N, K) * 4 <= need)) {
+      g.split_ws = (float*)scratch_dev;
+      g.most_slices = tail ? 0u : (uint32_t)std::min<uint64_t>(room, 0xffffffffu);
+    }
+    QZO_HIP(launch_w4a16_gemm(g, s));
+    return QZO_OK;
+  }
   unsigned char* wexp = (unsigned char*)scratch_dev;
   float* se = (float*)(wexp + up256((uint64_t)N * K * 2));
   QZO_HIP(launch_expand_nf4(q_dev, s_dev, N, K, row_base, (uint32_t)seed, (uint32_t)(seed >> 32),
                             sign > 0 ? eps : -eps, false, se, wexp, s));
-  GemmArgs g = {};
-  g.x = x_dev; g.w = wexp; g.y = y_dev; g.M = M; g.N = N; g.K = K;
+  g.w = wexp;
   QZO_HIP(launch_bf16_gemm(g, PLAIN_GEMM_PIPE, s));
   return QZO_OK;
 }

@@ -783,7 +783,7 @@ static GemmArgs column_block(const GemmArgs& a, uint32_t first, uint32_t count, 
   s.N = count; s.ldy = ld;
   s.w = (const char*)a.w + (uint64_t)first * a.K * w_bits / 8;
   if (w_bits == 4) {
-    if (a.s) s.s = (const char*)a.s + (uint64_t)first * (a.K >> 7) * 2;
+    if (a.s) s.s = (const char*)a.s + (uint64_t)first * (a.K >> (a.nf4 ? 6 : 7)) * 2;
     if (a.zp) s.zp = (const char*)a.zp + (uint64_t)first * (a.K >> 7);
     s.row_base = a.row_base + first;
   }
@@ -798,18 +798,16 @@ hipError_t launch_w4a16_gemm(const GemmArgs& a0, hipStream_t st) {
   if (a0.M <= SKINNY_MAX_M && a0.skinny_ws) return launch_skinny_gemm(a0, a0.skinny_ws, st);
   if (a0.mid_ws) return launch_mid_gemm(a0, a0.mid_ws, st);
   GemmArgs a = a0;
-  if (a0.dual) {
-    // both passes of a step stacked: the second pass starts on a tile boundary and its tiles take -eps
-    const uint32_t stride = a0.pass_stride ? a0.pass_stride : a0.M;
-    if (stride % BM != 0 || stride < a0.M) return hipErrorInvalidValue;
-    a.M = stride + a0.M; a.flip_row = stride; a.dual = 0;
+  if (a0.dual) {            // both passes of a step stacked, the second one's rows behind the first one's
+    a.flip_row = a0.M; a.dual = 0;
   }
+  const uint32_t rows = a.flip_row ? a.flip_row + a.M : a.M, cut_rows = a.flip_row ? stacked_cut_rows(a.M) : a.M;
   // buffer loads address each operand with 32-bit byte offsets
-  if ((uint64_t)a.M * a.K * 2 >= (1ull << 31) || (uint64_t)a.N * a.K / 2 >= (1ull << 31))
+  if ((uint64_t)rows * a.K * 2 >= (1ull << 31) || (uint64_t)a.N * a.K / 2 >= (1ull << 31))
     return hipErrorInvalidValue;
   if (a.split_ws && !a.ldy) {
     // a little more than whole rounds of tiles: the whole rounds as they are, the rest cut along K
-    const uint32_t n1 = tile_tail_cols(a.M, a.N, a.K, a.epi);
+    const uint32_t n1 = tile_tail_cols(cut_rows, a.N, a.K, a.epi);
     if (n1) {
       GemmArgs h = column_block(a, 0, n1, 4), t = column_block(a, n1, a.N - n1, 4);
       h.split_ws = nullptr;
@@ -819,13 +817,16 @@ hipError_t launch_w4a16_gemm(const GemmArgs& a0, hipStream_t st) {
   }
   GemmArgs g = a;
   uint32_t ksplit = 1, kt_per = a.K / BK;
-  if (a.split_ws) ksplit = tile_ksplit(a.M, a.N, a.K, &kt_per);
+  if (a.split_ws) ksplit = tile_ksplit(cut_rows, a.N, a.K, &kt_per);
+  if (a.most_slices && ksplit > a.most_slices) {
+    kt_per = ((a.K / BK + a.most_slices - 1) / a.most_slices + 3u) & ~3u;
+    ksplit = (a.K / BK + kt_per - 1) / kt_per;
+  }
   if (ksplit > 1 && (a.epi & EPI_ROPE)) return hipErrorInvalidValue;     // the reduction knows no rotary embedding
   if (ksplit > 1) g.epi = 0;         // natural row order, fp32 partial sums; the reduction applies a.epi
-  if (a.flip_row) g.M = a.M - a.flip_row;
   hipError_t e = launch_w4_tiles(g, w4_plan(g.M, a.flip_row, a.N, a.K, ksplit, kt_per, g.epi & EPI_SUMSQ ? a.n_partials : 0u), st);
   if (e != hipSuccess || ksplit == 1) return e;
-  if (a.flip_row) { a.skip_row = g.M; a.skip = a.flip_row - g.M; }      // padding rows have no sums
+  a.M = rows;
   return launch_partial_reduce(a, a.split_ws, ksplit, st);
 }
 

@@ -6,7 +6,7 @@
 
 namespace qzo {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));        // as in qzo_nibble.hpp
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int BM = 256, BN = 256, BK = 64;

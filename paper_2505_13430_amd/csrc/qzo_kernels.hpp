@@ -57,17 +57,15 @@ struct GemmArgs {
   float* skinny_ws;     // fp32 scratch of skinny_ws_floats(rows, N, K) floats: enables the few-token path (M <= 64)
   float* mid_ws;        // fp32 scratch of mid_ws_floats(M, N, K, dual) floats: enables mid_gemm_kernel
   float* split_ws;      // fp32 scratch of tile_split_ws_floats(M, N, K) floats: enables split-K of the int4 tile kernel
+  uint32_t most_slices; // fused int4 kernel: K slices that split_ws has room for (0: as many as tile_ksplit takes)
   uint32_t ksplit, kt_per;   // set by the launcher: K slices and k-tiles per slice
   const float* rope;    // EPI_ROPE: (cos, sin) of [rope_S positions][dh/2 pairs]; row m sits at position m % rope_S
   uint32_t rope_S, rope_dh;
   uint32_t dual;        // both passes of a step stacked: x, y, resid hold 2 M rows; rows [0,M) use +eps_signed,
-                        // [M,2M) -eps_signed (few-token path and mid_gemm_kernel; tile path: see pass_stride)
-  uint32_t pass_stride; // dual, tile path: the second pass starts at this row (a multiple of 256 >= M; x, y, resid
-                        // hold pass_stride + M rows, the rows in between are padding); 0: at row M
+                        // [M,2M) -eps_signed
   uint32_t flip_row;    // tile kernels: first row of the second pass (0: one pass), whose rows take -eps_signed; set by
                         // the launcher of the fused kernel, by the caller of the plain bf16 GEMM (a multiple of 256)
   uint64_t w_flip;      // plain bf16 GEMM with flip_row: bytes from w to the matrix of the second pass
-  uint32_t skip_row, skip;   // slice reduction: rows skip_row .. skip_row + skip - 1 are padding and have no partial sums
   uint32_t M, N, K;
   uint32_t ldy;         // row stride of y and resid in elements when the call covers a column block of a wider
                         // matrix (0: N); plain epilogues only (bias, residual, ReLU)
@@ -76,7 +74,7 @@ struct GemmArgs {
   float eps_signed;
   uint32_t epi;
   uint32_t s_fp16;      // int4 formats: s holds fp16 instead of bf16
-  uint32_t nf4;         // mid_gemm_kernel: w holds NormalFloat-4 indices, s bf16 [N,K/64], no block sums
+  uint32_t nf4;         // mid_gemm_kernel and the fused kernel: w holds NormalFloat-4 indices, s bf16 [N,K/64], no block sums
   // Few-token path: block sums X[g][row] = sum of x[row, 128 g .. 128 g + 127] (fp32, [K/128][rows], rows = M or
   // 2 M when dual), delivered by the kernel that wrote x (null: the kernel sums them itself), and the same for
   // the output y of the K-slice reduction ([N_out/128][rows], N_out % 128 == 0; null: not wanted).
@@ -158,6 +156,9 @@ uint32_t tile_tail_cols(uint32_t M, uint32_t N, uint32_t K, uint32_t epi);
 // Estimated time (us) of launch_bf16_gemm with split_ws given: see there.
 double bf16_gemm_estimate(uint32_t M, uint32_t N, uint32_t K, uint32_t epi);
 uint64_t tile_split_ws_floats(uint32_t M, uint32_t N, uint32_t K);
+// Stacked passes of M tokens each: K slices and column tails are those of a launch whose second pass starts on a multiple
+// of 256 rows, in which every tile of 256 tokens lies in one pass.
+inline uint32_t stacked_cut_rows(uint32_t M) { return (M + 255u) / 256u * 256u + M; }
 // w = uint16 codes [N,K/8]; cb and s as above; N % 8 == 0, K % 128 == 0.
 hipError_t launch_codebook_gemm(const GemmArgs& a, hipStream_t st);
 // pipe: 0 / 1 = operand tiles staged through registers (compiler's / explicit issue order),

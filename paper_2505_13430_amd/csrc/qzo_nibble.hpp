@@ -54,15 +54,16 @@ __device__ const float NF4_LEVELS_DEV[16] = {
 // rounding is the same in every weight that has it: over activations of one sign the errors add up instead of averaging
 // out (silu(g) g of 2048 / 8192 features: 9.6e-3 / 1.7e-2 in the hidden states, rounded products 6.4e-3 / 6.3e-3).
 struct Nf4Table { uint32_t lo[4], hi[4]; };
+__device__ __forceinline__ void nf4_table_part(Nf4Table& t, float s, int q) {      // entries 4 q .. 4 q + 3
+  const uint32_t a = pack_bf16x2(s * NF4_LEVELS_DEV[4 * q], s * NF4_LEVELS_DEV[4 * q + 1]);
+  const uint32_t b = pack_bf16x2(s * NF4_LEVELS_DEV[4 * q + 2], s * NF4_LEVELS_DEV[4 * q + 3]);
+  t.lo[q] = __builtin_amdgcn_perm(b, a, 0x06040200u);
+  t.hi[q] = __builtin_amdgcn_perm(b, a, 0x07050301u);
+}
 __device__ __forceinline__ Nf4Table nf4_table(float s) {
   Nf4Table t;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t a = pack_bf16x2(s * NF4_LEVELS_DEV[4 * q], s * NF4_LEVELS_DEV[4 * q + 1]);
-    const uint32_t b = pack_bf16x2(s * NF4_LEVELS_DEV[4 * q + 2], s * NF4_LEVELS_DEV[4 * q + 3]);
-    t.lo[q] = __builtin_amdgcn_perm(b, a, 0x06040200u);
-    t.hi[q] = __builtin_amdgcn_perm(b, a, 0x07050301u);
-  }
+  for (int q = 0; q < 4; ++q) nf4_table_part(t, s, q);
   return t;
 }
 // Four indices: entry within a half of the table, and 0xff where bit 3 is set (permutation selectors 8 .. 11 return the
@@ -71,18 +72,21 @@ struct Nf4Select { uint32_t sel, upper; };
 __device__ __forceinline__ uint32_t nf4_bytes(const uint32_t (&t)[4], Nf4Select s) {
   return (__builtin_amdgcn_perm(t[3], t[2], s.sel) & s.upper) | (__builtin_amdgcn_perm(t[1], t[0], s.sel) & ~s.upper);
 }
+// a: indices 0, 1, 4, 5 of a dword, b: 2, 3, 6, 7
+__device__ __forceinline__ uint32_t nf4_entries_a(uint32_t w) { return __builtin_amdgcn_perm(w >> 4, w, 0x06020400u) & 0x07070707u; }
+__device__ __forceinline__ uint32_t nf4_upper_a(uint32_t w) { return __builtin_amdgcn_perm(w << 8, w << 12, 0x0b090a08u); }
+__device__ __forceinline__ uint32_t nf4_entries_b(uint32_t w) { return __builtin_amdgcn_perm(w >> 4, w, 0x07030501u) & 0x07070707u; }
+__device__ __forceinline__ uint32_t nf4_upper_b(uint32_t w) { return __builtin_amdgcn_perm(w, w << 4, 0x0b090a08u); }
+// high and low bytes of four products -> the first and the second two
+__device__ __forceinline__ void nf4_merge(uint32_t high, uint32_t low, uint32_t& first, uint32_t& second) {
+  first = __builtin_amdgcn_perm(high, low, 0x05010400u);
+  second = __builtin_amdgcn_perm(high, low, 0x07030602u);
+}
 __device__ __forceinline__ bf16x8 unpack8_nf4(uint32_t w, const Nf4Table& t) {
-  const uint32_t o = w >> 4;
-  const Nf4Select a = {__builtin_amdgcn_perm(o, w, 0x06020400u) & 0x07070707u,           // indices 0, 1, 4, 5
-                       __builtin_amdgcn_perm(w << 8, w << 12, 0x0b090a08u)};
-  const Nf4Select b = {__builtin_amdgcn_perm(o, w, 0x07030501u) & 0x07070707u,           // indices 2, 3, 6, 7
-                       __builtin_amdgcn_perm(w, w << 4, 0x0b090a08u)};
-  const uint32_t al = nf4_bytes(t.lo, a), ah = nf4_bytes(t.hi, a), bl = nf4_bytes(t.lo, b), bh = nf4_bytes(t.hi, b);
+  const Nf4Select a = {nf4_entries_a(w), nf4_upper_a(w)}, b = {nf4_entries_b(w), nf4_upper_b(w)};
   union { bf16x8 v; uint32_t u[4]; } r;
-  r.u[0] = __builtin_amdgcn_perm(ah, al, 0x05010400u);
-  r.u[1] = __builtin_amdgcn_perm(bh, bl, 0x05010400u);
-  r.u[2] = __builtin_amdgcn_perm(ah, al, 0x07030602u);
-  r.u[3] = __builtin_amdgcn_perm(bh, bl, 0x07030602u);
+  nf4_merge(nf4_bytes(t.hi, a), nf4_bytes(t.lo, a), r.u[0], r.u[2]);
+  nf4_merge(nf4_bytes(t.hi, b), nf4_bytes(t.lo, b), r.u[1], r.u[3]);
   return r.v;
 }
 // 8 consecutive bf16 (4 dwords) -> the same order 0,4,1,5,2,6,3,7

@@ -430,9 +430,9 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(GemmArgs a, const fl
   const uint32_t NO = (a.epi & EPI_SWIGLU) ? a.N >> 1 : a.N;                  // output width
   const uint32_t q = blockIdx.x * 256 + threadIdx.x, per_row = NO >> 2;
   float ssq = 0.0f, sx = 0.0f;
-  const bool own = q < (a.M - a.skip) * per_row;
+  const bool own = q < a.M * per_row;
   if (own) {
-    const uint32_t r = q / per_row, m = r + (r >= a.skip_row ? a.skip : 0u), f = (q % per_row) * 4;
+    const uint32_t m = q / per_row, f = (q % per_row) * 4;
     const uint32_t kf = MAPPED ? slices_of(mp, m, f) : ksplit;
     const uint32_t ku = MAPPED && (a.epi & EPI_SWIGLU) ? slices_of(mp, m, NO + f) : kf;
     ssq = reduce_item(a, part, kf, ku, m, f, sx);
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(1024) void reduce_norm_kernel(GemmArgs a, const flo
                                                            MidPlan mp, NextNorm nn) {
   __shared__ __attribute__((aligned(16))) uint2 row[2048];
   __shared__ float red[4];
-  const uint32_t m = blockIdx.x + (blockIdx.x >= a.skip_row ? a.skip : 0u);
+  const uint32_t m = blockIdx.x;
   for (uint32_t f = threadIdx.x * 4; f < a.N; f += blockDim.x * 4) {
     float sum;
     const uint32_t kf = MAPPED ? slices_of(mp, m, f) : ksplit;
@@ -474,25 +474,24 @@ __global__ __launch_bounds__(1024) void reduce_norm_kernel(GemmArgs a, const flo
   __syncthreads();
   auto chunk = [&](int i, uint32_t) { return reinterpret_cast<const uint4*>(row)[(threadIdx.x & 255u) + 256u * i]; };
   norm_row<LAYERNORM, true>(chunk, (const bf16_t*)nn.gain, (const bf16_t*)nn.bias, a.N, nn.eps,
-                            (bf16_t*)nn.out + (uint64_t)m * a.N, nn.xsum, m, a.M, red);
+                            (bf16_t*)nn.out + (uint64_t)m * a.N, nn.xsum, m, gridDim.x, red);
 }
 
 // Slice reduction of a.M rows, with the norm that reads its output where the caller named one.
 template <bool MAPPED>
 hipError_t launch_reduce(const GemmArgs& r, const float* part, uint32_t ksplit, const MidPlan& mp, hipStream_t st) {
-  const uint32_t rows = r.M - r.skip;
   if (r.next && !(r.epi & (EPI_SWIGLU | EPI_SUMSQ)) && !r.ldy && !r.xsum_out && r.N <= 8192 && r.N % 8 == 0 &&
-      rows <= 512 && (r.N <= 4096 || rows >= 256)) {
+      r.M <= 512 && (r.N <= 4096 || r.M >= 256)) {
     NextNorm nn = *r.next;
     // whole wavefronts, an equal number of features each; the norm itself wants 256 threads
     const uint32_t items = r.N / 4, per = (items + 1023) / 1024;
     const uint32_t threads = std::max(256u, ((items + per - 1) / per + 63) / 64 * 64);
     if (r.N % 128) nn.xsum = nullptr;
-    if (nn.bias) reduce_norm_kernel<true, MAPPED><<<rows, threads, 0, st>>>(r, part, ksplit, mp, nn);
-    else reduce_norm_kernel<false, MAPPED><<<rows, threads, 0, st>>>(r, part, ksplit, mp, nn);
+    if (nn.bias) reduce_norm_kernel<true, MAPPED><<<r.M, threads, 0, st>>>(r, part, ksplit, mp, nn);
+    else reduce_norm_kernel<false, MAPPED><<<r.M, threads, 0, st>>>(r, part, ksplit, mp, nn);
     r.next->done = true;
   } else {
-    skinny_reduce_kernel<MAPPED><<<skinny_reduce_blocks(rows, r.N, r.epi), 256, 0, st>>>(r, part, ksplit, mp);
+    skinny_reduce_kernel<MAPPED><<<skinny_reduce_blocks(r.M, r.N, r.epi), 256, 0, st>>>(r, part, ksplit, mp);
   }
   return hipGetLastError();
 }

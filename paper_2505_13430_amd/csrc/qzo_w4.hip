@@ -27,6 +27,7 @@
 // 22.1 -> 20.6; one linear 2048 x 11008 x 4096, both signs, 0.439 -> 0.336; the tests' smallest model 0.180 -> 0.119.
 // Outputs are the same bit for bit whatever MT: every one sums the same k-steps in the same order.
 #include "qzo_gemm_tile.hpp"
+#include "qzo_nibble.hpp"
 #include <algorithm>
 #include <type_traits>
 
@@ -34,13 +35,15 @@ namespace qzo {
 
 namespace {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+enum : int { W4_INT4 = 0, W4_ZP = 1, W4_NF4 = 2 };
 
 // LDS: three stages of activations (a k-tile of 32 MT rows of 128 bytes), two slots of packed weights (a group of 256
 // rows: 64 bytes each) with their scales and zero-points (a dword each).
-template <int MT, bool ZP>
+template <int MT, int FMT>
 struct W4Lds {
+  static constexpr bool ZP = FMT == W4_ZP;
   static constexpr uint32_t X = MT * 4096u, W0 = 3 * X, W = 256 * 64, S = 256 * 4, SLOT = W + S * (ZP ? 2 : 1);
   static constexpr uint32_t RED = W0 + 2 * SLOT, BYTES = RED + 64;
   static constexpr int NW = ZP ? 6 : 5;            // load instructions per wavefront for a group's weights
@@ -55,9 +58,10 @@ struct W4Lds {
 template <int V>
 using Int = std::integral_constant<int, V>;
 
-template <int MT, bool ZP>
+template <int MT, int FMT>
 __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
-  typedef W4Lds<MT, ZP> L;
+  typedef W4Lds<MT, FMT> L;
+  constexpr bool ZP = FMT == W4_ZP, NF4 = FMT == W4_NF4;
   constexpr int SLOTS = 2 * MT;                    // MFMAs of a k-step
   constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -79,7 +83,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   };
   const uint32_t rows_all = p.rows;
   const i32x4 rx = rsrc(a.x, (uint64_t)rows_all * K * 2), rw = rsrc(a.w, (uint64_t)a.N * (K >> 1));
-  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * G * 2), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * G);
+  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * G * (NF4 ? 4 : 2)), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * G);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
 
   // a unit of work: K slice kslice of output tile (tile_m, tile_n), k-tiles kt0 .. kt0 + 2 ng - 1
@@ -122,6 +126,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   auto load_w = [&](int q, uint32_t g, uint32_t slot) Q4_INLINE {
     const uint32_t base = lds0 + L::W0 + slot;
     if (q < 4) Q4_DTL("buffer_load_dwordx4", rw, base + wave * 4096 + q * 1024, wo[q], g * 64);
+    else if (q == 4 && NF4) Q4_DTL("buffer_load_dword", rs, base + L::W + wave * 256, so * 4, g * 4);    // of two blocks
     else if (q == 4) Q4_DTL("buffer_load_ushort", rs, base + L::W + wave * 256, so * 2, g * 2);
     else Q4_DTL("buffer_load_ubyte", rz, base + L::W + L::S + wave * 256, so, g);
   };
@@ -175,24 +180,26 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
     sbits = *reinterpret_cast<const uint32_t*>(lds + L::W0 + slot + L::W + wave * 256 + lane * 4);
     if (ZP) zbits = *reinterpret_cast<const uint32_t*>(lds + L::W0 + slot + L::W + L::S + wave * 256 + lane * 4);
   };
-  // noise of the lane's own row, group g of the row
+  // noise of the lane's own row: a counter serves eight scales, a word two: those of two groups, or of the two blocks of
+  // a NormalFloat-4 group g
   auto noise = [&](uint32_t g, bool first) Q4_INLINE {
-    if (first || (g & 7u) == 0) {
-      const u32x4_t w = philox4x32_10(noise_row, g >> 3, 0u, 0u, a.seed_lo, a.seed_hi);
+    const uint32_t pair = NF4 ? g : g >> 1;
+    if (first || ((pair & 3u) == 0 && (NF4 || (g & 1u) == 0))) {
+      const u32x4_t w = philox4x32_10(noise_row, pair >> 2, 0u, 0u, a.seed_lo, a.seed_hi);
       zw0 = w.x; zw1 = w.y; zw2 = w.z; zw3 = w.w;
     }
-    if ((g & 1u) == 0) {
-      const uint32_t q = (g & 7u) >> 1;
-      const uint32_t w0 = zw0, w1 = zw1, w2 = zw2, w3 = zw3;
+    if (NF4 || (g & 1u) == 0) {
+      const uint32_t q = pair & 3u, w0 = zw0, w1 = zw1, w2 = zw2, w3 = zw3;
       float even, odd;
       normal_pair(q == 0 ? w0 : (q == 1 ? w1 : (q == 2 ? w2 : w3)), even, odd);
       z_even = even; z_odd = odd;
     }
   };
   // the lane's row is row lane of the wavefront's 64: one exchange between the halves gives every lane its two tiles'
-  auto new_scale = [&](uint32_t g) Q4_INLINE {
+  // n: the group, of a NormalFloat-4 group the block
+  auto new_scale = [&](uint32_t n) Q4_INLINE {
     const float even = z_even, odd = z_odd;
-    const float s = __builtin_fmaf(eps, (g & 1u) ? odd : even, scale_to_f32(sbits & 0xffffu, s_fp16));
+    const float s = __builtin_fmaf(eps, (n & 1u) ? odd : even, scale_to_f32(NF4 && (n & 1u) ? sbits >> 16 : sbits & 0xffffu, s_fp16));
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
     const float s0 = __uint_as_float(r[0]), s1 = __uint_as_float(r[1]);
     if (ZP) {
@@ -200,6 +207,8 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(nz), __float_as_uint(nz), false, false);
       se[0] = s0; se[1] = s1;
       m8[0] = __uint_as_float(q[0]); m8[1] = __uint_as_float(q[1]);
+    } else if (NF4) {
+      se[0] = s0; se[1] = s1;
     } else {
       se[0] = 512.0f * s0; se[1] = 512.0f * s1;
       m8[0] = -8.0f * s0; m8[1] = -8.0f * s1;
@@ -217,8 +226,30 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   auto weight = [&](float u, int j) Q4_INLINE {
     return ZP ? __builtin_fmaf(u, 512.0f, m8[j]) * se[j] : __builtin_fmaf(u, se[j], m8[j]);
   };
+  // NormalFloat-4: products of scale and level, rounded, in tables per feature tile (this k-tile's and the next one's); a
+  // dword's eight are looked up by byte permutations (unpack8_nf4)
+  Nf4Table tab[NF4 ? 2 : 1], tab_next[NF4 ? 2 : 1];
+  Nf4Select sel;
+  uint32_t nf_a = 0, nf_b = 0;
+  auto next_table = [&](int piece) Q4_INLINE { if constexpr (NF4) nf4_table_part(tab_next[piece >> 2], se[piece >> 2], piece & 3); };
+  auto use_table = [&]() Q4_INLINE { if constexpr (NF4) { tab[0] = tab_next[0]; tab[1] = tab_next[1]; } };
   auto convert = [&](int buf, int piece, int kk) Q4_INLINE {
     const int j = piece >> 3;
+    if constexpr (NF4) {
+      const uint32_t w = raw[j][kk];
+      const Nf4Table& t = tab[j];
+      switch (piece & 7) {
+        case 0: sel.sel = nf4_entries_a(w); break;
+        case 1: sel.upper = nf4_upper_a(w); break;
+        case 2: nf_a = nf4_bytes(t.lo, sel); break;
+        case 3: nf_b = nf4_bytes(t.hi, sel); break;
+        case 4: nf4_merge(nf_b, nf_a, cf.u[0], cf.u[2]); sel.sel = nf4_entries_b(w); break;
+        case 5: sel.upper = nf4_upper_b(w); break;
+        case 6: nf_a = nf4_bytes(t.lo, sel); break;
+        default: nf_b = nf4_bytes(t.hi, sel); nf4_merge(nf_b, nf_a, cf.u[1], cf.u[3]); fw[buf][j] = cf.v;
+      }
+      return;
+    }
     switch (piece & 7) {
       case 0: clo = raw[j][kk] & 0x0f0f0f0fu; chi = (raw[j][kk] >> 4) & 0x0f0f0f0fu; break;
       case 1: cl = __builtin_amdgcn_cvt_pk_f32_fp8(clo, false); ch = __builtin_amdgcn_cvt_pk_f32_fp8(chi, false); break;
@@ -267,6 +298,10 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       if (!(START && D == 0 && S < 3)) loads(Int<E>(), l0, l1 - l0, lg, slot, S == 3 ? st_cur : st_load);
 #pragma unroll
       for (int c = m * 16 / SLOTS; c < (m + 1) * 16 / SLOTS; ++c) convert(nb, c, kk);
+      if (NF4 && S < 2) {
+#pragma unroll
+        for (int c = m * 4 / SLOTS; c < (m + 1) * 4 / SLOTS; ++c) next_table(S * 4 + c);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
     // keeps the conversion here (single uses behind a branch would be moved there, with no MFMA to hide behind)
@@ -304,20 +339,25 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       so = OUT_OF_RANGE >> 1;
     }
     read_raw(2, slot); read_raw(3, slot);
+    if (NF4) new_scale(1u);                         // of the second block, for k-tile 1
     step(Int<0>(), Int<0>(), START_, g, slot);
     step(Int<1>(), Int<0>(), START_, g, slot);
     noise(gb + 1, false);
     __builtin_amdgcn_sched_barrier(0);
     step(Int<2>(), Int<0>(), START_, g, slot);
     sync(Int<MT>(), START_);
+    if (NF4) { use_table(); read_scale(other); }
     step(Int<3>(), Int<0>(), START_, g, slot);
     next_stage();
-    read_raw(0, other); read_raw(1, other); read_scale(other);
+    read_raw(0, other); read_raw(1, other);
+    if (NF4) new_scale(0u);
+    else read_scale(other);
     step(Int<0>(), Int<1>(), START_, g, slot);
     step(Int<1>(), Int<1>(), START_, g, slot);
     step(Int<2>(), Int<1>(), START_, g, slot);
     sync(Int<MT + L::NW>(), START_);
-    new_scale(gb + 1);
+    if (NF4) use_table();
+    else new_scale(gb + 1);
     if (g + 2 >= ng) {
 #pragma unroll
       for (int i = 0; i < MT; ++i) xo[i] = OUT_OF_RANGE;
@@ -342,7 +382,12 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
 #pragma unroll
     for (int i = 0; i < MT; ++i) read_x(0, i, 0, 0u);
     noise(kt0 >> 1, true);
-    new_scale(kt0 >> 1);
+    new_scale(NF4 ? 0u : kt0 >> 1);
+    if (NF4) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) next_table(c);
+      use_table();
+    }
 #pragma unroll
     for (int c = 0; c < 16; ++c) convert(0, c, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -432,7 +477,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
         const uint32_t pos = (min(m0 + (u >> 1) * 32, m_last) - pass_row0) % a.rope_S;
         return reinterpret_cast<const float4*>(table + (uint64_t)pos * hd + (u & 1) * 16u);
       };
-      constexpr int AHEAD = 4;
+      constexpr int AHEAD = NF4 && MT == 8 ? 2 : 4;        // (registers)
       float4 tn[AHEAD][4] = {};
       if (rotate) {
 #pragma unroll
@@ -490,7 +535,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
         return m <= m_last && n < a.N ? (m * ldy + n) * 2u : OUT_OF_RANGE;
       };
       // residuals are requested AHEAD pieces before they are used: a few memory latencies per tile, not one per piece
-      constexpr int AHEAD = 12;
+      constexpr int AHEAD = NF4 && MT == 8 ? 8 : 12;
       u32x4 rr[AHEAD];
       uint4 bb[4];
       if (with_resid) {
@@ -562,20 +607,18 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
 
 // The LDS limits of all instantiations are set together: a size that is captured into a graph may be the first of its
 // tile height.
-template <int MT>
+template <int MT, int FMT>
 hipError_t w4_prepare() {
-  hipError_t e = hipFuncSetAttribute((const void*)w4_gemm_kernel<MT, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     W4Lds<MT, false>::BYTES);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)w4_gemm_kernel<MT, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            W4Lds<MT, true>::BYTES);
-  if constexpr (MT > 1) return e != hipSuccess ? e : w4_prepare<MT - 1>();
+  hipError_t e = hipFuncSetAttribute((const void*)w4_gemm_kernel<MT, FMT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     W4Lds<MT, FMT>::BYTES);
+  if constexpr (MT > 1) return e != hipSuccess ? e : w4_prepare<MT - 1, FMT>();
   return e;
 }
 template <int MT>
 void w4_launch(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
-  if (a.zp) w4_gemm_kernel<MT, true><<<p.wgs, 256, W4Lds<MT, true>::BYTES, st>>>(a, p);
-  else w4_gemm_kernel<MT, false><<<p.wgs, 256, W4Lds<MT, false>::BYTES, st>>>(a, p);
+  if (a.nf4) w4_gemm_kernel<MT, W4_NF4><<<p.wgs, 256, W4Lds<MT, W4_NF4>::BYTES, st>>>(a, p);
+  else if (a.zp) w4_gemm_kernel<MT, W4_ZP><<<p.wgs, 256, W4Lds<MT, W4_ZP>::BYTES, st>>>(a, p);
+  else w4_gemm_kernel<MT, W4_INT4><<<p.wgs, 256, W4Lds<MT, W4_INT4>::BYTES, st>>>(a, p);
 }
 
 }  // namespace
@@ -610,7 +653,9 @@ W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t
 hipError_t launch_w4_tiles(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
   static bool ready = false;
   if (!ready) {
-    hipError_t e = w4_prepare<8>();
+    hipError_t e = w4_prepare<8, W4_INT4>();
+    if (e == hipSuccess) e = w4_prepare<8, W4_ZP>();
+    if (e == hipSuccess) e = w4_prepare<8, W4_NF4>();
     if (e != hipSuccess) return e;
     ready = true;
   }

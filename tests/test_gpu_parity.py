@@ -1495,26 +1495,34 @@ def test_activation_reordering_matrix_bit_exact_and_linear(oracle, M, N, K):
         assert torch.equal(y, y2)
 
 
-@pytest.mark.parametrize("zp", [False, True])
+@pytest.mark.parametrize("fmt", ["int4", "zp", "nf4"])
 @pytest.mark.parametrize("M,N,K", [(144, 8, 256), (129, 13520, 384), (257, 13216, 384), (389, 13096, 128),
                                    (641, 10792, 128), (645, 13304, 256), (774, 13120, 256), (899, 13296, 128),
                                    (2049, 11016, 256)])
-def test_fused_linear_of_every_tile_height(M, N, K, zp):
+def test_fused_linear_of_every_tile_height(M, N, K, fmt):
     """The fused kernel at sizes whose rule picks tiles of 32, 64, .. 256 tokens (one each, then several tiles per
     workgroup), last tiles ragged in tokens and features: bit for bit the expanded weights through the plain GEMM."""
     rng = np.random.default_rng(M + N)
-    G = K // 128
     x = _dev(rng.standard_normal((M, K), dtype=np.float32), torch.bfloat16)
     q = _dev(rng.integers(0, 256, (N, K // 2), dtype=np.uint8))
-    s = _dev(rng.uniform(0.002, 0.02, (N, G)).astype(np.float32), torch.bfloat16)
-    z = _dev(rng.integers(0, 16, (N, G), dtype=np.uint8)) if zp else None
+    s = _dev(rng.uniform(0.002, 0.02, (N, K // (64 if fmt == "nf4" else 128))).astype(np.float32), torch.bfloat16)
+    z = _dev(rng.integers(0, 16, (N, K // 128), dtype=np.uint8)) if fmt == "zp" else None
     want = torch.zeros((M, N), dtype=torch.bfloat16, device=DEV)
-    scratch = torch.empty(qb.qzo_int4_scratch_bytes(N, K), dtype=torch.uint8, device=DEV)
-    qb.qzo_int4_gemm_expanded(x, q, s, z, None, 11, 31, 1e-3, -1, want, scratch)
     guard = torch.full(((M + 32) * N,), 7.0, dtype=torch.bfloat16, device=DEV)
     y, ssq = guard[:M * N].view(M, N), torch.zeros(1, dtype=torch.float32, device=DEV)
-    args = (x, q, s) + ((z,) if zp else ()) + (11, 31, 1e-3, -1, y, ssq)
-    (qb.qzo_dequant_gemm_zp if zp else qb.qzo_dequant_gemm)(*args)
+    if fmt == "nf4":
+        w = torch.zeros((N, K), dtype=torch.bfloat16, device=DEV)
+        qb.qzo_nf4_expand(q, s, 11, 31, 1e-3, -1, torch.zeros((N, K // 64), dtype=torch.float32, device=DEV), w)
+        qb.qzo_debug_bf16_gemm(x, w, want, 2)
+        scratch = torch.empty(qb.qzo_nf4_scratch_bytes(N, K), dtype=torch.uint8, device=DEV)
+        qb.qzo_nf4_gemm(x, q, s, 11, 31, 1e-3, -1, y, scratch)
+        assert torch.equal(y, want) and bool((guard[M * N:] == 7.0).all())
+        return
+    scratch = torch.empty(qb.qzo_int4_scratch_bytes(N, K), dtype=torch.uint8, device=DEV)
+    qb.qzo_int4_gemm_expanded(x, q, s, z, None, 11, 31, 1e-3, -1, want, scratch)
+    args = (x, q, s) + ((z,) if fmt == "zp" else ()) + (11, 31, 1e-3, -1, y, ssq)
+    run = qb.qzo_dequant_gemm_zp if fmt == "zp" else qb.qzo_dequant_gemm
+    run(*args)
     assert torch.equal(y, want)
     assert bool((guard[M * N:] == 7.0).all())
     ref = float((want.double() ** 2).sum())          # fp32 sums of up to 2000 terms a lane (2^-24 sqrt(2000) each), then 256
@@ -1522,8 +1530,48 @@ def test_fused_linear_of_every_tile_height(M, N, K, zp):
     # room for one partial sum per 256 x 256 tile only
     least = (-(-M // 256) * -(-N // 256) * 4 + 255) // 256 * 256
     y.zero_(), ssq.zero_()
-    (qb.qzo_dequant_gemm_zp if zp else qb.qzo_dequant_gemm)(*args, scratch=torch.empty(least, dtype=torch.uint8, device=DEV))
+    run(*args, scratch=torch.empty(least, dtype=torch.uint8, device=DEV))
     assert torch.equal(y, want) and abs(float(ssq) - ref) <= 1e-4 * ref
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 8, 128), (16, 520, 4096), (70, 264, 8192), (300, 256, 4096), (513, 4096, 1024)])
+def test_nf4_linear_cut_along_k(M, N, K):
+    """K slices as far as the scratch, sized for the expanded matrix, holds their sums (all of them; eight and two of sixteen
+    at 256 and 264 features): the expanded weights' product up to the order of fp32 sums and one bf16 rounding."""
+    rng = np.random.default_rng(M + N)
+    x = _dev(rng.standard_normal((M, K), dtype=np.float32), torch.bfloat16)
+    q = _dev(rng.integers(0, 256, (N, K // 2), dtype=np.uint8))
+    s = _dev(rng.uniform(0.02, 0.2, (N, K // 64)).astype(np.float32), torch.bfloat16)
+    w, y = torch.zeros((N, K), dtype=torch.bfloat16, device=DEV), torch.zeros((M, N), dtype=torch.bfloat16, device=DEV)
+    qb.qzo_nf4_expand(q, s, 11, 31, 1e-3, 1, torch.zeros((N, K // 64), dtype=torch.float32, device=DEV), w)
+    scratch = torch.full((qb.qzo_nf4_scratch_bytes(N, K) + 256,), 9, dtype=torch.uint8, device=DEV)
+    qb.qzo_nf4_gemm(x, q, s, 11, 31, 1e-3, 1, y, scratch[:-256])
+    want = x.float().cpu().double() @ w.float().cpu().double().T
+    size = x.float().cpu().double().abs() @ w.float().cpu().double().abs().T
+    err = (y.float().cpu().double() - want).abs()
+    assert bool((err <= 2.0 ** -8 * want.abs() + 2.0 ** -20 * size).all()) and bool((scratch[-256:] == 9).all())
+
+
+@pytest.mark.parametrize("arch,F,batch,seq", [("llama", 8320, 1, 70), ("llama", 8320, 3, 51), ("llama", 8320, 1, 300),
+                                              ("opt", 12416, 8, 50), ("opt", 12416, 1, 96)])
+def test_nf4_tile_kernel_weights_are_the_expanded_matrix(arch, F, batch, seq):
+    """Wide NormalFloat-4 layers from 65 tokens on run in the tile kernel: both passes' hidden states against the same
+    sequences in a batch on the expanded matrix, bounded by what another order of the fp32 sums alone does (as for
+    the kernel that serves narrow layers and few tokens, see test_nf4_weights_are_the_same_at_any_token_count)."""
+    shape = dict(WIDE_LLAMA if arch == "llama" else WIDE_OPT, n_layers=1, d_ffn=F, batch=-(-513 // seq), seq=seq, max_seq=512)
+    dm = DeviceModel.synthetic(shape, 1234, DEV, nf4=True)
+    dm.scales.mul_(0.3)
+    tok = synth.tokens(shape, 5678)
+    few, M1 = _dev(tok[:batch]), batch * seq
+    _, both = _step_hidden(dm, few, 9, 6e-3)
+    want = [_hidden(dm, _dev(tok), 9, 6e-3, sign)[:M1] for sign in (1, -1)]
+    order = _rms(_hidden(dm, _dev(np.concatenate([tok, tok])), 9, 6e-3, 1)[:M1] - want[0])
+    bound = max(2.5e-3 * _rms(want[0]), 2 * order)
+    for sign, h, w, other in ((1, both[0], want[0], want[1]), (-1, both[1], want[1], want[0])):
+        print(arch, M1, sign, "apart %.2e" % (_rms(h - w) / _rms(w)), "order %.2e" % (order / _rms(w)))
+        assert _rms(h - w) <= bound and _rms(h - other) > 10 * _rms(h - w)
+        assert _rms(_hidden(dm, few, 9, 6e-3, sign) - w) <= bound
+    dm.close()
 
 
 @pytest.mark.parametrize("name", ["tiny", "few_llama"])
