@@ -450,10 +450,10 @@ enum { PK_W4GEMM = 0, PK_LMHEAD = 1, PK_ATTN = 2, PK_UPDATE = 3, PK_OTHER = 4, P
 // The decoder forward with every quantized linear perturbed by sign*eps*z.
 // n_pass = 2 (see passes_stacked): both passes of a step stacked, rows [0,M1) perturbed by
 // +eps_signed and rows [P, P + M1) by -eps_signed, P = stacked_pass_stride(m, M1); their losses go to
-// loss_out and loss_out2.
+// loss_out[0] and [1].  tail: of a step's last forward.
 qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t seq, uint64_t seed,
                    float eps_signed, const Workspace& w, float* loss_out, hipStream_t st,
-                   void* hidden_out = nullptr, uint32_t n_pass = 1, float* loss_out2 = nullptr) {
+                   void* hidden_out = nullptr, uint32_t n_pass = 1, const StepTail& tail = StepTail{}) {
   const qzo_model_config& c = m->cfg;
   const uint32_t batch = batch1 * n_pass, M1 = batch1 * seq;
   const uint32_t P = n_pass == 2 ? (uint32_t)stacked_pass_stride(m, M1) : M1;     // rows per pass
@@ -476,8 +476,8 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
   }
   {
     ProfScope ps(PK_OTHER, 0, st);
-    if (llama) QZO_HIP(launch_rope_table(w.rope, seq, dh, c.rope_theta, st));
-    QZO_HIP(launch_embed(tok, M1, P, m->T[0].ptr_dev, llama ? nullptr : m->T[1].ptr_dev, M, seq, d, w.h, st));
+    QZO_HIP(launch_embed(tok, M1, P, m->T[0].ptr_dev, llama ? nullptr : m->T[1].ptr_dev, M, seq, d, w.h,
+                         llama ? w.rope : nullptr, dh, c.rope_theta, st));
   }
   const double attn_flops = 2.0 * batch * H * (double)seq * seq * dh;   // causal: half of 4 B H S^2 dh
   const double Mreal = (double)n_pass * M1;                             // rows that count as work
@@ -700,9 +700,9 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       QZO_HIP(gemm(3, w.ff, ti(11), w.h, w.h, EPI_BIAS | EPI_RESIDUAL));
     }
   }
-  const size_t tail = m->first_layer_tensor + (size_t)c.n_layers * m->tensors_per_layer;
-  QZO_HIP(norm(m->T[tail].ptr_dev, llama ? nullptr : m->T[tail + 1].ptr_dev, nullptr));
-  const void* lm_head = m->T[tail + (llama ? 1 : 2)].ptr_dev;
+  const size_t end = m->first_layer_tensor + (size_t)c.n_layers * m->tensors_per_layer;
+  QZO_HIP(norm(m->T[end].ptr_dev, llama ? nullptr : m->T[end + 1].ptr_dev, nullptr));
+  const void* lm_head = m->T[end + (llama ? 1 : 2)].ptr_dev;
   if (hidden_out)
     QZO_HIP(hipMemcpyAsync(hidden_out, w.a, (size_t)M * d * 2, hipMemcpyDeviceToDevice, st));
   CeArgs ce = {};
@@ -718,10 +718,7 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
     QZO_HIP(launch_lmhead_ce(ce, st));
     if (!padded) break;
   }
-  QZO_HIP(launch_ce_reduce(w.ce_part, w.tgt, M1, seq, ce.n_slices, w.rowloss, loss_out, st));
-  if (n_pass == 2)
-    QZO_HIP(launch_ce_reduce(w.ce_part + (size_t)P * ce.n_slices * 2, w.tgt + P, M1, seq, ce.n_slices,
-                             w.rowloss + P, loss_out2, st));
+  QZO_HIP(launch_ce_reduce(w.ce_part, w.tgt, M1, P, n_pass, seq, ce.n_slices, w.rowloss, loss_out, tail, st));
   return QZO_OK;
 }
 
@@ -915,17 +912,17 @@ static qzo_status step_impl(qzo_model* m, const int32_t* tokens_dev, uint32_t ba
     return fail(QZO_ERR_ARG, "eps/eta not finite");
   hipStream_t s = (hipStream_t)stream;
   Workspace w = carve(m, batch, seq, workspace_dev);
+  const StepTail tail = {result_dev, eps, clip, w.losses};
   if (passes_stacked(m, (uint64_t)batch * seq)) {
     // one forward over both passes
-    st = forward(m, tokens_dev, batch, seq, seed, eps, w, w.losses, s, nullptr, 2, w.losses + 1);
+    st = forward(m, tokens_dev, batch, seq, seed, eps, w, w.losses, s, nullptr, 2, tail);
     if (st != QZO_OK) return st;
   } else {
     st = forward(m, tokens_dev, batch, seq, seed, eps, w, w.losses, s);
     if (st != QZO_OK) return st;
-    st = forward(m, tokens_dev, batch, seq, seed, -eps, w, w.losses + 1, s);
+    st = forward(m, tokens_dev, batch, seq, seed, -eps, w, w.losses + 1, s, nullptr, 1, tail);
     if (st != QZO_OK) return st;
   }
-  QZO_HIP(launch_spsa_clip(w.losses, eps, clip, result_dev, s));
   {
     ProfScope ps(PK_UPDATE, 4.0 * (double)m->n_scales, s);
     if (m->cfg.quant == 1)

@@ -238,11 +238,9 @@ hipError_t launch_dense_update(float* master, uint64_t n_dense, uint32_t seed_lo
 }
 
 // ------------------------------------------- SPSA scalar + DDC (Eq. 6) ----
-__global__ void spsa_clip_kernel(const float* __restrict__ losses, float eps, float clip,
-                                 qzo_step_result* __restrict__ res) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  float lp = losses[0], lm = losses[1];
-  float d = (lp - lm) / (2.0f * eps);
+__device__ __forceinline__ void spsa_clip(float lp, float lm, const StepTail& t) {
+  const float d = (lp - lm) / (2.0f * t.eps);
+  qzo_step_result* res = t.res;
   res->loss_plus = lp;
   res->loss_minus = lm;
   res->d = d;
@@ -250,16 +248,11 @@ __global__ void spsa_clip_kernel(const float* __restrict__ losses, float eps, fl
     res->d_clipped = 0.0f;
     res->status = QZO_ERR_NONFINITE;
   } else {
-    float dc = d > clip ? clip : (d < -clip ? -clip : d);
+    float dc = d > t.clip ? t.clip : (d < -t.clip ? -t.clip : d);
     res->d_clipped = dc;
     res->status = QZO_OK;
   }
   res->reserved[0] = res->reserved[1] = res->reserved[2] = 0u;
-}
-hipError_t launch_spsa_clip(const float* losses, float eps, float clip, qzo_step_result* res,
-                            hipStream_t st) {
-  spsa_clip_kernel<<<1, 64, 0, st>>>(losses, eps, clip, res);
-  return hipGetLastError();
 }
 
 // ------------------------------------------------------ RTN (Eq. 3) -------
@@ -460,10 +453,20 @@ hipError_t launch_repack_kmajor(const void* qweight, const void* qzeros, const v
 // -------------------------------------------------------- embedding -------
 // Row m belongs to pass m / pass_stride and is row r = m % pass_stride of it: it embeds tok[r] at
 // position r % S, or zeros when r >= tok_rows (rows that pad a pass to a whole number of GEMM tiles).
+// Workgroups from embed_wgs on write the table of rotary angles, (cos, sin) of [S positions][half pairs].
 __global__ void embed_kernel(const int32_t* __restrict__ tok, uint32_t tok_rows, uint32_t pass_stride,
                              const bf16_t* __restrict__ te,
                              const bf16_t* __restrict__ pe, uint32_t M, uint32_t S, uint32_t d,
-                             bf16_t* __restrict__ h) {
+                             bf16_t* __restrict__ h, uint32_t embed_wgs, float2* __restrict__ table, uint32_t half,
+                             double theta, double dh) {
+  if (blockIdx.x >= embed_wgs) {
+    const uint32_t u = (blockIdx.x - embed_wgs) * blockDim.x + threadIdx.x;
+    if (u >= S * half) return;
+    const uint32_t t = u / half, i = u % half;
+    const double ang = (double)t * pow(theta, -2.0 * (double)i / dh);
+    table[u] = make_float2((float)cos(ang), (float)sin(ang));
+    return;
+  }
   const uint32_t cpr = d >> 3;
   const uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (u >= (uint64_t)M * cpr) return;
@@ -484,11 +487,11 @@ __global__ void embed_kernel(const int32_t* __restrict__ tok, uint32_t tok_rows,
   *reinterpret_cast<uint4*>(h + (uint64_t)m * d + c * 8) = v;
 }
 hipError_t launch_embed(const int32_t* tok, uint32_t tok_rows, uint32_t pass_stride, const void* tok_emb,
-                        const void* pos_emb, uint32_t M, uint32_t S, uint32_t d, void* h, hipStream_t st) {
-  uint64_t units = (uint64_t)M * (d >> 3);
-  embed_kernel<<<(uint32_t)((units + 255) / 256), 256, 0, st>>>(tok, tok_rows, pass_stride, (const bf16_t*)tok_emb,
-                                                               (const bf16_t*)pos_emb, M, S, d,
-                                                               (bf16_t*)h);
+                        const void* pos_emb, uint32_t M, uint32_t S, uint32_t d, void* h, float* rope, uint32_t dh,
+                        float theta, hipStream_t st) {
+  const uint32_t wgs = (uint32_t)(((uint64_t)M * (d >> 3) + 255) / 256), table = rope ? (S * (dh / 2) + 255) / 256 : 0u;
+  embed_kernel<<<wgs + table, 256, 0, st>>>(tok, tok_rows, pass_stride, (const bf16_t*)tok_emb, (const bf16_t*)pos_emb, M, S, d,
+                                            (bf16_t*)h, wgs, (float2*)rope, dh / 2, (double)theta, (double)dh);
   return hipGetLastError();
 }
 
@@ -543,21 +546,6 @@ hipError_t launch_layernorm(const void* x, const void* gain, const void* bias, u
 
 // ------------------------------------------------------------- RoPE -------
 // table[t][i] = (cos, sin)(t * theta^(-2i/dh)), i < dh/2, evaluated in double.
-__global__ void rope_table_kernel(float2* table, uint32_t max_seq, uint32_t half, double theta,
-                                  double dh) {
-  uint32_t u = blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= max_seq * half) return;
-  uint32_t t = u / half, i = u % half;
-  double ang = (double)t * pow(theta, -2.0 * (double)i / dh);
-  table[u] = make_float2((float)cos(ang), (float)sin(ang));
-}
-hipError_t launch_rope_table(float* table, uint32_t max_seq, uint32_t dh, float theta,
-                             hipStream_t st) {
-  uint32_t n = max_seq * (dh / 2);
-  rope_table_kernel<<<(n + 255) / 256, 256, 0, st>>>((float2*)table, max_seq, dh / 2,
-                                                     (double)theta, (double)dh);
-  return hipGetLastError();
-}
 // rotate-half pairing (i, i+dh/2) on the q and k thirds of qkv [M, 3d], in place; row m is at
 // position (m % pass_stride) % S.
 __global__ void rope_kernel(bf16_t* __restrict__ qkv, const float2* __restrict__ table, uint32_t M,
@@ -598,13 +586,15 @@ hipError_t launch_rope(void* qkv, const float* table, uint32_t M, uint32_t S, ui
 // part[m][slice] = (max, sum exp(l - max)) over the slice's columns.  One
 // wavefront merges a row: lse - target logit; rows at the last position of a
 // sequence predict nothing and contribute 0.
+// Pass blockIdx.y of a stacked step: M rows from row blockIdx.y * stride on.
 __global__ __launch_bounds__(256) void ce_rows_kernel(const float* __restrict__ part,
-                                                      const float* __restrict__ tgt, uint32_t M,
+                                                      const float* __restrict__ tgt, uint32_t M, uint32_t stride,
                                                       uint32_t S, uint32_t n_slices,
                                                       float* __restrict__ rowloss) {
-  const uint32_t m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (m >= M) return;
-  if (m % S == S - 1) {
+  const uint32_t r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (r >= M) return;
+  const uint32_t m = blockIdx.y * stride + r;
+  if (r % S == S - 1) {
     if (lane == 0) rowloss[m] = 0.0f;
     return;
   }
@@ -620,25 +610,42 @@ __global__ __launch_bounds__(256) void ce_rows_kernel(const float* __restrict__ 
   sum = wave_sum(sum);
   if (lane == 0) rowloss[m] = (mx + logf(sum)) - tgt[m];
 }
-// Fixed-order sum of n floats in double by one workgroup; out = sum * scale.
+// Fixed-order sum of n floats in double by 256 threads (thread t of them); lane 0 returns sum * scale.
+__device__ __forceinline__ float fixed_sum(const float* __restrict__ v, uint32_t n, double scale, double* red, uint32_t t) {
+  double acc = 0.0;
+  for (uint32_t i = t; i < n; i += 256) acc += (double)v[i];
+  red[t] = acc;
+  __syncthreads();
+  for (uint32_t o = 128; o > 0; o >>= 1) {
+    if (t < o) red[t] += red[t + o];
+    __syncthreads();
+  }
+  return (float)(red[0] * scale);
+}
 __global__ __launch_bounds__(256) void sum_kernel(const float* __restrict__ v, uint32_t n,
                                                   double scale, float* __restrict__ out) {
   __shared__ double red[256];
-  double acc = 0.0;
-  for (uint32_t i = threadIdx.x; i < n; i += 256) acc += (double)v[i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = (float)(red[0] * scale);
+  const float s = fixed_sum(v, n, scale, red, threadIdx.x);
+  if (threadIdx.x == 0) *out = s;
 }
-hipError_t launch_ce_reduce(const float* part, const float* tgt, uint32_t M, uint32_t S,
-                            uint32_t n_slices, float* rowloss, float* loss_out, hipStream_t st) {
-  ce_rows_kernel<<<(M + 3) / 4, 256, 0, st>>>(part, tgt, M, S, n_slices, rowloss);
+// The mean losses of one or two passes (256 threads each) and, behind the last forward of a step, d and its clipping
+// (Eq. 6): one launch where a step had four (each a few microseconds of nothing but latency).
+__global__ __launch_bounds__(512) void loss_kernel(const float* __restrict__ rowloss, uint32_t M, uint32_t stride, double scale,
+                                                   float* __restrict__ out, StepTail tail) {
+  __shared__ double red[512];
+  __shared__ float loss[2];
+  const uint32_t pass = threadIdx.x >> 8, t = threadIdx.x & 255u;
+  const float s = fixed_sum(rowloss + (uint64_t)pass * stride, M, scale, red + pass * 256, t);
+  if (t == 0) out[pass] = loss[pass] = s;
+  if (!tail.res) return;
+  __syncthreads();
+  if (threadIdx.x == 0) spsa_clip(blockDim.x > 256 ? loss[0] : *tail.loss_plus, blockDim.x > 256 ? loss[1] : loss[0], tail);
+}
+hipError_t launch_ce_reduce(const float* part, const float* tgt, uint32_t M, uint32_t stride, uint32_t n_pass, uint32_t S,
+                            uint32_t n_slices, float* rowloss, float* loss_out, const StepTail& tail, hipStream_t st) {
+  ce_rows_kernel<<<dim3((M + 3) / 4, n_pass), 256, 0, st>>>(part, tgt, M, stride, S, n_slices, rowloss);
   const uint32_t B = M / S;
-  sum_kernel<<<1, 256, 0, st>>>(rowloss, M, 1.0 / ((double)B * (double)(S - 1)), loss_out);
+  loss_kernel<<<1, 256 * n_pass, 0, st>>>(rowloss, M, stride, 1.0 / ((double)B * (double)(S - 1)), loss_out, tail);
   return hipGetLastError();
 }
 hipError_t launch_sum_partials(const float* partials, uint32_t n, float* out, hipStream_t st) {

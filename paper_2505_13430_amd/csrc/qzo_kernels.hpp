@@ -236,31 +236,40 @@ struct CeArgs {
   uint32_t n_slices;    // ceil(V/256)*4
 };
 hipError_t launch_lmhead_ce(const CeArgs& a, hipStream_t st);
+// The kernel for few rows: tiles of 32 mt (1, 2, 4) rows x 128 columns; mt, or 0 where the tile kernel is the faster one.
+uint32_t lmhead_rows_mt(const CeArgs& c);
+hipError_t launch_lmhead_rows(const CeArgs& c, uint32_t mt, hipStream_t st);
 hipError_t launch_mfma_rate(float* sink, uint32_t workgroups, uint32_t iters, int random_operands,
                             hipStream_t st);
-hipError_t launch_ce_reduce(const float* part, const float* tgt, uint32_t M, uint32_t S,
-                            uint32_t n_slices, float* rowloss, float* loss_out, hipStream_t st);
+// Behind the last forward of a step: d and its clipping into res (null: not wanted).  loss_plus: where an earlier forward
+// left the other pass's loss, when n_pass = 1.
+struct StepTail {
+  qzo_step_result* res;
+  float eps, clip;
+  const float* loss_plus;
+};
+// Mean losses of n_pass passes of M rows each (pass p from row p * stride on) into loss_out[p].
+hipError_t launch_ce_reduce(const float* part, const float* tgt, uint32_t M, uint32_t stride, uint32_t n_pass, uint32_t S,
+                            uint32_t n_slices, float* rowloss, float* loss_out, const StepTail& tail, hipStream_t st);
 
 hipError_t launch_sum_partials(const float* partials, uint32_t n, float* out, hipStream_t st);
 
+// rope (nullable): receives the table of rotary angles, (cos, sin) of [S positions][dh/2 pairs].
 // pass_stride: rows per pass of a stacked forward (M for a single pass); rows m % pass_stride >= tok_rows get zeros.
 hipError_t launch_embed(const int32_t* tok, uint32_t tok_rows, uint32_t pass_stride, const void* tok_emb,
-                        const void* pos_emb, uint32_t M, uint32_t S, uint32_t d, void* h, hipStream_t st);
+                        const void* pos_emb, uint32_t M, uint32_t S, uint32_t d, void* h, float* rope, uint32_t dh,
+                        float theta, hipStream_t st);
 // xsum_t (nullable, d % 128 == 0): receives the block sums of the output, [d/128][M] fp32 (see GemmArgs::xsum)
 hipError_t launch_rmsnorm(const void* x, const void* gain, uint32_t M, uint32_t d, float eps,
                           void* y, hipStream_t st, float* xsum_t = nullptr);
 hipError_t launch_layernorm(const void* x, const void* gain, const void* bias, uint32_t M,
                             uint32_t d, float eps, void* y, hipStream_t st, float* xsum_t = nullptr);
-hipError_t launch_rope_table(float* table, uint32_t max_seq, uint32_t dh, float theta,
-                             hipStream_t st);
 hipError_t launch_rope(void* qkv, const float* table, uint32_t M, uint32_t S, uint32_t pass_stride, uint32_t d,
                        uint32_t n_heads, hipStream_t st);
 // rope (nullable): the (cos, sin) table; with it the kernel rotates q and k itself (qkv holds them unrotated).
 constexpr uint32_t ATTENTION_ROPE_MAX_S = 256;   // up to this sequence length the models let it do so
 hipError_t launch_attention(const void* qkv, uint32_t B, uint32_t S, uint32_t n_heads,
                             uint32_t dh, void* out, const float* rope, hipStream_t st);
-hipError_t launch_spsa_clip(const float* losses, float eps, float clip, qzo_step_result* res,
-                            hipStream_t st);
 hipError_t launch_scale_update(void* arena, const UpdPlan& plan, uint32_t seed_lo,
                                uint32_t seed_hi, float eta, float d_clipped,
                                const qzo_step_result* res, hipStream_t st);
