@@ -907,6 +907,7 @@ hipError_t launch_lmhead_ce(const CeArgs& c, hipStream_t st) {
   }
   if ((uint64_t)c.M * c.K * 2 >= (1ull << 31) || (uint64_t)c.V * c.K * 2 >= (1ull << 31))
     return hipErrorInvalidValue;
+  if (const uint32_t mt = lmhead_rows_mt(c)) return launch_lmhead_rows(c, mt, st);
   GemmArgs a = {};
   a.x = c.x; a.w = c.w; a.M = c.M; a.N = c.V; a.K = c.K;
   CeEpilogue ce = {c.tok, c.part, c.tgt, c.S, c.n_slices, c.tok_rows ? c.tok_rows : c.M};

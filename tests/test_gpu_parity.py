@@ -1574,6 +1574,24 @@ def test_nf4_tile_kernel_weights_are_the_expanded_matrix(arch, F, batch, seq):
     dm.close()
 
 
+@pytest.mark.parametrize("vocab,batch,seq", [(1000, 1, 2), (1000, 1, 33), (603, 3, 32), (1024, 4, 64), (33000, 1, 31),
+                                             (32000, 2, 31), (32000, 2, 64), (32000, 2, 65)])
+def test_lm_head_of_few_rows(vocab, batch, seq):
+    """The lm_head kernel of few rows (row tiles of 32, 64, 128; ragged rows and vocabularies; the last case is beyond it):
+    the mean cross-entropy of the device's own final hidden states, in 64 bits.  fp32 sums of 256 products and
+    up to 64 exponentials at a time: 1e-5."""
+    shape = dict(synth.SHAPES["tiny"], vocab=vocab, n_layers=1, max_seq=128)
+    dm = DeviceModel.synthetic(shape, 7, DEV)
+    tok = _dev(synth.tokens(dict(shape, batch=batch, seq=seq), 3))
+    hid = torch.zeros((batch * seq, shape["d_model"]), dtype=torch.bfloat16, device=DEV)
+    loss = torch.zeros(1, dtype=torch.float32, device=DEV)
+    qb.qzo_debug_forward(dm.handle, tok, 9, 1e-3, 1, dm.workspace(batch, seq), loss, hid)
+    logits = (hid.float().cpu().double() @ dm.tensors[-1].float().cpu().double().T).view(batch, seq, vocab)[:, :-1]
+    want = torch.nn.functional.cross_entropy(logits.reshape(-1, vocab), tok.cpu()[:, 1:].reshape(-1).long())
+    assert abs(float(loss) - float(want)) <= 1e-5 * float(want)
+    dm.close()
+
+
 @pytest.mark.parametrize("name", ["tiny", "few_llama"])
 def test_step_replays_from_a_captured_graph(oracle, name):
     """qzo_step allocates nothing and never synchronises, so after one eager call (which sets the
