@@ -440,6 +440,15 @@ qzo_status qzo_debug_reduce_norm(const float* part_dev, uint32_t slices, uint32_
                                  int joined, void* y_dev, void* out_dev, float* xsum_dev, uint32_t* joined_out,
                                  void* stream);
 
+/* Inspection: attention behind a K-split qkv projection.  part_dev fp32 [slices, batch * seq, 3 n_heads head_dim], added up in
+ * order and rounded to bf16; rope_dev fp32 [seq][head_dim / 2] pairs (cos, sin); out_dev bf16 [batch * seq, n_heads head_dim].
+ * joined = 0: by way of qkv_dev (bf16, part's rows and columns); 1: as the models do, the attention adding the slices up
+ * where their rule says so (*joined_out, host, tells; qkv_dev is not written then).  head_dim 64 or 128, seq <= 256,
+ * batch * seq <= 2^20, slices of less than 2^31 bytes in all, pointers 16-byte aligned. */
+qzo_status qzo_debug_attention_slices(const float* part_dev, uint32_t slices, uint32_t batch, uint32_t seq, uint32_t n_heads,
+                                      uint32_t head_dim, const float* rope_dev, int joined, void* qkv_dev, void* out_dev,
+                                      uint32_t* joined_out, void* stream);
+
 /* Measurement aid, not part of the method: one 512-thread workgroup per compute unit, each
  * wavefront issuing iters x 16 v_mfma_f32_32x32x16_bf16 (32768 flop each) on register operands
  * that are all zero (random_operands = 0) or pseudo-random bf16 values, with no memory traffic.

@@ -30,7 +30,8 @@ EXPORTS = [
     "qzo_nf4_expand", "qzo_nf4_scratch_bytes", "qzo_nf4_gemm",
     "qzo_codebook_scratch_bytes", "qzo_codebook_gemm", "qzo_apply_update_channel",
     "qzo_debug_philox", "qzo_debug_normal_pairs", "qzo_debug_normals", "qzo_debug_dequant", "qzo_debug_dequant_zp",
-    "qzo_debug_forward", "qzo_debug_bf16_gemm", "qzo_debug_reduce_norm", "qzo_debug_mfma_rate",
+    "qzo_debug_forward", "qzo_debug_bf16_gemm", "qzo_debug_reduce_norm", "qzo_debug_attention_slices",
+    "qzo_debug_mfma_rate",
     "qzo_profile_begin", "qzo_profile_collect", "qzo_profile_stride",
     "qzo_last_error",
 ]
@@ -353,6 +354,16 @@ def qzo_debug_reduce_norm(part, bias, resid, gain, norm_bias, eps, joined, y, ou
     _check(lib().qzo_debug_reduce_norm(_ptr(part), C.c_uint32(slices), C.c_uint32(M), C.c_uint32(N), _ptr(bias),
                                        _ptr(resid), _ptr(gain), _ptr(norm_bias), C.c_float(eps), C.c_int(int(joined)),
                                        _ptr(y), _ptr(out), _ptr(xsum), C.byref(done), _stream(stream)))
+    return bool(done.value)
+
+
+def qzo_debug_attention_slices(part, rope, n_heads, joined, qkv, out, stream=None) -> bool:
+    """part [slices, batch, seq, 3 d].  Returns whether the attention added up the slices itself."""
+    slices, B, S, d3 = part.shape
+    done = C.c_uint32(0)
+    _check(lib().qzo_debug_attention_slices(_ptr(part), C.c_uint32(slices), C.c_uint32(B), C.c_uint32(S), C.c_uint32(n_heads),
+                                            C.c_uint32(d3 // 3 // n_heads), _ptr(rope), C.c_int(int(joined)), _ptr(qkv),
+                                            _ptr(out), C.byref(done), _stream(stream)))
     return bool(done.value)
 
 

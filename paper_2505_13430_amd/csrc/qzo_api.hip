@@ -484,9 +484,11 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
   // attention over both passes: one launch when they are contiguous, one per pass otherwise
   // short sequences: no RoPE launch, the attention kernel rotates q and k itself
   const bool rope_in_attention = llama && seq <= ATTENTION_ROPE_MAX_S;
+  NextAttention na = {batch, seq, H, dh, nullptr, 0};
   auto attention = [&](bool rotated) {
     ProfScope ps(PK_ATTN, attn_flops, st);
     const float* tb = (llama && !rotated) ? w.rope : nullptr;
+    if (na.part) return launch_attention(nullptr, batch, seq, H, dh, w.att, tb, st, na.part, na.slices);
     if (!padded) return launch_attention(w.qkv, batch, seq, H, dh, w.att, tb, st);
     hipError_t e = launch_attention(w.qkv, batch1, seq, H, dh, w.att, tb, st);
     if (e != hipSuccess) return e;
@@ -539,6 +541,7 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       g.split_ws = w.split;
       g.mid_ws = mid_ws;
       g.next = li == 1 || li == 3 ? &nn : nullptr;
+      g.next_attention = llama && li == 0 && rope_in_attention && !padded ? &na : nullptr;
       g.nf4 = c.quant == 3;
       if (few) {     // the few-token kernel takes the block sums of its input from the kernel that wrote it
         g.xsum = (li == 0 || li == 2) ? w.xs_a : (li == 3 ? w.xs_act : nullptr);
@@ -678,6 +681,7 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       // attn_norm, wqkv, wo, ffn_norm, wgu, wdown (symmetric-table positions)
       QZO_HIP(norm(ti(0), nullptr, xs_a));
       rope_fused = false;
+      na.part = nullptr;
       QZO_HIP(gemm(0, w.a, nullptr, nullptr, w.qkv, EPI_ROPE));
       if (!rope_fused && !rope_in_attention) QZO_HIP(launch_rope(w.qkv, w.rope, M, seq, P, d, H, st));
       QZO_HIP(attention(rope_fused || !rope_in_attention));
@@ -1355,6 +1359,26 @@ qzo_status qzo_debug_bf16_gemm(const void* x_dev, const void* w_dev, uint32_t M,
   GemmArgs g = {};
   g.x = x_dev; g.w = w_dev; g.y = y_dev; g.M = M; g.N = N; g.K = K;
   QZO_HIP(launch_bf16_gemm(g, pipe, (hipStream_t)stream));
+  return QZO_OK;
+}
+
+qzo_status qzo_debug_attention_slices(const float* part_dev, uint32_t slices, uint32_t batch, uint32_t seq, uint32_t n_heads,
+                                      uint32_t head_dim, const float* rope_dev, int joined, void* qkv_dev, void* out_dev,
+                                      uint32_t* joined_out, void* stream) {
+  if (!part_dev || !rope_dev || !qkv_dev || !out_dev || !joined_out) return fail(QZO_ERR_ARG, "null pointer");
+  if (!aligned16(part_dev) || !aligned16(rope_dev) || !aligned16(qkv_dev) || !aligned16(out_dev))
+    return fail(QZO_ERR_ALIGN, "device pointer not 16-byte aligned");
+  if (batch == 0 || seq == 0 || seq > ATTENTION_ROPE_MAX_S || n_heads == 0 || n_heads > 1024 || (head_dim != 64 && head_dim != 128) ||
+      slices == 0 || (uint64_t)batch * seq > (1u << 20) || (uint64_t)slices * batch * seq * 3 * n_heads * head_dim >= (1ull << 29))
+    return fail(QZO_ERR_SHAPE, "need seq <= 256, heads of 64 or 128 features, slices of less than 2^31 bytes in all");
+  hipStream_t st = (hipStream_t)stream;
+  NextAttention na = {batch, seq, n_heads, head_dim, nullptr, 0};
+  GemmArgs g = {};
+  g.y = qkv_dev; g.M = batch * seq; g.N = 3 * n_heads * head_dim;
+  g.next_attention = joined ? &na : nullptr;
+  QZO_HIP(launch_partial_reduce(g, part_dev, slices, st));
+  *joined_out = na.part ? 1u : 0u;
+  QZO_HIP(launch_attention(qkv_dev, batch, seq, n_heads, head_dim, out_dev, rope_dev, st, na.part, na.slices));
   return QZO_OK;
 }
 

@@ -40,10 +40,16 @@ __device__ __forceinline__ void rope_pair8(uint32_t (&a)[4], uint32_t (&b)[4], c
   }
 }
 
-template <int DH, bool ROPE, bool LONG>
+// PART: q, k and v of a sequence of at most one key tile arrive as the K slices of their projection (fp32
+// [slices][rows][3d]) and are added up here, in slice order and rounded to bf16 like the reduction that this saves: every
+// element is read once either way.  The loads go along the rows (a lane: four features of each slice), the sums
+// through the LDS: loaded in the fragments' places, 16 bytes a row, they cost 13 us a launch.
+template <int DH, bool ROPE, bool LONG, bool PART = false>
 __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restrict__ qkv, uint32_t S,
                                                            uint32_t n_heads, bf16_t* __restrict__ out,
-                                                           const float2* __restrict__ rope, uint32_t walk) {
+                                                           const float2* __restrict__ rope, uint32_t walk,
+                                                           const float* __restrict__ part, uint32_t slices) {
+  static_assert(!PART || (ROPE && !LONG), "slices: short sequences with the rotation here");
   constexpr int KB = 64;             // keys per tile
   constexpr int KT = DH / 16;        // k-steps of the score MFMA
   constexpr int DT = DH / 32;        // 32-wide slices of the head for the PV MFMA
@@ -120,12 +126,15 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
       const uint32_t row = QZO_ATT_KROW(i), ch = QZO_ATT_KCH(i);                             \
       *reinterpret_cast<u32x4*>((smem + (BUF) * 2 * TILE) + row * DH + ((ch ^ swz(row)) * 8)) = kreg[i];      \
     }                                                                                        \
-    _Pragma("unroll") for (int i = 0; i < NK; ++i) {                                         \
+    if (!PART) _Pragma("unroll") for (int i = 0; i < NK; ++i) {                              \
       const uint32_t c = t + 256u * i;                                                       \
       const uint32_t row = c / CH, ch = c % CH;                                              \
       *reinterpret_cast<u32x4*>((smem + (BUF) * 2 * TILE + TILE) + row * DH + (((ch >> 1) ^ vsw(row)) * 16 + (ch & 1u) * 8)) = vreg[i]; \
     }                                                                                        \
   } while (0)
+  const uint32_t pstride = PART ? gridDim.z * S * ld * 4u : 0u;             // bytes of a slice
+  const __amdgpu_buffer_rsrc_t rpart = __builtin_amdgcn_make_buffer_rsrc((void*)(PART ? part : nullptr), 0,
+                                                                         PART ? (int)(slices * pstride) : 0, 0x00020000);
   // Direct loads: load n of wavefront w fills bytes (4 n + w) 1024 .. + 1023 of a tile, lane l its 16 bytes at
   // l 16: row and physical chunk follow, the logical chunk is the physical one un-swizzled.
   typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -210,6 +219,52 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
       const uint32_t q = min(q0 + row, S - 1);
       QZO_ATT_DTL16(lds_k + (uint32_t)(4 * TILE + n * 4096), q * (ld * 2) + ((pc ^ swz(row)) * 8) * 2);
     }
+  } else if constexpr (PART) {
+    // sums of the rows: queries to where buffer 1 begins, keys as they are behind them, values to their tile
+    constexpr uint32_t C4 = DH / 4;                // items (four features) of a row's third
+    constexpr int U = 4;
+    const uint32_t n_items = 3 * S * C4;
+    for (uint32_t i0 = t; i0 < n_items; i0 += 256 * U) {
+      float v[U][4];
+      uint32_t off[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t i = i0 + 256u * u, rt = i / C4, row = rt / 3, third = rt % 3;
+        off[u] = i < n_items ? ((b * S + row) * ld + third * d + h * DH + (i % C4) * 4) * 4u : 0x80000000u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][e] = 0.0f;
+      }
+      for (uint32_t k0 = 0; k0 < slices; k0 += 4) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            // no such slice: out of the buffer's range, zeros; a sum that began with +0 is never -0, so they change nothing
+            const auto x = __builtin_amdgcn_raw_buffer_load_b128(rpart, (int)(k0 + k < slices ? off[u] + (k0 + k) * pstride : 0x80000000u), 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[u][e] += __uint_as_float(x[e]);
+          }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t i = i0 + 256u * u, rt = i / C4, row = rt / 3, third = rt % 3, ch = (i % C4) >> 1, lo = (i & 1u) * 4;
+        const uint32_t at = third == 2 ? TILE + row * DH + (((ch >> 1) ^ vsw(row)) * 16 + (ch & 1u) * 8)
+                                       : (2 + third) * TILE + row * DH + ((ch ^ swz(row)) * 8);
+        if (i < n_items)
+          *reinterpret_cast<uint2*>(smem + at + lo) = make_uint2(pack_bf16x2(v[u][0], v[u][1]), pack_bf16x2(v[u][2], v[u][3]));
+      }
+    }
+    for (uint32_t i = S * (DH / 8) + t; i < KB * (DH / 8); i += 256)       // values of keys that are not there: zeros
+      *reinterpret_cast<u32x4*>(smem + TILE + i * 8) = u32x4{0, 0, 0, 0};
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < KT; ++ks)
+      qf[ks] = *reinterpret_cast<const bf16x8*>(smem + 2 * TILE + (qc - q0) * DH + (((uint32_t)(ks * 2) + lhalf) ^ swz(qc - q0)) * 8);
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      const uint32_t row = min(QZO_ATT_KROW(i), S - 1);
+      kreg[i] = *reinterpret_cast<const u32x4*>(smem + 3 * TILE + row * DH + (QZO_ATT_KCH(i) ^ swz(row)) * 8);
+    }
   } else {
 #pragma unroll
     for (int ks = 0; ks < KT; ++ks)
@@ -217,7 +272,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
   }
   if (DTL) {
     QZO_ATT_DTL(0, 0u);
-  } else {
+  } else if (!PART) {
     QZO_ATT_GLOAD(0u);
   }
   if (via_lds) {
@@ -242,7 +297,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
 
   if (!DTL) {
     QZO_ATT_LSTORE(0, 0u);
-    if (nkb > 1) QZO_ATT_GLOAD(1u);
+    if (!PART && nkb > 1) QZO_ATT_GLOAD(1u);
   } else if (!via_lds) {
     __builtin_amdgcn_s_waitcnt(0x0F70);         // vmcnt(0): this wavefront's part of tile 0
   }
@@ -436,9 +491,19 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
 #undef QZO_ATT_DTL_ONE
 #undef QZO_ATT_DTL16
 
+// Whole steps of eight layers, reduction and attention -> attention of the slices: 7B widths 1 x 8 tokens 0.974 of the time, 1 x 16
+// (four slices) 0.978, 1 x 32 0.972, 16 x 16 (two) 0.980, 4 x 64 (two) 0.982; widths of 1024 and 2048 1 x 16 0.974, 8 x 64
+// (two) 0.992.  A workgroup adds up a head by itself, so more than 128 rows of slices take it as long as the launch that
+// they save: 1 x 57 (four) 0.991, 2 x 64 (five) 1.006, 13B widths 1 x 57 (three) 1.004, width 2048 1 x 64 (four) 1.006.
+bool attention_adds_slices(uint32_t B, uint32_t S, uint32_t n_heads, uint32_t dh, uint32_t slices) {
+  return S <= 64 && (uint64_t)slices * S <= 128 && (dh == 64 || dh == 128) && slices &&
+         (uint64_t)slices * B * S * 3 * n_heads * dh * 4 < (1ull << 31);        // byte offsets of 32 bits
+}
+
 // rope (nullable): (cos, sin) of [S positions][dh/2 pairs]; with it q and k are rotated on the fly.
 hipError_t launch_attention(const void* qkv, uint32_t B, uint32_t S, uint32_t n_heads,
-                            uint32_t dh, void* out, const float* rope, hipStream_t st) {
+                            uint32_t dh, void* out, const float* rope, hipStream_t st, const float* part,
+                            uint32_t slices) {
   // the direct loads address qkv with 32-bit byte offsets and use an offset near 2^32 as "out of range"
   if ((uint64_t)B * S * 3 * n_heads * dh * 2 >= (1ull << 31)) return hipErrorInvalidValue;
   // The (batch, head) pairs alone fill the chip twice over (two workgroups fit a CU): their workgroups walk
@@ -456,18 +521,24 @@ hipError_t launch_attention(const void* qkv, uint32_t B, uint32_t S, uint32_t n_
   const uint32_t walk = per_head ? 1u : 0u;
   dim3 grid(pair ? 2 : (per_head ? 1 : (S + 127) / 128), n_heads, B);
   const float2* tb = (const float2*)rope;
-  if (dh == 128 && rope)
-    attention_kernel<128, true, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk);
+  if (part) {
+    if (!rope || !attention_adds_slices(B, S, n_heads, dh, slices)) return hipErrorInvalidValue;
+    if (dh == 128)
+      attention_kernel<128, true, false, true><<<grid, 256, 0, st>>>(nullptr, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+    else
+      attention_kernel<64, true, false, true><<<grid, 256, 0, st>>>(nullptr, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+  } else if (dh == 128 && rope)
+    attention_kernel<128, true, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
   else if (dh == 128 && lng)
-    attention_kernel<128, false, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk);
+    attention_kernel<128, false, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
   else if (dh == 128)
-    attention_kernel<128, false, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk);
+    attention_kernel<128, false, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
   else if (dh == 64 && rope)
-    attention_kernel<64, true, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk);
+    attention_kernel<64, true, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
   else if (dh == 64 && lng)
-    attention_kernel<64, false, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk);
+    attention_kernel<64, false, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
   else if (dh == 64)
-    attention_kernel<64, false, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk);
+    attention_kernel<64, false, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

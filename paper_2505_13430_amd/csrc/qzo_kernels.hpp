@@ -43,6 +43,12 @@ struct NextNorm {
   float* xsum;                 // nullable: block sums of out, [N/128][rows]
   bool done;                   // set by the launcher that took it over
 };
+// The attention that reads a qkv projection next: a slice reduction may leave its slices to it.
+struct NextAttention {
+  uint32_t batch, seq, heads, dh;
+  const float* part;           // set by the launcher that left them: fp32 [slices][batch * seq][3 heads dh]
+  uint32_t slices;
+};
 struct GemmArgs {
   const void* x;        // bf16 [M,K]
   const void* w;        // packed int4 [N,K/2] (W4) or bf16 [N,K] (dense)
@@ -82,6 +88,7 @@ struct GemmArgs {
   float* xsum_out;
   // The norm that reads y next (null: none wanted): a slice reduction norms the rows it completes (NextNorm::done).
   struct NextNorm* next;
+  struct NextAttention* next_attention;      // (null: y is wanted)
 };
 hipError_t launch_w4a16_gemm(const GemmArgs& a, hipStream_t st);
 // Output tiles of the fused kernel: 32 mt tokens x 256 features, each in one pass of a stacked step; units of work are
@@ -269,7 +276,10 @@ hipError_t launch_rope(void* qkv, const float* table, uint32_t M, uint32_t S, ui
 // rope (nullable): the (cos, sin) table; with it the kernel rotates q and k itself (qkv holds them unrotated).
 constexpr uint32_t ATTENTION_ROPE_MAX_S = 256;   // up to this sequence length the models let it do so
 hipError_t launch_attention(const void* qkv, uint32_t B, uint32_t S, uint32_t n_heads,
-                            uint32_t dh, void* out, const float* rope, hipStream_t st);
+                            uint32_t dh, void* out, const float* rope, hipStream_t st, const float* part = nullptr,
+                            uint32_t slices = 0);
+// Whether it takes the projection's K slices in qkv's place (with rope).
+bool attention_adds_slices(uint32_t B, uint32_t S, uint32_t n_heads, uint32_t dh, uint32_t slices);
 hipError_t launch_scale_update(void* arena, const UpdPlan& plan, uint32_t seed_lo,
                                uint32_t seed_hi, float eta, float d_clipped,
                                const qzo_step_result* res, hipStream_t st);

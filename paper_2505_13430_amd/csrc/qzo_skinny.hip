@@ -477,9 +477,17 @@ __global__ __launch_bounds__(1024) void reduce_norm_kernel(GemmArgs a, const flo
                             (bf16_t*)nn.out + (uint64_t)m * a.N, nn.xsum, m, gridDim.x, red);
 }
 
-// Slice reduction of a.M rows, with the norm that reads its output where the caller named one.
+// Slice reduction of a.M rows, with the norm that reads its output where the caller named one; left to the attention that
+// reads its output where the caller named that and it takes them.
 template <bool MAPPED>
 hipError_t launch_reduce(const GemmArgs& r, const float* part, uint32_t ksplit, const MidPlan& mp, hipStream_t st) {
+  NextAttention* na = MAPPED ? nullptr : r.next_attention;
+  if (na && !r.epi && !r.ldy && !r.xsum_out && r.M == na->batch * na->seq &&
+      attention_adds_slices(na->batch, na->seq, na->heads, na->dh, ksplit)) {
+    na->part = part;
+    na->slices = ksplit;
+    return hipSuccess;
+  }
   if (r.next && !(r.epi & (EPI_SWIGLU | EPI_SUMSQ)) && !r.ldy && !r.xsum_out && r.N <= 8192 && r.N % 8 == 0 &&
       r.M <= 512 && (r.N <= 4096 || r.M >= 256)) {
     NextNorm nn = *r.next;

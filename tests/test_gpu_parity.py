@@ -912,6 +912,44 @@ def test_reduction_and_norm_stay_two_launches_outside_the_rule(M, N):
     assert (h == 2).all() and (out == 1).all()
 
 
+@pytest.mark.parametrize("B,S,H,dh,slices,joins", [
+    (1, 2, 1, 64, 1, True), (2, 3, 2, 128, 5, True), (3, 16, 4, 128, 8, True), (2, 31, 3, 64, 4, True), (1, 32, 2, 128, 4, True),
+    (3, 33, 2, 64, 3, True), (2, 64, 3, 128, 2, True), (9, 64, 2, 64, 2, True), (40, 5, 16, 64, 25, True),
+    # more rows of slices, or of keys, than the rule takes
+    (1, 43, 2, 128, 3, False), (1, 32, 2, 64, 5, False), (2, 65, 2, 128, 1, False)])
+def test_attention_that_adds_up_slices_equals_reduction_and_attention(B, S, H, dh, slices, joins):
+    """Same partial sums through the reduction and the attention kernel, and through the attention kernel alone: bit for bit.
+    The common result against softmax attention in float64 of the bf16 sums (16-bit inputs after the rotation and 16-bit
+    probabilities: 2^-7 of the largest value)."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B * S * H + slices)
+    d = H * dh
+    part = torch.randn(slices, B, S, 3 * d, generator=gen, device=DEV) / math.sqrt(slices)
+    pos = torch.arange(S, device=DEV, dtype=torch.float64)
+    ang = pos[:, None] * 10000.0 ** (-torch.arange(dh // 2, device=DEV, dtype=torch.float64) * 2 / dh)
+    rope = torch.stack([ang.cos(), ang.sin()], -1).float().contiguous()
+    got = []
+    for joined in (False, True):
+        qkv = torch.zeros(B, S, 3 * d, dtype=torch.bfloat16, device=DEV)
+        out = torch.full((B, S, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+        assert qb.qzo_debug_attention_slices(part, rope, H, joined, qkv, out) == (joined and joins)
+        assert bool(qkv.any()) == (not (joined and joins))
+        got.append(out)
+    assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
+    acc = torch.zeros_like(part[0])
+    for p in part:
+        acc += p
+    q, k, v = (t.view(B, S, H, dh).transpose(1, 2) for t in acc.to(torch.bfloat16).double().split(d, dim=2))
+
+    def rotate(x):
+        a, b = x[..., :dh // 2], x[..., dh // 2:]
+        return torch.cat([a * ang.cos() - b * ang.sin(), b * ang.cos() + a * ang.sin()], -1).to(torch.bfloat16).double()
+    s = (rotate(q) @ rotate(k).transpose(2, 3)) / math.sqrt(dh)
+    s = s.masked_fill(torch.ones(S, S, device=DEV, dtype=torch.bool).triu(1), -math.inf)
+    want = (s.softmax(-1) @ v).transpose(1, 2).reshape(B, S, d)
+    assert (got[1].double() - want).abs().max() <= 2 ** -7 * v.abs().max()
+
+
 def test_failing_calls_enqueue_nothing(oracle):
     """Every error that the library finds itself (anything but a failing HIP call) is found before
     the first launch: outputs, workspace and scales are untouched afterwards."""
