@@ -121,7 +121,7 @@ def fused_leg(torch, qb, dm, tok, steps, n_lin, eps, eta, clip):
     g = qb.qzo_profile_collect(qb.PROFILE_KINDS["w4a16_gemm"])
     rate = g["work"] / (g["total_ms"] * 1e-3)
     dm.set_int4_path(0)
-    return {"bound": "mfma", "kernel": "gemm_kernel<0,false,4,2> (fused perturbed W4A16 GEMM)",
+    return {"bound": "mfma", "kernel": "w4_gemm_kernel (fused perturbed W4A16 GEMM)",
             "achieved": rate / 1e12, "peak": PEAK_BF16_MFMA / 1e12, "unit": "TFLOP/s", "frac": rate / PEAK_BF16_MFMA,
             "traffic": measured_traffic("traffic_bytes_per_launch_gemm_qkv_fused"),
             "launches": g["launches"], "avg_launch_ms": g["total_ms"] / max(g["launches"], 1),
@@ -213,8 +213,8 @@ def main():
                          "zero-points, NormalFloat-4 blocks of 64, or the codebook variant with per-channel "
                          "scales (no cpu_baseline leg)")
     ap.add_argument("--fused", action="store_true",
-                    help="int4 variants: always the fused dequantizing GEMM (default: expand-then-multiply "
-                         "for linears with enough tokens per pass, about 2700-4300 at the 7B widths)")
+                    help="int4 variants: always the fused dequantizing GEMM (the default route, too; its "
+                         "two passes share launches up to 4096 tokens whatever the linears)")
     ap.add_argument("--expanded", action="store_true",
                     help="int4 variants: always expand-then-multiply, whatever the token count")
     ap.add_argument("--graph", action="store_true",
@@ -367,7 +367,7 @@ def main():
                      "kernel": "wide_gemm_kernel (qkv, o, down) and gemm_kernel<1,false,4,3> (gate/up with SwiGLU): plain bf16 GEMM on the expanded perturbed weights"
                      if expanded
                      else ("gemm_kernel<2,...> (codebook GEMM, perturbed channel scales)" if codebook
-                           else "gemm_kernel<0,false,4,2> (fused perturbed W4A16 GEMM)"),
+                           else "w4_gemm_kernel (fused perturbed W4A16 GEMM)"),
                      "achieved": linear_flops_s / 1e12, "peak": PEAK_BF16_MFMA / 1e12,
                      "unit": "TFLOP/s", "frac": linear_flops_s / PEAK_BF16_MFMA,
                      "achieved_note": "2MNK of the perturbed linears over the time of their matrix kernel PLUS "

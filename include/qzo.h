@@ -173,14 +173,14 @@ qzo_status qzo_forward_loss(qzo_model* m, const int32_t* tokens_dev, uint32_t ba
  * With int4 weights (no joint mode, no group index per column) the two forwards run as one
  * forward over 2*batch sequences.  Up to 64 tokens the few-token kernel serves both (up to 32
  * it reads the weights once): losses bit-identical to two qzo_forward_loss calls.  Beyond, up
- * to the token count from which the model's linears take the expand-then-multiply route (about
- * 3200 at Llama-2-7B widths; at most 4096; never when that route is forced), a launch of the
- * tile kernel holds the token tiles of both passes, the second pass's with -eps and starting
- * on a 256-row tile boundary (padding rows in between); losses equal to two qzo_forward_loss
+ * to 4096 tokens (from some 3000 on only where none of the model's linears is cut along K; never when expand-then-multiply
+ * is forced), a launch of the tile kernel holds the token tiles of both passes, the second pass's
+ * with -eps; losses equal to two qzo_forward_loss
  * calls within the 16-bit activations' noise, the K split of a linear being a function of the
  * number of token tiles.  Zero-point models with fp16 scales (33 to 128 tokens, up to 192 where a
  * layer's linears hold at most 2^28 weights; 65 to 256 where they hold at most 2^26) and NormalFloat-4 models (up
- * to 384 or 512 tokens) work in tiles of 32 tokens, each of one pass, with the same agreement;
+ * to 64 tokens, narrow layers up to 512) work in tiles of 32 tokens, each of one pass, NormalFloat-4 models of wide layers
+ * up to 384 or 512 tokens in the tile kernel, with the same agreement;
  * NormalFloat-4 models beyond, up to 4096 tokens, in 256-row tiles on both passes' expanded
  * matrices where that is estimated to be faster than two forwards (the workspace then holds both
  * matrices of a linear).  qzo_workspace_bytes accounts for it.

@@ -209,15 +209,16 @@ bool nf4_tile_route(const qzo_model* m, uint64_t M1) {
 
 // Token counts per pass that take mid_gemm_kernel: NormalFloat-4, and zero-point int4 with fp16 scales beyond the
 // few-token kernel's stacked range.
-//   Its time grows by tiles of 32 tokens, the tile kernel's by tiles of 256, and the wider the layer the better the tile
-// kernel fills the chip.  Whole steps of zero-point models, mid_gemm_kernel's time over the tile kernel's: 7B widths 0.65
-// (96 tokens), 0.85 (132), 0.90 (192), 1.00 (224), 1.03 (256); 13B widths 0.73 (96), 0.98 (132), 1.2 (256); OPT-1.3B widths
-// 0.81 (132), 0.90 (256); smaller models 0.53-0.97 up to 256.  Up to 64 tokens, over the few-token kernel's with a workgroup
+//   Zero-points: it applies the perturbed scale in fp32 to exact integers, where the tile kernel rounds every weight to bf16.
+// The range is the one in which that cost no time while the tile kernel's tiles were all 256 tokens high.  Since they are
+// not, the tile kernel is faster beyond 64 tokens: mid_gemm_kernel's time over its, steps of eight layers: 7B widths 1.09 (96
+// tokens), 1.19 (132), 1.14 (192); 13B widths 1.19 (96), 1.24 (128); OPT-1.3B widths 1.03 (96), 0.97 (128), 1.04 (132), 0.94 (256).
+// The range stays, for its precision.  Up to 64 tokens, over the few-token kernel's with a workgroup
 // per pass: 7B widths 0.91-0.94, 13B 0.88-0.89, 2560 x 10240 and 3072 x 8192 0.93-0.96, but OPT-1.3B 1.01-1.04, 2048 x 5632
 // 1.05-1.07, smaller models 0.97-1.02: there the few-token kernel stays, whose losses are those of two separate passes.
 // A route that the caller chose stays: 1 (fused) keeps the tile kernel beyond the few-token kernel's 64 tokens.
-//   NormalFloat-4 has no other fused kernel.  Whole steps against two forwards / one stacked forward on expanded matrices:
-// 7B widths 0.27 / 0.26 (16 tokens), 0.33 / 0.32 (57), 0.50 / 0.59 (192), 0.49 / 0.63 (256), 0.86 / 0.90 (400), 0.77 / 0.83
+//   NormalFloat-4: the tile kernel where nf4_tile_route says so.  Whole steps of this kernel against two forwards / one
+// stacked forward on expanded matrices: 7B widths 0.27 / 0.26 (16 tokens), 0.33 / 0.32 (57), 0.50 / 0.59 (192), 0.49 / 0.63 (256), 0.86 / 0.90 (400), 0.77 / 0.83
 // (512); 13B widths 0.29 (57), 0.53 / 0.67 (256), and beyond the limit 0.88 / 0.95 (400), 0.82 / 0.93 (512); OPT-1.3B widths
 // 0.41 / 0.50 (57), 0.45 / 0.72 (256), 0.62 / 0.88 (512), and beyond 0.95 (640), 1.08 (768).  Single passes: 0.43-0.72 (57
 // tokens), 0.81-0.89 (512).

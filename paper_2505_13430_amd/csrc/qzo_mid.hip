@@ -10,7 +10,7 @@
 // s_eff (128 + zp) X with X the block sum of the activations (delivered by the kernel that wrote them), is taken off
 // for two groups at a time by one fp32 MFMA per tile (32x32x2: its depth is the two groups), which costs no vector
 // instruction and no broadcast reads.  A token tile lies in one pass of a stacked step and takes that pass's sign.
-// Hidden states of one layer against 64 bits: 7.8e-3 (the bf16 weight tile of the 256-row kernel) -> 6.4e-3.
+// Hidden states of one layer against 64 bits: 7.8e-3 (the tile kernel, whose weights are rounded to bf16) -> 6.4e-3.
 //
 // Everything a group needs comes by direct-to-LDS loads into a ring of three or four stages, requested two or three
 // groups ahead (swizzled on the memory side, nothing passes through registers); one barrier per group.  Inside a group
@@ -27,16 +27,14 @@
 // its places for either (BOTH: a second table, and a second lookup behind the same selectors): about 310 or 470 vector
 // instructions per group and wavefront with four tiles against 32 MFMAs, which bound it.
 // Against expand-then-multiply, which writes and reads 2 bytes per weight and pass: 1 x 16 tokens at 7B widths
-// 16.5 -> 4.2 ms per step, 1 x 57 17.1 -> 5.6, 4 x 33 19.7 -> 10.4, 4 x 64 23.8 -> 11.6, 4 x 100 25.8 -> 21.7,
-// 8 x 64 27.2 -> 20.5.  Blocks of either kind in one launch (BOTH for the remainder only): 6-13 % slower, the second
+// 16.5 -> 4.2 ms per step, 1 x 57 17.1 -> 5.6 (wide layers beyond 64 tokens run in the tile kernel, nf4_tile_route).  Blocks of either kind in one launch (BOTH for the remainder only): 6-13 % slower, the second
 // copy of the loop is more cold code per launch.
 //
 // What bounds the integer format: at 57 tokens per pass (4096 x 4096 .. 22016) a launch takes 16-43 us, of which about
 // 10 us do not depend on the work (start of a kernel whose code and operands come from HBM, 15-30 MB of partial sums
 // out); a group of four tiles takes 4200-5300 cycles with the matrix unit busy for 2300 and the LDS for 2700 of them.
-// Whole steps of zero-point models at 7B widths against two passes of the few-token kernel (up to 64 tokens) or the
-// 256-row tile kernel (beyond): 1 x 33 tokens 7.24 -> 4.70 ms, 1 x 57 7.74 -> 5.00, 2 x 40 9.75 -> 6.11, 4 x 33 9.90 -> 8.37,
-// 4 x 48 10.2 -> 9.1.
+// Whole steps of zero-point models at 7B widths against two passes of the few-token kernel: 1 x 33 tokens 7.24 -> 4.70 ms,
+// 1 x 57 7.74 -> 5.00.  Beyond 64 tokens the tile kernel is the faster one (mid_route), but rounds the weights.
 // Tried: one wavefront per SIMD with 64 rows each (half the LDS reads, but the accumulators move to AGPRs and every
 // rescaling then pays two register moves: 15-25 % slower); K split between two halves of a workgroup (LDS merge
 // instead of partial sums: more activation traffic, slower); activations and weights staged through registers

@@ -23,8 +23,12 @@
 // are 1.15 us of that at the clock the board grants on such data.  Timing-only variants (board with 1.69): loads not
 // issued 1.59; noise left out -0.02 to -0.05; fragment reads left out -0.08.
 // Lower tiles serve the sizes whose rounds of 256-token tiles are badly filled (w4_plan): steps at 7B widths, before ->
-// after: 4 x 33 tokens 9.5 -> 6.9 ms, 8 x 200 with zero-points 45.9 -> 39.6, 16 x 64 28.6 -> 25.8; OPT-1.3B 16 x 256
-// 22.1 -> 20.6; one linear 2048 x 11008 x 4096, both signs, 0.439 -> 0.336; the tests' smallest model 0.180 -> 0.119.
+// after: 4 x 33 tokens 9.4 -> 6.6 ms, 8 x 200 with zero-points 45.2 -> 39.4, 16 x 64 28.2 -> 25.8; OPT-1.3B 16 x 256
+// 21.8 -> 19.4; one linear 2048 x 11008 x 4096, both signs, 0.432 -> 0.336; the tests' smallest model 0.180 -> 0.119.  With a
+// unit's first three k-tiles loaded ahead of the stores of the one before, the time around a k-loop fell from 6.4 to 3.8 us.
+// The rotary embedding rides on the epilogue (rows in an order that gives a lane both features of a pair).  NormalFloat-4
+// takes 6 % more per k-tile than int4 (products of a level by byte permutations): 4 x 100 tokens 21.7 -> 14.8 ms.
+// The noise's instructions as straight-line pieces behind the MFMAs: 1.609 against 1.612 us a k-tile, not kept.
 // Outputs are the same bit for bit whatever MT: every one sums the same k-steps in the same order.
 #include "qzo_gemm_tile.hpp"
 #include "qzo_nibble.hpp"
