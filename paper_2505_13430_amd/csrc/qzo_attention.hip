@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
   const uint32_t lds_v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)&smem[TILE] +
                          __builtin_amdgcn_readfirstlane(wave) * 1024u;
 #define QZO_ATT_DTL16(LDSADDR, VOFF)                                                         \
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"                 \
+  asm volatile(QZO_SET_M0 "buffer_load_dwordx4 %1, %2, 0 offen lds"                          \
                : : "s"(LDSADDR), "v"(VOFF), "s"(rqkv) : "memory", "m0")
 // load J of a tile: J < NI the K loads, then the V loads; BUF, KB_ may be run-time values.  ON (uniform)
 // false: the offset is out of the buffer's range, the load fetches nothing and writes zeros to a buffer

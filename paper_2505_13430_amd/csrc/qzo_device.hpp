@@ -10,6 +10,11 @@ namespace qzo {
 
 typedef unsigned short bf16_t;   // raw bf16 bits
 
+// Head of every direct-to-LDS load in asm: M0 carries the LDS address (operand 0).  Between a scalar write of M0 and an
+// LDS-DMA load that reads it gfx9 needs one wait state, or the load may still see the address before; the compiler puts
+// one behind instructions that it knows, never inside an asm block.
+#define QZO_SET_M0 "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) {
   return __uint_as_float(((uint32_t)b) << 16);
 }

@@ -238,7 +238,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void gemm_kernel(GemmArgs a, CeEpilog
 // the wavefront's 1 KB; the hardware adds 16 bytes per lane.  The compiler does not see these
 // LDS writes: every read of the stage is separated from them by an explicit vmcnt(0) and a barrier.
 #define QZO_DTL16(RSRC, LDSADDR, VOFF, SOFF)                                                 \
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"                \
+  asm volatile(QZO_SET_M0 "buffer_load_dwordx4 %1, %2, %3 offen lds"                         \
                : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC), "s"(SOFF) : "memory", "m0")
 #define QZO_DTL_PART(KT, STAGE, I0, I1)                                                      \
   do {                                                                                       \

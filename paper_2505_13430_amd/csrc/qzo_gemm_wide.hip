@@ -27,7 +27,7 @@
 namespace qzo {
 
 #define QW_DTL16(RSRC, LDSADDR, VOFF, SOFF)                                                  \
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"                \
+  asm volatile(QZO_SET_M0 "buffer_load_dwordx4 %1, %2, %3 offen lds"                         \
                : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC), "s"(SOFF) : "memory", "m0")
 
 template <int ST_AUX>

@@ -16,7 +16,7 @@ namespace {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 #define QH_DTL(RSRC, LDSADDR, VOFF, SOFF)                                                    \
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"                \
+  asm volatile(QZO_SET_M0 "buffer_load_dwordx4 %1, %2, %3 offen lds"                         \
                : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC), "s"(SOFF) : "memory", "m0")
 
 template <int MT>

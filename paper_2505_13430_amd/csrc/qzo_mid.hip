@@ -63,7 +63,7 @@ struct MidLds {
 };
 
 #define QM_DTL(INSTR, RSRC, LDSADDR, VOFF)                                                   \
-  asm volatile("s_mov_b32 m0, %0\n\t" INSTR " %1, %2, 0 offen lds" : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC) : "memory", "m0")
+  asm volatile(QZO_SET_M0 INSTR " %1, %2, 0 offen lds" : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC) : "memory", "m0")
 
 // BOTH: NormalFloat-4, every token block holds tiles of both passes.
 template <int MT, bool NF4, bool BOTH>

@@ -55,7 +55,7 @@ struct W4Lds {
 };
 
 #define Q4_DTL(INSTR, RSRC, LDSADDR, VOFF, SOFF)                                             \
-  asm volatile("s_mov_b32 m0, %0\n\t" INSTR " %1, %2, %3 offen lds"                          \
+  asm volatile(QZO_SET_M0 INSTR " %1, %2, %3 offen lds"                                      \
                : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC), "s"(SOFF) : "memory", "m0")
 
 #define Q4_INLINE __attribute__((always_inline))

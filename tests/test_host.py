@@ -4,10 +4,13 @@ reported before anything touches a GPU."""
 import ctypes as C
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
 from paper_2505_13430_amd import binding as qb
+from paper_2505_13430_amd import build as hip_build
 from paper_2505_13430_amd import synth
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -27,6 +30,53 @@ def test_library_exports_every_declared_symbol():
     for n in names:
         assert hasattr(lib, n), n
     assert sorted(qb.EXPORTS) == names
+
+
+def _device_code(tmp_path):
+    """Instructions of the built library's kernels: lists of (mnemonic, operands), a list per kernel."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    shutil.copy(hip_build.LIB, tmp_path / "lib.so")
+    subprocess.run([objdump, "--offloading", "lib.so"], cwd=tmp_path, check=True, capture_output=True)
+    bundles = [f for f in os.listdir(tmp_path) if "gfx950" in f]
+    assert len(bundles) >= len(hip_build.SOURCES) - 1            # every source but the API's holds kernels
+    kernels = []
+    for f in bundles:
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", f], cwd=tmp_path, check=True, capture_output=True, text=True)
+        for line in text.stdout.split("\n"):
+            if re.match(r"[0-9a-f]+ <", line):
+                kernels.append([])
+            elif line.startswith("\t") and kernels:
+                op, _, args = line.split("//")[0].strip().partition(" ")
+                kernels[-1].append((op, [a.strip() for a in args.split(",")]))
+    return kernels
+
+
+def _scalars(args):
+    out = set()
+    for a in args:
+        for m in re.finditer(r"(?<![a-z0-9_])s(?:(\d+)|\[(\d+):(\d+)\])", a):
+            out |= set(range(int(m[2]), int(m[3]) + 1)) if m[2] else {int(m[1])}
+    return out
+
+
+def test_wait_states_of_direct_to_lds_loads(tmp_path):
+    """The loads that write the LDS directly are asm, behind which the compiler inserts no wait states: one between a scalar
+    write of M0 (the LDS address) and the load, five between a vector instruction that writes a scalar register and the load
+    that reads it."""
+    loads = 0
+    for kernel in _device_code(tmp_path):
+        for i, (op, args) in enumerate(kernel):
+            if not (op.startswith("buffer_load") and args[-1].endswith(" lds")):
+                continue
+            loads += 1
+            reads, states, j = _scalars(args), 0, i - 1
+            while j >= 0 and states < 5:
+                before, operands = kernel[j]
+                assert not (states < 1 and operands[0] == "m0"), (i, op, args)
+                assert not (before.startswith("v_") and _scalars(operands[:1]) & reads), (i, before, operands, args)
+                states += int(operands[0]) + 1 if before == "s_nop" else 1
+                j -= 1
+    assert loads > 1000
 
 
 def test_scale_count_is_table2(oracle):
