@@ -236,8 +236,8 @@ qzo_status qzo_model_apply_update(qzo_model* m, uint64_t seed, float eta, float 
  * device memory, 256-byte aligned (may be NULL when that size is 0), contents undefined
  * afterwards; calls that share a scratch buffer must not overlap.  It holds the
  * partial sums of sum y^2 and the K-slice partial sums of the two paths below.  (Where the partial sums are all there is,
- * up to 256 floats, one per 256 x 256 output tile, rounded up to 256 bytes, are accepted too: the outputs are the same,
- * small calls take longer.)
+ * up to 256 floats, one per 256 x 256 output tile, rounded up to 256 bytes, are accepted too: y is the same bit for bit,
+ * sum y^2 to within a few 2^-24 of it (its terms are grouped otherwise), small calls take longer.)
  * With M <= 64 the call takes the few-token path (the paper's batch-1 memory
  * profile and short-prompt batches, Sec. 4.3): the int4 weights are streamed once and
  * enter the matrix unit as integer codes, each 128-wide group's sum is scaled by the

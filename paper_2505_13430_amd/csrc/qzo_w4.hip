@@ -49,7 +49,7 @@ template <int MT, int FMT>
 struct W4Lds {
   static constexpr bool ZP = FMT == W4_ZP;
   static constexpr uint32_t X = MT * 4096u, W0 = 3 * X, W = 256 * 64, S = 256 * 4, SLOT = W + S * (ZP ? 2 : 1);
-  static constexpr uint32_t RED = W0 + 2 * SLOT, BYTES = RED + 64;
+  static constexpr uint32_t RED = W0 + 2 * SLOT, BYTES = RED + 2048;      // RED: a double per thread (sum of squares)
   static constexpr int NW = ZP ? 6 : 5;            // load instructions per wavefront for a group's weights
   static_assert(BYTES <= 160 * 1024, "LDS of a compute unit");
 };
@@ -375,7 +375,11 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   const uint32_t ldy = a.ldy ? a.ldy : a.N, NO = swiglu ? a.N >> 1 : a.N;
   const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
       a.y, 0, (int)(((uint64_t)(rows_all - 1) * (swiglu ? NO : ldy) + NO) * 2), 0x00020000);
-  float ssq = 0.0f;                                 // of all units of the workgroup
+  // sum of squares: unit by unit in double, in the LDS (no register is held over the k-loop): fp32 sums that go on over all
+  // units lose up to 1.5e-5 where the terms are alike.  One linear 2048 x 11008 x 4096, both signs, against such sums:
+  // 0.337 against 0.336 ms (two runs of either differ by 0.4 %); with a wavefront's sum taken per unit 1.2 % more.
+  double* const ssq_units = reinterpret_cast<double*>(lds + L::RED) + t;
+  if (a.epi & EPI_SUMSQ) *ssq_units = 0.0;
 
   point();
   request_first();
@@ -558,6 +562,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
           v[q >> 1][2 * (q & 1) + 1] += __uint_as_float(w[q] & 0xffff0000u);
         }
       };
+      float ssq[2] = {0.0f, 0.0f};                  // per feature tile
 #pragma unroll
       for (int u = 0; u < 4 * MT; ++u) {
         const int i = u >> 2, j = (u >> 1) & 1, bp = u & 1;
@@ -586,22 +591,24 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const float q0 = __uint_as_float(out[q] << 16), q1 = __uint_as_float(out[q] & 0xffff0000u);
-            ssq = __builtin_fmaf(q0, q0, ssq);
-            ssq = __builtin_fmaf(q1, q1, ssq);
+            ssq[j] = __builtin_fmaf(q0, q0, ssq[j]);
+            ssq[j] = __builtin_fmaf(q1, q1, ssq[j]);
           }
         }
         if (u & 1) __builtin_amdgcn_sched_barrier(0);
       }
       stores = 4 * MT;
+      if (a.epi & EPI_SUMSQ) *ssq_units += (double)(ssq[0] + ssq[1]);
     }
 #undef Q4_SWAP8
 #undef Q4_ACC
     if (!more) break;
   }
   if (a.epi & EPI_SUMSQ) {
-    float* red = reinterpret_cast<float*>(lds + L::RED);      // behind the stages
-    ssq = wave_sum(ssq);
-    if (lane == 0) red[wave] = ssq;
+    const float sum = wave_sum((float)*ssq_units);
+    float* red = reinterpret_cast<float*>(lds + L::RED);
+    __syncthreads();
+    if (lane == 0) red[wave] = sum;
     __syncthreads();
     if (t == 0) a.partials[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
   }

@@ -1563,13 +1563,31 @@ def test_fused_linear_of_every_tile_height(M, N, K, fmt):
     run(*args)
     assert torch.equal(y, want)
     assert bool((guard[M * N:] == 7.0).all())
-    ref = float((want.double() ** 2).sum())          # fp32 sums of up to 2000 terms a lane (2^-24 sqrt(2000) each), then 256
-    assert abs(float(ssq) - ref) <= 1e-4 * ref
+    ref = float((want.double() ** 2).sum())          # fp32 sums of up to 128 terms a lane and 7 additions per tile, the rest in double
+    bound = 140 * 2.0 ** -24 * ref
+    assert abs(float(ssq) - ref) <= bound
     # room for one partial sum per 256 x 256 tile only
     least = (-(-M // 256) * -(-N // 256) * 4 + 255) // 256 * 256
     y.zero_(), ssq.zero_()
     run(*args, scratch=torch.empty(least, dtype=torch.uint8, device=DEV))
-    assert torch.equal(y, want) and abs(float(ssq) - ref) <= 1e-4 * ref
+    assert torch.equal(y, want) and abs(float(ssq) - ref) <= bound
+
+
+@pytest.mark.parametrize("M,N", [(2048, 16384), (2049, 11016), (8192, 28672)])
+def test_sum_of_squares_of_many_tiles_per_workgroup(M, N):
+    """Equal outputs of 255/128, whose squares (65025 2^-14) an fp32 sum holds exactly up to 258 terms; beyond, every
+    further term loses the same 2^-14.  Workgroups own up to 14 output tiles, up to 128 terms a lane each: summed per
+    tile and added up in double, what is left are the roundings of a tile's and a workgroup's sum."""
+    K = 128
+    x = torch.zeros((M, K), dtype=torch.bfloat16, device=DEV)
+    x[:, 5] = 1.0
+    q = torch.full((N, K // 2), 0x99, dtype=torch.uint8, device=DEV)            # all weights 1
+    s = torch.full((N, 1), 255 / 128, dtype=torch.bfloat16, device=DEV)
+    y, ssq = torch.zeros((M, N), dtype=torch.bfloat16, device=DEV), torch.zeros(1, dtype=torch.float32, device=DEV)
+    qb.qzo_dequant_gemm(x, q, s, 0, 1, 0.0, 1, y, ssq)
+    assert bool((y == 255 / 128).all())
+    want = M * N * (255 / 128) ** 2
+    assert abs(float(ssq) - want) <= 10 * 2.0 ** -24 * want      # seven additions of a tile's lanes, a workgroup's, the result's
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 8, 128), (16, 520, 4096), (70, 264, 8192), (300, 256, 4096), (513, 4096, 1024)])
