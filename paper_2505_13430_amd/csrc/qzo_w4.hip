@@ -67,7 +67,11 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   typedef W4Lds<MT, FMT> L;
   constexpr bool ZP = FMT == W4_ZP, NF4 = FMT == W4_NF4;
   constexpr int SLOTS = 2 * MT;                    // MFMAs of a k-step
-  constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
+  // A byte offset beyond every buffer (each is below 2^31 bytes), and an index of scales whose byte offset (times 1, 2 or
+  // 4: zero-points, scales, pairs of NormalFloat-4 scales) is beyond theirs (at most N K / 32 < 2^27 bytes, and a group's
+  // offset on top of it does not wrap).
+  constexpr uint32_t OUT_OF_RANGE = 0x80000000u, SCALE_OUT_OF_RANGE = OUT_OF_RANGE >> 2, SCALE_BYTES = NF4 ? 4 : 2;
+  static_assert((uint64_t)SCALE_OUT_OF_RANGE * SCALE_BYTES + (1u << 27) < (1ull << 32) && SCALE_OUT_OF_RANGE >= (1u << 27));
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -87,7 +91,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   };
   const uint32_t rows_all = p.rows;
   const i32x4 rx = rsrc(a.x, (uint64_t)rows_all * K * 2), rw = rsrc(a.w, (uint64_t)a.N * (K >> 1));
-  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * G * (NF4 ? 4 : 2)), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * G);
+  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * G * SCALE_BYTES), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * G);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
 
   // a unit of work: K slice kslice of output tile (tile_m, tile_n), k-tiles kt0 .. kt0 + 2 ng - 1
@@ -130,8 +134,8 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   auto load_w = [&](int q, uint32_t g, uint32_t slot) Q4_INLINE {
     const uint32_t base = lds0 + L::W0 + slot;
     if (q < 4) Q4_DTL("buffer_load_dwordx4", rw, base + wave * 4096 + q * 1024, wo[q], g * 64);
-    else if (q == 4 && NF4) Q4_DTL("buffer_load_dword", rs, base + L::W + wave * 256, so * 4, g * 4);    // of two blocks
-    else if (q == 4) Q4_DTL("buffer_load_ushort", rs, base + L::W + wave * 256, so * 2, g * 2);
+    else if (q == 4 && NF4) Q4_DTL("buffer_load_dword", rs, base + L::W + wave * 256, so * SCALE_BYTES, g * SCALE_BYTES);    // of two blocks
+    else if (q == 4) Q4_DTL("buffer_load_ushort", rs, base + L::W + wave * 256, so * SCALE_BYTES, g * SCALE_BYTES);
     else Q4_DTL("buffer_load_ubyte", rz, base + L::W + L::S + wave * 256, so, g);
   };
   auto request_first = [&]() Q4_INLINE {       // groups 0 and 1, k-tiles 0, 1 and 2, in the order the k-loop goes on with
@@ -142,7 +146,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
     if (ng < 2) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) wo[q] = OUT_OF_RANGE;
-      so = OUT_OF_RANGE >> 1;
+      so = SCALE_OUT_OF_RANGE;
     }
 #pragma unroll
     for (int q = 0; q < L::NW; ++q) load_w(q, 1u, L::SLOT);
@@ -340,7 +344,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
     if (g + 2 >= ng) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) wo[q] = OUT_OF_RANGE;
-      so = OUT_OF_RANGE >> 1;
+      so = SCALE_OUT_OF_RANGE;
     }
     read_raw(2, slot); read_raw(3, slot);
     if (NF4) new_scale(1u);                         // of the second block, for k-tile 1
