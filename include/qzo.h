@@ -440,6 +440,18 @@ qzo_status qzo_debug_reduce_norm(const float* part_dev, uint32_t slices, uint32_
                                  int joined, void* y_dev, void* out_dev, float* xsum_dev, uint32_t* joined_out,
                                  void* stream);
 
+/* Inspection: the kernel that serves int4 and NormalFloat-4 linears of many tokens, K uncut, with the height of its output
+ * tiles given: *height (host) is 1 to 8, for 32 to 256 tokens, or 0 for the library's choice, which is stored there.  Operands as
+ * for qzo_dequant_gemm(_zp) with bf16 scales (zp_dev null: symmetric) or, with nf4, as for qzo_nf4_gemm.  passes = 2: x, y and
+ * resid hold 2 M rows, the second M of which take -sign.  epilogue: a sum of 1 (+ bias_dev, bf16 [N]), 2 (+ resid_dev,
+ * like y), 4 (ReLU), or one of 0, 16 (N = 2 F, F % 128 == 0: y [rows, F] = silu(first half) * second half), 32 (the rotary embedding of
+ * heads of rope_head_dim 64 or 128 on the first two thirds of y; rope_dev fp32 [rope_seq][head_dim / 2] pairs (cos, sin), row m
+ * of a pass at position m % rope_seq; heads of 128: N % 256 == 0).  Pointers 16-byte aligned, operands below 2^31 bytes. */
+qzo_status qzo_debug_fused_linear(const void* x_dev, const void* q_dev, const void* s_dev, const void* zp_dev, int nf4,
+                                  uint32_t row_base, uint32_t M, uint32_t passes, uint32_t N, uint32_t K, uint64_t seed, float eps,
+                                  int sign, uint32_t epilogue, const void* bias_dev, const void* resid_dev, const float* rope_dev,
+                                  uint32_t rope_seq, uint32_t rope_head_dim, uint32_t* height, void* y_dev, void* stream);
+
 /* Inspection: attention behind a K-split qkv projection.  part_dev fp32 [slices, batch * seq, 3 n_heads head_dim], added up in
  * order and rounded to bf16; rope_dev fp32 [seq][head_dim / 2] pairs (cos, sin); out_dev bf16 [batch * seq, n_heads head_dim].
  * joined = 0: by way of qkv_dev (bf16, part's rows and columns); 1: as the models do, the attention adding the slices up

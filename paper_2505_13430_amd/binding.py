@@ -30,7 +30,7 @@ EXPORTS = [
     "qzo_nf4_expand", "qzo_nf4_scratch_bytes", "qzo_nf4_gemm",
     "qzo_codebook_scratch_bytes", "qzo_codebook_gemm", "qzo_apply_update_channel",
     "qzo_debug_philox", "qzo_debug_normal_pairs", "qzo_debug_normals", "qzo_debug_dequant", "qzo_debug_dequant_zp",
-    "qzo_debug_forward", "qzo_debug_bf16_gemm", "qzo_debug_reduce_norm", "qzo_debug_attention_slices",
+    "qzo_debug_forward", "qzo_debug_bf16_gemm", "qzo_debug_reduce_norm", "qzo_debug_fused_linear", "qzo_debug_attention_slices",
     "qzo_debug_mfma_rate",
     "qzo_profile_begin", "qzo_profile_collect", "qzo_profile_stride",
     "qzo_last_error",
@@ -355,6 +355,19 @@ def qzo_debug_reduce_norm(part, bias, resid, gain, norm_bias, eps, joined, y, ou
                                        _ptr(resid), _ptr(gain), _ptr(norm_bias), C.c_float(eps), C.c_int(int(joined)),
                                        _ptr(y), _ptr(out), _ptr(xsum), C.byref(done), _stream(stream)))
     return bool(done.value)
+
+
+def qzo_debug_fused_linear(x, q, s, zp, row_base, seed, eps, sign, y, passes=1, nf4=False, epilogue=0, bias=None, resid=None,
+                           rope=None, head_dim=0, height=0, stream=None) -> int:
+    """Returns the height of the output tiles, in units of 32 tokens.  rope [seq, head_dim / 2, 2]."""
+    N, K, mt = q.shape[0], x.shape[1], C.c_uint32(height)
+    assert x.shape[0] % passes == 0 and y.shape == (x.shape[0], N // 2 if epilogue == 16 else N)
+    _check(lib().qzo_debug_fused_linear(_ptr(x), _ptr(q), _ptr(s), _ptr(zp), C.c_int(int(nf4)), C.c_uint32(row_base),
+                                        C.c_uint32(x.shape[0] // passes), C.c_uint32(passes), C.c_uint32(N), C.c_uint32(K),
+                                        C.c_uint64(seed & 0xFFFFFFFFFFFFFFFF), C.c_float(eps), C.c_int(sign), C.c_uint32(epilogue),
+                                        _ptr(bias), _ptr(resid), _ptr(rope), C.c_uint32(0 if rope is None else rope.shape[0]),
+                                        C.c_uint32(head_dim), C.byref(mt), _ptr(y), _stream(stream)))
+    return mt.value
 
 
 def qzo_debug_attention_slices(part, rope, n_heads, joined, qkv, out, stream=None) -> bool:

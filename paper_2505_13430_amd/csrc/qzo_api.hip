@@ -1363,6 +1363,38 @@ qzo_status qzo_debug_bf16_gemm(const void* x_dev, const void* w_dev, uint32_t M,
   return QZO_OK;
 }
 
+qzo_status qzo_debug_fused_linear(const void* x_dev, const void* q_dev, const void* s_dev, const void* zp_dev, int nf4,
+                                  uint32_t row_base, uint32_t M, uint32_t passes, uint32_t N, uint32_t K, uint64_t seed, float eps,
+                                  int sign, uint32_t epilogue, const void* bias_dev, const void* resid_dev, const float* rope_dev,
+                                  uint32_t rope_seq, uint32_t rope_head_dim, uint32_t* height, void* y_dev, void* stream) {
+  const bool swiglu = epilogue & EPI_SWIGLU, rope = epilogue & EPI_ROPE;
+  if (!x_dev || !q_dev || !s_dev || !y_dev || !height || ((epilogue & EPI_BIAS) && !bias_dev) ||
+      ((epilogue & EPI_RESIDUAL) && !resid_dev) || (rope && !rope_dev))
+    return fail(QZO_ERR_ARG, "null pointer");
+  if (!aligned16(x_dev) || !aligned16(q_dev) || !aligned16(s_dev) || !aligned16(zp_dev) || !aligned16(y_dev) || !aligned16(bias_dev) ||
+      !aligned16(resid_dev) || !aligned16(rope_dev))
+    return fail(QZO_ERR_ALIGN, "device pointer not 16-byte aligned");
+  if ((epilogue & ~(EPI_BIAS | EPI_RESIDUAL | EPI_RELU | EPI_SWIGLU | EPI_ROPE)) || ((swiglu || rope) && (epilogue & (epilogue - 1))) ||
+      (nf4 && zp_dev) || *height > 8 || passes < 1 || passes > 2 || !std::isfinite(eps))
+    return fail(QZO_ERR_ARG, "no such epilogue, format, tile height or number of passes");
+  if (M == 0 || N == 0 || N % 8 || K == 0 || K % 128 || (swiglu && N % 256) ||
+      (rope && (rope_seq == 0 || (rope_head_dim != 64 && rope_head_dim != 128) || N % (3 * rope_head_dim) || (rope_head_dim == 128 && N % 256))))
+    return fail(QZO_ERR_SHAPE, "need K % 128 == 0, N % 8 == 0, SwiGLU N % 256 == 0, rotary embedding heads of 64 or 128 (whole tiles of two)");
+  const uint64_t rows = (uint64_t)passes * M;
+  if (rows * K * 2 >= (1ull << 31) || (uint64_t)N * K / 2 >= (1ull << 31) || rows * N * 2 >= (1ull << 31))
+    return fail(QZO_ERR_SHAPE, "an operand exceeds 2^31 bytes");
+  GemmArgs g = {};
+  g.x = x_dev; g.w = q_dev; g.s = s_dev; g.zp = zp_dev; g.nf4 = nf4 != 0;
+  g.bias = bias_dev; g.resid = resid_dev; g.y = y_dev;
+  g.M = M; g.N = N; g.K = K; g.row_base = row_base; g.flip_row = passes == 2 ? M : 0;
+  g.seed_lo = (uint32_t)seed; g.seed_hi = (uint32_t)(seed >> 32); g.eps_signed = sign > 0 ? eps : -eps;
+  g.epi = epilogue; g.rope = rope_dev; g.rope_S = rope_seq; g.rope_dh = rope_head_dim;
+  const W4Plan p = w4_plan(M, g.flip_row, N, K, 1, 0, 0, *height);
+  QZO_HIP(launch_w4_tiles(g, p, (hipStream_t)stream));
+  *height = p.mt;
+  return QZO_OK;
+}
+
 qzo_status qzo_debug_attention_slices(const float* part_dev, uint32_t slices, uint32_t batch, uint32_t seq, uint32_t n_heads,
                                       uint32_t head_dim, const float* rope_dev, int joined, void* qkv_dev, void* out_dev,
                                       uint32_t* joined_out, void* stream) {

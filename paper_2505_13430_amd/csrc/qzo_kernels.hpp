@@ -99,8 +99,9 @@ struct W4Plan {
   uint32_t wgs;                      // persistent workgroups
 };
 // most_parts (0: no limit): room for one partial sum of squares per workgroup; never refused when it holds one per
-// 256 x 256 tile, rounded up to a multiple of 8.
-W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t ksplit, uint32_t kt_per, uint32_t most_parts);
+// 256 x 256 tile, rounded up to a multiple of 8.  height (0: by the rule): mt.
+W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t ksplit, uint32_t kt_per, uint32_t most_parts,
+               uint32_t height = 0);
 hipError_t launch_w4_tiles(const GemmArgs& a, const W4Plan& p, hipStream_t st);
 // Order of the rows of an expanded (bf16) weight matrix: natural; the fused-SwiGLU consumer's tile order;
 // the fused-RoPE consumer's order for heads of 128 features (within every 256 rows, so that a lane of the

@@ -643,12 +643,12 @@ void w4_launch(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
 // 16384, one round each); the matrix unit alone accounts for 0.13 us per tile of 32 tokens, what does not shrink with the
 // tile is the conversion of its 256 weight rows.
 W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t ksplit, uint32_t kt_per,
-               uint32_t most_parts) {
+               uint32_t most_parts, uint32_t height) {
   static const double K_TILE[9] = {0, 0.58, 0.71, 0.83, 0.95, 1.11, 1.26, 1.42, 1.58};
   const uint32_t cus = gemm_workgroups(1u << 20, 1u << 20);
   W4Plan best = {};
   double best_time = 0.0;
-  for (uint32_t mt = 8; mt > 0; --mt) {
+  for (uint32_t mt = height ? height : 8; mt > 0; --mt) {
     W4Plan p = {};
     p.mt = mt;
     p.ksplit = ksplit; p.kt_per = ksplit > 1 ? kt_per : K / BK;
@@ -660,7 +660,8 @@ W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t
     p.wgs = (uint32_t)std::min<uint64_t>(places, cus);
     if (most_parts && p.wgs > most_parts && mt < 8) continue;
     const double time = (double)((places + cus - 1) / cus) * (p.kt_per * K_TILE[mt] + 1.5 + 0.9 * mt);
-    if (mt == 8 || time < 0.98 * best_time) { best = p; best_time = time; }
+    if (!best.mt || time < 0.98 * best_time) { best = p; best_time = time; }
+    if (height) break;
   }
   return best;
 }

@@ -301,13 +301,16 @@ MANY = {"many_llama": dict(synth.SHAPES["tiny"], batch=9, seq=64),
 # Sequences as long as the benchmark's: the attention kernel's steady state (a key tile refills an LDS
 # buffer that was already read, loads run two tiles ahead, several 128-query blocks per sequence that
 # are dispatched last-first).  long_llama: head size 128, 512 positions = 8 key tiles, 4 query blocks;
-# long_opt: head size 64, 256 positions; long_ragged: 300 positions (a ragged last query block and key tile)
+# long_opt: head size 64, 256 positions; long_ragged: 300 positions (a ragged last query block and key tile);
+# long_heads64: the same with heads of 64.  Beyond 256 positions the qkv linear's epilogue rotates q and k
 LONG = {"long_llama": dict(arch="llama", n_layers=2, d_model=256, n_heads=2, d_ffn=512, vocab=520, max_seq=512,
                            batch=2, seq=512),
         "long_opt": dict(arch="opt", n_layers=2, d_model=256, n_heads=4, d_ffn=512, vocab=520, max_seq=256,
                          batch=3, seq=256),
         "long_ragged": dict(arch="llama", n_layers=1, d_model=256, n_heads=2, d_ffn=512, vocab=520, max_seq=320,
-                            batch=2, seq=300)}
+                            batch=2, seq=300),
+        "long_heads64": dict(arch="llama", n_layers=1, d_model=256, n_heads=4, d_ffn=512, vocab=520, max_seq=320,
+                             batch=2, seq=300)}
 FEW = {"few_llama": dict(synth.SHAPES["tiny"], batch=1, seq=24),        # 24 tokens: one token tile
        "few_opt": dict(synth.SHAPES["tiny_opt"], batch=2, seq=32)}      # 64 tokens: two token tiles
 
@@ -362,7 +365,7 @@ def _check_both_passes(oracle, om, tok, seed, eps, both):
                                        ("tiny+nf4", 4.0), ("tiny_opt+nf4", 4.0), ("sharp+nf4", 4.0),
                                        ("few_llama+nf4", 1.0),
                                        ("many_llama", 4.0), ("many_opt", 4.0), ("many_llama+zp", 4.0),
-                                       ("long_llama", 4.0), ("long_opt", 4.0), ("long_ragged", 4.0),
+                                       ("long_llama", 4.0), ("long_opt", 4.0), ("long_ragged", 4.0), ("long_heads64", 4.0),
                                        ("long_llama+zp", 1.0),
                                        # the checkpoints' own scale type (fp16), and a group index per column
                                        ("tiny+zp16", 1.0), ("tiny_opt+zp16", 1.0), ("few_llama+zp16", 1.0),
@@ -504,15 +507,15 @@ def test_stacked_passes_equal_separate_passes(oracle, name):
     dm.close()
 
 
-@pytest.mark.parametrize("name,batch,seq", [("tiny", 4, 64), ("long_opt+zp", 3, 256), ("long_ragged", 2, 300),
+@pytest.mark.parametrize("name,batch,seq", [("tiny", 4, 64), ("long_opt+zp", 3, 256), ("long_ragged", 2, 300), ("long_heads64", 2, 300),
                                             ("tiny_opt", 3, 40), ("tiny+zp", 3, 40)])
 def test_stacked_tile_passes_match_separate_passes(oracle, name, batch, seq):
     """Beyond the few-token kernel's range qzo_step runs both perturbed passes as one stacked forward
-    through the tile kernel, the second pass's token tiles with -eps; the second pass starts on a
-    256-row tile boundary, with padding rows in between when a pass is not a whole number of tiles
-    (600 -> 768, 120 -> 256 here).  The K split of a linear depends on the number of token tiles, so
-    the sums are ordered differently than in two separate passes: equal to within the 16-bit
-    activations' noise, not bit for bit."""
+    through the tile kernel, the second pass's token tiles with -eps; the second pass's rows start behind the
+    first one's, each pass ending in a ragged tile of its own (600 and 120 tokens here).  The K split of a linear
+    depends on the number of token tiles, so the sums are ordered differently than in two separate passes: equal
+    to within the 16-bit activations' noise, not bit for bit.  The hidden states of both passes against the oracle's,
+    element by element, at an eps that sets them apart."""
     base, asym = _case(name)
     shape = dict(base, batch=batch, seq=seq)
     om, dm = _models(oracle, shape, 1234, 4.0, **_variant_args(asym))
@@ -531,6 +534,8 @@ def test_stacked_tile_passes_match_separate_passes(oracle, name, batch, seq):
     want = oracle.qzo_step(om, tok, seed=21, eps=1e-3, eta=0.0, Cthr=100.0)
     assert abs(res["loss_plus"] - want["loss_plus"]) <= 2e-2 * want["loss_plus"]
     assert abs(res["loss_minus"] - want["loss_minus"]) <= 2e-2 * want["loss_minus"]
+    _, both = _step_hidden(dm, tokd, 21, 1e-2)
+    _check_both_passes(oracle, om, tok, 21, 1e-2, both)
     dm.close()
 
 
@@ -726,7 +731,7 @@ def test_real_width_one_layer_step(oracle, name, batch, seq, eta):
 @pytest.mark.parametrize("name,asym", [("llama-2-7b", False), ("llama-2-13b", False), ("opt-1.3b", False),
                                        ("llama-2-7b", True)])
 def test_real_width_one_layer_expanded_route(oracle, name, asym):
-    """The route the benchmark's linears take (perturbed scales of the whole arena in one launch, the
+    """The expand-then-multiply route (on request: perturbed scales of the whole arena in one launch, the
     perturbed bf16 matrix written out, plain GEMM), at real widths: 86 / 108 groups per row in the
     down projection, the gate/up row interleave at 11008 / 13824 features, K = 11008 / 13824 in the
     plain GEMM, two token tiles (272 tokens).  One layer, a short vocabulary for the Llama shapes."""
@@ -766,9 +771,9 @@ def test_real_width_one_layer_expanded_route(oracle, name, asym):
 @pytest.mark.parametrize("name,asym", [("llama-2-7b", False), ("opt-1.3b", True)])
 def test_real_width_one_layer_stacked_tile_step(oracle, name, asym):
     """The step of the paper's batch regime at real widths: 272 tokens per pass on the default route,
-    i.e. both passes in one forward through the fused tile kernel (the second pass from row 512 on, 240
-    padding rows), K split of the 4096- / 2048-wide projections, RoPE inside the attention kernel.
-    Losses, and the scales after the update, against the oracle."""
+    i.e. both passes in one forward through the fused tile kernel (the second pass from row 272 on, no
+    padding), K split of the 4096- / 2048-wide projections, RoPE inside the attention kernel.
+    Losses, both passes' hidden states, and the scales after the update, against the oracle."""
     shape = dict(synth.SHAPES[name], n_layers=1, batch=2, seq=136, max_seq=136)
     if shape["arch"] == "llama":
         shape["vocab"] = 1000
@@ -776,6 +781,8 @@ def test_real_width_one_layer_stacked_tile_step(oracle, name, asym):
     tok = synth.tokens(shape, 78)
     eta = 1e-5 if name == "opt-1.3b" else 1e-7
     ref = oracle.qzo_step(om, tok, seed=3, eps=1e-3, eta=eta, Cthr=100.0)
+    _, both = _step_hidden(dm, _dev(tok), 3, 1e-2)
+    _check_both_passes(oracle, om, tok, 3, 1e-2, both)
     res = qb.read_step_result(dm.step(_dev(tok), 3, 1e-3, eta, 100.0))
     assert res["status"] == 0
     for k in ("loss_plus", "loss_minus"):
@@ -1302,14 +1309,17 @@ def test_nf4_linear_matches_oracle(oracle, M, N, K):
         qb.qzo_nf4_gemm(_dev(x, torch.bfloat16), _dev(qp), _dev(s, torch.bfloat16), 11, 31, 1e-3, 1, y, scratch[:256])
 
 
-@pytest.mark.parametrize("name", ["many_llama", "many_opt+zp", "long_llama", "long_llama+zp"])
+@pytest.mark.parametrize("name", ["many_llama", "many_opt+zp", "long_llama", "long_llama+zp", "long_ragged", "long_ragged+zp",
+                                  "long_heads64", "long_heads64+zp"])
 def test_int4_expand_then_multiply_equals_the_fused_path(oracle, name):
     """Both routes form the same bf16 weights (one rounding of scale x integer) and accumulate each
     output over k in the same order, so losses and hidden states agree bit for bit.  (d_ffn = 256 keeps
     every K at 256, too short for the fused kernel's split-K, which would change the order.)
-    On the expanded route the rotary embedding is applied by the qkv GEMM's epilogue (heads of 64 in
-    many_llama, heads of 128 with the permuted weight rows in long_llama), on the fused route by its own
-    kernel: the same arithmetic on the same bf16 values, so this equality covers it too."""
+    The rotary embedding is applied by the expanded route's qkv GEMM (heads of 64 in many_llama and long_heads64,
+    heads of 128 with the permuted weight rows in the others); the fused route leaves it to the attention kernel up to
+    256 positions (many_llama) and applies it in its own kernel's epilogue beyond: the same arithmetic on the
+    same bf16 values, so this equality covers it too.  And both passes of a step, which the fused route stacks, the
+    second one's tiles starting wherever the first one's rows end: the expanded route's two single passes."""
     base, asym = _case(name)
     shape = dict(base, d_ffn=256)
     om, dm = _models(oracle, shape, 1234, 4.0, **_variant_args(asym))
@@ -1323,8 +1333,14 @@ def test_int4_expand_then_multiply_equals_the_fused_path(oracle, name):
         loss = torch.zeros(1, dtype=torch.float32, device=DEV)
         qb.qzo_debug_forward(dm.handle, _dev(tok), 9, 1e-3, -1, dm.workspace(B, S), loss, hid)
         outs.append((float(loss.item()), hid.float().cpu().numpy()))
+        if mode == 2:
+            single = [_hidden(dm, _dev(tok), 9, 1e-3, sign) for sign in (1, -1)]
+            losses = [float(dm.forward_loss(_dev(tok), 9, 1e-3, sign).item()) for sign in (1, -1)]
     assert outs[0][0] == outs[1][0]
     assert np.array_equal(outs[0][1], outs[1][1])
+    res, both = _step_hidden(dm, _dev(tok), 9, 1e-3)
+    assert np.array_equal(both[0], single[0]) and np.array_equal(both[1], single[1])
+    assert [res["loss_plus"], res["loss_minus"]] == losses
     # the expanded route keeps one linear in bf16 and every perturbed scale in fp32 in the workspace
     # (the fused route's workspace is not smaller any more: at this token count its step stacks both passes)
     n_scales = qb.qzo_model_scale_count(dict(shape, quant=2) if asym is True else shape)
@@ -1334,8 +1350,8 @@ def test_int4_expand_then_multiply_equals_the_fused_path(oracle, name):
 
 
 def test_full_size_token_count_sampled_sequence_matches_oracle(oracle):
-    """The benchmark's launch configuration (16 x 512 tokens, the default route: expansion, plain GEMM at
-    32 token tiles, RoPE in the qkv epilogue at positions up to 511, attention over 8 key tiles) through
+    """The benchmark's launch configuration (16 x 512 tokens, the default route: the fused kernel at 32 or more
+    token tiles, RoPE in its qkv epilogue at positions up to 511, attention over 8 key tiles) through
     one decoder layer at Llama-2-7B widths, checked on a sample the oracle can afford: a decoder treats
     the sequences of a batch independently, so the oracle runs sequence 11 alone and its final hidden
     states are compared with rows 11*512 .. 12*512-1 of the batch's."""
@@ -1460,11 +1476,11 @@ def _walk_case(oracle, shape, n_seq, S, b):
 
 def test_full_size_token_count_one_layer_routes_agree_bit_for_bit():
     """The benchmark's token count (16 x 512) through one decoder layer at Llama-2-7B widths, once on the
-    route the benchmark times (perturbed scales of the arena, expanded bf16 weights, plain GEMM with the
+    expand-then-multiply route (perturbed scales of the arena, expanded bf16 weights, plain GEMM with the
     rotary embedding in the qkv epilogue: 6 / 2 / 10.75 / 2 rounds of output tiles per CU) and once on
-    the fused dequantizing GEMM with the separate RoPE kernel: the same bf16 weights, the same order of
-    the sums, so loss and final hidden states agree bit for bit.  (The fused route is the one that the
-    smaller cases compare with the oracle element by element.)"""
+    the fused dequantizing GEMM, the one that the benchmark times, with the rotary embedding in its own epilogue: the same
+    bf16 weights, the same order of the sums, so loss and final hidden states agree bit for bit.  (The fused route is
+    the one that the smaller cases compare with the oracle element by element.)"""
     shape = dict(synth.SHAPES["llama-2-7b"], n_layers=1, vocab=2000)
     dm = DeviceModel.synthetic(shape, seed=5, device=DEV)
     B, S = shape["batch"], shape["seq"]
@@ -1534,18 +1550,19 @@ def test_activation_reordering_matrix_bit_exact_and_linear(oracle, M, N, K):
 
 
 @pytest.mark.parametrize("fmt", ["int4", "zp", "nf4"])
-@pytest.mark.parametrize("M,N,K", [(144, 8, 256), (129, 13520, 384), (257, 13216, 384), (389, 13096, 128),
-                                   (641, 10792, 128), (645, 13304, 256), (774, 13120, 256), (899, 13296, 128),
-                                   (2049, 11016, 256)])
-def test_fused_linear_of_every_tile_height(M, N, K, fmt):
-    """The fused kernel at sizes whose rule picks tiles of 32, 64, .. 256 tokens (one each, then several tiles per
-    workgroup), last tiles ragged in tokens and features: bit for bit the expanded weights through the plain GEMM."""
+@pytest.mark.parametrize("M,N,K,height", [(144, 8, 256, 1), (129, 13520, 384, 2), (257, 13216, 384, 3), (389, 13096, 128, 4),
+                                          (641, 10792, 128, 5), (645, 13304, 256, 6), (774, 13120, 256, 7), (899, 13296, 128, 8),
+                                          (2049, 11016, 256, 6)])
+def test_fused_linear_of_every_tile_height(M, N, K, height, fmt):
+    """The fused kernel at sizes whose rule picks tiles of 32, 64, .. 256 tokens (one each per workgroup, then several),
+    last tiles ragged in tokens and features: bit for bit the expanded weights through the plain GEMM."""
     rng = np.random.default_rng(M + N)
     x = _dev(rng.standard_normal((M, K), dtype=np.float32), torch.bfloat16)
     q = _dev(rng.integers(0, 256, (N, K // 2), dtype=np.uint8))
     s = _dev(rng.uniform(0.002, 0.02, (N, K // (64 if fmt == "nf4" else 128))).astype(np.float32), torch.bfloat16)
     z = _dev(rng.integers(0, 16, (N, K // 128), dtype=np.uint8)) if fmt == "zp" else None
     want = torch.zeros((M, N), dtype=torch.bfloat16, device=DEV)
+    assert qb.qzo_debug_fused_linear(x, q, s, z, 11, 31, 1e-3, -1, torch.empty_like(want), nf4=fmt == "nf4") == height
     guard = torch.full(((M + 32) * N,), 7.0, dtype=torch.bfloat16, device=DEV)
     y, ssq = guard[:M * N].view(M, N), torch.zeros(1, dtype=torch.float32, device=DEV)
     if fmt == "nf4":
@@ -1571,6 +1588,72 @@ def test_fused_linear_of_every_tile_height(M, N, K, fmt):
     y.zero_(), ssq.zero_()
     run(*args, scratch=torch.empty(least, dtype=torch.uint8, device=DEV))
     assert torch.equal(y, want) and abs(float(ssq) - ref) <= bound
+
+
+@pytest.mark.parametrize("fmt", ["int4", "zp", "nf4"])
+@pytest.mark.parametrize("epilogue,head_dim", [(1 | 4, 0), (2, 0), (1 | 2, 0), (16, 0), (32, 64), (32, 128)],
+                         ids=["bias_relu", "residual", "bias_residual", "swiglu", "rope64", "rope128"])
+def test_fused_linear_epilogues_at_every_tile_height(epilogue, head_dim, fmt):
+    """Every epilogue of the fused kernel in tiles of 32 to 256 tokens, of both passes of a step (1029 tokens: the last
+    tile of each is ragged at every height, and workgroups own several tiles), against the product in 64 bits: fp32 sums
+    of 384 terms (2^-20 of the sum of their sizes) and one rounding to bf16 (two under the rotary embedding).  The same bits
+    at every height."""
+    M, N, K, S = 1029, 6912, 384, 100
+    rng = np.random.default_rng(epilogue + head_dim)
+    x = _dev(rng.standard_normal((2 * M, K), dtype=np.float32), torch.bfloat16)
+    q = _dev(rng.integers(0, 256, (N, K // 2), dtype=np.uint8))
+    s = _dev(rng.uniform(0.01, 0.05, (N, K // (64 if fmt == "nf4" else 128))).astype(np.float32), torch.bfloat16)
+    if fmt == "nf4":
+        s = (s.float() * 4).to(torch.bfloat16)
+    z = _dev(rng.integers(0, 16, (N, K // 128), dtype=np.uint8)) if fmt == "zp" else None
+    bias = _dev(rng.standard_normal(N, dtype=np.float32), torch.bfloat16) if epilogue & 1 else None
+    resid = _dev(rng.standard_normal((2 * M, N), dtype=np.float32), torch.bfloat16) if epilogue & 2 else None
+    ang = torch.outer(torch.arange(S, dtype=torch.float64), 1e4 ** (-torch.arange(head_dim // 2, dtype=torch.float64) * 2 / max(head_dim, 1)))
+    rope = torch.stack([ang.cos(), ang.sin()], 2).float().to(DEV) if head_dim else None
+    want, size = [], []
+    for p, sign in enumerate((1, -1)):
+        w = torch.zeros((N, K), dtype=torch.bfloat16, device=DEV)
+        if fmt == "nf4":
+            qb.qzo_nf4_expand(q, s, 11, 31, 1e-2, sign, torch.zeros((N, K // 64), dtype=torch.float32, device=DEV), w)
+        elif fmt == "zp":
+            qb.qzo_debug_dequant_zp(q, s, z, 11, 31, 1e-2, sign, w)
+        else:
+            qb.qzo_debug_dequant(q, s, 11, 31, 1e-2, sign, w)
+        xp = x[p * M:(p + 1) * M].double()
+        want.append(xp @ w.double().T), size.append(xp.abs() @ w.double().abs().T)
+    want, err = torch.cat(want), torch.cat(size) * 2.0 ** -20
+    if epilogue & 1:
+        want, err = want + bias.double(), err + 2.0 ** -23 * bias.double().abs()
+    if epilogue & 2:
+        want, err = want + resid.double(), err + 2.0 ** -23 * resid.double().abs()
+    if epilogue & 4:
+        want = want.clamp_min(0)
+    if epilogue == 16:
+        (g, u), (eg, eu) = want.chunk(2, 1), err.chunk(2, 1)
+        silu = g * torch.sigmoid(g)                       # its slope is at most 1.1; device exp2 and reciprocal: 2^-18
+        want, err = silu * u, 1.1 * eg * (u.abs() + eu) + silu.abs() * eu + 2.0 ** -18 * (silu * u).abs()
+    if head_dim:
+        err[:, :2 * N // 3] += 2.0 ** -8 * want[:, :2 * N // 3].abs()          # rounded before the rotation
+        v, e = (a[:, :2 * N // 3].reshape(2 * M, -1, 2, head_dim // 2) for a in (want, err))
+        pos = torch.arange(M, device=DEV).repeat(2) % S
+        c, d = (rope.double()[pos, :, i][:, None, :] for i in (0, 1))
+        turned = torch.stack([v[:, :, 0] * c - v[:, :, 1] * d, v[:, :, 1] * c + v[:, :, 0] * d], 2)
+        off = torch.stack([e[:, :, 0] * c.abs() + e[:, :, 1] * d.abs(), e[:, :, 1] * c.abs() + e[:, :, 0] * d.abs()], 2)
+        want[:, :2 * N // 3], err[:, :2 * N // 3] = turned.reshape(2 * M, -1), off.reshape(2 * M, -1)
+    bound, first = err + 2.0 ** -8 * want.abs(), None
+    for height in range(8, 0, -1):
+        guard = torch.full(((2 * M + 32) * want.shape[1],), 7.0, dtype=torch.bfloat16, device=DEV)
+        y = guard[:want.numel()].view(want.shape)
+        if epilogue & 2:
+            y.copy_(resid)                                # in place, as the models do it
+        used = qb.qzo_debug_fused_linear(x, q, s, z, 11, 31, 1e-2, 1, y, passes=2, nf4=fmt == "nf4", epilogue=epilogue, bias=bias,
+                                         resid=y if epilogue & 2 else None, rope=rope, head_dim=head_dim, height=height)
+        assert used == height and bool((guard[want.numel():] == 7.0).all())
+        assert bool(((y.double() - want).abs() <= bound).all()), (height, float(((y.double() - want).abs() / bound).max()))
+        first = y if first is None else first
+        assert torch.equal(y, first)
+    other = torch.cat([want[M:], want[:M]])               # rows of the other pass
+    assert float(((first.double() - other).abs() > bound).double().mean()) > 0.5 or epilogue & 4
 
 
 @pytest.mark.parametrize("M,N", [(2048, 16384), (2049, 11016), (8192, 28672)])
@@ -1609,12 +1692,15 @@ def test_nf4_linear_cut_along_k(M, N, K):
 
 
 @pytest.mark.parametrize("arch,F,batch,seq", [("llama", 8320, 1, 70), ("llama", 8320, 3, 51), ("llama", 8320, 1, 300),
+                                              ("llama22", 4352, 1, 300), ("llama44", 4352, 1, 300),
                                               ("opt", 12416, 8, 50), ("opt", 12416, 1, 96)])
 def test_nf4_tile_kernel_weights_are_the_expanded_matrix(arch, F, batch, seq):
     """Wide NormalFloat-4 layers from 65 tokens on run in the tile kernel: both passes' hidden states against the same
     sequences in a batch on the expanded matrix, bounded by what another order of the fp32 sums alone does (as for
-    the kernel that serves narrow layers and few tokens, see test_nf4_weights_are_the_same_at_any_token_count)."""
-    shape = dict(WIDE_LLAMA if arch == "llama" else WIDE_OPT, n_layers=1, d_ffn=F, batch=-(-513 // seq), seq=seq, max_seq=512)
+    the kernel that serves narrow layers and few tokens, see test_nf4_weights_are_the_same_at_any_token_count).  llama22 and
+    llama44: 2816 features in heads of 128 and 64, where the qkv linear is not cut along K and its epilogue rotates."""
+    base = {"llama": WIDE_LLAMA, "opt": WIDE_OPT}.get(arch) or dict(WIDE_LLAMA, d_model=2816, n_heads=int(arch[5:]))
+    shape = dict(base, n_layers=1, d_ffn=F, batch=-(-513 // seq), seq=seq, max_seq=512)
     dm = DeviceModel.synthetic(shape, 1234, DEV, nf4=True)
     dm.scales.mul_(0.3)
     tok = synth.tokens(shape, 5678)

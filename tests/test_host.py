@@ -106,6 +106,22 @@ def test_config_errors_are_reported():
                              C.c_float(1), None, C.c_uint64(0), None, None) == qb.QZO_ERR_ARG
 
 
+@pytest.mark.parametrize("over,status", [
+    (dict(x=None), qb.QZO_ERR_ARG), (dict(epi=1), qb.QZO_ERR_ARG), (dict(epi=32, rope=None), qb.QZO_ERR_ARG), (dict(y=24), qb.QZO_ERR_ALIGN),
+    (dict(height=9), qb.QZO_ERR_ARG), (dict(passes=3), qb.QZO_ERR_ARG), (dict(epi=8), qb.QZO_ERR_ARG), (dict(epi=17, bias=16), qb.QZO_ERR_ARG),
+    (dict(nf4=1, zp=16), qb.QZO_ERR_ARG), (dict(K=192), qb.QZO_ERR_SHAPE), (dict(N=388), qb.QZO_ERR_SHAPE), (dict(epi=16), qb.QZO_ERR_SHAPE),
+    (dict(epi=32, N=256, dh=64), qb.QZO_ERR_SHAPE), (dict(epi=32, dh=128), qb.QZO_ERR_SHAPE), (dict(epi=32, dh=32), qb.QZO_ERR_SHAPE),
+    (dict(epi=32, dh=64, S=0), qb.QZO_ERR_SHAPE), (dict(M=1 << 22), qb.QZO_ERR_SHAPE)])
+def test_inspection_of_the_fused_linear_refuses(over, status):
+    v = dict(x=16, zp=0, nf4=0, M=64, passes=1, N=384, K=128, epi=0, bias=0, rope=16, S=8, dh=128, height=0, y=16)
+    v.update(over)
+    p, u = (lambda k: C.c_void_p(v[k] or None)), (lambda k: C.c_uint32(v[k]))
+    height = C.c_uint32(v["height"])
+    assert qb.lib().qzo_debug_fused_linear(p("x"), C.c_void_p(16), C.c_void_p(16), p("zp"), C.c_int(v["nf4"]), C.c_uint32(0), u("M"),
+                                           u("passes"), u("N"), u("K"), C.c_uint64(1), C.c_float(0), C.c_int(1), u("epi"), p("bias"),
+                                           None, p("rope"), u("S"), u("dh"), C.byref(height), p("y"), None) == status
+
+
 def test_counts_of_the_other_formats(oracle):
     tiny = synth.SHAPES["tiny"]
     n0 = qb.qzo_model_scale_count(tiny)
