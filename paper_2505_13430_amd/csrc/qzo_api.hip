@@ -247,7 +247,8 @@ bool mid_route(const qzo_model* m, uint64_t M1) {
 
 // One pass on its own (qzo_forward_loss, joint mode): the few-token kernel is the faster one over its whole range
 // (7B widths, 33 / 57 tokens: 3.34 / 3.65 ms a pass against 3.60 / 3.92; OPT-1.3B, 57: 1.88 against 2.22).
-// NormalFloat-4 has mid_gemm_kernel only (16 tokens: 3.9 ms a pass, expanded 8.1).
+// NormalFloat-4 has no few-token kernel: where mid_route holds, mid_gemm_kernel serves its single passes, too (16 tokens: 3.9 ms
+// a pass, expanded 8.1).
 bool mid_single_pass(const qzo_model* m, uint64_t M1) { return m->cfg.quant == 3 || M1 > SKINNY_MAX_M; }
 
 // Row at which the second pass of a stacked forward starts: behind the first one's, on a multiple of 256 where the plain
@@ -536,7 +537,7 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       g.dual = n_pass == 2;
       g.row_base = l * m->rows_per_layer + m->lin[li].row_base;
       g.seed_lo = seed_lo; g.seed_hi = seed_hi; g.eps_signed = eps_signed;
-      g.epi = epi & ~EPI_ROPE;                // a request: only the plain GEMM of the int4 expansion route serves it
+      g.epi = epi & ~EPI_ROPE;                // a request: granted below where the kernel's epilogue can rotate
       g.s_fp16 = c.scale_fp16;
       g.skinny_ws = mid_ws ? nullptr : w.skinny;
       g.split_ws = w.split;

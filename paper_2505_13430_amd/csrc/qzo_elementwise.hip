@@ -453,7 +453,8 @@ hipError_t launch_repack_kmajor(const void* qweight, const void* qzeros, const v
 // -------------------------------------------------------- embedding -------
 // Row m belongs to pass m / pass_stride and is row r = m % pass_stride of it: it embeds tok[r] at
 // position r % S, or zeros when r >= tok_rows (rows that pad a pass to a whole number of GEMM tiles).
-// Workgroups from embed_wgs on write the table of rotary angles, (cos, sin) of [S positions][half pairs].
+// Workgroups from embed_wgs on write the table of rotary angles: table[t][i] = (cos, sin)(t * theta^(-2i/dh)), t < S,
+// i < half = dh/2, evaluated in double.
 __global__ void embed_kernel(const int32_t* __restrict__ tok, uint32_t tok_rows, uint32_t pass_stride,
                              const bf16_t* __restrict__ te,
                              const bf16_t* __restrict__ pe, uint32_t M, uint32_t S, uint32_t d,
@@ -545,7 +546,6 @@ hipError_t launch_layernorm(const void* x, const void* gain, const void* bias, u
 }
 
 // ------------------------------------------------------------- RoPE -------
-// table[t][i] = (cos, sin)(t * theta^(-2i/dh)), i < dh/2, evaluated in double.
 // rotate-half pairing (i, i+dh/2) on the q and k thirds of qkv [M, 3d], in place; row m is at
 // position (m % pass_stride) % S.
 __global__ void rope_kernel(bf16_t* __restrict__ qkv, const float2* __restrict__ table, uint32_t M,

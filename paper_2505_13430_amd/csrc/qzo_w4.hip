@@ -19,9 +19,9 @@
 // two, one exchange between the wavefront's halves hands the perturbed scales to both.
 //
 // Per k-tile at MT = 8 on a full chip, against the kernel this one replaces (eight wavefronts in alternating phases,
-// weight tile in the LDS), same board: 1.79 -> 1.58 us (1203 -> 1358 TFLOP/s), with zero-points 1.95 -> 1.64.  The MFMAs
-// are 1.15 us of that at the clock the board grants on such data.  Timing-only variants (board with 1.69): loads not
-// issued 1.59; noise left out -0.02 to -0.05; fragment reads left out -0.08.
+// weight tile in the LDS), same board: 1.79 -> 1.58 us (1203 -> 1358 TFLOP/s), with zero-points 1.95 -> 1.64.  Counters
+// (8192 x 12288 x 4096): 2990 cycles a k-tile at 1.66 GHz, 2048 of them MFMAs; wavefronts wait 31 % of them.  Timing-only
+// variants (board with 1.69): loads not issued 1.59; noise left out -0.02 to -0.05; fragment reads left out -0.08.
 // Lower tiles serve the sizes whose rounds of 256-token tiles are badly filled (w4_plan): steps at 7B widths, before ->
 // after: 4 x 33 tokens 9.4 -> 6.6 ms, 8 x 200 with zero-points 45.2 -> 39.4, 16 x 64 28.2 -> 25.8; OPT-1.3B 16 x 256
 // 21.8 -> 19.4; one linear 2048 x 11008 x 4096, both signs, 0.432 -> 0.336; the tests' smallest model 0.180 -> 0.119.  With a

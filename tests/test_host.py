@@ -51,10 +51,10 @@ def _device_code(tmp_path):
     return kernels
 
 
-def _scalars(args):
+def _scalars(args, file="s"):
     out = set()
     for a in args:
-        for m in re.finditer(r"(?<![a-z0-9_])s(?:(\d+)|\[(\d+):(\d+)\])", a):
+        for m in re.finditer(rf"(?<![a-z0-9_]){file}(?:(\d+)|\[(\d+):(\d+)\])", a):
             out |= set(range(int(m[2]), int(m[3]) + 1)) if m[2] else {int(m[1])}
     return out
 
@@ -77,6 +77,33 @@ def test_wait_states_of_direct_to_lds_loads(tmp_path):
                 states += int(operands[0]) + 1 if before == "s_nop" else 1
                 j -= 1
     assert loads > 1000
+
+
+def test_wait_states_of_accumulator_reads(tmp_path):
+    """Kernels that hold accumulators in AGPRs read them with asm: twelve wait states behind a matrix instruction of eight
+    passes that wrote the register (all that the library uses on AGPRs), and two between a vector instruction, asm among
+    them, and the exchange between a wavefront's halves that reads its result."""
+    def since(kernel, i, most, writes):
+        states = 0
+        for before, operands in reversed(kernel[max(0, i - most):i]):
+            if writes(before, operands):
+                return states
+            states += int(operands[0]) + 1 if before == "s_nop" else 1
+            if states >= most:
+                break
+        return most
+
+    reads = swaps = 0
+    for kernel in _device_code(tmp_path):
+        for i, (op, args) in enumerate(kernel):
+            if op.startswith("v_accvgpr_read"):
+                acc, reads = _scalars(args[1:2], "a"), reads + 1
+                assert since(kernel, i, 12, lambda o, a: "mfma" in o and _scalars(a[:1], "a") & acc) == 12, (i, args)
+            elif op.startswith("v_permlane32_swap"):
+                both, swaps = _scalars(args[:2], "v"), swaps + 1
+                assert since(kernel, i, 2, lambda o, a: o.startswith("v_") and _scalars(a[:1], "v") & both) == 2, (i, args)
+        assert not any("mfma" in op and "32x32x16" not in op and _scalars(args[:1], "a") for op, args in kernel)
+    assert reads > 1000 and swaps > 1000
 
 
 def test_scale_count_is_table2(oracle):
