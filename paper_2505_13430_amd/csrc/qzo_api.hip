@@ -340,12 +340,15 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
     off += up256(bytes);
     return p;
   };
+  // rows of the norm output and of the MLP's activation: whole tiles where the few-token kernel takes them packed
+  const bool few = M1 <= SKINNY_MAX_M && int4 && !c.act_order;
+  const uint64_t Mp = few ? std::max<uint64_t>({M, few_pack((uint32_t)M1, false).rows, few_pack((uint32_t)M1, stack).rows}) : M;
   w.h = take(M * d * 2);
-  w.a = take(M * d * 2);
+  w.a = take(Mp * d * 2);
   w.qkv = take(M * 3 * d * 2);
   w.att = take(M * d * 2);
-  w.ff = take(c.arch == 0 ? 0 : M * F * 2);     // Llama: SwiGLU is folded into the gate/up GEMM
-  w.act = take(c.arch == 0 ? M * F * 2 : 0);
+  w.ff = take(c.arch == 0 ? 0 : Mp * F * 2);    // Llama: SwiGLU is folded into the gate/up GEMM
+  w.act = take(c.arch == 0 ? Mp * F * 2 : 0);
   w.ce_part = (float*)take(M * n_slices * 8);
   w.tgt = (float*)take(M * 4);
   w.rowloss = (float*)take(M * 4);
@@ -353,14 +356,14 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
   // few-token path of the int4 GEMM: fp32 partial sums of the K slices of the largest linear
   uint64_t sk = 0;
   const bool mid = mid_route(m, M1), nf4_expanded = c.quant == 3 && !mid && !nf4_tile_route(m, M1);
-  if (M1 <= SKINNY_MAX_M && int4 && !c.act_order)
+  if (few)
     for (int i = 0; i < 4; ++i)
       sk = std::max<uint64_t>(sk, skinny_ws_floats((uint32_t)(mid ? M1 : M), m->lin[i].N, m->lin[i].K));
   w.skinny = (float*)take(sk * 4);
   if (sk == 0) w.skinny = nullptr;
   const bool sums = sk || (mid && int4);        // NormalFloat-4 needs none
-  w.xs_a = sums ? (float*)take((d / 128) * M * 4) : nullptr;
-  w.xs_act = sums ? (float*)take((F / 128) * M * 4) : nullptr;
+  w.xs_a = sums ? (float*)take((d / 128) * Mp * 4) : nullptr;
+  w.xs_act = sums ? (float*)take((F / 128) * Mp * 4) : nullptr;
   uint64_t mw = 0;
   if (mid)
     for (int i = 0; i < 4; ++i)
@@ -504,15 +507,17 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
   float* const mid_ws = n_pass == 2 || mid_single_pass(m, M1) ? w.mid : nullptr;
   const bool few = (mid_ws && c.quant != 3) || (w.skinny && M1 <= SKINNY_MAX_M && (c.quant == 0 || c.quant == 2) && !c.act_order);
   float* const xs_a = few ? w.xs_a : nullptr;
+  // layout of the norms' outputs and the MLP's activation
+  const XPack pack = few && !mid_ws && !w.wexp ? few_pack(M1, n_pass == 2) : XPack{};
   // the norm that follows a linear into the residual stream: taken over by the linear's slice reduction where it has one
   NextNorm nn = {};
   auto norm = [&](const void* gain, const void* nbias, float* xs) {
     if (nn.done) { nn.done = false; return hipSuccess; }
-    return nbias ? launch_layernorm(w.h, gain, nbias, M, d, c.norm_eps, w.a, st, xs)
-                 : launch_rmsnorm(w.h, gain, M, d, c.norm_eps, w.a, st, xs);
+    return nbias ? launch_layernorm(w.h, gain, nbias, M, d, c.norm_eps, w.a, st, xs, xs ? pack : XPack{})
+                 : launch_rmsnorm(w.h, gain, M, d, c.norm_eps, w.a, st, xs, xs ? pack : XPack{});
   };
   auto before = [&](const void* gain, const void* nbias, float* xs) {
-    nn = {gain, nbias, c.norm_eps, w.a, xs, false};
+    nn = {gain, nbias, c.norm_eps, w.a, xs, xs ? pack : XPack{}, false};
   };
   for (uint32_t l = 0; l < c.n_layers; ++l) {
     const qzo_buf* T = &m->T[m->first_layer_tensor + (size_t)l * m->tensors_per_layer];
@@ -548,6 +553,8 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       if (few) {     // the few-token kernel takes the block sums of its input from the kernel that wrote it
         g.xsum = (li == 0 || li == 2) ? w.xs_a : (li == 3 ? w.xs_act : nullptr);
         g.xsum_out = li == 2 ? w.xs_act : nullptr;
+        if (li != 1) g.xp = pack;
+        if (li == 2) g.yp = pack;
         if (mid_ws && li == 1 && c.quant != 3) {      // the attention output's block sums, where the norm's were
           hipError_t e = launch_block_sums(x, M, g.K, w.xs_a, st);
           if (e != hipSuccess) return e;
@@ -1427,7 +1434,7 @@ qzo_status qzo_debug_reduce_norm(const float* part_dev, uint32_t slices, uint32_
   if (M == 0 || N == 0 || N % 128 || slices == 0 || (uint64_t)slices * M * N >= (1ull << 31))
     return fail(QZO_ERR_SHAPE, "need M >= 1, N a positive multiple of 128, slices >= 1, slices*M*N below 2^31");
   hipStream_t st = (hipStream_t)stream;
-  NextNorm nn = {gain_dev, norm_bias_dev, eps, out_dev, xsum_dev, false};
+  NextNorm nn = {gain_dev, norm_bias_dev, eps, out_dev, xsum_dev, XPack{}, false};
   GemmArgs g = {};
   g.bias = bias_dev; g.resid = resid_dev; g.y = y_dev; g.M = M; g.N = N;
   g.epi = EPI_RESIDUAL | (bias_dev ? EPI_BIAS : 0u);

@@ -505,7 +505,7 @@ __global__ __launch_bounds__(256) void norm_kernel(const bf16_t* __restrict__ x,
                                                    const bf16_t* __restrict__ gain,
                                                    const bf16_t* __restrict__ bias, uint32_t d,
                                                    float eps, bf16_t* __restrict__ y,
-                                                   float* __restrict__ xsum_t) {
+                                                   float* __restrict__ xsum_t, XPack pack) {
   __shared__ float red[4];
   const bf16_t* xr = x + (uint64_t)blockIdx.x * d;
   const uint32_t cpr = d >> 3;
@@ -520,28 +520,30 @@ __global__ __launch_bounds__(256) void norm_kernel(const bf16_t* __restrict__ x,
   }
   // chunk i of this thread (CACHED) or chunk c of the row
   auto chunk = [&](int i, uint32_t c) { return CACHED ? xv[i] : *reinterpret_cast<const uint4*>(xr + c * 8); };
-  norm_row<LAYERNORM, CACHED>(chunk, gain, bias, d, eps, y + (uint64_t)blockIdx.x * d, xsum_t, blockIdx.x, gridDim.x, red);
+  norm_row<LAYERNORM, CACHED>(chunk, gain, bias, d, eps, y, xsum_t, blockIdx.x, gridDim.x, pack, red);
 }
 hipError_t launch_rmsnorm(const void* x, const void* gain, uint32_t M, uint32_t d, float eps,
-                          void* y, hipStream_t st, float* xsum_t) {
+                          void* y, hipStream_t st, float* xsum_t, const XPack& pack0) {
   if (d % 128) xsum_t = nullptr;
+  const XPack pack = xsum_t ? pack0 : XPack{};
   if (d <= 8192)
     norm_kernel<false, true><<<M, 256, 0, st>>>((const bf16_t*)x, (const bf16_t*)gain, nullptr, d, eps, (bf16_t*)y,
-                                                xsum_t);
+                                                xsum_t, pack);
   else
     norm_kernel<false, false><<<M, 256, 0, st>>>((const bf16_t*)x, (const bf16_t*)gain, nullptr, d, eps, (bf16_t*)y,
-                                                 xsum_t);
+                                                 xsum_t, pack);
   return hipGetLastError();
 }
 hipError_t launch_layernorm(const void* x, const void* gain, const void* bias, uint32_t M,
-                            uint32_t d, float eps, void* y, hipStream_t st, float* xsum_t) {
+                            uint32_t d, float eps, void* y, hipStream_t st, float* xsum_t, const XPack& pack0) {
   if (d % 128) xsum_t = nullptr;
+  const XPack pack = xsum_t ? pack0 : XPack{};
   if (d <= 8192)
     norm_kernel<true, true><<<M, 256, 0, st>>>((const bf16_t*)x, (const bf16_t*)gain, (const bf16_t*)bias, d, eps,
-                                               (bf16_t*)y, xsum_t);
+                                               (bf16_t*)y, xsum_t, pack);
   else
     norm_kernel<true, false><<<M, 256, 0, st>>>((const bf16_t*)x, (const bf16_t*)gain, (const bf16_t*)bias, d, eps,
-                                                (bf16_t*)y, xsum_t);
+                                                (bf16_t*)y, xsum_t, pack);
   return hipGetLastError();
 }
 

@@ -1,0 +1,315 @@
+// Perturbed W4A16 linear for few tokens inside a model (up to 64 per pass, both passes of a step in one launch): the
+// product of the few-token kernel (qzo_skinny.hip) bit for bit - 0x4300 | u as the bf16 value 128 + u, group sums
+// P by MFMA, y += s_eff (P - (128 + zp) X) in fp32 - for activations that their producer has laid out for it (XPack) and
+// whose block sums X it has delivered.
+//
+// A workgroup of W wavefronts owns 32 W output rows and one K slice; W is chosen so that the launch is one workgroup per
+// compute unit and one round.  The slice's activations come by direct-to-LDS loads in the order in which the MFMA wants them
+// (1 KB a load, no permutation, no address arithmetic in the loop), weights two rounds (four groups) ahead into registers;
+// everyone's first round is requested before anyone's second, or the youngest wavefront's first weights queue behind all of the
+// oldest one's.  The arguments of the first loads arrive in registers (read from memory: 1.2 us); the noise of the eight groups
+// is drawn while the first loads are on their way, either half of a wavefront half of the variates.  With one token tile the K
+// loop holds no barrier: a wavefront waits for its own weights only.  With more tiles the activations are a ring of six (two
+// tiles) or three (four) groups.  One wavefront serves the tokens of both passes: a weight is unpacked once for a step, where
+// a workgroup per pass unpacked it twice.
+//
+// Bound, 1 x 16 tokens of the 7B shape, one launch of 12288 / 22016 / 4096 rows (25 / 45 / 23 MB): 7.2 / 10.1 / 8.2 us from its
+// first instruction to its last (before: 12.3 / 17.1 / 12.9), of which reading alone takes some 3.5 / 6.5 / 3.5 whatever the
+// pattern (128 bytes of eight rows, 512 of two, linear: 8.4 us a launch of 45 MB, all included); eight groups of 850 cycles
+// behind the first loads and 1400 cycles of stores are what does not overlap.  Step 2.67 -> 2.26 ms.
+// Four tiles (57 tokens): 3600 cycles a group of 256 rows, of which the LDS delivers fragments and block sums for 3300 and the
+// matrix unit is busy 2050; step 4.81 -> 4.43 ms.
+// Tried: all four rounds of weights requested at once (everything arrives, then everything is computed: 10.0 / 13.7 / 9.9 us);
+// activations of the later groups behind the first weights (no difference).
+#include "qzo_device.hpp"
+#include "qzo_kernels.hpp"
+#include "qzo_nibble.hpp"
+#include <algorithm>
+#include <type_traits>
+
+namespace qzo {
+
+namespace {
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// LDS: a ring of XS groups of activations, the slice's block sums, 4 KB per wavefront in which a round of weights (two
+// groups of 32 rows) turns from "a lane per 16 bytes of a line" to "a lane per row".
+template <int MT>
+struct FewLds {
+  static constexpr int XS = MT == 1 ? 8 : (MT == 2 ? 6 : 3), W = MT == 1 ? 12 : 8;      // W: most wavefronts
+  static constexpr uint32_t GROUP = MT * 8192u, SUMS = XS * GROUP, WT = SUMS + 8 * MT * 128u;
+  static constexpr uint32_t bytes(uint32_t waves) { return WT + waves * 4096u; }
+  static_assert(WT + W * 4096u <= 160 * 1024, "LDS of a compute unit");
+};
+
+#define QF_DTL(RSRC, LDSADDR, VOFF)                                                          \
+  asm volatile(QZO_SET_M0 "buffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(LDSADDR), "v"(VOFF), "s"(RSRC) : "memory", "m0")
+
+// What a wavefront needs later than its first loads.
+struct FewRest { uint32_t row_base, seed_lo, seed_hi; float eps_signed; };
+
+// MT tiles of 32 token rows; DUAL: the first half of the tile rows is the +eps pass, the second half the -eps pass.
+template <int MT, bool DUAL, bool ZP>
+__global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void* x, const void* w, const void* s, const float* xsum,
+    uint32_t N, uint32_t K, uint32_t per, uint32_t packed, float* part, const void* zp, FewRest a) {
+  const uint32_t M = packed & 0xffu, W = (packed >> 8) & 0xffu;       // tokens of a pass, wavefronts
+  const bool s_fp16 = (packed >> 16) != 0;
+  typedef FewLds<MT> L;
+  constexpr int XS = L::XS;
+  constexpr uint32_t ROWS = 32 * MT, TPP = DUAL ? ROWS / 2 : ROWS;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const uint32_t t = threadIdx.x, lane = t & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const uint32_t lrow = lane & 31u, half = lane >> 5;     // MFMA operand: row of the wavefront, half of the k-step
+  const uint32_t lr = lane >> 3, lc = lane & 7u;          // weight loads: row within an instruction's 8, 16-byte chunk
+  const uint32_t ngrp = K >> 7;
+  const uint32_t g0 = blockIdx.y * per, g1 = min(g0 + per, ngrp);
+  const uint32_t nb = (blockIdx.x * W + wave) * 32, n_own = nb + lrow;
+  const uint32_t n = min(n_own, N - 1);
+  const NibbleConsts nc = nibble_constants();
+  constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
+  const i32x4 rx = {(int)(uint32_t)(uintptr_t)x, (int)(uint32_t)((uintptr_t)x >> 32), (int)(ngrp * L::GROUP), 0x00020000};
+  const i32x4 rxs = {(int)(uint32_t)(uintptr_t)xsum, (int)(uint32_t)((uintptr_t)xsum >> 32), (int)(ngrp * ROWS * 4), 0x00020000};
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(w), 0, (int)((uint64_t)N * (K >> 1)), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(s), 0, (int)((uint64_t)N * ngrp * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(ZP ? zp : s), 0, (int)((uint64_t)N * ngrp), 0x00020000);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+  unsigned char* const wtw = lds + L::WT + wave * 4096u;
+  const uint32_t woff = (nb + lr) * (K >> 1) + lc * 16, wstep = 8 * (K >> 1), soff = n * ngrp;
+
+  // y[m][4 b + c]: weight row n, tile row 32 m + 8 b + 4 half + c
+  floatx16 y[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) y[m][r] = 0.0f;
+
+  for (uint32_t gb = g0; gb < g1; gb += 8) {
+    const uint32_t cnt = min(g1 - gb, 8u);
+    if (gb != g0) __syncthreads();                  // the groups before have been read
+    asm volatile("" ::: "memory");
+    // First what the first two groups need: weights, activations, block sums, scales; behind it the other activations
+    // and the second round of weights, which are on their way while the first groups are computed.  The wait for the
+    // scales is one for everything before them, that for the second round of weights one for all activations.
+    u32x4 wq[2][4];                                 // round r (groups gb + 2 r and the next) in r % 2: rows 8 i + lr, chunk lc
+    auto wload = [&](int r) __attribute__((always_inline)) {
+      const uint32_t wo = woff + (2u * r < cnt ? (gb + 2 * r) * 64u : OUT_OF_RANGE);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) wq[r & 1][i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(wo + i * wstep), 0, 0);
+    };
+    auto xload = [&](uint32_t first, uint32_t last) __attribute__((always_inline)) {
+      for (uint32_t q = first * MT * 8 + wave; q < min(last, cnt) * MT * 8; q += W)
+        QF_DTL(rx, lds0 + q * 1024, gb * L::GROUP + q * 1024 + lane * 16);
+    };
+    xload(0, XS);
+    if (wave < MT) QF_DTL(rxs, lds0 + L::SUMS + wave * 1024, gb * (ROWS * 4) + wave * 1024 + lane * 16);
+    u32x4 sv;
+    if (((ngrp | gb) & 1u) == 0) {
+      sv = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((soff + gb) * 2), 0, 0);
+    } else {
+      uint32_t h[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        h[j] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)((soff + gb) * 2), 2 * j, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sv[j] = h[2 * j] | (h[2 * j + 1] << 16);
+    }
+    uint32_t zv[2] = {0, 0};
+    if (ZP && ((ngrp | gb) & 3u) == 0) {
+      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+      const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rz, (int)(soff + gb), 0, 0);
+      zv[0] = v.x; zv[1] = v.y;
+    } else if (ZP) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        zv[j >> 2] |= (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rz, (int)(soff + gb), j, 0) << (8 * (j & 3));
+    }
+    asm volatile("" ::: "memory");
+    wload(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    wload(1);
+    asm volatile("" ::: "memory");
+    // noise of groups gb .. gb + 7 of the lane's row, by way of the wavefront's LDS: a counter serves eight groups, a
+    // lane draws the variates of its half of them
+    float z[8];
+    {
+      uint32_t* const zb = reinterpret_cast<uint32_t*>(wtw);          // [group of two counters][row]
+      const uint32_t first = gb & 7u;
+      uint32_t row_id = a.row_base, seed_lo = a.seed_lo, seed_hi = a.seed_hi;
+      asm volatile("" : "+s"(row_id), "+s"(seed_lo), "+s"(seed_hi));       // (waited for here, not before the first loads)
+      row_id += n;
+      for (uint32_t c = 0; c < (first + cnt > 8 ? 2u : 1u); ++c) {
+        const u32x4_t pw = philox4x32_10(row_id, (gb >> 3) + c, 0u, 0u, seed_lo, seed_hi);
+        float v[4];
+        normal_pair(half ? pw.z : pw.x, v[0], v[1]);
+        normal_pair(half ? pw.w : pw.y, v[2], v[3]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) zb[(c * 8 + half * 4 + i) * 32 + lrow] = __float_as_uint(v[i]);
+      }
+#pragma unroll
+      for (int d = 0; d < 8; ++d) z[d] = __uint_as_float(zb[(first + d) * 32 + lrow]);
+      asm volatile("" ::: "memory");                // read before the weights take the place
+    }
+    // a round to the wavefront's LDS buffer: row r, chunk c at 128 r + 16 (c ^ r % 8)
+    auto wstore = [&](auto R_) __attribute__((always_inline)) {
+      constexpr int r = decltype(R_)::value;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(wtw + (8 * i + lr) * 128 + ((lc ^ lr) << 4)) = wq[r & 1][i];
+      if (r < 2) wload(r + 2);
+    };
+    uint32_t wd[2][8];                              // the lane's 64 nibbles of a group
+    auto wread = [&](auto D_) __attribute__((always_inline)) {
+      constexpr int d = decltype(D_)::value;
+      const uint32_t c0 = 4 * (d & 1) + 2 * half;
+      const u32x4 w0 = *reinterpret_cast<const u32x4*>(wtw + lrow * 128 + ((c0 ^ (lrow & 7u)) << 4));
+      const u32x4 w1 = *reinterpret_cast<const u32x4*>(wtw + lrow * 128 + (((c0 + 1) ^ (lrow & 7u)) << 4));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { wd[d & 1][i] = w0[i]; wd[d & 1][4 + i] = w1[i]; }
+    };
+    // the scales have landed, and with them everything requested before them
+    asm volatile("" : "+v"(sv));
+    __syncthreads();
+    wstore(std::integral_constant<int, 0>());
+    wread(std::integral_constant<int, 0>());
+
+    // group d and those behind it (nested, so that a wait for weights counts the loads that were issued in between and
+    // not the least of several paths)
+    auto group = [&](auto&& self, auto D_) __attribute__((always_inline)) -> void {
+      constexpr int d = decltype(D_)::value;
+      // the next round's weights take the place of this one's, whose last group is in registers
+      if constexpr ((d & 1) && d < 7) wstore(std::integral_constant<int, (d + 1) / 2>());
+      if constexpr (XS < 8) {
+        // group d has landed (those behind it may be on their way), everyone has read group d - 1
+        constexpr bool wait = MT == 4 ? d >= XS : d == XS, refill = d >= 1 && d - 1 + XS < 8;
+        if (wait) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(MT == 4 && d < 7 ? MT * 8 / L::W : 0) : "memory");
+        if (wait || refill) {
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+        }
+        if (refill) {
+          constexpr uint32_t slot = (d - 1) % XS;
+          for (uint32_t q = wave; q < MT * 8; q += W)
+            QF_DTL(rx, lds0 + slot * L::GROUP + q * 1024,
+                   d - 1 + XS < (int)cnt ? (gb + d - 1 + XS) * L::GROUP + q * 1024 + lane * 16 : OUT_OF_RANGE);
+        }
+      }
+      const unsigned char* const xb = lds + (d % XS) * L::GROUP + lane * 16;
+      const float* const sums = reinterpret_cast<const float*>(lds + L::SUMS) + d * ROWS + 4 * half;
+      const float s0 = scale_to_f32((d & 1) ? sv[d >> 1] >> 16 : sv[d >> 1] & 0xffffu, s_fp16);
+      const float se_p = __builtin_fmaf(a.eps_signed, z[d], s0), se_m = __builtin_fmaf(-a.eps_signed, z[d], s0);
+      const float cz = ZP ? -(128.0f + (float)((zv[d >> 2] >> (8 * (d & 3))) & 0xffu)) : -136.0f;
+      constexpr int R = 4;                          // fragments read ahead of their MFMA
+      bf16x8 xf[R], wf[8];
+      floatx16 p[2];
+      float4 xg[2][4];
+      auto xread = [&](int q) __attribute__((always_inline)) { xf[q % R] = *reinterpret_cast<const bf16x8*>(xb + q * 1024); };
+      auto rescale = [&](int m, int b) __attribute__((always_inline)) {
+        const float se = DUAL && 2 * m + (b >= 2) >= MT ? se_m : se_p;
+        const float4 x = xg[m & 1][b];
+        const floatx16& q = p[m & 1];
+        y[m][4 * b + 0] = __builtin_fmaf(se, __builtin_fmaf(cz, x.x, q[4 * b + 0]), y[m][4 * b + 0]);
+        y[m][4 * b + 1] = __builtin_fmaf(se, __builtin_fmaf(cz, x.y, q[4 * b + 1]), y[m][4 * b + 1]);
+        y[m][4 * b + 2] = __builtin_fmaf(se, __builtin_fmaf(cz, x.z, q[4 * b + 2]), y[m][4 * b + 2]);
+        y[m][4 * b + 3] = __builtin_fmaf(se, __builtin_fmaf(cz, x.w, q[4 * b + 3]), y[m][4 * b + 3]);
+      };
+#pragma unroll
+      for (int q = 0; q < R; ++q) xread(q);
+      wf[0] = unpack8_biased(wd[d & 1][0], nc);
+      __builtin_amdgcn_sched_barrier(0);
+      // one slot per MFMA: what else the wavefront has to do is dealt out behind them
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {               // k-step j: inputs 64 half + 8 j .. + 7 of the group
+          const int q = m * 8 + j;
+          const floatx16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+          p[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[q % R], wf[j], j == 0 ? zero : p[m & 1], 0, 0, 0);
+          if (q + R < MT * 8) xread(q + R);
+          if (m == 0 && j < 7) wf[j + 1] = unpack8_biased(wd[d & 1][j + 1], nc);
+          if (j < 4) xg[m & 1][j] = *reinterpret_cast<const float4*>(sums + m * 32 + 8 * j);
+          if (m > 0 && j >= 1 && j <= 4) rescale(m - 1, j - 1);
+          if constexpr (d < 7)
+            if (m == MT - 1 && j == 6) wread(std::integral_constant<int, d + 1>());
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+      for (int b = 0; b < 4; ++b) rescale(MT - 1, b);
+      if constexpr (d < 7)
+        if (d + 1 < (int)cnt) self(self, std::integral_constant<int, d + 1>());
+    };
+    group(group, std::integral_constant<int, 0>());
+    __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0): loads that nobody waited for would be waited for above
+  }
+
+  // partial sums of this slice
+  const uint32_t rows = DUAL ? 2 * M : M;
+  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(part, 0, (int)((uint64_t)gridDim.y * rows * N * 4), 0x00020000);
+  if (n_own < N) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const uint32_t tr = 32 * m + 8 * (r >> 2) + 4 * half + (r & 3), tok = tr % TPP;
+        const uint32_t off = ((blockIdx.y * rows + (tr / TPP) * M + tok) * N + n_own) * 4u;
+        if (tok < M) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[m][r]), rp, (int)off, 0, WRITE_THROUGH);
+      }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");        // loads past the end still write the LDS
+}
+#undef QF_DTL
+
+template <int MT, bool DUAL, bool ZP>
+hipError_t few_prepare() {
+  return hipFuncSetAttribute((const void*)few_gemm_kernel<MT, DUAL, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             FewLds<MT>::bytes(FewLds<MT>::W));
+}
+template <int MT, bool DUAL>
+hipError_t few_launch(const GemmArgs& a, float* ws, uint32_t ks, uint32_t per, hipStream_t st) {
+  // wavefronts per workgroup: as few as make one round, but one per SIMD
+  const uint32_t tiles = (a.N + 31) / 32, cus = gemm_workgroups(1u << 20, 1u << 20), most = FewLds<MT>::W;
+  uint32_t w = MT == 4 ? most : std::min(most, std::max(4u, (uint32_t)(((uint64_t)tiles * ks + cus - 1) / cus)));
+  while (w < most && (uint64_t)((tiles + w - 1) / w) * ks > cus) ++w;
+  const dim3 grid((tiles + w - 1) / w, ks);
+  const FewRest r = {a.row_base, a.seed_lo, a.seed_hi, a.eps_signed};
+  const uint32_t packed = a.M | (w << 8) | (a.s_fp16 ? 1u << 16 : 0u);
+  if (a.zp)
+    few_gemm_kernel<MT, DUAL, true><<<grid, w * 64, FewLds<MT>::bytes(w), st>>>(a.x, a.w, a.s, a.xsum, a.N, a.K, per, packed, ws, a.zp, r);
+  else
+    few_gemm_kernel<MT, DUAL, false><<<grid, w * 64, FewLds<MT>::bytes(w), st>>>(a.x, a.w, a.s, a.xsum, a.N, a.K, per, packed, ws, nullptr, r);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_few_gemm(const GemmArgs& a, float* ws, uint32_t ks, uint32_t per, hipStream_t st) {
+  static bool ready = false;
+  if (!ready) {
+    hipError_t e = few_prepare<1, true, false>();
+    if (e == hipSuccess) e = few_prepare<1, true, true>();
+    if (e == hipSuccess) e = few_prepare<1, false, false>();
+    if (e == hipSuccess) e = few_prepare<1, false, true>();
+    if (e == hipSuccess) e = few_prepare<2, true, false>();
+    if (e == hipSuccess) e = few_prepare<2, true, true>();
+    if (e == hipSuccess) e = few_prepare<2, false, false>();
+    if (e == hipSuccess) e = few_prepare<2, false, true>();
+    if (e == hipSuccess) e = few_prepare<4, true, false>();
+    if (e == hipSuccess) e = few_prepare<4, true, true>();
+    if (e != hipSuccess) return e;
+    ready = true;
+  }
+  if (!a.xsum || a.xp.M != a.M || a.xp.rows != few_pack(a.M, a.dual != 0).rows) return hipErrorInvalidValue;
+  switch (a.xp.rows >> 5) {
+    case 1: return a.dual ? few_launch<1, true>(a, ws, ks, per, st) : few_launch<1, false>(a, ws, ks, per, st);
+    case 2: return a.dual ? few_launch<2, true>(a, ws, ks, per, st) : few_launch<2, false>(a, ws, ks, per, st);
+    case 4: return a.dual ? few_launch<4, true>(a, ws, ks, per, st) : hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace qzo

@@ -36,11 +36,30 @@ enum : uint32_t {
                        // of an expanded W must be in ROW_ORDER_ROPE128 order (the fused kernel takes them so by itself)
 };
 
+// Activations as the few-token kernel inside a model (qzo_few.hip) takes them, written so by the kernel that makes them:
+// tile rows in whole tiles of 32, the +eps pass's from row 0 on, the -eps pass's from row tpp on; for a group of 128
+// features and a tile, 8 KB in the order of the MFMA's operand: [k-step][half * 32 + row] of 16 bytes, the eight inputs
+// 64 half + 8 k-step .. + 7 in the order 0,4,1,5,2,6,3,7 that the nibbles are unpacked in.  Rows beyond a pass's tokens
+// are never written (what they hold reaches no output).  Block sums beside it: fp32 [K/128][rows].
+struct XPack {
+  uint32_t M, tpp, rows;       // tokens of a pass; tile rows of a pass, of all passes (0: plain row-major)
+  __host__ __device__ uint32_t tile_row(uint32_t m) const { return m < M ? m : tpp + m - M; }
+  // byte offset of features 8 c .. 8 c + 7 of row m
+  __host__ __device__ uint32_t chunk(uint32_t m, uint32_t c) const {
+    const uint32_t r = tile_row(m);
+    return ((c >> 4) * (rows >> 5) + (r >> 5)) * 8192u + (c & 7u) * 1024u + (((c >> 3) & 1u) * 32u + (r & 31u)) * 16u;
+  }
+};
+inline XPack few_pack(uint32_t M, bool dual) {
+  const uint32_t tpp = dual && M <= 16 ? 16u : (M + 31) / 32 * 32;
+  return {M, tpp, dual ? 2 * tpp : tpp};
+}
 struct NextNorm {
   const void *gain, *bias;     // bias: LayerNorm, null: RMSNorm
   float eps;
   void* out;                   // bf16 [rows, N]
   float* xsum;                 // nullable: block sums of out, [N/128][rows]
+  XPack pack;                  // of out and xsum
   bool done;                   // set by the launcher that took it over
 };
 // The attention that reads a qkv projection next: a slice reduction may leave its slices to it.
@@ -81,11 +100,12 @@ struct GemmArgs {
   uint32_t epi;
   uint32_t s_fp16;      // int4 formats: s holds fp16 instead of bf16
   uint32_t nf4;         // mid_gemm_kernel and the fused kernel: w holds NormalFloat-4 indices, s bf16 [N,K/64], no block sums
-  // Few-token path: block sums X[g][row] = sum of x[row, 128 g .. 128 g + 127] (fp32, [K/128][rows], rows = M or
+  // Few-token paths: block sums X[g][row] = sum of x[row, 128 g .. 128 g + 127] (fp32, [K/128][rows], rows = M or
   // 2 M when dual), delivered by the kernel that wrote x (null: the kernel sums them itself), and the same for
   // the output y of the K-slice reduction ([N_out/128][rows], N_out % 128 == 0; null: not wanted).
   const float* xsum;
   float* xsum_out;
+  XPack xp, yp;               // layout of x and xsum, of the reduction's y and xsum_out
   // The norm that reads y next (null: none wanted): a slice reduction norms the rows it completes (NextNorm::done).
   struct NextNorm* next;
   struct NextAttention* next_attention;      // (null: y is wanted)
@@ -116,6 +136,8 @@ uint64_t skinny_ws_floats(uint32_t rows, uint32_t N, uint32_t K);      // rows =
 bool skinny_fits(uint32_t rows, uint32_t N, uint32_t K);
 uint32_t skinny_reduce_blocks(uint32_t M, uint32_t N, uint32_t epi);   // EPI_SUMSQ partial count
 hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st);
+// Its product for packed activations (a.xp), ks slices of per groups.
+hipError_t launch_few_gemm(const GemmArgs& a, float* ws, uint32_t ks, uint32_t per, hipStream_t st);
 // Adds K-slice partial sums part[slice][M][N] in slice order and applies a's epilogue.
 hipError_t launch_partial_reduce(const GemmArgs& a, const float* part, uint32_t ksplit, hipStream_t st);
 // Some dozen to a few hundred tokens per pass (mid_gemm_kernel): items (block of MID_ROWS output rows, block of mt token
@@ -267,11 +289,13 @@ hipError_t launch_sum_partials(const float* partials, uint32_t n, float* out, hi
 hipError_t launch_embed(const int32_t* tok, uint32_t tok_rows, uint32_t pass_stride, const void* tok_emb,
                         const void* pos_emb, uint32_t M, uint32_t S, uint32_t d, void* h, float* rope, uint32_t dh,
                         float theta, hipStream_t st);
-// xsum_t (nullable, d % 128 == 0): receives the block sums of the output, [d/128][M] fp32 (see GemmArgs::xsum)
+// xsum_t (nullable, d % 128 == 0): receives the block sums of the output, [d/128][M] fp32 (see GemmArgs::xsum); with it
+// pack: layout of the output and the sums
 hipError_t launch_rmsnorm(const void* x, const void* gain, uint32_t M, uint32_t d, float eps,
-                          void* y, hipStream_t st, float* xsum_t = nullptr);
+                          void* y, hipStream_t st, float* xsum_t = nullptr, const XPack& pack = XPack{});
 hipError_t launch_layernorm(const void* x, const void* gain, const void* bias, uint32_t M,
-                            uint32_t d, float eps, void* y, hipStream_t st, float* xsum_t = nullptr);
+                            uint32_t d, float eps, void* y, hipStream_t st, float* xsum_t = nullptr,
+                            const XPack& pack = XPack{});
 hipError_t launch_rope(void* qkv, const float* table, uint32_t M, uint32_t S, uint32_t pass_stride, uint32_t d,
                        uint32_t n_heads, hipStream_t st);
 // rope (nullable): the (cos, sin) table; with it the kernel rotates q and k itself (qkv holds them unrotated).

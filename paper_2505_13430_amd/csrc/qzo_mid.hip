@@ -266,7 +266,7 @@ __global__ __launch_bounds__(512, 2) void mid_gemm_kernel(GemmArgs a, MidPlan mp
         const uint32_t tok = k.tile * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
         const uint32_t off = ((slot * mp.rows + k.pass * a.M + tok) * a.N + nb + lrow) * 4u;
         if (k.valid && tok < a.M && nb + lrow < a.N)
-          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[m][r]), rp, (int)off, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[m][r]), rp, (int)off, 0, WRITE_THROUGH);
       }
     }
   }

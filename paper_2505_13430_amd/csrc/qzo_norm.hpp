@@ -1,6 +1,8 @@
 // The norm of one row, shared by the norm kernel and by the slice reduction that norms the rows it completes.
 #pragma once
 #include "qzo_device.hpp"
+#include "qzo_kernels.hpp"
+#include "qzo_nibble.hpp"
 
 namespace qzo {
 
@@ -14,13 +16,14 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// Row `row` of `rows`, d features, to yr; chunk(i, c): 16-byte chunk c = thread + 256 i of the row (any value beyond it).
+// Row `row` of `rows`, d features, to its place in y; chunk(i, c): 16-byte chunk c = thread + 256 i of the row (any value beyond it).
 // fp32 statistics by the first 256 threads; the others only take part in the barriers.
-// CACHED: the row fits four chunks per thread.  xsum_t (nullable): block sums of the output, [d/128][rows].
+// CACHED: the row fits four chunks per thread.  xsum_t (nullable): block sums of the output, [d/128][rows].  pack: both as
+// the few-token kernel takes them.
 template <bool LAYERNORM, bool CACHED, class Chunk>
 __device__ __forceinline__ void norm_row(const Chunk& chunk, const bf16_t* __restrict__ gain, const bf16_t* __restrict__ bias,
-                                         uint32_t d, float eps, bf16_t* __restrict__ yr, float* __restrict__ xsum_t,
-                                         uint32_t row, uint32_t rows, float* red) {
+                                         uint32_t d, float eps, bf16_t* __restrict__ y, float* __restrict__ xsum_t,
+                                         uint32_t row, uint32_t rows, const XPack& pack, float* red) {
   const uint32_t cpr = threadIdx.x < 256 ? d >> 3 : 0u;
   constexpr int NC = 4;
   const uint32_t passes = CACHED ? NC : ((d >> 3) + 255) / 256;
@@ -78,7 +81,8 @@ __device__ __forceinline__ void norm_row(const Chunk& chunk, const bf16_t* __res
         }
         o[j] = pack_bf16x2(lo, hi);
       }
-      *reinterpret_cast<uint4*>(yr + c * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+      if (pack.rows) *reinterpret_cast<u32x4*>((unsigned char*)y + pack.chunk(row, c)) = permute8(u32x4{o[0], o[1], o[2], o[3]});
+      else *reinterpret_cast<uint4*>(y + (uint64_t)row * d + c * 8) = make_uint4(o[0], o[1], o[2], o[3]);
     }
     if (xsum_t) {
       // block sums of the row's output for a few-token linear that reads it: the 16 chunks of 128 features
@@ -92,7 +96,8 @@ __device__ __forceinline__ void norm_row(const Chunk& chunk, const bf16_t* __res
       float sx = lo + hi;
       sx += __shfl_xor(sx, 1, 64); sx += __shfl_xor(sx, 2, 64);
       sx += __shfl_xor(sx, 4, 64); sx += __shfl_xor(sx, 8, 64);
-      if (c < cpr && (c & 15u) == 0u) xsum_t[(uint64_t)(c >> 4) * rows + row] = sx;
+      if (c < cpr && (c & 15u) == 0u)
+        xsum_t[(uint64_t)(c >> 4) * (pack.rows ? pack.rows : rows) + (pack.rows ? pack.tile_row(row) : row)] = sx;
     }
   }
 }

@@ -49,11 +49,18 @@ namespace {
 constexpr int SK_ROWS = 128;      // output rows per workgroup
 constexpr int SK_WD = 8;          // groups per pass of the K loop: four rounds of two groups, all in flight
 
+// What a slice reduction reads of its linear's GemmArgs.
+struct ReduceArgs {
+  uint32_t M, N, epi, ldy;
+  void* y;
+  const void *resid, *bias;
+  XPack yp;
+};
 // One output item of the slice reduction: 4 consecutive output features f .. f+3 of token m.
 // Adds the K-slice partials in slice order and applies the epilogue; returns the sum of the squares
 // of the stored bf16 values (and their plain sum in `sum`).
 // ksplit: slices of feature f (and of the up feature NO + f with SwiGLU: ksplit_up).
-__device__ __forceinline__ float reduce_item(const GemmArgs& a, const float* __restrict__ part, uint32_t ksplit,
+__device__ __forceinline__ float reduce_item(const ReduceArgs& a, const float* __restrict__ part, uint32_t ksplit,
                                              uint32_t ksplit_up, uint32_t m, uint32_t f, float& sum,
                                              uint2* packed = nullptr) {
   const bool swiglu = (a.epi & EPI_SWIGLU) != 0;
@@ -101,7 +108,7 @@ __device__ __forceinline__ float reduce_item(const GemmArgs& a, const float* __r
   uint2 out;
   out.x = pack_bf16x2(v[0], v[1]);
   out.y = pack_bf16x2(v[2], v[3]);
-  *reinterpret_cast<uint2*>((bf16_t*)a.y + o) = out;
+  if (!a.yp.rows) *reinterpret_cast<uint2*>((bf16_t*)a.y + o) = out;
   if (packed) *packed = out;
   const float q0 = __uint_as_float(out.x << 16), q1 = __uint_as_float(out.x & 0xffff0000u);
   const float q2 = __uint_as_float(out.y << 16), q3 = __uint_as_float(out.y & 0xffff0000u);
@@ -115,18 +122,13 @@ __device__ __forceinline__ float reduce_item(const GemmArgs& a, const float* __r
 // the -eps pass (M <= 16 MT).
 // XSUM_BY_MFMA (one token tile, at most 16 tokens per pass: the stacked and the separate passes of
 // a step then sum alike, bit for bit): the block sums come from the matrix unit, see below.
-// XIN: the block sums come from memory (GemmArgs::xsum, written by the kernel that wrote x); a pass's 8 groups
-// x tile rows are fetched one pass ahead, one or two values per thread, and handed on through the LDS.
-// (One token tile with XIN fits 168 registers: three workgroups per CU, which holds the 688 workgroups of a
-// 22016-row gate/up linear in one round.)
-template <int MT, bool DUAL, bool ZP, bool XSUM_BY_MFMA, bool XIN>
-__global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_kernel(GemmArgs a, float* part,
+template <int MT, bool DUAL, bool ZP, bool XSUM_BY_MFMA>
+__global__ __launch_bounds__(256, 2) void skinny_gemm_kernel(GemmArgs a, float* part,
                                                              uint32_t groups_per_split) {
   constexpr uint32_t TPP = DUAL ? MT * 16 : MT * 32;      // tile rows per pass
   __shared__ __attribute__((aligned(16))) unsigned char xs[2][MT * 32 * 256];
   __shared__ __attribute__((aligned(16))) float xsum[2][MT * 32];          // X[m,g] of the block in the same buffer
   __shared__ __attribute__((aligned(16))) unsigned char wt[4][32 * 128];   // per wavefront: a round of its 32 rows
-  __shared__ __attribute__((aligned(16))) float xin[2][XIN ? SK_WD : 1][MT * 32];   // XIN: X[g][tile row] of two passes
   const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
   const uint32_t lrow = lane & 31u, half = lane >> 5;     // MFMA operand: row of the wavefront, half of the k-step
   const uint32_t lr = lane >> 3, lc = lane & 7u;          // loads: row within an instruction's 8 rows, 16-byte chunk
@@ -176,7 +178,6 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
     // activation staging: a group's block is MT*32 rows x 16 chunks of 16 bytes; a thread moves MT*2 chunks.
     // Tile row -> row of x: clamped to the pass's last token.
     static_assert(!XSUM_BY_MFMA || MT == 1, "no registers for it with two token tiles");
-    static_assert(!(XIN && XSUM_BY_MFMA), "one source of the block sums");
     constexpr int NX = MT * 2;
     uint32_t xoff[NX];
 #pragma unroll
@@ -188,9 +189,8 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
     // The counter of outstanding loads retires in issue order: waiting for a load waits for every
     // older one.  So the activation blocks are requested as far ahead as the weights (four groups);
     // a block requested just in time would cut the weights' lead down to its own.
-    // With two token tiles the registers do not allow it: two groups ahead there, and also where one tile
-    // runs three workgroups per CU (XIN).
-    constexpr int XD = (MT == 1 && !XIN) ? 4 : 2;
+    // With two token tiles the registers do not allow it: two groups ahead there.
+    constexpr int XD = MT == 1 ? 4 : 2;
     u32x4 xr[XD][NX];           // the next XD blocks on their way: block g0 + j in slot j % XD
 #define QZO_SK_XLOAD(SLOT, G_)                                                               \
   do {                                                                                       \
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
     _Pragma("unroll") for (int i = 0; i < NX; ++i) {                                         \
       const uint32_t c = t + 256u * i, row = c >> 4, ch = c & 15u;                           \
       *reinterpret_cast<u32x4*>(xs[BUF] + x_lds_off(row, ch)) = permute8(xr[SLOT][i]);       \
-      if (!XSUM_BY_MFMA && !XIN) {                                                           \
+      if (!XSUM_BY_MFMA) {                                                                   \
         float sx_ = sum8_bf16(xr[SLOT][i]);                                                  \
         sx_ += __shfl_xor(sx_, 1, 64); sx_ += __shfl_xor(sx_, 2, 64);                        \
         sx_ += __shfl_xor(sx_, 4, 64); sx_ += __shfl_xor(sx_, 8, 64);                        \
@@ -266,29 +266,6 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
     }                                                                                        \
   } while (0)
 
-    // XIN: element e = t + 256 i of a pass is (group e / (32 MT), tile row e % (32 MT)); X is [K/128][rows]
-    const uint32_t xrows = rows_all;
-    const __amdgpu_buffer_rsrc_t rxs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(XIN ? a.xsum : (const float*)a.x), 0, (int)((uint64_t)xrows * ngrp * 4), 0x00020000);
-    uint32_t xin_off[MT];
-    float xin_next[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const uint32_t e = t + 256u * i, row = e % (MT * 32u);
-      const uint32_t xrow = DUAL ? (row / TPP) * a.M + min(row % TPP, a.M - 1) : row0 + min(row, a.M - 1);
-      xin_off[i] = ((e / (MT * 32u)) * xrows + xrow) * 4u;
-      xin_next[i] = 0.0f;
-    }
-#define QZO_SK_XINLOAD(G_)                                                                   \
-  do {                                                                                       \
-    if (XIN) {                                                                               \
-      _Pragma("unroll") for (int i = 0; i < MT; ++i) {                                       \
-        const uint32_t gi_ = (G_) + (t + 256u * i) / (MT * 32u);                             \
-        xin_next[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(                  \
-            rxs, (int)(gi_ < g1 ? xin_off[i] + (G_) * xrows * 4u : OUT_OF_RANGE), 0, 0));    \
-      }                                                                                      \
-    }                                                                                        \
-  } while (0)
     union { bf16x8 v; uint32_t u[4]; } ones;
     ones.u[0] = ones.u[1] = ones.u[2] = ones.u[3] = 0x3f803f80u;
     // noise: one Philox counter per 8 groups, one Box-Muller pair per 2 groups
@@ -301,7 +278,6 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
     QZO_SK_XLOAD(0, g0);
     QZO_SK_WLOAD(0, g0);
     QZO_SK_SLOAD(g0);
-    QZO_SK_XINLOAD(g0);
     QZO_SK_XLOAD(1, g0 + 1);
     QZO_SK_WLOAD(1, g0 + 2);
 #pragma unroll
@@ -316,12 +292,6 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
       sv = sv_next;
       zv[0] = zv_next[0]; zv[1] = zv_next[1];
       QZO_SK_SLOAD(gb + SK_WD);
-      const uint32_t xpp = ((gb - g0) / SK_WD) & 1u;      // XIN: this pass's LDS buffer (visible after the barrier of d = 0)
-      if (XIN) {
-#pragma unroll
-        for (int i = 0; i < MT; ++i) (&xin[xpp][0][0])[t + 256u * i] = xin_next[i];
-      }
-      QZO_SK_XINLOAD(gb + SK_WD);
 #pragma unroll
       for (int d = 0; d < SK_WD; ++d) {
         const uint32_t g = gb + d;
@@ -375,10 +345,8 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
           for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-              const float4 xg = XIN ? *reinterpret_cast<const float4*>(&xin[xpp][XIN ? d : 0][m * 32 + 8 * b + 4 * half])
-                                : XSUM_BY_MFMA
-                                    ? make_float4(px[4 * b], px[4 * b + 1], px[4 * b + 2], px[4 * b + 3])
-                                    : *reinterpret_cast<const float4*>(&xsum[buf][m * 32 + 8 * b + 4 * half]);
+              const float4 xg = XSUM_BY_MFMA ? make_float4(px[4 * b], px[4 * b + 1], px[4 * b + 2], px[4 * b + 3])
+                                             : *reinterpret_cast<const float4*>(&xsum[buf][m * 32 + 8 * b + 4 * half]);
               const float se = !DUAL ? se_p : ((MT == 2 ? m == 1 : b >= 2) ? se_m : se_p);
               y[m][4 * b + 0] = __builtin_fmaf(se, __builtin_fmaf(cz, xg.x, pg[m][4 * b + 0]), y[m][4 * b + 0]);
               y[m][4 * b + 1] = __builtin_fmaf(se, __builtin_fmaf(cz, xg.y, pg[m][4 * b + 1]), y[m][4 * b + 1]);
@@ -393,7 +361,6 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
 #undef QZO_SK_WLOAD
 #undef QZO_SK_WSTORE
 #undef QZO_SK_SLOAD
-#undef QZO_SK_XINLOAD
 
     // partial sums of this slice
     const uint32_t rows = rows_all;
@@ -408,7 +375,7 @@ __global__ __launch_bounds__(256, (MT == 1 && XIN) ? 3 : 2) void skinny_gemm_ker
           const uint32_t tok = DUAL ? tr % TPP : tr;
           const uint32_t orow = DUAL ? (tr / TPP) * a.M + tok : row0 + tok;
           const uint32_t off = ((blockIdx.y * rows + orow) * a.N + n_own) * 4u;
-          if (tok < a.M) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[m][r]), rp, (int)off, 0, 0);
+          if (tok < a.M) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[m][r]), rp, (int)off, 0, WRITE_THROUGH);
         }
     }
   }
@@ -425,31 +392,45 @@ __device__ __forceinline__ uint32_t slices_of(const MidPlan& mp, uint32_t m, uin
 // MAPPED: the slices come from mid_gemm_kernel, whose ranges of work give every block of the output a number of
 // slices of its own.
 template <bool MAPPED>
-__global__ __launch_bounds__(256) void skinny_reduce_kernel(GemmArgs a, const float* __restrict__ part,
-                                                            uint32_t ksplit, MidPlan mp) {
+__global__ __launch_bounds__(256) void skinny_reduce_kernel(const float* __restrict__ part, uint32_t M, uint32_t N, uint32_t ksplit,
+                                                            uint32_t epi, uint32_t ldy, void* y, const void* resid, const void* bias,
+                                                            XPack yp, float* xsum_out, float* partials, MidPlan mp) {
+  const ReduceArgs a = {M, N, epi, ldy, y, resid, bias, yp};
   const uint32_t NO = (a.epi & EPI_SWIGLU) ? a.N >> 1 : a.N;                  // output width
   const uint32_t q = blockIdx.x * 256 + threadIdx.x, per_row = NO >> 2;
   float ssq = 0.0f, sx = 0.0f;
   const bool own = q < a.M * per_row;
+  const uint32_t m = q / per_row, f = (q % per_row) * 4;
+  uint2 out = make_uint2(0, 0);
   if (own) {
-    const uint32_t m = q / per_row, f = (q % per_row) * 4;
     const uint32_t kf = MAPPED ? slices_of(mp, m, f) : ksplit;
     const uint32_t ku = MAPPED && (a.epi & EPI_SWIGLU) ? slices_of(mp, m, NO + f) : kf;
-    ssq = reduce_item(a, part, kf, ku, m, f, sx);
+    ssq = reduce_item(a, part, kf, ku, m, f, sx, &out);
   }
-  if (a.xsum_out) {
+  if (!MAPPED && a.yp.rows) {
+    // packed: features 0,4,1,5 of a chunk of eight by its first thread, 2,6,3,7 by its second (the output width is a
+    // multiple of 128, so a row starts on an even thread)
+    const bool second = (threadIdx.x & 1u) != 0;
+    const uint32_t other = (uint32_t)__shfl_xor((int)(second ? out.x : out.y), 1, 64);
+    const uint32_t lo = second ? other : out.x, hi = second ? out.y : other;
+    if (own)
+      *reinterpret_cast<uint2*>((unsigned char*)a.y + a.yp.chunk(m, f >> 3) + (f & 4u) * 2) =
+          make_uint2(__builtin_amdgcn_perm(hi, lo, 0x05040100u), __builtin_amdgcn_perm(hi, lo, 0x07060302u));
+  }
+  if (xsum_out) {
     // block sums of the output for a few-token linear that reads it: 128 features = 32 consecutive
     // threads of one token (the output width is a multiple of 128)
     sx += __shfl_xor(sx, 1, 64); sx += __shfl_xor(sx, 2, 64); sx += __shfl_xor(sx, 4, 64);
     sx += __shfl_xor(sx, 8, 64); sx += __shfl_xor(sx, 16, 64);
-    if (own && (threadIdx.x & 31u) == 0u) a.xsum_out[(uint64_t)((q % per_row) >> 5) * a.M + q / per_row] = sx;
+    if (own && (threadIdx.x & 31u) == 0u)
+      xsum_out[(uint64_t)(f >> 7) * (a.yp.rows ? a.yp.rows : a.M) + (a.yp.rows ? a.yp.tile_row(m) : m)] = sx;
   }
   if (a.epi & EPI_SUMSQ) {
     __shared__ float red[4];
     ssq = wave_sum(ssq);
     if ((threadIdx.x & 63u) == 0) red[threadIdx.x >> 6] = ssq;
     __syncthreads();
-    if (threadIdx.x == 0) a.partials[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    if (threadIdx.x == 0) partials[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
   }
 }
 
@@ -461,12 +442,14 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(GemmArgs a, const fl
 // launches are bound by their bytes and a row of 2048 features leaves too few loads in flight (OPT-1.3B 16 x 64: +2.8 %).  Rows that take more than one item per thread
 // want a few hundred workgroups (13B widths: 388 rows of 5120 features -1.5 %, 32 rows +0.7 %).
 template <bool LAYERNORM, bool MAPPED>
-__global__ __launch_bounds__(1024) void reduce_norm_kernel(GemmArgs a, const float* __restrict__ part, uint32_t ksplit,
-                                                           MidPlan mp, NextNorm nn) {
+__global__ __launch_bounds__(1024) void reduce_norm_kernel(const float* __restrict__ part, uint32_t M, uint32_t N, uint32_t ksplit,
+                                                           uint32_t epi, uint32_t threads, const void* resid, void* y,
+                                                           const void* bias, NextNorm nn, MidPlan mp) {
+  const ReduceArgs a = {M, N, epi, 0u, y, resid, bias, XPack{}};
   __shared__ __attribute__((aligned(16))) uint2 row[2048];
   __shared__ float red[4];
   const uint32_t m = blockIdx.x;
-  for (uint32_t f = threadIdx.x * 4; f < a.N; f += blockDim.x * 4) {
+  for (uint32_t f = threadIdx.x * 4; f < a.N; f += threads * 4) {
     float sum;
     const uint32_t kf = MAPPED ? slices_of(mp, m, f) : ksplit;
     (void)reduce_item(a, part, kf, kf, m, f, sum, row + (f >> 2));
@@ -474,7 +457,7 @@ __global__ __launch_bounds__(1024) void reduce_norm_kernel(GemmArgs a, const flo
   __syncthreads();
   auto chunk = [&](int i, uint32_t) { return reinterpret_cast<const uint4*>(row)[(threadIdx.x & 255u) + 256u * i]; };
   norm_row<LAYERNORM, true>(chunk, (const bf16_t*)nn.gain, (const bf16_t*)nn.bias, a.N, nn.eps,
-                            (bf16_t*)nn.out + (uint64_t)m * a.N, nn.xsum, m, gridDim.x, red);
+                            (bf16_t*)nn.out, nn.xsum, m, M, nn.pack, red);
 }
 
 // Slice reduction of a.M rows, with the norm that reads its output where the caller named one; left to the attention that
@@ -495,11 +478,15 @@ hipError_t launch_reduce(const GemmArgs& r, const float* part, uint32_t ksplit, 
     const uint32_t items = r.N / 4, per = (items + 1023) / 1024;
     const uint32_t threads = std::max(256u, ((items + per - 1) / per + 63) / 64 * 64);
     if (r.N % 128) nn.xsum = nullptr;
-    if (nn.bias) reduce_norm_kernel<true, MAPPED><<<r.M, threads, 0, st>>>(r, part, ksplit, mp, nn);
-    else reduce_norm_kernel<false, MAPPED><<<r.M, threads, 0, st>>>(r, part, ksplit, mp, nn);
+    if (!nn.xsum) nn.pack = XPack{};
+    if (nn.bias)
+      reduce_norm_kernel<true, MAPPED><<<r.M, threads, 0, st>>>(part, r.M, r.N, ksplit, r.epi, threads, r.resid, r.y, r.bias, nn, mp);
+    else
+      reduce_norm_kernel<false, MAPPED><<<r.M, threads, 0, st>>>(part, r.M, r.N, ksplit, r.epi, threads, r.resid, r.y, r.bias, nn, mp);
     r.next->done = true;
   } else {
-    skinny_reduce_kernel<MAPPED><<<skinny_reduce_blocks(r.M, r.N, r.epi), 256, 0, st>>>(r, part, ksplit, mp);
+    skinny_reduce_kernel<MAPPED><<<skinny_reduce_blocks(r.M, r.N, r.epi), 256, 0, st>>>(
+        part, r.M, r.N, ksplit, r.epi, r.ldy, r.y, r.resid, r.bias, r.yp, r.xsum_out, r.partials, mp);
   }
   return hipGetLastError();
 }
@@ -535,17 +522,10 @@ uint32_t skinny_reduce_blocks(uint32_t M, uint32_t N, uint32_t epi) {
 // floats; with EPI_SUMSQ a.partials holds skinny_reduce_blocks floats.
 template <int MT, bool DUAL, bool XMF>
 static void skinny_launch(const GemmArgs& a, dim3 grid, float* ws, uint32_t per, hipStream_t st) {
-  if (a.xsum) {       // block sums delivered by the kernel that wrote x
-    if (a.zp)
-      skinny_gemm_kernel<MT, DUAL, true, false, true><<<grid, 256, 0, st>>>(a, ws, per);
-    else
-      skinny_gemm_kernel<MT, DUAL, false, false, true><<<grid, 256, 0, st>>>(a, ws, per);
-    return;
-  }
   if (a.zp)
-    skinny_gemm_kernel<MT, DUAL, true, XMF, false><<<grid, 256, 0, st>>>(a, ws, per);
+    skinny_gemm_kernel<MT, DUAL, true, XMF><<<grid, 256, 0, st>>>(a, ws, per);
   else
-    skinny_gemm_kernel<MT, DUAL, false, XMF, false><<<grid, 256, 0, st>>>(a, ws, per);
+    skinny_gemm_kernel<MT, DUAL, false, XMF><<<grid, 256, 0, st>>>(a, ws, per);
 }
 hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
@@ -553,7 +533,10 @@ hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   if (!skinny_fits(a.dual ? 2 * a.M : a.M, a.N, a.K)) return hipErrorInvalidValue;
   const uint32_t ks = skinny_ksplit(a.N, a.K), ngrp = a.K >> 7, per = (ngrp + ks - 1) / ks;
   dim3 grid((a.N + SK_ROWS - 1) / SK_ROWS, ks);
-  if (a.dual && a.M > SKINNY_MAX_M_DUAL) {        // a workgroup per pass
+  if (a.xp.rows) {                                // activations packed by the kernel that made them
+    const hipError_t e = launch_few_gemm(a, ws, ks, per, st);
+    if (e != hipSuccess) return e;
+  } else if (a.dual && a.M > SKINNY_MAX_M_DUAL) {        // a workgroup per pass
     grid.x = (grid.x + 7) / 8 * 16;
     skinny_launch<2, false, false>(a, grid, ws, per, st);
   } else if (a.dual) {
@@ -571,6 +554,7 @@ hipError_t launch_skinny_gemm(const GemmArgs& a, float* ws, hipStream_t st) {
   GemmArgs r = a;                               // the reduction sees the stacked rows as one matrix
   if (a.dual) r.M = 2 * a.M;
   if (r.ldy || ((r.epi & EPI_SWIGLU) ? r.N >> 1 : r.N) % 128) r.xsum_out = nullptr;
+  if (!r.xsum_out) r.yp = XPack{};
   return launch_reduce<false>(r, ws, ks, MidPlan{}, st);
 }
 

@@ -479,6 +479,22 @@ def test_stacked_workgroups_of_either_pass_equal_separate_passes(oracle, name, b
     dm.close()
 
 
+@pytest.mark.parametrize("batch,seq", [(1, 2), (1, 16), (1, 17), (4, 8), (3, 11), (1, 57), (1, 64)])
+@pytest.mark.parametrize("arch,var", [("llama", ""), ("opt", ""), ("llama", True), ("opt", "zp16")])
+def test_few_token_layers_with_odd_slices(oracle, arch, var, batch, seq):
+    """Packed activations in one, two and four tiles: K slices of three groups that start on odd ones and reach into a second
+    noise counter (640 and 1152 inputs), a ragged last workgroup.  Hidden states of both passes against the oracle's, element by
+    element, and the losses of a step bit for bit those of two single passes."""
+    shape = dict(arch=arch, n_layers=1, d_model=640, n_heads=5, d_ffn=1152, vocab=500, max_seq=64, batch=batch, seq=seq)
+    om, dm = _models(oracle, shape, 77, 2.0, **_variant_args(var))
+    tok = synth.tokens(shape, 99)
+    res, both = _step_hidden(dm, _dev(tok), 5, 1e-2)
+    _check_both_passes(oracle, om, tok, 5, 1e-2, both)
+    if not (var == "zp16" and 32 < batch * seq):          # (that one's step takes another kernel in wide layers)
+        single = [float(dm.forward_loss(_dev(tok), 5, 1e-2, sign).item()) for sign in (1, -1)]
+        assert [res["loss_plus"], res["loss_minus"]] == single
+
+
 def test_few_token_step_of_a_layer_with_millions_of_rows():
     """64 tokens through a gate/up linear of 2^22 rows: the partial sums of both passes would need 2^31 bytes, those of one
     pass half of that, so the step runs two forwards: bit-identical to forward_loss."""
