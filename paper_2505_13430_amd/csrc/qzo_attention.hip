@@ -48,7 +48,8 @@ template <int DH, bool ROPE, bool LONG, bool PART = false>
 __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restrict__ qkv, uint32_t S,
                                                            uint32_t n_heads, bf16_t* __restrict__ out,
                                                            const float2* __restrict__ rope, uint32_t walk,
-                                                           const float* __restrict__ part, uint32_t slices) {
+                                                           const float* __restrict__ part, uint32_t slices,
+                                                           uint32_t B, uint32_t nx) {
   static_assert(!PART || (ROPE && !LONG), "slices: short sequences with the rotation here");
   constexpr int KB = 64;             // keys per tile
   constexpr int KT = DH / 16;        // k-steps of the score MFMA
@@ -70,14 +71,14 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
   // Workgroups are handed to the 8 XCDs round-robin in launch order, and each XCD has its own L2: the
   // query blocks of one (batch, head) are given to workgroups of one XCD, so that its K and V are
   // fetched into one L2 only; within that, heavy query blocks (late positions, many keys) come first.
-  uint32_t bx = blockIdx.x, hb = blockIdx.y + gridDim.y * blockIdx.z;
-  const uint32_t nhb = gridDim.y * gridDim.z;
+  uint32_t bx = blockIdx.x, hb = blockIdx.y + n_heads * blockIdx.z;
+  const uint32_t nhb = n_heads * B;
   if ((nhb & 7u) == 0u) {
-    const uint32_t L = blockIdx.x + gridDim.x * hb, slot = L >> 3;
-    hb = (L & 7u) + 8u * (slot / gridDim.x);
-    bx = slot % gridDim.x;
+    const uint32_t L = blockIdx.x + nx * hb, slot = L >> 3;
+    hb = (L & 7u) + 8u * (slot / nx);
+    bx = slot % nx;
   }
-  const uint32_t b = hb / gridDim.y, h = hb % gridDim.y;
+  const uint32_t b = hb / n_heads, h = hb % n_heads;
   const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
   const uint32_t lrow = lane & 31u, lhalf = lane >> 5;
   const bf16_t* base = qkv + (uint64_t)b * S * ld + h * DH;
@@ -132,14 +133,14 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
       *reinterpret_cast<u32x4*>((smem + (BUF) * 2 * TILE + TILE) + row * DH + (((ch >> 1) ^ vsw(row)) * 16 + (ch & 1u) * 8)) = vreg[i]; \
     }                                                                                        \
   } while (0)
-  const uint32_t pstride = PART ? gridDim.z * S * ld * 4u : 0u;             // bytes of a slice
+  const uint32_t pstride = PART ? B * S * ld * 4u : 0u;             // bytes of a slice
   const __amdgpu_buffer_rsrc_t rpart = __builtin_amdgcn_make_buffer_rsrc((void*)(PART ? part : nullptr), 0,
                                                                          PART ? (int)(slices * pstride) : 0, 0x00020000);
   // Direct loads: load n of wavefront w fills bytes (4 n + w) 1024 .. + 1023 of a tile, lane l its 16 bytes at
   // l 16: row and physical chunk follow, the logical chunk is the physical one un-swizzled.
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   const uint64_t base_addr = (uint64_t)(uintptr_t)base;
-  const uint64_t left = ((uint64_t)(gridDim.z - b) * S * ld - h * DH) * 2;      // bytes from base to the end of qkv
+  const uint64_t left = ((uint64_t)(B - b) * S * ld - h * DH) * 2;      // bytes from base to the end of qkv
   const i32x4 rqkv = {(int)(uint32_t)base_addr, (int)(uint32_t)(base_addr >> 32),
                       (int)(uint32_t)(left < 0xffffffffull ? left : 0xffffffffull), 0x00020000};
   uint32_t d_row[DTL ? NI : 1], d_koff[DTL ? NI : 1], d_voff[DTL ? NI : 1];
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
   // and has landed when each wavefront's own loads are back and the next barrier is passed.  One barrier
   // per tile either way.
   // walk != 0: the workgroups of a (batch, head) walk its query blocks themselves, late (heavy) blocks
-  // first.  gridDim.x == 1: one workgroup takes them all.  gridDim.x == 2: two workgroups share them in
+  // first.  nx == 1: one workgroup takes them all.  nx == 2: two workgroups share them in
   // snake order (blocks n-1 | n-2, n-3 | n-4, n-5 | ... from the heavy end: equal work for 4 blocks);
   // the launch-index remap above puts the two on one XCD in neighbouring slots, they start together
   // and ask for the same K and V tiles at about the same time, so the second one's loads hit the L2
@@ -191,8 +192,8 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
   const bool walk_ = LONG && walk != 0u;
   const uint32_t n_it = walk_ ? nqb : 1u;
   for (uint32_t it = 0; it < n_it; ++it) {
-  if (walk_ && gridDim.x == 2u && (((it + 1u) >> 1) & 1u) != bx) continue;
-  const uint32_t q0 = (walk_ ? nqb - 1 - it : gridDim.x - 1 - bx) * 128;
+  if (walk_ && nx == 2u && (((it + 1u) >> 1) & 1u) != bx) continue;
+  const uint32_t q0 = (walk_ ? nqb - 1 - it : nx - 1 - bx) * 128;
   const uint32_t qq = q0 + wave * 32 + lrow;            // this lane's query
   const uint32_t qc = min(qq, S - 1);
   bf16x8 qf[KT];
@@ -524,21 +525,21 @@ hipError_t launch_attention(const void* qkv, uint32_t B, uint32_t S, uint32_t n_
   if (part) {
     if (!rope || !attention_adds_slices(B, S, n_heads, dh, slices)) return hipErrorInvalidValue;
     if (dh == 128)
-      attention_kernel<128, true, false, true><<<grid, 256, 0, st>>>(nullptr, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+      attention_kernel<128, true, false, true><<<grid, 256, 0, st>>>(nullptr, S, n_heads, (bf16_t*)out, tb, walk, part, slices, B, grid.x);
     else
-      attention_kernel<64, true, false, true><<<grid, 256, 0, st>>>(nullptr, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+      attention_kernel<64, true, false, true><<<grid, 256, 0, st>>>(nullptr, S, n_heads, (bf16_t*)out, tb, walk, part, slices, B, grid.x);
   } else if (dh == 128 && rope)
-    attention_kernel<128, true, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+    attention_kernel<128, true, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices, B, grid.x);
   else if (dh == 128 && lng)
-    attention_kernel<128, false, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+    attention_kernel<128, false, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices, B, grid.x);
   else if (dh == 128)
-    attention_kernel<128, false, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+    attention_kernel<128, false, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices, B, grid.x);
   else if (dh == 64 && rope)
-    attention_kernel<64, true, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+    attention_kernel<64, true, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices, B, grid.x);
   else if (dh == 64 && lng)
-    attention_kernel<64, false, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+    attention_kernel<64, false, true><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices, B, grid.x);
   else if (dh == 64)
-    attention_kernel<64, false, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices);
+    attention_kernel<64, false, false><<<grid, 256, 0, st>>>((const bf16_t*)qkv, S, n_heads, (bf16_t*)out, tb, walk, part, slices, B, grid.x);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

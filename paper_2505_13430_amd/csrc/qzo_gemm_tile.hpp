@@ -27,14 +27,14 @@ struct TileWalk {
   uint32_t tiles_m, tiles_n, id, end, stride;      // entries of the order; this workgroup's next one
   uint32_t first, in;                              // first M-tile of its group, entry within the group
 };
-__device__ __forceinline__ TileWalk tile_walk_of(uint32_t tiles_m, uint32_t tiles_n) {
+__device__ __forceinline__ TileWalk tile_walk_of(uint32_t tiles_m, uint32_t tiles_n, uint32_t wgs) {
   const uint32_t total = tiles_m * tiles_n, per = (total + 7) >> 3, xcd = blockIdx.x & 7u;
   TileWalk w;
   w.tiles_m = tiles_m;
   w.tiles_n = tiles_n;
   w.id = xcd * per + (blockIdx.x >> 3);
   w.end = min((xcd + 1) * per, total);
-  w.stride = gridDim.x >> 3;
+  w.stride = wgs >> 3;
   const uint32_t width = WALK_M * tiles_n, group = w.id / width;
   w.first = group * WALK_M;
   w.in = w.id - group * width;
@@ -43,7 +43,7 @@ __device__ __forceinline__ TileWalk tile_walk_of(uint32_t tiles_m, uint32_t tile
 // With K slices (split-K) the walk runs over feature-tiles x slices: entry tn of the walk is feature
 // tile tn % real_tiles_n, slice tn / real_tiles_n.
 __device__ __forceinline__ TileWalk tile_walk_init(uint32_t M, uint32_t N, uint32_t ksplit = 1) {
-  return tile_walk_of((M + BM - 1) / BM, ((N + BN - 1) / BN) * ksplit);
+  return tile_walk_of((M + BM - 1) / BM, ((N + BN - 1) / BN) * ksplit, gridDim.x);
 }
 // Tile of the walk's current entry; false when the walk is over.
 __device__ __forceinline__ bool tile_walk_get(const TileWalk& w, uint32_t& tm, uint32_t& tn) {

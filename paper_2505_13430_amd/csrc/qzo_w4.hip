@@ -33,6 +33,7 @@
 #include "qzo_gemm_tile.hpp"
 #include "qzo_nibble.hpp"
 #include <algorithm>
+#include <cstddef>
 #include <type_traits>
 
 namespace qzo {
@@ -62,8 +63,38 @@ struct W4Lds {
 template <int V>
 using Int = std::integral_constant<int, V>;
 
+// What a wavefront needs later than its first loads.  (Those want x .. zp, which arrive in registers; an argument read from
+// memory takes 1.2 us.)
+struct W4Rest {
+  void* y;
+  const void *resid, *bias;
+  float *partials, *split_ws;
+  const float* rope;
+  uint32_t rope_S, ldy, row_base, seed_lo, seed_hi;
+  float eps_signed;
+};
+struct W4Args {
+  const void *x, *w, *s;
+  uint32_t M, N, K, second_row, kt_per, packed;
+  const void* zp;
+  W4Rest rest;
+};
+// The rest, read where it is asked for: left to itself the compiler reads all of it first and waits.
+typedef const __attribute__((address_space(4))) W4Rest* W4RestPtr;
+__device__ __forceinline__ W4RestPtr w4_rest() {
+  auto p = (const __attribute__((address_space(4))) unsigned char*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(W4Args, rest);
+  asm volatile("" : "+s"(p));
+  return (W4RestPtr)p;
+}
+// packed: epilogue flags, fp16 scales, heads of 128, workgroups, K slices
+__host__ __device__ constexpr uint32_t w4_pack(uint32_t epi, bool s_fp16, bool rope128, uint32_t wgs, uint32_t ksplit) {
+  return epi | (s_fp16 ? 64u : 0u) | (rope128 ? 128u : 0u) | (wgs << 8) | (ksplit << 20);
+}
+
 template <int MT, int FMT>
-__global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
+__global__ __launch_bounds__(256, 1) void w4_gemm_kernel(const void* x, const void* w, const void* s, uint32_t M, uint32_t N, uint32_t K,
+                                                         uint32_t second_row, uint32_t kt_per, uint32_t packed, const void* zp,
+                                                         W4Rest) {
   typedef W4Lds<MT, FMT> L;
   constexpr bool ZP = FMT == W4_ZP, NF4 = FMT == W4_NF4;
   constexpr int SLOTS = 2 * MT;                    // MFMAs of a k-step
@@ -76,43 +107,43 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const uint32_t lrow = lane & 31u, half = lane >> 5;
-  const uint32_t K = a.K, G = K >> 7;
-  const bool swiglu = (a.epi & EPI_SWIGLU) != 0, rope = (a.epi & EPI_ROPE) != 0, s_fp16 = a.s_fp16 != 0;
-  const bool rope128 = rope && a.rope_dh == 128;
-  TileWalk walk = tile_walk_of(p.tiles_m, p.tiles_n * p.ksplit);
+  const uint32_t G = K >> 7, epi = packed & 63u, wgs = (packed >> 8) & 0xfffu, ksplit = packed >> 20;
+  const bool swiglu = (epi & EPI_SWIGLU) != 0, rope = (epi & EPI_ROPE) != 0, s_fp16 = (packed & 64u) != 0;
+  const bool rope128 = (packed & 128u) != 0;
+  const uint32_t tiles_n = (N + 255u) >> 8, tiles_per_pass = (M + 32 * MT - 1) / (32 * MT);
+  TileWalk walk = tile_walk_of(second_row ? 2 * tiles_per_pass : tiles_per_pass, tiles_n * ksplit, wgs);
   uint32_t tile_m, tile_n;
   if (!tile_walk_get(walk, tile_m, tile_n)) {
-    if ((a.epi & EPI_SUMSQ) && threadIdx.x == 0) a.partials[blockIdx.x] = 0.0f;
+    if ((epi & EPI_SUMSQ) && threadIdx.x == 0) w4_rest()->partials[blockIdx.x] = 0.0f;
     return;
   }
 
   auto rsrc = [](const void* q, uint64_t bytes) {
     return i32x4{(int)(uint32_t)(uintptr_t)q, (int)(uint32_t)((uintptr_t)q >> 32), (int)bytes, 0x00020000};
   };
-  const uint32_t rows_all = p.rows;
-  const i32x4 rx = rsrc(a.x, (uint64_t)rows_all * K * 2), rw = rsrc(a.w, (uint64_t)a.N * (K >> 1));
-  const i32x4 rs = rsrc(a.s, (uint64_t)a.N * G * SCALE_BYTES), rz = rsrc(ZP ? a.zp : a.s, (uint64_t)a.N * G);
+  const uint32_t rows_all = second_row ? second_row + M : M;
+  const i32x4 rx = rsrc(x, (uint64_t)rows_all * K * 2), rw = rsrc(w, (uint64_t)N * (K >> 1));
+  const i32x4 rs = rsrc(s, (uint64_t)N * G * SCALE_BYTES), rz = rsrc(ZP ? zp : s, (uint64_t)N * G);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
 
   // a unit of work: K slice kslice of output tile (tile_m, tile_n), k-tiles kt0 .. kt0 + 2 ng - 1
-  uint32_t kslice, kt0, ng, row0, row_last, noise_row, pass;
+  uint32_t kslice, kt0, ng, row0, row_last, own, noise_row, pass;
   uint32_t xo[MT], wo[4], so;
   float eps;
   auto point = [&]() Q4_INLINE {
-    kslice = p.ksplit > 1 ? tile_n / p.tiles_n : 0u;
-    tile_n -= kslice * p.tiles_n;
-    kt0 = kslice * p.kt_per;
-    ng = min(p.kt_per, K / BK - kt0) >> 1;
-    pass = tile_m >= p.tiles_per_pass ? 1u : 0u;
-    row0 = pass * p.second_row + (tile_m - pass * p.tiles_per_pass) * (32 * MT);
-    row_last = pass * p.second_row + a.M - 1;
-    eps = pass ? -a.eps_signed : a.eps_signed;
+    kslice = ksplit > 1 ? tile_n / tiles_n : 0u;
+    tile_n -= kslice * tiles_n;
+    kt0 = kslice * kt_per;
+    ng = min(kt_per, K / BK - kt0) >> 1;
+    pass = tile_m >= tiles_per_pass ? 1u : 0u;
+    row0 = pass * second_row + (tile_m - pass * tiles_per_pass) * (32 * MT);
+    row_last = pass * second_row + M - 1;
     // fused SwiGLU: a wavefront's rows are 32 gate rows and the 32 up rows of the same features; rotary embedding of
     // heads of 128 (N % 256 == 0): 32 features and their partners 64 further on
     auto wrow = [&](uint32_t r) Q4_INLINE {
       if (rope128) return tile_n * 256u + (r >> 7) * 128u + ((r >> 6) & 1u) * 32u + ((r >> 5) & 1u) * 64u + (r & 31u);
-      return swiglu ? ((r >> 5) & 1u) * (a.N >> 1) + tile_n * 128u + (r >> 6) * 32u + (r & 31u)
-                    : min(tile_n * 256u + r, a.N - 1);
+      return swiglu ? ((r >> 5) & 1u) * (N >> 1) + tile_n * 128u + (r >> 6) * 32u + (r & 31u)
+                    : min(tile_n * 256u + r, N - 1);
     };
     // a load instruction fills 1 KB of LDS in lane order: 8 rows of 128 bytes of activations, 16 rows of 64 bytes of
     // weights; the swizzles of their 16-byte chunks are applied on the memory side
@@ -124,9 +155,8 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       wo[q] = wrow(wave * 64 + 16 * q + (lane >> 2)) * (K >> 1) + (((lane & 3u) ^ ((lane >> 4) & 3u)) << 4) + kt0 * (BK / 2);
-    const uint32_t own = wrow(wave * 64 + lane);
+    own = wrow(wave * 64 + lane);
     so = own * G + (kt0 >> 1);
-    noise_row = a.row_base + own;
   };
   auto load_x = [&](int i, uint32_t kt, uint32_t stage) Q4_INLINE {
     Q4_DTL("buffer_load_dwordx4", rx, lds0 + stage + (4 * i + wave) * 1024, xo[i], kt * (BK * 2));
@@ -190,10 +220,12 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
   };
   // noise of the lane's own row: a counter serves eight scales, a word two: those of two groups, or of the two blocks of
   // a NormalFloat-4 group g
+  uint32_t row_base, seed_lo, seed_hi;
+  float eps_signed;
   auto noise = [&](uint32_t g, bool first) Q4_INLINE {
     const uint32_t pair = NF4 ? g : g >> 1;
     if (first || ((pair & 3u) == 0 && (NF4 || (g & 1u) == 0))) {
-      const u32x4_t w = philox4x32_10(noise_row, pair >> 2, 0u, 0u, a.seed_lo, a.seed_hi);
+      const u32x4_t w = philox4x32_10(noise_row, pair >> 2, 0u, 0u, seed_lo, seed_hi);
       zw0 = w.x; zw1 = w.y; zw2 = w.z; zw3 = w.w;
     }
     if (NF4 || (g & 1u) == 0) {
@@ -374,20 +406,21 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
     next_stage();
   };
 
-  // output rows and features of a lane: token row0 + 32 i + lrow, features 8 b + 4 half + c of feature tile j; after
-  // QZO swap of two register groups a lane owns eight consecutive features
-  const uint32_t ldy = a.ldy ? a.ldy : a.N, NO = swiglu ? a.N >> 1 : a.N;
-  const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
-      a.y, 0, (int)(((uint64_t)(rows_all - 1) * (swiglu ? NO : ldy) + NO) * 2), 0x00020000);
   // sum of squares: unit by unit in double, in the LDS (no register is held over the k-loop): fp32 sums that go on over all
   // units lose up to 1.5e-5 where the terms are alike.  One linear 2048 x 11008 x 4096, both signs, against such sums:
   // 0.337 against 0.336 ms (two runs of either differ by 0.4 %); with a wavefront's sum taken per unit 1.2 % more.
   double* const ssq_units = reinterpret_cast<double*>(lds + L::RED) + t;
-  if (a.epi & EPI_SUMSQ) *ssq_units = 0.0;
+  if (epi & EPI_SUMSQ) *ssq_units = 0.0;
 
   point();
   request_first();
+  {
+    const W4RestPtr a = w4_rest();
+    row_base = a->row_base; seed_lo = a->seed_lo; seed_hi = a->seed_hi; eps_signed = a->eps_signed;
+  }
   for (;;) {
+    noise_row = row_base + own;
+    eps = pass ? -eps_signed : eps_signed;
     sync(Int<2 * MT + L::NW>(), Int<1>());          // the first group's weights and the first k-tile have landed
     st_cur = 0; st_next = L::X; st_load = 2 * L::X;
     read_raw(0, 0u); read_raw(1, 0u); read_scale(0u);
@@ -406,7 +439,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
     group(0u, Int<1>());
     for (uint32_t g = 1; g < ng; ++g) group(g, Int<0>());
 
-    const uint32_t m0 = row0 + lrow, m_last = row_last, n0 = tile_n * 256u + wave * 64u, slice = kslice;
+    const uint32_t r0 = row0, m0 = row0 + lrow, m_last = row_last, n0 = tile_n * 256u + wave * 64u, slice = kslice;
     const uint32_t done_n = tile_n;
     tile_walk_next(walk);
     const bool more = tile_walk_get(walk, tile_m, tile_n);
@@ -414,6 +447,12 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       point();
       request_first();
     }
+    const W4RestPtr a = w4_rest();
+    // output rows and features of a lane: token row0 + 32 i + lrow, features 8 b + 4 half + c of feature tile j; after
+    // QZO swap of two register groups a lane owns eight consecutive features
+    const uint32_t ldy = a->ldy ? a->ldy : N, NO = swiglu ? N >> 1 : N;
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
+        a->y, 0, (int)(((uint64_t)(rows_all - 1) * (swiglu ? NO : ldy) + NO) * 2), 0x00020000);
     asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 // accumulators are read out one piece at a time (left to itself the compiler copies all of them to vector registers)
@@ -431,9 +470,10 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       (HI)[c_] = __uint_as_float(r_[1]);                                                     \
     }                                                                                        \
   } while (0)
-    if (p.ksplit > 1) {
+    if (ksplit > 1) {
       // this slice's fp32 sums, [slice][rows][N]; the epilogue proper runs in the reduction
-      float* part = a.split_ws + (uint64_t)slice * rows_all * a.N;
+      const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+          a->split_ws + ((uint64_t)slice * rows_all + r0) * N, 0, (int)((m_last - r0 + 1) * N * 4), 0x00020000);
 #pragma unroll
       for (int u = 0; u < 4 * MT; ++u) {
         const int i = u >> 2, j = (u >> 1) & 1, bp = u & 1;
@@ -444,11 +484,11 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
           for (int c = 0; c < 4; ++c) Q4_ACC(i, j, 4 * (2 * bp + h) + c, v[h][c]);
         Q4_SWAP8(v[0], v[1]);
         const uint32_t m = m0 + i * 32, n = n0 + j * 32 + (2u * bp + half) * 8u;
-        if (m <= m_last && n < a.N) {
-          float4* dst = reinterpret_cast<float4*>(part + (uint64_t)m * a.N + n);
-          dst[0] = make_float4(v[0][0], v[0][1], v[0][2], v[0][3]);
-          dst[1] = make_float4(v[1][0], v[1][1], v[1][2], v[1][3]);
-        }
+        const uint32_t o = m <= m_last && n < N ? ((m - r0) * N + n) * 4u : OUT_OF_RANGE;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(v[h][0]), __float_as_uint(v[h][1]), __float_as_uint(v[h][2]),
+                                                       __float_as_uint(v[h][3])}, rp, (int)(o + 16 * h), 0, 0);
         if (u & 1) __builtin_amdgcn_sched_barrier(0);
       }
       stores = 1;
@@ -479,14 +519,14 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       // qkv [rows, 3d] with the rotary embedding on its q and k thirds: the wavefront's two feature tiles hold feature f
       // and feature f + dh/2 of a head for the same token.  An output is rounded to bf16 first (what a separate pass
       // would read), rotated in fp32 at its position and rounded again.
-      const uint32_t hd = a.rope_dh >> 1;
+      const uint32_t hd = rope128 ? 64u : 32u;
       const uint32_t na = (rope128 ? done_n * 256u + (wave >> 1) * 128u + (wave & 1u) * 32u : n0) + half * 8u;
-      const bool rotate = na < (a.N / 3u) * 2u;            // a wavefront's columns lie within one third of qkv
-      const float2* table = reinterpret_cast<const float2*>(a.rope) + (rope128 ? (wave & 1u) * 32u : 0u) + half * 8u;
-      const uint32_t pass_row0 = m0 >= p.second_row ? p.second_row : 0u;
+      const bool rotate = na < (N / 3u) * 2u;            // a wavefront's columns lie within one third of qkv
+      const float2* table = reinterpret_cast<const float2*>(a->rope) + (rope128 ? (wave & 1u) * 32u : 0u) + half * 8u;
+      const uint32_t pass_row0 = m0 >= second_row ? second_row : 0u;
       // the (cos, sin) values of a step are requested AHEAD steps before they are used
       auto table_of = [&](int u) Q4_INLINE {
-        const uint32_t pos = (min(m0 + (u >> 1) * 32, m_last) - pass_row0) % a.rope_S;
+        const uint32_t pos = (min(m0 + (u >> 1) * 32, m_last) - pass_row0) % a->rope_S;
         return reinterpret_cast<const float4*>(table + (uint64_t)pos * hd + (u & 1) * 16u);
       };
       constexpr int AHEAD = NF4 && MT == 8 ? 2 : 4;        // (registers)
@@ -531,20 +571,20 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
           }
         }
         const uint32_t m = m0 + i * 32, n = na + bp * 16u;
-        const bool inside = m <= m_last && n < a.N;
-        const uint32_t o = (m * a.N + n) * 2u;
+        const bool inside = m <= m_last && n < N;
+        const uint32_t o = (m * N + n) * 2u;
         __builtin_amdgcn_raw_buffer_store_b128(oa, ry, (int)(inside ? o : OUT_OF_RANGE), 0, 0);
         __builtin_amdgcn_raw_buffer_store_b128(ob, ry, (int)(inside ? o + hd * 2u : OUT_OF_RANGE), 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
       stores = 4 * MT;
     } else {
-      const bool with_resid = (a.epi & EPI_RESIDUAL) != 0, with_bias = (a.epi & EPI_BIAS) != 0;
+      const bool with_resid = (epi & EPI_RESIDUAL) != 0, with_bias = (epi & EPI_BIAS) != 0;
       const __amdgpu_buffer_rsrc_t rr_ = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<void*>(with_resid ? a.resid : a.y), 0, (int)(((uint64_t)(rows_all - 1) * ldy + a.N) * 2), 0x00020000);
+          const_cast<void*>(with_resid ? a->resid : a->y), 0, (int)(((uint64_t)(rows_all - 1) * ldy + N) * 2), 0x00020000);
       auto at = [&](int u) Q4_INLINE {
         const uint32_t m = m0 + (u >> 2) * 32, n = n0 + ((u >> 1) & 1) * 32 + (2u * (u & 1) + half) * 8u;
-        return m <= m_last && n < a.N ? (m * ldy + n) * 2u : OUT_OF_RANGE;
+        return m <= m_last && n < N ? (m * ldy + n) * 2u : OUT_OF_RANGE;
       };
       // residuals are requested AHEAD pieces before they are used: a few memory latencies per tile, not one per piece
       constexpr int AHEAD = NF4 && MT == 8 ? 8 : 12;
@@ -557,7 +597,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
       if (with_bias) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          bb[c] = *reinterpret_cast<const uint4*>((const bf16_t*)a.bias + min(n0 + (c >> 1) * 32 + (2u * (c & 1) + half) * 8u, a.N - 8));
+          bb[c] = *reinterpret_cast<const uint4*>((const bf16_t*)a->bias + min(n0 + (c >> 1) * 32 + (2u * (c & 1) + half) * 8u, N - 8));
       }
       auto add8 = [&](float (&v)[2][4], u32x4 w) Q4_INLINE {
 #pragma unroll
@@ -582,7 +622,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
           add8(v, rr[u % AHEAD]);
           if (u + AHEAD < 4 * MT) rr[u % AHEAD] = __builtin_amdgcn_raw_buffer_load_b128(rr_, (int)at(u + AHEAD), 0, 0);
         }
-        if (a.epi & EPI_RELU) {
+        if (epi & EPI_RELU) {
 #pragma unroll
           for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -591,7 +631,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
         const u32x4 out = {pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3]),
                            pack_bf16x2(v[1][0], v[1][1]), pack_bf16x2(v[1][2], v[1][3])};
         __builtin_amdgcn_raw_buffer_store_b128(out, ry, (int)o, 0, 0);
-        if ((a.epi & EPI_SUMSQ) && o != OUT_OF_RANGE) {
+        if ((epi & EPI_SUMSQ) && o != OUT_OF_RANGE) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const float q0 = __uint_as_float(out[q] << 16), q1 = __uint_as_float(out[q] & 0xffff0000u);
@@ -602,19 +642,19 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(GemmArgs a, W4Plan p) {
         if (u & 1) __builtin_amdgcn_sched_barrier(0);
       }
       stores = 4 * MT;
-      if (a.epi & EPI_SUMSQ) *ssq_units += (double)(ssq[0] + ssq[1]);
+      if (epi & EPI_SUMSQ) *ssq_units += (double)(ssq[0] + ssq[1]);
     }
 #undef Q4_SWAP8
 #undef Q4_ACC
     if (!more) break;
   }
-  if (a.epi & EPI_SUMSQ) {
+  if (epi & EPI_SUMSQ) {
     const float sum = wave_sum((float)*ssq_units);
     float* red = reinterpret_cast<float*>(lds + L::RED);
     __syncthreads();
     if (lane == 0) red[wave] = sum;
     __syncthreads();
-    if (t == 0) a.partials[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+    if (t == 0) w4_rest()->partials[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
   }
   asm volatile("s_waitcnt vmcnt(0)" : : : "memory");         // loads past the end still write the LDS
 }
@@ -631,9 +671,14 @@ hipError_t w4_prepare() {
 }
 template <int MT>
 void w4_launch(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
-  if (a.nf4) w4_gemm_kernel<MT, W4_NF4><<<p.wgs, 256, W4Lds<MT, W4_NF4>::BYTES, st>>>(a, p);
-  else if (a.zp) w4_gemm_kernel<MT, W4_ZP><<<p.wgs, 256, W4Lds<MT, W4_ZP>::BYTES, st>>>(a, p);
-  else w4_gemm_kernel<MT, W4_INT4><<<p.wgs, 256, W4Lds<MT, W4_INT4>::BYTES, st>>>(a, p);
+  const W4Rest r = {a.y, a.resid, a.bias, a.partials, a.split_ws, a.rope, a.rope_S, a.ldy, a.row_base, a.seed_lo, a.seed_hi, a.eps_signed};
+  const uint32_t packed = w4_pack(a.epi, a.s_fp16 != 0, (a.epi & EPI_ROPE) && a.rope_dh == 128, p.wgs, p.ksplit);
+#define Q4_LAUNCH(FMT) \
+  w4_gemm_kernel<MT, FMT><<<p.wgs, 256, W4Lds<MT, FMT>::BYTES, st>>>(a.x, a.w, a.s, a.M, a.N, a.K, p.second_row, p.kt_per, packed, a.zp, r)
+  if (a.nf4) Q4_LAUNCH(W4_NF4);
+  else if (a.zp) Q4_LAUNCH(W4_ZP);
+  else Q4_LAUNCH(W4_INT4);
+#undef Q4_LAUNCH
 }
 
 }  // namespace
@@ -676,6 +721,7 @@ hipError_t launch_w4_tiles(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
     ready = true;
   }
   if ((a.epi & EPI_SUMSQ) && p.wgs > a.n_partials) return hipErrorInvalidValue;
+  if (a.epi >= 64u || p.wgs >= 4096u || p.ksplit >= 4096u) return hipErrorInvalidValue;        // w4_pack
   switch (p.mt) {
     case 1: w4_launch<1>(a, p, st); break;
     case 2: w4_launch<2>(a, p, st); break;
