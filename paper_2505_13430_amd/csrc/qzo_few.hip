@@ -10,15 +10,17 @@
 // oldest one's.  The arguments of the first loads arrive in registers (read from memory: 1.2 us); the noise of the eight groups
 // is drawn while the first loads are on their way, either half of a wavefront half of the variates.  With one token tile the K
 // loop holds no barrier: a wavefront waits for its own weights only.  With more tiles the activations are a ring of six (two
-// tiles) or three (four) groups.  One wavefront serves the tokens of both passes: a weight is unpacked once for a step, where
+// tiles) or four (four) groups, refilled by loads dealt out behind the MFMAs.  One wavefront serves the tokens of both passes: a weight is unpacked once for a step, where
 // a workgroup per pass unpacked it twice.
 //
 // Bound, 1 x 16 tokens of the 7B shape, one launch of 12288 / 22016 / 4096 rows (25 / 45 / 23 MB): 7.2 / 10.1 / 8.2 us from its
 // first instruction to its last (before: 12.3 / 17.1 / 12.9), of which reading alone takes some 3.5 / 6.5 / 3.5 whatever the
 // pattern (128 bytes of eight rows, 512 of two, linear: 8.4 us a launch of 45 MB, all included); eight groups of 850 cycles
 // behind the first loads and 1400 cycles of stores are what does not overlap.  Step 2.67 -> 2.26 ms.
-// Four tiles (57 tokens): 3600 cycles a group of 256 rows, of which the LDS delivers fragments and block sums for 3300 and the
-// matrix unit is busy 2050; step 4.81 -> 4.43 ms.
+// Four tiles (57 tokens), workgroups of 192 rows: a group takes 2000 cycles (two wavefronts on a SIMD, 1024 of MFMAs each), 2950
+// with the six loads of 1 KB that refill the ring, whatever places they take; then 4400 cycles of stores, 22 MB of partial sums
+// at the rate of the last-level cache.  12288 / 22016 / 4096 rows 17.4 / 33.7 / 17.9 us, step 4.81 -> 4.10 ms (refills in a
+// row and the barrier at the head of a group, 256 rows: 3600 cycles a group, 4.43 ms).
 // Tried: all four rounds of weights requested at once (everything arrives, then everything is computed: 10.0 / 13.7 / 9.9 us);
 // activations of the later groups behind the first weights (no difference).
 #include "qzo_device.hpp"
@@ -37,7 +39,7 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 // groups of 32 rows) turns from "a lane per 16 bytes of a line" to "a lane per row".
 template <int MT>
 struct FewLds {
-  static constexpr int XS = MT == 1 ? 8 : (MT == 2 ? 6 : 3), W = MT == 1 ? 12 : 8;      // W: most wavefronts
+  static constexpr int XS = MT == 1 ? 8 : (MT == 2 ? 6 : 4), W = MT == 1 ? 12 : (MT == 2 ? 8 : 6);      // W: most wavefronts
   static constexpr uint32_t GROUP = MT * 8192u, SUMS = XS * GROUP, WT = SUMS + 8 * MT * 128u;
   static constexpr uint32_t bytes(uint32_t waves) { return WT + waves * 4096u; }
   static_assert(WT + W * 4096u <= 160 * 1024, "LDS of a compute unit");
@@ -178,48 +180,41 @@ __global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void
     wstore(std::integral_constant<int, 0>());
     wread(std::integral_constant<int, 0>());
 
-    // group d and those behind it (nested, so that a wait for weights counts the loads that were issued in between and
-    // not the least of several paths)
+    // Group d and those behind it (nested, so that a wait for weights counts the loads that were issued in between and not the
+    // least of several paths).  Its last tile is rescaled behind the next group's first MFMAs, its first fragments are read
+    // behind the last ones of the group before; the barrier of the ring stands in its second half, where nobody waits for
+    // operands (at the head of a group, with everything begun and ended there: 3300 cycles a group of four tiles).
+    constexpr int R = 4;                            // fragments read ahead of their MFMA
+    constexpr bool LATE = MT > 1;                   // (one tile: three wavefronts a SIMD, and 135 registers too many)
+    bf16x8 xf[R], wf[8];
+    floatx16 p[2];                                  // sums of the tile at work and of the one before
+    float4 xg[4];                                   // block sums of the latter's, then the former's tile rows
+    float se_last_p = 0.0f, se_last_m = 0.0f, cz_last = 0.0f;
+    auto rescale = [&](int i, int m, int b, float se_p, float se_m, float cz) __attribute__((always_inline)) {
+      const float se = DUAL && 2 * m + (b >= 2) >= MT ? se_m : se_p;
+      const float4 x = xg[b];
+      const floatx16& q = p[i];
+      y[m][4 * b + 0] = __builtin_fmaf(se, __builtin_fmaf(cz, x.x, q[4 * b + 0]), y[m][4 * b + 0]);
+      y[m][4 * b + 1] = __builtin_fmaf(se, __builtin_fmaf(cz, x.y, q[4 * b + 1]), y[m][4 * b + 1]);
+      y[m][4 * b + 2] = __builtin_fmaf(se, __builtin_fmaf(cz, x.z, q[4 * b + 2]), y[m][4 * b + 2]);
+      y[m][4 * b + 3] = __builtin_fmaf(se, __builtin_fmaf(cz, x.w, q[4 * b + 3]), y[m][4 * b + 3]);
+    };
+#pragma unroll
+    for (int q = 0; q < R; ++q) xf[q] = *reinterpret_cast<const bf16x8*>(lds + q * 1024 + lane * 16);
     auto group = [&](auto&& self, auto D_) __attribute__((always_inline)) -> void {
-      constexpr int d = decltype(D_)::value;
-      // the next round's weights take the place of this one's, whose last group is in registers
-      if constexpr ((d & 1) && d < 7) wstore(std::integral_constant<int, (d + 1) / 2>());
-      if constexpr (XS < 8) {
-        // group d has landed (those behind it may be on their way), everyone has read group d - 1
-        constexpr bool wait = MT == 4 ? d >= XS : d == XS, refill = d >= 1 && d - 1 + XS < 8;
-        if (wait) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(MT == 4 && d < 7 ? MT * 8 / L::W : 0) : "memory");
-        if (wait || refill) {
-          __builtin_amdgcn_s_barrier();
-          asm volatile("" ::: "memory");
-        }
-        if (refill) {
-          constexpr uint32_t slot = (d - 1) % XS;
-          for (uint32_t q = wave; q < MT * 8; q += W)
-            QF_DTL(rx, lds0 + slot * L::GROUP + q * 1024,
-                   d - 1 + XS < (int)cnt ? (gb + d - 1 + XS) * L::GROUP + q * 1024 + lane * 16 : OUT_OF_RANGE);
-        }
-      }
+      constexpr int d = decltype(D_)::value, Q = MT * 8;
+      // the ring: group d + 1 has landed (those behind it may be on their way), everyone has read group d - 1, whose place
+      // is refilled, a load behind every other MFMA
+      constexpr bool wait = d + 1 >= XS && d < 7, refill = d >= 1 && d - 1 + XS < 8;
+      constexpr int NR = (Q + (MT == 4 ? L::W : 4) - 1) / (MT == 4 ? L::W : 4), BAR = Q - 2 * NR;       // NR: loads of a wavefront
+      static_assert(XS == 8 || BAR >= 0, "slots for the loads");
+      const uint32_t refill_off = d - 1 + XS < (int)cnt ? (gb + d - 1 + XS) * L::GROUP + lane * 16 : OUT_OF_RANGE;
       const unsigned char* const xb = lds + (d % XS) * L::GROUP + lane * 16;
+      const unsigned char* const xb_next = lds + ((d + 1) % XS) * L::GROUP + lane * 16;
       const float* const sums = reinterpret_cast<const float*>(lds + L::SUMS) + d * ROWS + 4 * half;
       const float s0 = scale_to_f32((d & 1) ? sv[d >> 1] >> 16 : sv[d >> 1] & 0xffffu, s_fp16);
       const float se_p = __builtin_fmaf(a.eps_signed, z[d], s0), se_m = __builtin_fmaf(-a.eps_signed, z[d], s0);
       const float cz = ZP ? -(128.0f + (float)((zv[d >> 2] >> (8 * (d & 3))) & 0xffu)) : -136.0f;
-      constexpr int R = 4;                          // fragments read ahead of their MFMA
-      bf16x8 xf[R], wf[8];
-      floatx16 p[2];
-      float4 xg[2][4];
-      auto xread = [&](int q) __attribute__((always_inline)) { xf[q % R] = *reinterpret_cast<const bf16x8*>(xb + q * 1024); };
-      auto rescale = [&](int m, int b) __attribute__((always_inline)) {
-        const float se = DUAL && 2 * m + (b >= 2) >= MT ? se_m : se_p;
-        const float4 x = xg[m & 1][b];
-        const floatx16& q = p[m & 1];
-        y[m][4 * b + 0] = __builtin_fmaf(se, __builtin_fmaf(cz, x.x, q[4 * b + 0]), y[m][4 * b + 0]);
-        y[m][4 * b + 1] = __builtin_fmaf(se, __builtin_fmaf(cz, x.y, q[4 * b + 1]), y[m][4 * b + 1]);
-        y[m][4 * b + 2] = __builtin_fmaf(se, __builtin_fmaf(cz, x.z, q[4 * b + 2]), y[m][4 * b + 2]);
-        y[m][4 * b + 3] = __builtin_fmaf(se, __builtin_fmaf(cz, x.w, q[4 * b + 3]), y[m][4 * b + 3]);
-      };
-#pragma unroll
-      for (int q = 0; q < R; ++q) xread(q);
       wf[0] = unpack8_biased(wd[d & 1][0], nc);
       __builtin_amdgcn_sched_barrier(0);
       // one slot per MFMA: what else the wavefront has to do is dealt out behind them
@@ -227,21 +222,42 @@ __global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void
       for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int j = 0; j < 8; ++j) {               // k-step j: inputs 64 half + 8 j .. + 7 of the group
-          const int q = m * 8 + j;
+          const int q = m * 8 + j, i = (d * MT + m) & 1;
           const floatx16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-          p[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[q % R], wf[j], j == 0 ? zero : p[m & 1], 0, 0, 0);
-          if (q + R < MT * 8) xread(q + R);
+          p[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[q % R], wf[j], j == 0 ? zero : p[i], 0, 0, 0);
+          // the next round's weights take the place of this one's, whose last group is in registers
+          if constexpr ((d & 1) && d < 7)
+            if (q == Q / 2) wstore(std::integral_constant<int, (d + 1) / 2>());
+          if (q == BAR && (wait || refill)) {
+            if (wait) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(MT == 4 && d < 6 ? NR : 0) : "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+          }
+          if (refill && q > BAR && ((q - BAR) & 1)) {
+            const uint32_t c = wave + ((q - BAR) >> 1) * W, r = c < (uint32_t)Q ? c : wave;      // (past the end: its first one again)
+            QF_DTL(rx, lds0 + ((d + XS - 1) % XS) * L::GROUP + r * 1024, refill_off + r * 1024);
+          }
+          if (q + R < Q) xf[q % R] = *reinterpret_cast<const bf16x8*>(xb + (q + R) * 1024);
+          else if (d < 7) xf[q % R] = *reinterpret_cast<const bf16x8*>(xb_next + (q + R - Q) * 1024);
           if (m == 0 && j < 7) wf[j + 1] = unpack8_biased(wd[d & 1][j + 1], nc);
-          if (j < 4) xg[m & 1][j] = *reinterpret_cast<const float4*>(sums + m * 32 + 8 * j);
-          if (m > 0 && j >= 1 && j <= 4) rescale(m - 1, j - 1);
+          if (j >= 1 && j <= 4 && m > 0) rescale(i ^ 1, m - 1, j - 1, se_p, se_m, cz);
+          if (LATE && j >= 1 && j <= 4 && m == 0 && d > 0) rescale(i ^ 1, MT - 1, j - 1, se_last_p, se_last_m, cz_last);
+          if (j >= 4) xg[j - 4] = *reinterpret_cast<const float4*>(sums + m * 32 + 8 * (j - 4));
           if constexpr (d < 7)
-            if (m == MT - 1 && j == 6) wread(std::integral_constant<int, d + 1>());
+            if (q == Q - 2) wread(std::integral_constant<int, d + 1>());
           __builtin_amdgcn_sched_barrier(0);
         }
+      if (!LATE) {
 #pragma unroll
-      for (int b = 0; b < 4; ++b) rescale(MT - 1, b);
-      if constexpr (d < 7)
-        if (d + 1 < (int)cnt) self(self, std::integral_constant<int, d + 1>());
+        for (int b = 0; b < 4; ++b) rescale((d * MT + MT - 1) & 1, MT - 1, b, se_p, se_m, cz);
+      }
+      if (d < 7 && d + 1 < (int)cnt) {
+        se_last_p = se_p; se_last_m = se_m; cz_last = cz;
+        if constexpr (d < 7) self(self, std::integral_constant<int, d + 1>());
+      } else if (LATE) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) rescale((d * MT + MT - 1) & 1, MT - 1, b, se_p, se_m, cz);
+      }
     };
     group(group, std::integral_constant<int, 0>());
     __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0): loads that nobody waited for would be waited for above
@@ -271,10 +287,14 @@ hipError_t few_prepare() {
 }
 template <int MT, bool DUAL>
 hipError_t few_launch(const GemmArgs& a, float* ws, uint32_t ks, uint32_t per, hipStream_t st) {
-  // wavefronts per workgroup: as few as make one round, but one per SIMD
-  const uint32_t tiles = (a.N + 31) / 32, cus = gemm_workgroups(1u << 20, 1u << 20), most = FewLds<MT>::W;
-  uint32_t w = MT == 4 ? most : std::min(most, std::max(4u, (uint32_t)(((uint64_t)tiles * ks + cus - 1) / cus)));
-  while (w < most && (uint64_t)((tiles + w - 1) / w) * ks > cus) ++w;
+  // wavefronts per workgroup: the least time, rounds of a workgroup per compute unit, each (start and stores) + W
+  const uint32_t tiles = (a.N + 31) / 32, cus = gemm_workgroups(1u << 20, 1u << 20);
+  uint32_t w = MT == 4 ? FewLds<MT>::W : 4;
+  uint64_t best = ~0ull;
+  for (uint32_t v = w; v <= FewLds<MT>::W; ++v) {
+    const uint64_t time = ((uint64_t)((tiles + v - 1) / v) * ks + cus - 1) / cus * (4 + v);
+    if (time < best) { best = time; w = v; }
+  }
   const dim3 grid((tiles + w - 1) / w, ks);
   const FewRest r = {a.row_base, a.seed_lo, a.seed_hi, a.eps_signed};
   const uint32_t packed = a.M | (w << 8) | (a.s_fp16 ? 1u << 16 : 0u);
