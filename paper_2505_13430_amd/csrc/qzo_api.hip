@@ -1398,7 +1398,7 @@ qzo_status qzo_debug_fused_linear(const void* x_dev, const void* q_dev, const vo
   g.seed_lo = (uint32_t)seed; g.seed_hi = (uint32_t)(seed >> 32); g.eps_signed = sign > 0 ? eps : -eps;
   g.epi = epilogue; g.rope = rope_dev; g.rope_S = rope_seq; g.rope_dh = rope_head_dim;
   const W4Plan p = w4_plan(M, g.flip_row, N, K, 1, 0, 0, *height);
-  QZO_HIP(launch_w4_tiles(g, p, (hipStream_t)stream));
+  QZO_HIP(*height ? launch_w4_tiles(g, p, (hipStream_t)stream) : launch_w4(g, p, (hipStream_t)stream));
   *height = p.mt;
   return QZO_OK;
 }

@@ -824,7 +824,7 @@ hipError_t launch_w4a16_gemm(const GemmArgs& a0, hipStream_t st) {
   }
   if (ksplit > 1 && (a.epi & EPI_ROPE)) return hipErrorInvalidValue;     // the reduction knows no rotary embedding
   if (ksplit > 1) g.epi = 0;         // natural row order, fp32 partial sums; the reduction applies a.epi
-  hipError_t e = launch_w4_tiles(g, w4_plan(g.M, a.flip_row, a.N, a.K, ksplit, kt_per, g.epi & EPI_SUMSQ ? a.n_partials : 0u), st);
+  hipError_t e = launch_w4(g, w4_plan(g.M, a.flip_row, a.N, a.K, ksplit, kt_per, g.epi & EPI_SUMSQ ? a.n_partials : 0u), st);
   if (e != hipSuccess || ksplit == 1) return e;
   a.M = rows;
   return launch_partial_reduce(a, a.split_ws, ksplit, st);

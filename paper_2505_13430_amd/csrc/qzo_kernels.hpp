@@ -116,13 +116,18 @@ hipError_t launch_w4a16_gemm(const GemmArgs& a, hipStream_t st);
 struct W4Plan {
   uint32_t mt, tiles_m, tiles_per_pass, tiles_n, ksplit, kt_per;
   uint32_t second_row, rows;         // rows: of x, y and resid
-  uint32_t wgs;                      // persistent workgroups
+  uint32_t wgs, rounds;              // persistent workgroups, units of the busiest one
+  double last;                       // share of the workgroups that take part in the last round
+  uint32_t first_n, count_n;         // a launch of some feature tiles only: the first, how many (0: all of them)
 };
 // most_parts (0: no limit): room for one partial sum of squares per workgroup; never refused when it holds one per
 // 256 x 256 tile, rounded up to a multiple of 8.  height (0: by the rule): mt.
 W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t ksplit, uint32_t kt_per, uint32_t most_parts,
                uint32_t height = 0);
 hipError_t launch_w4_tiles(const GemmArgs& a, const W4Plan& p, hipStream_t st);
+// The plan p of a.M, a.N, a.K, or two launches of different heights where they are faster; same results bit for bit.
+bool w4_two_heights(const W4Plan& p, uint32_t M, uint32_t K, W4Plan* head, W4Plan* tail);
+hipError_t launch_w4(const GemmArgs& a, const W4Plan& p, hipStream_t st);
 // Order of the rows of an expanded (bf16) weight matrix: natural; the fused-SwiGLU consumer's tile order;
 // the fused-RoPE consumer's order for heads of 128 features (within every 256 rows, so that a lane of the
 // GEMM holds feature i and feature i + 64 of a head).

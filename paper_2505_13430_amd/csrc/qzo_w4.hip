@@ -86,14 +86,17 @@ __device__ __forceinline__ W4RestPtr w4_rest() {
   asm volatile("" : "+s"(p));
   return (W4RestPtr)p;
 }
-// packed: epilogue flags, fp16 scales, heads of 128, workgroups, K slices
+// packed: epilogue flags, fp16 scales, heads of 128, workgroups, K slices.  No K slices (0): all of K, and kt_per holds the
+// launch's feature tiles in its place (w4_columns), so that the arguments of the first loads fit the registers.
 __host__ __device__ constexpr uint32_t w4_pack(uint32_t epi, bool s_fp16, bool rope128, uint32_t wgs, uint32_t ksplit) {
   return epi | (s_fp16 ? 64u : 0u) | (rope128 ? 128u : 0u) | (wgs << 8) | (ksplit << 20);
 }
 
+__host__ __device__ constexpr uint32_t w4_columns(uint32_t first_n, uint32_t tiles_n) { return first_n | (tiles_n << 16); }
+
 template <int MT, int FMT>
 __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(const void* x, const void* w, const void* s, uint32_t M, uint32_t N, uint32_t K,
-                                                         uint32_t second_row, uint32_t kt_per, uint32_t packed, const void* zp,
+                                                         uint32_t second_row, uint32_t kt_per_or_columns, uint32_t packed, const void* zp,
                                                          W4Rest) {
   typedef W4Lds<MT, FMT> L;
   constexpr bool ZP = FMT == W4_ZP, NF4 = FMT == W4_NF4;
@@ -108,10 +111,11 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(const void* x, const vo
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const uint32_t lrow = lane & 31u, half = lane >> 5;
   const uint32_t G = K >> 7, epi = packed & 63u, wgs = (packed >> 8) & 0xfffu, ksplit = packed >> 20;
+  const uint32_t kt_per = ksplit ? kt_per_or_columns : K / BK, first_n = ksplit ? 0u : kt_per_or_columns & 0xffffu;
   const bool swiglu = (epi & EPI_SWIGLU) != 0, rope = (epi & EPI_ROPE) != 0, s_fp16 = (packed & 64u) != 0;
   const bool rope128 = (packed & 128u) != 0;
-  const uint32_t tiles_n = (N + 255u) >> 8, tiles_per_pass = (M + 32 * MT - 1) / (32 * MT);
-  TileWalk walk = tile_walk_of(second_row ? 2 * tiles_per_pass : tiles_per_pass, tiles_n * ksplit, wgs);
+  const uint32_t tiles_n = ksplit ? (N + 255u) >> 8 : kt_per_or_columns >> 16, tiles_per_pass = (M + 32 * MT - 1) / (32 * MT);
+  TileWalk walk = tile_walk_of(second_row ? 2 * tiles_per_pass : tiles_per_pass, ksplit ? tiles_n * ksplit : tiles_n, wgs);
   uint32_t tile_m, tile_n;
   if (!tile_walk_get(walk, tile_m, tile_n)) {
     if ((epi & EPI_SUMSQ) && threadIdx.x == 0) w4_rest()->partials[blockIdx.x] = 0.0f;
@@ -132,7 +136,7 @@ __global__ __launch_bounds__(256, 1) void w4_gemm_kernel(const void* x, const vo
   float eps;
   auto point = [&]() Q4_INLINE {
     kslice = ksplit > 1 ? tile_n / tiles_n : 0u;
-    tile_n -= kslice * tiles_n;
+    tile_n = first_n + tile_n - kslice * tiles_n;
     kt0 = kslice * kt_per;
     ng = min(kt_per, K / BK - kt0) >> 1;
     pass = tile_m >= tiles_per_pass ? 1u : 0u;
@@ -672,9 +676,10 @@ hipError_t w4_prepare() {
 template <int MT>
 void w4_launch(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
   const W4Rest r = {a.y, a.resid, a.bias, a.partials, a.split_ws, a.rope, a.rope_S, a.ldy, a.row_base, a.seed_lo, a.seed_hi, a.eps_signed};
-  const uint32_t packed = w4_pack(a.epi, a.s_fp16 != 0, (a.epi & EPI_ROPE) && a.rope_dh == 128, p.wgs, p.ksplit);
+  const uint32_t packed = w4_pack(a.epi, a.s_fp16 != 0, (a.epi & EPI_ROPE) && a.rope_dh == 128, p.wgs, p.count_n ? 0u : p.ksplit);
+  const uint32_t kt_per = p.count_n ? w4_columns(p.first_n, p.count_n) : p.kt_per;
 #define Q4_LAUNCH(FMT) \
-  w4_gemm_kernel<MT, FMT><<<p.wgs, 256, W4Lds<MT, FMT>::BYTES, st>>>(a.x, a.w, a.s, a.M, a.N, a.K, p.second_row, p.kt_per, packed, a.zp, r)
+  w4_gemm_kernel<MT, FMT><<<p.wgs, 256, W4Lds<MT, FMT>::BYTES, st>>>(a.x, a.w, a.s, a.M, a.N, a.K, p.second_row, kt_per, packed, a.zp, r)
   if (a.nf4) Q4_LAUNCH(W4_NF4);
   else if (a.zp) Q4_LAUNCH(W4_ZP);
   else Q4_LAUNCH(W4_INT4);
@@ -683,32 +688,94 @@ void w4_launch(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
 
 }  // namespace
 
-// Height of the output tiles: the one whose rounds of units take the least time.  A round lasts as long as one unit,
-// K_TILE us per k-tile on a full chip and 1.5 + 0.9 mt us around the k-loop (repeated launches, N = 8192, K from 2048 to
-// 16384, one round each); the matrix unit alone accounts for 0.13 us per tile of 32 tokens, what does not shrink with the
-// tile is the conversion of its 256 weight rows.
+namespace {
+
+W4Plan w4_plan_of(uint32_t M, uint32_t second_row, uint32_t tiles_n, uint32_t K, uint32_t ksplit, uint32_t kt_per, uint32_t mt) {
+  W4Plan p = {};
+  p.mt = mt;
+  p.ksplit = ksplit; p.kt_per = ksplit > 1 ? kt_per : K / BK;
+  p.second_row = second_row; p.rows = second_row ? second_row + M : M;
+  p.tiles_n = tiles_n;
+  p.tiles_per_pass = (M + 32 * mt - 1) / (32 * mt);
+  p.tiles_m = second_row ? 2 * p.tiles_per_pass : p.tiles_per_pass;
+  const uint32_t cus = gemm_workgroups(1u << 20, 1u << 20);
+  const uint64_t places = ((uint64_t)p.tiles_m * p.tiles_n * ksplit + 7) / 8 * 8;     // an equal share for every XCD
+  p.wgs = (uint32_t)std::min<uint64_t>(places, cus);
+  p.rounds = (uint32_t)((places + cus - 1) / cus);
+  p.last = (double)(places - (uint64_t)(p.rounds - 1) * cus) / cus;
+  return p;
+}
+// A round lasts as long as one unit, K_TILE us per k-tile on a full chip and 1.5 + 0.9 mt us around the k-loop (repeated
+// launches, N = 8192, K from 2048 to 16384, one round each); the matrix unit alone accounts for 0.13 us per tile of 32 tokens,
+// what does not shrink with the tile is the conversion of its 256 weight rows.
+double w4_time(const W4Plan& p) {
+  static const double K_TILE[9] = {0, 0.58, 0.71, 0.83, 0.95, 1.11, 1.26, 1.42, 1.58};
+  return p.rounds * (p.kt_per * K_TILE[p.mt] + 1.5 + 0.9 * p.mt);
+}
+
+}  // namespace
+
+// Height of the output tiles: the one whose rounds of units take the least time.
 W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t ksplit, uint32_t kt_per,
                uint32_t most_parts, uint32_t height) {
-  static const double K_TILE[9] = {0, 0.58, 0.71, 0.83, 0.95, 1.11, 1.26, 1.42, 1.58};
-  const uint32_t cus = gemm_workgroups(1u << 20, 1u << 20);
   W4Plan best = {};
   double best_time = 0.0;
   for (uint32_t mt = height ? height : 8; mt > 0; --mt) {
-    W4Plan p = {};
-    p.mt = mt;
-    p.ksplit = ksplit; p.kt_per = ksplit > 1 ? kt_per : K / BK;
-    p.second_row = second_row; p.rows = second_row ? second_row + M : M;
-    p.tiles_n = (N + BN - 1) / BN;
-    p.tiles_per_pass = (M + 32 * mt - 1) / (32 * mt);
-    p.tiles_m = second_row ? 2 * p.tiles_per_pass : p.tiles_per_pass;
-    const uint64_t places = ((uint64_t)p.tiles_m * p.tiles_n * ksplit + 7) / 8 * 8;     // an equal share for every XCD
-    p.wgs = (uint32_t)std::min<uint64_t>(places, cus);
+    const W4Plan p = w4_plan_of(M, second_row, (N + BN - 1) / BN, K, ksplit, kt_per, mt);
     if (most_parts && p.wgs > most_parts && mt < 8) continue;
-    const double time = (double)((places + cus - 1) / cus) * (p.kt_per * K_TILE[mt] + 1.5 + 0.9 * mt);
+    const double time = w4_time(p);
     if (!best.mt || time < 0.98 * best_time) { best = p; best_time = time; }
     if (height) break;
   }
   return best;
+}
+
+// A last round that one height fills badly: whole rounds of one height, the other feature tiles in tiles of another height,
+// two launches (5 us for the second).  A last round filled to a share f takes 0.7 + 0.3 f of a whole one (the clock rises, and
+// workgroups do not end together): with that the ratio of both sides is foretold to 0.02, without it 0.05 to 0.1 too low.
+// Two heights over one, both passes, int4 / NormalFloat-4 / zero-points: 22016 x 4096 400 tokens 0.92 / 0.93 / 0.93, 450 tokens
+// 0.93 / 0.86 / 0.87, 260 0.95 / 0.95 / 0.96; 27648 x 5120 800 tokens 0.90 / 0.87 / 0.89, 1200 0.94 / 0.91 / 0.91; 11008 x 4096 1000
+// tokens 0.97 / 0.97 / 0.95.  Where less than GAIN is foretold the measured ratios reach 1.0 (12288 x 4096 1000 tokens 0.96 /
+// 0.98 / 0.99 at 0.93 are the worst beyond it).  Not in tiles of 32: a tail of them was foretold at 0.94 and measured 1.03.
+bool w4_two_heights(const W4Plan& one, uint32_t M, uint32_t K, W4Plan* head, W4Plan* tail) {
+  constexpr double TWO_LAUNCHES = 5.0, GAIN = 0.95;
+  constexpr uint32_t MOST_ROUNDS = 8, LEAST = 2;      // (beyond eight rounds the last one is too small a part)
+  if (one.ksplit > 1 || one.rounds < 2 || one.rounds > MOST_ROUNDS || one.tiles_n >= 65536u) return false;
+  const uint32_t cus = gemm_workgroups(1u << 20, 1u << 20);
+  auto time = [](const W4Plan& p) {
+    const double part = p.last < 1.0 ? 0.7 + 0.3 * p.last : 1.0;
+    return w4_time(p) * (p.rounds - 1 + part) / p.rounds;
+  };
+  double best = GAIN * time(one);
+  bool found = false;
+  for (uint32_t mt = 8; mt >= LEAST; --mt) {
+    const W4Plan p = w4_plan_of(M, one.second_row, one.tiles_n, K, 1, 0, mt);
+    for (uint32_t whole = p.rounds - 1, tries = 3; whole > 0 && tries > 0; --whole, --tries) {
+      const uint32_t n1 = (uint32_t)std::min<uint64_t>((uint64_t)whole * cus / p.tiles_m, one.tiles_n);
+      if (n1 == 0 || n1 == one.tiles_n) continue;
+      W4Plan h = w4_plan_of(M, one.second_row, n1, K, 1, 0, mt);
+      h.count_n = n1;
+      const double t1 = time(h) + TWO_LAUNCHES;
+      if (t1 >= best) continue;
+      for (uint32_t m2 = 8; m2 >= LEAST; --m2) {
+        W4Plan t = w4_plan_of(M, one.second_row, one.tiles_n - n1, K, 1, 0, m2);
+        if (m2 == mt || t1 + time(t) >= best) continue;
+        t.first_n = n1; t.count_n = t.tiles_n;
+        best = t1 + time(t);
+        *head = h; *tail = t;
+        found = true;
+      }
+    }
+  }
+  return found;
+}
+
+hipError_t launch_w4(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
+  W4Plan head, tail;
+  // (a sum of squares has a place per workgroup of one launch)
+  if ((a.epi & EPI_SUMSQ) || !w4_two_heights(p, a.M, a.K, &head, &tail)) return launch_w4_tiles(a, p, st);
+  const hipError_t e = launch_w4_tiles(a, head, st);
+  return e != hipSuccess ? e : launch_w4_tiles(a, tail, st);
 }
 
 hipError_t launch_w4_tiles(const GemmArgs& a, const W4Plan& p, hipStream_t st) {

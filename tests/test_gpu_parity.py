@@ -1672,6 +1672,31 @@ def test_fused_linear_epilogues_at_every_tile_height(epilogue, head_dim, fmt):
     assert float(((first.double() - other).abs() > bound).double().mean()) > 0.5 or epilogue & 4
 
 
+@pytest.mark.parametrize("fmt", ["int4", "zp", "nf4"])
+@pytest.mark.parametrize("M,N,K,epilogue,head_dim", [(400, 22016, 4096, 16, 0), (1000, 12288, 4096, 32, 128), (1000, 12288, 4096, 32, 64),
+                                                     (401, 22008, 4096, 1 | 2, 0), (450, 22008, 4096, 0, 0), (801, 27648, 5120, 16, 0)])
+def test_fused_linear_of_two_tile_heights(M, N, K, epilogue, head_dim, fmt):
+    """Sizes whose last round is filled by tiles of another height, of both passes of a step, ragged in tokens and features:
+    the bits of one height for all columns."""
+    gen = torch.Generator(device=DEV).manual_seed(M + N + epilogue)
+    x = torch.randn(2 * M, K, generator=gen, device=DEV).to(torch.bfloat16)
+    q = torch.randint(0, 256, (N, K // 2), generator=gen, device=DEV, dtype=torch.uint8)
+    s = (torch.rand(N, K // (64 if fmt == "nf4" else 128), generator=gen, device=DEV) * 0.01 + 0.005).to(torch.bfloat16)
+    z = torch.randint(0, 16, (N, K // 128), generator=gen, device=DEV, dtype=torch.uint8) if fmt == "zp" else None
+    bias = torch.randn(N, generator=gen, device=DEV).to(torch.bfloat16) if epilogue & 1 else None
+    resid = torch.randn(2 * M, N, generator=gen, device=DEV).to(torch.bfloat16) if epilogue & 2 else None
+    rope = torch.randn(100, head_dim // 2, 2, generator=gen, device=DEV) if head_dim else None
+    ys, cols = [], N // 2 if epilogue == 16 else N
+    for height in (8, 0):
+        guard = torch.full(((2 * M + 32) * cols,), 7.0, dtype=torch.bfloat16, device=DEV)
+        y = guard[:2 * M * cols].view(2 * M, cols)
+        qb.qzo_debug_fused_linear(x, q, s, z, 11, 31, 1e-2, 1, y, passes=2, nf4=fmt == "nf4", epilogue=epilogue, bias=bias,
+                                  resid=resid, rope=rope, head_dim=head_dim, height=height)
+        assert bool((guard[2 * M * cols:] == 7.0).all())
+        ys.append(y)
+    assert torch.equal(ys[0], ys[1])
+
+
 @pytest.mark.parametrize("M,N", [(2048, 16384), (2049, 11016), (8192, 28672)])
 def test_sum_of_squares_of_many_tiles_per_workgroup(M, N):
     """Equal outputs of 255/128, whose squares (65025 2^-14) an fp32 sum holds exactly up to 258 terms; beyond, every
