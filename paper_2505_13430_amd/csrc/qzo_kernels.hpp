@@ -117,7 +117,7 @@ struct W4Plan {
   uint32_t mt, tiles_m, tiles_per_pass, tiles_n, ksplit, kt_per;
   uint32_t second_row, rows;         // rows: of x, y and resid
   uint32_t wgs, rounds;              // persistent workgroups, units of the busiest one
-  double last;                       // share of the workgroups that take part in the last round
+  uint32_t last;                     // units of the last round
   uint32_t first_n, count_n;         // a launch of some feature tiles only: the first, how many (0: all of them)
 };
 // most_parts (0: no limit): room for one partial sum of squares per workgroup; never refused when it holds one per

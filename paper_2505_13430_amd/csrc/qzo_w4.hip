@@ -690,7 +690,7 @@ void w4_launch(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
 
 namespace {
 
-W4Plan w4_plan_of(uint32_t M, uint32_t second_row, uint32_t tiles_n, uint32_t K, uint32_t ksplit, uint32_t kt_per, uint32_t mt) {
+W4Plan w4_plan_of(uint32_t cus, uint32_t M, uint32_t second_row, uint32_t tiles_n, uint32_t K, uint32_t ksplit, uint32_t kt_per, uint32_t mt) {
   W4Plan p = {};
   p.mt = mt;
   p.ksplit = ksplit; p.kt_per = ksplit > 1 ? kt_per : K / BK;
@@ -698,11 +698,10 @@ W4Plan w4_plan_of(uint32_t M, uint32_t second_row, uint32_t tiles_n, uint32_t K,
   p.tiles_n = tiles_n;
   p.tiles_per_pass = (M + 32 * mt - 1) / (32 * mt);
   p.tiles_m = second_row ? 2 * p.tiles_per_pass : p.tiles_per_pass;
-  const uint32_t cus = gemm_workgroups(1u << 20, 1u << 20);
   const uint64_t places = ((uint64_t)p.tiles_m * p.tiles_n * ksplit + 7) / 8 * 8;     // an equal share for every XCD
   p.wgs = (uint32_t)std::min<uint64_t>(places, cus);
   p.rounds = (uint32_t)((places + cus - 1) / cus);
-  p.last = (double)(places - (uint64_t)(p.rounds - 1) * cus) / cus;
+  p.last = (uint32_t)(places - (uint64_t)(p.rounds - 1) * cus);
   return p;
 }
 // A round lasts as long as one unit, K_TILE us per k-tile on a full chip and 1.5 + 0.9 mt us around the k-loop (repeated
@@ -718,10 +717,11 @@ double w4_time(const W4Plan& p) {
 // Height of the output tiles: the one whose rounds of units take the least time.
 W4Plan w4_plan(uint32_t M, uint32_t second_row, uint32_t N, uint32_t K, uint32_t ksplit, uint32_t kt_per,
                uint32_t most_parts, uint32_t height) {
+  const uint32_t cus = gemm_workgroups(1u << 20, 1u << 20);
   W4Plan best = {};
   double best_time = 0.0;
   for (uint32_t mt = height ? height : 8; mt > 0; --mt) {
-    const W4Plan p = w4_plan_of(M, second_row, (N + BN - 1) / BN, K, ksplit, kt_per, mt);
+    const W4Plan p = w4_plan_of(cus, M, second_row, (N + BN - 1) / BN, K, ksplit, kt_per, mt);
     if (most_parts && p.wgs > most_parts && mt < 8) continue;
     const double time = w4_time(p);
     if (!best.mt || time < 0.98 * best_time) { best = p; best_time = time; }
@@ -742,23 +742,23 @@ bool w4_two_heights(const W4Plan& one, uint32_t M, uint32_t K, W4Plan* head, W4P
   constexpr uint32_t MOST_ROUNDS = 8, LEAST = 2;      // (beyond eight rounds the last one is too small a part)
   if (one.ksplit > 1 || one.rounds < 2 || one.rounds > MOST_ROUNDS || one.tiles_n >= 65536u) return false;
   const uint32_t cus = gemm_workgroups(1u << 20, 1u << 20);
-  auto time = [](const W4Plan& p) {
-    const double part = p.last < 1.0 ? 0.7 + 0.3 * p.last : 1.0;
+  auto time = [cus](const W4Plan& p) {
+    const double part = p.last < cus ? 0.7 + 0.3 * p.last / cus : 1.0;
     return w4_time(p) * (p.rounds - 1 + part) / p.rounds;
   };
   double best = GAIN * time(one);
   bool found = false;
   for (uint32_t mt = 8; mt >= LEAST; --mt) {
-    const W4Plan p = w4_plan_of(M, one.second_row, one.tiles_n, K, 1, 0, mt);
+    const W4Plan p = w4_plan_of(cus, M, one.second_row, one.tiles_n, K, 1, 0, mt);
     for (uint32_t whole = p.rounds - 1, tries = 3; whole > 0 && tries > 0; --whole, --tries) {
       const uint32_t n1 = (uint32_t)std::min<uint64_t>((uint64_t)whole * cus / p.tiles_m, one.tiles_n);
       if (n1 == 0 || n1 == one.tiles_n) continue;
-      W4Plan h = w4_plan_of(M, one.second_row, n1, K, 1, 0, mt);
+      W4Plan h = w4_plan_of(cus, M, one.second_row, n1, K, 1, 0, mt);
       h.count_n = n1;
       const double t1 = time(h) + TWO_LAUNCHES;
       if (t1 >= best) continue;
       for (uint32_t m2 = 8; m2 >= LEAST; --m2) {
-        W4Plan t = w4_plan_of(M, one.second_row, one.tiles_n - n1, K, 1, 0, m2);
+        W4Plan t = w4_plan_of(cus, M, one.second_row, one.tiles_n - n1, K, 1, 0, m2);
         if (m2 == mt || t1 + time(t) >= best) continue;
         t.first_n = n1; t.count_n = t.tiles_n;
         best = t1 + time(t);
