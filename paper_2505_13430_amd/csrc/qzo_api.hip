@@ -340,13 +340,13 @@ Workspace carve(const qzo_model* m, uint32_t batch, uint32_t seq, void* base) {
     off += up256(bytes);
     return p;
   };
-  // rows of the norm output and of the MLP's activation: whole tiles where the few-token kernel takes them packed
+  // rows of the norm's and the attention's outputs and of the MLP's activation: whole tiles where the few-token kernel takes them packed
   const bool few = M1 <= SKINNY_MAX_M && int4 && !c.act_order;
   const uint64_t Mp = few ? std::max<uint64_t>({M, few_pack((uint32_t)M1, false).rows, few_pack((uint32_t)M1, stack).rows}) : M;
   w.h = take(M * d * 2);
   w.a = take(Mp * d * 2);
   w.qkv = take(M * 3 * d * 2);
-  w.att = take(M * d * 2);
+  w.att = take(Mp * d * 2);
   w.ff = take(c.arch == 0 ? 0 : Mp * F * 2);    // Llama: SwiGLU is folded into the gate/up GEMM
   w.act = take(c.arch == 0 ? Mp * F * 2 : 0);
   w.ce_part = (float*)take(M * n_slices * 8);
@@ -489,12 +489,20 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
   // attention over both passes: one launch when they are contiguous, one per pass otherwise
   // short sequences: no RoPE launch, the attention kernel rotates q and k itself
   const bool rope_in_attention = llama && seq <= ATTENTION_ROPE_MAX_S;
+  // few-token linears take the block sums of their input from its producer
+  float* const mid_ws = n_pass == 2 || mid_single_pass(m, M1) ? w.mid : nullptr;
+  const bool few = (mid_ws && c.quant != 3) || (w.skinny && M1 <= SKINNY_MAX_M && (c.quant == 0 || c.quant == 2) && !c.act_order);
+  float* const xs_a = few ? w.xs_a : nullptr;
+  // layout of the norms' outputs and the MLP's activation
+  const XPack pack = few && !mid_ws && !w.wexp ? few_pack(M1, n_pass == 2) : XPack{};
+  // and the attention's where a head is a group; its block sums take the place of the norm's, which the qkv linear has read
+  const XPack att_pack = dh == 128 && !padded && xs_a ? pack : XPack{};
   NextAttention na = {batch, seq, H, dh, nullptr, 0};
   auto attention = [&](bool rotated) {
     ProfScope ps(PK_ATTN, attn_flops, st);
     const float* tb = (llama && !rotated) ? w.rope : nullptr;
-    if (na.part) return launch_attention(nullptr, batch, seq, H, dh, w.att, tb, st, na.part, na.slices);
-    if (!padded) return launch_attention(w.qkv, batch, seq, H, dh, w.att, tb, st);
+    if (na.part) return launch_attention(nullptr, batch, seq, H, dh, w.att, tb, st, na.part, na.slices, att_pack, xs_a);
+    if (!padded) return launch_attention(w.qkv, batch, seq, H, dh, w.att, tb, st, nullptr, 0, att_pack, xs_a);
     hipError_t e = launch_attention(w.qkv, batch1, seq, H, dh, w.att, tb, st);
     if (e != hipSuccess) return e;
     return launch_attention((const unsigned char*)w.qkv + (size_t)P * 3 * d * 2, batch1, seq, H, dh,
@@ -503,12 +511,6 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
   auto other = [&](hipError_t e) { return e; };
   (void)other;
   bool rope_fused = false;     // set by a qkv linear whose GEMM applied the rotary embedding itself
-  // few-token linears take the block sums of their input from its producer
-  float* const mid_ws = n_pass == 2 || mid_single_pass(m, M1) ? w.mid : nullptr;
-  const bool few = (mid_ws && c.quant != 3) || (w.skinny && M1 <= SKINNY_MAX_M && (c.quant == 0 || c.quant == 2) && !c.act_order);
-  float* const xs_a = few ? w.xs_a : nullptr;
-  // layout of the norms' outputs and the MLP's activation
-  const XPack pack = few && !mid_ws && !w.wexp ? few_pack(M1, n_pass == 2) : XPack{};
   // the norm that follows a linear into the residual stream: taken over by the linear's slice reduction where it has one
   NextNorm nn = {};
   auto norm = [&](const void* gain, const void* nbias, float* xs) {
@@ -553,7 +555,8 @@ qzo_status forward(qzo_model* m, const int32_t* tok, uint32_t batch1, uint32_t s
       if (few) {     // the few-token kernel takes the block sums of its input from the kernel that wrote it
         g.xsum = (li == 0 || li == 2) ? w.xs_a : (li == 3 ? w.xs_act : nullptr);
         g.xsum_out = li == 2 ? w.xs_act : nullptr;
-        if (li != 1) g.xp = pack;
+        g.xp = li == 1 ? att_pack : pack;
+        if (li == 1 && att_pack.rows) g.xsum = w.xs_a;
         if (li == 2) g.yp = pack;
         if (mid_ws && li == 1 && c.quant != 3) {      // the attention output's block sums, where the norm's were
           hipError_t e = launch_block_sums(x, M, g.K, w.xs_a, st);

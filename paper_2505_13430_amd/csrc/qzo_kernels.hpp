@@ -307,7 +307,8 @@ hipError_t launch_rope(void* qkv, const float* table, uint32_t M, uint32_t S, ui
 constexpr uint32_t ATTENTION_ROPE_MAX_S = 256;   // up to this sequence length the models let it do so
 hipError_t launch_attention(const void* qkv, uint32_t B, uint32_t S, uint32_t n_heads,
                             uint32_t dh, void* out, const float* rope, hipStream_t st, const float* part = nullptr,
-                            uint32_t slices = 0);
+                            uint32_t slices = 0, const XPack& pack = XPack{}, float* xsum = nullptr);
+// pack: layout of out, xsum receives its block sums (heads of 128, at most 128 positions).
 // Whether it takes the projection's K slices in qkv's place (with rope).
 bool attention_adds_slices(uint32_t B, uint32_t S, uint32_t n_heads, uint32_t dh, uint32_t slices);
 hipError_t launch_scale_update(void* arena, const UpdPlan& plan, uint32_t seed_lo,

@@ -483,7 +483,7 @@ def test_stacked_workgroups_of_either_pass_equal_separate_passes(oracle, name, b
 @pytest.mark.parametrize("arch,var", [("llama", ""), ("opt", ""), ("llama", True), ("opt", "zp16")])
 def test_few_token_layers_with_odd_slices(oracle, arch, var, batch, seq):
     """Packed activations in one, two and four tiles: K slices of three groups that start on odd ones and reach into a second
-    noise counter (640 and 1152 inputs), a ragged last workgroup.  Hidden states of both passes against the oracle's, element by
+    noise counter (640 and 1152 inputs), a ragged last workgroup; heads of 128, whose attention packs its output.  Hidden states of both passes against the oracle's, element by
     element, and the losses of a step bit for bit those of two single passes."""
     shape = dict(arch=arch, n_layers=1, d_model=640, n_heads=5, d_ffn=1152, vocab=500, max_seq=64, batch=batch, seq=seq)
     om, dm = _models(oracle, shape, 77, 2.0, **_variant_args(var))
