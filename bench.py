@@ -401,7 +401,7 @@ def main():
         # every int4 weight and scale is read once per launch: the roof is HBM
         wbytes = sum(N * K // 2 + N * K // 64 for _, N, K in synth.quantized_linears(shape))
         per_launch = wbytes / 4.0
-        out["roofline"] = {"bound": "hbm", "kernel": "skinny_gemm_kernel + skinny_reduce_kernel (few-token W4A16 linear)",
+        out["roofline"] = {"bound": "hbm", "kernel": "few_gemm_kernel + skinny_reduce_kernel (few-token W4A16 linear)",
                            "achieved": per_launch / (g["total_ms"] / max(g["launches"], 1) * 1e-3) / 1e9,
                            "peak": PEAK_HBM / 1e9, "unit": "GB/s",
                            "frac": per_launch / (g["total_ms"] / max(g["launches"], 1) * 1e-3) / PEAK_HBM,
