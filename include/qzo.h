@@ -461,6 +461,19 @@ qzo_status qzo_debug_attention_slices(const float* part_dev, uint32_t slices, ui
                                       uint32_t head_dim, const float* rope_dev, int joined, void* qkv_dev, void* out_dev,
                                       uint32_t* joined_out, void* stream);
 
+/* Inspection: attention (heads of 128) and an int4 linear of few tokens that reads it, of one or two passes (the second one's rows
+ * behind the first one's, with -sign).  qkv_dev bf16 [passes * batch * seq, 3 n_heads 128], rope_dev (nullable) fp32 [seq][64] pairs
+ * (cos, sin); q_dev, s_dev, zp_dev (nullable) as for qzo_dequant_gemm_zp with K = n_heads 128.  packed = 0: the attention's output
+ * plain in att_dev, the linear sums its blocks; 1: as the models do, in the linear's operand order, with the sums of every head in
+ * xsum_dev.  att_dev bf16 [128, K], xsum_dev fp32 [n_heads, 128] (the first 32, 64 or 128 rows are used).  part_dev: part_floats
+ * floats, receives fp32 [*slices_out (host)][passes * batch * seq][N] partial sums; y_dev bf16 [passes * batch * seq, N] their sum.
+ * batch * seq <= 64, N a multiple of 8, n_heads <= 1024, pointers 16-byte aligned, operands and partial sums below 2^31 bytes. */
+qzo_status qzo_debug_attention_linear(const void* qkv_dev, uint32_t batch, uint32_t seq, uint32_t n_heads, uint32_t passes,
+                                      const float* rope_dev, int packed, void* att_dev, float* xsum_dev, const void* q_dev,
+                                      const void* s_dev, const void* zp_dev, int scale_fp16, uint32_t N, uint32_t row_base,
+                                      uint64_t seed, float eps, int sign, float* part_dev, uint64_t part_floats,
+                                      uint32_t* slices_out, void* y_dev, void* stream);
+
 /* Measurement aid, not part of the method: one 512-thread workgroup per compute unit, each
  * wavefront issuing iters x 16 v_mfma_f32_32x32x16_bf16 (32768 flop each) on register operands
  * that are all zero (random_operands = 0) or pseudo-random bf16 values, with no memory traffic.

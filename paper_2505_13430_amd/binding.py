@@ -31,6 +31,7 @@ EXPORTS = [
     "qzo_codebook_scratch_bytes", "qzo_codebook_gemm", "qzo_apply_update_channel",
     "qzo_debug_philox", "qzo_debug_normal_pairs", "qzo_debug_normals", "qzo_debug_dequant", "qzo_debug_dequant_zp",
     "qzo_debug_forward", "qzo_debug_bf16_gemm", "qzo_debug_reduce_norm", "qzo_debug_fused_linear", "qzo_debug_attention_slices",
+    "qzo_debug_attention_linear",
     "qzo_debug_mfma_rate",
     "qzo_profile_begin", "qzo_profile_collect", "qzo_profile_stride",
     "qzo_last_error",
@@ -378,6 +379,20 @@ def qzo_debug_attention_slices(part, rope, n_heads, joined, qkv, out, stream=Non
                                             C.c_uint32(d3 // 3 // n_heads), _ptr(rope), C.c_int(int(joined)), _ptr(qkv),
                                             _ptr(out), C.byref(done), _stream(stream)))
     return bool(done.value)
+
+
+def qzo_debug_attention_linear(qkv, n_heads, passes, rope, packed, att, xsum, q, s, zp, row_base, seed, eps, sign, part, y,
+                               stream=None) -> int:
+    """qkv [passes, batch, seq, 3 n_heads 128].  Returns the number of K slices in part."""
+    _, B, S, _ = qkv.shape
+    slices = C.c_uint32(0)
+    assert att.numel() >= 128 * 128 * n_heads and xsum.numel() >= 128 * n_heads and y.shape == (passes * B * S, q.shape[0])
+    _check(lib().qzo_debug_attention_linear(
+        _ptr(qkv), C.c_uint32(B), C.c_uint32(S), C.c_uint32(n_heads), C.c_uint32(passes), _ptr(rope), C.c_int(int(packed)), _ptr(att),
+        _ptr(xsum), _ptr(q), _ptr(s), _ptr(zp), C.c_int(int(s.dtype == torch.float16)), C.c_uint32(q.shape[0]), C.c_uint32(row_base),
+        C.c_uint64(seed & 0xFFFFFFFFFFFFFFFF), C.c_float(eps), C.c_int(sign), _ptr(part), C.c_uint64(part.numel()),
+        C.byref(slices), _ptr(y), _stream(stream)))
+    return slices.value
 
 
 def qzo_debug_dequant_zp(q, s, zp, row_base, seed, eps, sign, w_eff, group=128, stream=None):

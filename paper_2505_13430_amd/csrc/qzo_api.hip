@@ -1426,6 +1426,34 @@ qzo_status qzo_debug_attention_slices(const float* part_dev, uint32_t slices, ui
   return QZO_OK;
 }
 
+qzo_status qzo_debug_attention_linear(const void* qkv_dev, uint32_t batch, uint32_t seq, uint32_t n_heads, uint32_t passes,
+                                      const float* rope_dev, int packed, void* att_dev, float* xsum_dev, const void* q_dev,
+                                      const void* s_dev, const void* zp_dev, int scale_fp16, uint32_t N, uint32_t row_base,
+                                      uint64_t seed, float eps, int sign, float* part_dev, uint64_t part_floats,
+                                      uint32_t* slices_out, void* y_dev, void* stream) {
+  if (!qkv_dev || !att_dev || !xsum_dev || !q_dev || !s_dev || !part_dev || !slices_out || !y_dev) return fail(QZO_ERR_ARG, "null pointer");
+  if (!aligned16(qkv_dev) || !aligned16(rope_dev) || !aligned16(att_dev) || !aligned16(xsum_dev) || !aligned16(q_dev) || !aligned16(s_dev) ||
+      !aligned16(zp_dev) || !aligned16(part_dev) || !aligned16(y_dev))
+    return fail(QZO_ERR_ALIGN, "device pointer not 16-byte aligned");
+  if ((passes != 1 && passes != 2) || (sign != 1 && sign != -1)) return fail(QZO_ERR_ARG, "passes must be 1 or 2, sign +1 or -1");
+  const uint64_t M1 = (uint64_t)batch * seq, K = (uint64_t)n_heads * 128;
+  if (M1 == 0 || M1 > SKINNY_MAX_M || n_heads == 0 || n_heads > 1024 || N == 0 || N % 8 || !skinny_fits(passes * (uint32_t)M1, N, (uint32_t)K))
+    return fail(QZO_ERR_SHAPE, "need 1 to 64 tokens a pass, N a multiple of 8, operands and partial sums below 2^31 bytes");
+  if (part_floats < skinny_ws_floats(passes * (uint32_t)M1, N, (uint32_t)K)) return fail(QZO_ERR_WORKSPACE, "part_dev too small");
+  hipStream_t st = (hipStream_t)stream;
+  const XPack pack = packed ? few_pack((uint32_t)M1, passes == 2) : XPack{};
+  QZO_HIP(launch_attention(qkv_dev, passes * batch, seq, n_heads, 128, att_dev, rope_dev, st, nullptr, 0, pack, xsum_dev));
+  GemmArgs g = {};
+  g.x = att_dev; g.w = q_dev; g.s = s_dev; g.zp = zp_dev; g.y = y_dev;
+  g.M = (uint32_t)M1; g.N = N; g.K = (uint32_t)K; g.dual = passes == 2;
+  g.row_base = row_base; g.s_fp16 = scale_fp16 != 0;
+  g.seed_lo = (uint32_t)seed; g.seed_hi = (uint32_t)(seed >> 32); g.eps_signed = sign > 0 ? eps : -eps;
+  g.xp = pack; g.xsum = packed ? xsum_dev : nullptr;
+  QZO_HIP(launch_skinny_gemm(g, part_dev, st));
+  *slices_out = (uint32_t)(skinny_ws_floats(1, N, (uint32_t)K) / N);
+  return QZO_OK;
+}
+
 qzo_status qzo_debug_reduce_norm(const float* part_dev, uint32_t slices, uint32_t M, uint32_t N, const void* bias_dev,
                                  const void* resid_dev, const void* gain_dev, const void* norm_bias_dev, float eps,
                                  int joined, void* y_dev, void* out_dev, float* xsum_dev, uint32_t* joined_out,

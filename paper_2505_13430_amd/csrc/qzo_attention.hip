@@ -17,11 +17,9 @@
 // the LDS as it is.  Two LDS buffers, one barrier per tile.
 #include "qzo_device.hpp"
 #include "qzo_kernels.hpp"
+#include "qzo_nibble.hpp"
 
 namespace qzo {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // ROPE: q and k arrive without the rotary embedding and get it here: the queries once in
 // registers, the keys of a tile on their way from registers to the LDS (the table of (cos, sin)
@@ -90,7 +88,6 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
   const float sc = 1.44269504088896f / sqrtf((float)DH);   // log2(e)/sqrt(dh)
 
   // staging registers: K and V chunks (row c / CH, chunk c % CH of the tile, c = t + 256 i)
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 kreg[NK], vreg[NK];
   // (macros, not lambdas: arrays captured by reference would be kept in scratch memory)
   // K chunk i of this thread: (row, chunk) = (c / CH, c % CH) with c = t + 256 i; with ROPE a thread
@@ -468,27 +465,42 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const bf16_t* __restr
       const uint4 v = *reinterpret_cast<const uint4*>(Os + row * OS + ch * 8);
       if (q < S) *reinterpret_cast<uint4*>(out + ((uint64_t)b * S + q) * d + h * DH + ch * 8) = v;
     }
-  } else if (DH == 128 && qq < S && pack.rows) {
-    // for the few-token kernel (XPack): a lane and its partner of the other half hold features 0-3 and 4-7 of a chunk, and store
-    // 0,4,1,5 and 2,6,3,7; a head is a group, whose block sum is that of the two lanes' rounded outputs.
+  } else if (DH == 128 && pack.rows) {
+    // For the few-token kernel (XPack): the lower half of the wavefront takes over chunks 0-7 of the head, the upper half chunks 8-15,
+    // as the operand of its MFMA has them.  A head is a group, whose block sum is that of the few-token kernel on the plain layout,
+    // bit for bit: by the matrix unit up to 16 tokens a pass, else the tree over the chunks' sums.
     // With it the o projection takes the few-token kernel inside a model: 7B shape, 1 x 16 tokens 2.489 -> 2.442 ms a step, 1 x 57
-    // 4.614 -> 4.607 (22 row blocks of 192 in four slices: 88 workgroups).  Heads of 64, two to a group, keep the plain layout.
+    // 4.614 -> 4.607 (22 row blocks of 192 in eight slices: 176 workgroups).  Summed in the lane's own order instead, which moved the
+    // losses of a step by up to 1.1e-3 of their value, six layers took as long: 16 tokens 0.470 ms (this: 0.465), 57 0.853 (0.853).
+    // Heads of 64, two to a group, keep the plain layout.
     const uint32_t m = b * S + qq;
-    float sum = 0.0f;
+    const bool by_mfma = pack.M <= 16u;
+    union { u32x4 u; bf16x8 v; } ones, x;
+    ones.u = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+    floatx16 px = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    float sums[8];
 #pragma unroll
-    for (int i = 0; i < DT; ++i)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const uint32_t x = pack_bf16x2(o[i][4 * g] * inv, o[i][4 * g + 1] * inv);
-        const uint32_t y = pack_bf16x2(o[i][4 * g + 2] * inv, o[i][4 * g + 3] * inv);
-        sum += (__uint_as_float(x << 16) + __uint_as_float(x & 0xffff0000u)) +
-               (__uint_as_float(y << 16) + __uint_as_float(y & 0xffff0000u));
-        const auto r_ = __builtin_amdgcn_permlane32_swap(x, y, false, false);
-        *reinterpret_cast<uint2*>((unsigned char*)out + pack.chunk(m, (h * DH + i * 32 + 8 * g) >> 3) + lhalf * 8) =
-            make_uint2(__builtin_amdgcn_perm(r_[1], r_[0], 0x05040100u), __builtin_amdgcn_perm(r_[1], r_[0], 0x07060302u));
-      }
-    const auto r_ = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
-    if (lhalf == 0) xsum[h * pack.rows + pack.tile_row(m)] = __uint_as_float(r_[0]) + __uint_as_float(r_[1]);
+    for (int j = 0; j < 8; ++j) {
+      const int g = 4 * (j & 3);
+      const int i = (j >> 2) & (DT / 2 - 1);
+      const floatx16 &lo = o[i], &hi = o[DT / 2 + i];
+      const auto a = __builtin_amdgcn_permlane32_swap(pack_bf16x2(lo[g] * inv, lo[g + 1] * inv), pack_bf16x2(hi[g] * inv, hi[g + 1] * inv),
+                                                      false, false);
+      const auto c = __builtin_amdgcn_permlane32_swap(pack_bf16x2(lo[g + 2] * inv, lo[g + 3] * inv),
+                                                      pack_bf16x2(hi[g + 2] * inv, hi[g + 3] * inv), false, false);
+      const u32x4 chunk = {a[0], c[0], a[1], c[1]};
+      x.u = permute8(chunk);
+      if (qq < S) *reinterpret_cast<u32x4*>((unsigned char*)out + pack.chunk(m, (h * DH >> 3) + 8 * lhalf + j)) = x.u;
+      if (by_mfma) px = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones.v, x.v, px, 0, 0, 0);
+      else sums[j] = sum8_bf16(chunk);
+    }
+    float sum = px[0];                             // every row of the product holds the sums of the lanes' queries
+    if (!by_mfma) {
+      sum = ((sums[0] + sums[1]) + (sums[2] + sums[3])) + ((sums[4] + sums[5]) + (sums[6] + sums[7]));
+      const auto r_ = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
+      sum = __uint_as_float(r_[0]) + __uint_as_float(r_[1]);
+    }
+    if (lhalf == 0 && qq < S) xsum[h * pack.rows + pack.tile_row(m)] = sum;
   } else if (qq < S) {
     bf16_t* dst = out + ((uint64_t)b * S + qq) * d + h * DH;
 #pragma unroll

@@ -973,6 +973,51 @@ def test_attention_that_adds_up_slices_equals_reduction_and_attention(B, S, H, d
     assert (got[1].double() - want).abs().max() <= 2 ** -7 * v.abs().max()
 
 
+@pytest.mark.parametrize("passes", [1, 2])
+@pytest.mark.parametrize("B,S,H,N,fmt", [
+    # slices of three groups that start on odd ones; ragged last workgroups
+    (1, 2, 5, 1152, "int4"), (1, 16, 5, 1144, "zp"), (4, 4, 5, 640, "zp16"), (3, 5, 5, 1152, "int4"), (1, 17, 5, 1144, "int4"),
+    (4, 8, 5, 640, "zp16"), (3, 11, 5, 1152, "zp"), (1, 64, 5, 1144, "int4"),
+    # slices of eight groups: the ring of activations is refilled once around with two and four token tiles
+    (1, 16, 32, 8200, "int4"), (1, 24, 32, 8200, "zp"), (1, 32, 32, 12288, "int4"), (1, 57, 32, 12288, "int4"), (1, 57, 32, 8200, "zp"),
+    (4, 16, 32, 8200, "zp16"),
+    # slices of fourteen: a second pass of the K loop, over six
+    (1, 16, 40, 27648, "zp"), (1, 24, 40, 27648, "int4"), (1, 57, 40, 27640, "int4"), (2, 32, 40, 27648, "zp")])
+def test_linear_behind_attention_that_packs_equals_plain_layout(B, S, H, N, fmt, passes):
+    """Partial sums of the few-token linear whose input, and its block sums, the attention delivers, against those of the
+    kernel that takes the plain layout and adds up the blocks itself: bit for bit.  The block sums themselves, beyond 16
+    tokens: eight features' even and odd ones in a row, the two added, sixteen such sums as a tree."""
+    gen = torch.Generator(device=DEV).manual_seed(B * S * H + N + passes)
+    d, M = 128 * H, passes * B * S
+    rand = lambda *sz: torch.rand(*sz, generator=gen, device=DEV)
+    qkv = (torch.randn(passes, B, S, 3 * d, generator=gen, device=DEV) * (0.1 + 3 * rand(3 * d))).to(torch.bfloat16)
+    rope = torch.stack([rand(S, 64), rand(S, 64)], -1) if S % 2 else None
+    q = torch.randint(0, 256, (N, d // 2), generator=gen, device=DEV, dtype=torch.uint8)
+    s = (rand(N, H) * 0.01 + 0.005).to(torch.float16 if fmt == "zp16" else torch.bfloat16)
+    z = torch.randint(0, 16, (N, H), generator=gen, device=DEV, dtype=torch.uint8) if fmt != "int4" else None
+    res = []
+    for packed in (0, 1):
+        att = torch.full((128 * d,), float("nan"), dtype=torch.bfloat16, device=DEV)
+        xsum = torch.full((128 * H,), float("nan"), device=DEV)
+        part = torch.full((H * M * N // 2 + 1024 * M,), float("nan"), device=DEV)
+        y = torch.empty(M, N, dtype=torch.bfloat16, device=DEV)
+        slices = qb.qzo_debug_attention_linear(qkv, H, passes, rope, packed, att, xsum, q, s, z, 7, 31, 1e-2, 1, part, y)
+        used = slices * M * N
+        assert bool(part[:used].isfinite().all()) and bool(part[used:].isnan().all())
+        res.append((att, xsum, part[:used].clone(), y))
+    assert torch.equal(res[0][2].view(torch.int32), res[1][2].view(torch.int32))
+    assert torch.equal(res[0][3].view(torch.int16), res[1][3].view(torch.int16))
+    if B * S > 16:
+        x = res[0][0][:M * d].view(M, H, 16, 4, 2).float()
+        c = [x[:, :, :, i] for i in range(4)]
+        c = (((c[0] + c[1]) + c[2]) + c[3]).sum(-1)
+        while c.shape[-1] > 1:
+            c = c[..., ::2] + c[..., 1::2]
+        tpp = (B * S + 31) // 32 * 32
+        sums = res[1][1][:H * passes * tpp].view(H, passes, tpp)[:, :, :B * S].reshape(H, M).t()
+        assert torch.equal(c[..., 0].contiguous().view(torch.int32), sums.contiguous().view(torch.int32))
+
+
 def test_failing_calls_enqueue_nothing(oracle):
     """Every error that the library finds itself (anything but a failing HIP call) is found before
     the first launch: outputs, workspace and scales are untouched afterwards."""
