@@ -185,7 +185,10 @@ __global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void
     // behind the last ones of the group before; the barrier of the ring stands in its second half, where nobody waits for
     // operands (at the head of a group, with everything begun and ended there: 3300 cycles a group of four tiles).
     constexpr int R = 4;                            // fragments read ahead of their MFMA
-    constexpr bool LATE = MT > 1;                   // (one tile: three wavefronts a SIMD, and 135 registers too many)
+    // (One tile: three wavefronts a SIMD, and 135 registers too many.  Four with zero-points: 46 too many, which went to scratch memory
+    // by the counter that the ring's waits count; without, steps of six layers of 7B widths, 33 / 64 tokens 1.045 / 1.113 -> 0.784 / 0.861
+    // ms, five of 13B 1.439 / 1.529 -> 1.015 / 1.102; the plain kernel 0.960 / 1.056, 1.103 / 1.211.)
+    constexpr bool LATE = MT > 1 && !(MT == 4 && ZP);
     bf16x8 xf[R], wf[8];
     floatx16 p[2];                                  // sums of the tile at work and of the one before
     float4 xg[4];                                   // block sums of the latter's, then the former's tile rows

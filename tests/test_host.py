@@ -32,16 +32,23 @@ def test_library_exports_every_declared_symbol():
     assert sorted(qb.EXPORTS) == names
 
 
-def _device_code(tmp_path):
-    """Instructions of the built library's kernels: lists of (mnemonic, operands), a list per kernel."""
-    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+LLVM = "/opt/rocm/llvm/bin/llvm-"
+
+
+def _device_objects(tmp_path):
+    """File names of the built library's code objects, extracted to tmp_path."""
     shutil.copy(hip_build.LIB, tmp_path / "lib.so")
-    subprocess.run([objdump, "--offloading", "lib.so"], cwd=tmp_path, check=True, capture_output=True)
+    subprocess.run([LLVM + "objdump", "--offloading", "lib.so"], cwd=tmp_path, check=True, capture_output=True)
     bundles = [f for f in os.listdir(tmp_path) if "gfx950" in f]
     assert len(bundles) >= len(hip_build.SOURCES) - 1            # every source but the API's holds kernels
+    return bundles
+
+
+def _device_code(tmp_path):
+    """Instructions of the built library's kernels: lists of (mnemonic, operands), a list per kernel."""
     kernels = []
-    for f in bundles:
-        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", f], cwd=tmp_path, check=True, capture_output=True, text=True)
+    for f in _device_objects(tmp_path):
+        text = subprocess.run([LLVM + "objdump", "-d", "--no-show-raw-insn", f], cwd=tmp_path, check=True, capture_output=True, text=True)
         for line in text.stdout.split("\n"):
             if re.match(r"[0-9a-f]+ <", line):
                 kernels.append([])
@@ -104,6 +111,20 @@ def test_wait_states_of_accumulator_reads(tmp_path):
                 assert since(kernel, i, 2, lambda o, a: o.startswith("v_") and _scalars(a[:1], "v") & both) == 2, (i, args)
         assert not any("mfma" in op and "32x32x16" not in op and _scalars(args[:1], "a") for op, args in kernel)
     assert reads > 1000 and swaps > 1000
+
+
+def test_kernels_with_counted_waits_do_not_spill(tmp_path):
+    """Scratch memory is accessed by the counter of outstanding loads: a register spilled in a kernel whose waits leave a number of
+    loads on their way empties that queue at every access."""
+    seen = 0
+    for f in _device_objects(tmp_path):
+        notes = subprocess.run([LLVM + "readelf", "--notes", f], cwd=tmp_path, check=True, capture_output=True, text=True).stdout
+        for kernel in re.split(r"^  - ", notes, flags=re.M):
+            name = re.search(r"\.name: +(_Z\S+)", kernel)
+            if name and re.search("few_gemm_kernel|w4_gemm_kernel|mid_gemm_kernel", name[1]):
+                seen += 1
+                assert re.search(r"\.vgpr_spill_count: +0$", kernel, flags=re.M), name[1]
+    assert seen == 10 + 24 + 6          # tiles, passes, zero-points; tile heights, formats; widths, formats
 
 
 def test_scale_count_is_table2(oracle):
