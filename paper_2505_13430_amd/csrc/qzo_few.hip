@@ -51,28 +51,40 @@ struct FewLds {
 // What a wavefront needs later than its first loads.
 struct FewRest { uint32_t row_base, seed_lo, seed_hi; float eps_signed; };
 
-// MT tiles of 32 token rows; DUAL: the first half of the tile rows is the +eps pass, the second half the -eps pass.
-template <int MT, bool DUAL, bool ZP>
+// Passes of a launch: one, both in a wavefront (the first half of its tile rows is the +eps pass, the second half the -eps pass), or
+// both, a workgroup for each (the tiles of the two passes behind each other in every group of x).
+enum { ONE_PASS, BOTH_PASSES, PASS_EACH };
+
+// MT tiles of 32 token rows.
+template <int MT, int PASSES, bool ZP>
 __global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void* x, const void* w, const void* s, const float* xsum,
     uint32_t N, uint32_t K, uint32_t per, uint32_t packed, float* part, const void* zp, FewRest a) {
-  const uint32_t M = packed & 0xffu, W = (packed >> 8) & 0xffu;       // tokens of a pass, wavefronts
-  const bool s_fp16 = (packed >> 16) != 0;
+  const uint32_t M = packed & 0xffu, W = (packed >> 8) & 0xfu;        // tokens of a pass, wavefronts
+  const bool s_fp16 = (packed >> 12 & 1u) != 0;
   typedef FewLds<MT> L;
   constexpr int XS = L::XS;
+  constexpr bool DUAL = PASSES == BOTH_PASSES, EACH = PASSES == PASS_EACH;
+  uint32_t pass = 0, slice = blockIdx.y, block = blockIdx.x;
+  if (EACH) {         // unit u of both passes: neighbours on one XCD, equal shares for the XCDs
+    const uint32_t blocks = packed >> 16, u = (blockIdx.x >> 4) * 8 + (blockIdx.x & 7u);
+    pass = (blockIdx.x >> 3) & 1u; slice = u / blocks; block = u - slice * blocks;
+  }
   constexpr uint32_t ROWS = 32 * MT, TPP = DUAL ? ROWS / 2 : ROWS;
+  constexpr uint32_t ROWS_X = EACH ? 2 * ROWS : ROWS, GROUP_X = ROWS_X * 256;      // of a group in memory
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const uint32_t lrow = lane & 31u, half = lane >> 5;     // MFMA operand: row of the wavefront, half of the k-step
   const uint32_t lr = lane >> 3, lc = lane & 7u;          // weight loads: row within an instruction's 8, 16-byte chunk
   const uint32_t ngrp = K >> 7;
-  const uint32_t g0 = blockIdx.y * per, g1 = min(g0 + per, ngrp);
-  const uint32_t nb = (blockIdx.x * W + wave) * 32, n_own = nb + lrow;
+  const uint32_t g0 = slice * per, g1 = min(g0 + per, ngrp);
+  if (EACH && g0 >= ngrp) return;
+  const uint32_t nb = (block * W + wave) * 32, n_own = nb + lrow;
   const uint32_t n = min(n_own, N - 1);
   const NibbleConsts nc = nibble_constants();
   constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
-  const i32x4 rx = {(int)(uint32_t)(uintptr_t)x, (int)(uint32_t)((uintptr_t)x >> 32), (int)(ngrp * L::GROUP), 0x00020000};
-  const i32x4 rxs = {(int)(uint32_t)(uintptr_t)xsum, (int)(uint32_t)((uintptr_t)xsum >> 32), (int)(ngrp * ROWS * 4), 0x00020000};
+  const i32x4 rx = {(int)(uint32_t)(uintptr_t)x, (int)(uint32_t)((uintptr_t)x >> 32), (int)(ngrp * GROUP_X), 0x00020000};
+  const i32x4 rxs = {(int)(uint32_t)(uintptr_t)xsum, (int)(uint32_t)((uintptr_t)xsum >> 32), (int)(ngrp * ROWS_X * 4), 0x00020000};
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(w), 0, (int)((uint64_t)N * (K >> 1)), 0x00020000);
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
@@ -105,10 +117,12 @@ __global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void
     };
     auto xload = [&](uint32_t first, uint32_t last) __attribute__((always_inline)) {
       for (uint32_t q = first * MT * 8 + wave; q < min(last, cnt) * MT * 8; q += W)
-        QF_DTL(rx, lds0 + q * 1024, gb * L::GROUP + q * 1024 + lane * 16);
+        QF_DTL(rx, lds0 + q * 1024, gb * GROUP_X + (EACH ? q / (MT * 8) + pass : 0u) * L::GROUP + q * 1024 + lane * 16);
     };
     xload(0, XS);
-    if (wave < MT) QF_DTL(rxs, lds0 + L::SUMS + wave * 1024, gb * (ROWS * 4) + wave * 1024 + lane * 16);
+    if (wave < MT)
+      QF_DTL(rxs, lds0 + L::SUMS + wave * 1024,
+             gb * (ROWS_X * 4) + (EACH ? (wave * 1024 + lane * 16) / (ROWS * 4) + pass : 0u) * (ROWS * 4) + wave * 1024 + lane * 16);
     u32x4 sv;
     if (((ngrp | gb) & 1u) == 0) {
       sv = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((soff + gb) * 2), 0, 0);
@@ -211,12 +225,13 @@ __global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void
       constexpr bool wait = d + 1 >= XS && d < 7, refill = d >= 1 && d - 1 + XS < 8;
       constexpr int NR = (Q + (MT == 4 ? L::W : 4) - 1) / (MT == 4 ? L::W : 4), BAR = Q - 2 * NR;       // NR: loads of a wavefront
       static_assert(XS == 8 || BAR >= 0, "slots for the loads");
-      const uint32_t refill_off = d - 1 + XS < (int)cnt ? (gb + d - 1 + XS) * L::GROUP + lane * 16 : OUT_OF_RANGE;
+      const uint32_t refill_off = d - 1 + XS < (int)cnt ? (gb + d - 1 + XS) * GROUP_X + pass * L::GROUP + lane * 16 : OUT_OF_RANGE;
       const unsigned char* const xb = lds + (d % XS) * L::GROUP + lane * 16;
       const unsigned char* const xb_next = lds + ((d + 1) % XS) * L::GROUP + lane * 16;
       const float* const sums = reinterpret_cast<const float*>(lds + L::SUMS) + d * ROWS + 4 * half;
+      const float eps = EACH && pass ? -a.eps_signed : a.eps_signed;
       const float s0 = scale_to_f32((d & 1) ? sv[d >> 1] >> 16 : sv[d >> 1] & 0xffffu, s_fp16);
-      const float se_p = __builtin_fmaf(a.eps_signed, z[d], s0), se_m = __builtin_fmaf(-a.eps_signed, z[d], s0);
+      const float se_p = __builtin_fmaf(eps, z[d], s0), se_m = __builtin_fmaf(-eps, z[d], s0);
       const float cz = ZP ? -(128.0f + (float)((zv[d >> 2] >> (8 * (d & 3))) & 0xffu)) : -136.0f;
       wf[0] = unpack8_biased(wd[d & 1][0], nc);
       __builtin_amdgcn_sched_barrier(0);
@@ -267,15 +282,15 @@ __global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void
   }
 
   // partial sums of this slice
-  const uint32_t rows = DUAL ? 2 * M : M;
-  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(part, 0, (int)((uint64_t)gridDim.y * rows * N * 4), 0x00020000);
+  const uint32_t rows = PASSES == ONE_PASS ? M : 2 * M;
+  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(part, 0, (int)((uint64_t)(slice + 1) * rows * N * 4), 0x00020000);
   if (n_own < N) {
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const uint32_t tr = 32 * m + 8 * (r >> 2) + 4 * half + (r & 3), tok = tr % TPP;
-        const uint32_t off = ((blockIdx.y * rows + (tr / TPP) * M + tok) * N + n_own) * 4u;
+        const uint32_t off = ((slice * rows + (tr / TPP + pass) * M + tok) * N + n_own) * 4u;
         if (tok < M) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[m][r]), rp, (int)off, 0, WRITE_THROUGH);
       }
   }
@@ -283,29 +298,48 @@ __global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void
 }
 #undef QF_DTL
 
-template <int MT, bool DUAL, bool ZP>
+template <int MT, int PASSES, bool ZP>
 hipError_t few_prepare() {
-  return hipFuncSetAttribute((const void*)few_gemm_kernel<MT, DUAL, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  return hipFuncSetAttribute((const void*)few_gemm_kernel<MT, PASSES, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              FewLds<MT>::bytes(FewLds<MT>::W));
 }
-template <int MT, bool DUAL>
-hipError_t few_launch(const GemmArgs& a, float* ws, uint32_t ks, uint32_t per, hipStream_t st) {
-  // wavefronts per workgroup: the least time, rounds of a workgroup per compute unit, each (start and stores) + W
-  const uint32_t tiles = (a.N + 31) / 32, cus = gemm_workgroups(1u << 20, 1u << 20);
-  uint32_t w = MT == 4 ? FewLds<MT>::W : 4;
-  uint64_t best = ~0ull;
-  for (uint32_t v = w; v <= FewLds<MT>::W; ++v) {
-    const uint64_t time = ((uint64_t)((tiles + v - 1) / v) * ks + cus - 1) / cus * (4 + v);
-    if (time < best) { best = time; w = v; }
+// Wavefronts per workgroup: the least time, rounds of a workgroup per compute unit, each (start and stores) + W.  Four tiles: six, as the
+// refills of the ring are dealt out.
+struct FewPlan { uint32_t waves, blocks, rounds; };
+template <int MT>
+FewPlan few_plan(uint32_t N, uint32_t slices) {
+  const uint32_t tiles = (N + 31) / 32, cus = gemm_workgroups(1u << 20, 1u << 20);
+  FewPlan best = {};
+  for (uint32_t w = MT == 4 ? FewLds<MT>::W : 4; w <= FewLds<MT>::W; ++w) {
+    const uint32_t blocks = (tiles + w - 1) / w, rounds = (uint32_t)(((uint64_t)blocks * slices + cus - 1) / cus);
+    if (!best.waves || (uint64_t)rounds * (4 + w) < (uint64_t)best.rounds * (4 + best.waves)) best = {w, blocks, rounds};
   }
-  const dim3 grid((tiles + w - 1) / w, ks);
+  return best;
+}
+template <int MT, int PASSES>
+hipError_t few_launch(const GemmArgs& a, const FewPlan& p, float* ws, uint32_t ks, uint32_t per, hipStream_t st) {
+  const uint32_t w = p.waves, blocks = p.blocks;
+  const dim3 grid = PASSES == PASS_EACH ? dim3((blocks * ks + 7) / 8 * 16) : dim3(blocks, ks);
   const FewRest r = {a.row_base, a.seed_lo, a.seed_hi, a.eps_signed};
-  const uint32_t packed = a.M | (w << 8) | (a.s_fp16 ? 1u << 16 : 0u);
+  const uint32_t packed = a.M | (w << 8) | (a.s_fp16 ? 1u << 12 : 0u) | (PASSES == PASS_EACH ? blocks << 16 : 0u);
   if (a.zp)
-    few_gemm_kernel<MT, DUAL, true><<<grid, w * 64, FewLds<MT>::bytes(w), st>>>(a.x, a.w, a.s, a.xsum, a.N, a.K, per, packed, ws, a.zp, r);
+    few_gemm_kernel<MT, PASSES, true><<<grid, w * 64, FewLds<MT>::bytes(w), st>>>(a.x, a.w, a.s, a.xsum, a.N, a.K, per, packed, ws, a.zp, r);
   else
-    few_gemm_kernel<MT, DUAL, false><<<grid, w * 64, FewLds<MT>::bytes(w), st>>>(a.x, a.w, a.s, a.xsum, a.N, a.K, per, packed, ws, nullptr, r);
+    few_gemm_kernel<MT, PASSES, false><<<grid, w * 64, FewLds<MT>::bytes(w), st>>>(a.x, a.w, a.s, a.xsum, a.N, a.K, per, packed, ws, nullptr, r);
   return hipGetLastError();
+}
+template <int MT, int PASSES>
+hipError_t few_launch(const GemmArgs& a, float* ws, uint32_t ks, uint32_t per, hipStream_t st) {
+  return few_launch<MT, PASSES>(a, few_plan<MT>(a.N, ks), ws, ks, per, st);
+}
+// Both passes of 33 to 64 tokens.  A workgroup for each pass has half the work, but unpacks every weight a second time; its
+// launch is the faster one where it takes no more rounds (both launches' times, us, 64 tokens: 1024 x 1024 11.4 -> 5.8, 6144 x 2048 14.7 ->
+// 11.6, 2048 x 8192 14.4 -> 13.8 and 16384 x 4096 34.0 -> 27.3; one round more: 12288 x 4096 20.1 -> 22.9, 11264 x 2048 15.0 ->
+// 17.8, 22016 x 4096 36.5 -> 37.4, 15360 x 5120 35.6 -> 33.2).
+hipError_t few_launch_wide(const GemmArgs& a, float* ws, uint32_t ks, uint32_t per, hipStream_t st) {
+  const FewPlan both = few_plan<4>(a.N, ks), each = few_plan<2>(a.N, 2 * ks);
+  if (each.rounds <= both.rounds && each.blocks < 65536u) return few_launch<2, PASS_EACH>(a, each, ws, ks, per, st);
+  return few_launch<4, BOTH_PASSES>(a, both, ws, ks, per, st);
 }
 
 }  // namespace
@@ -313,24 +347,26 @@ hipError_t few_launch(const GemmArgs& a, float* ws, uint32_t ks, uint32_t per, h
 hipError_t launch_few_gemm(const GemmArgs& a, float* ws, uint32_t ks, uint32_t per, hipStream_t st) {
   static bool ready = false;
   if (!ready) {
-    hipError_t e = few_prepare<1, true, false>();
-    if (e == hipSuccess) e = few_prepare<1, true, true>();
-    if (e == hipSuccess) e = few_prepare<1, false, false>();
-    if (e == hipSuccess) e = few_prepare<1, false, true>();
-    if (e == hipSuccess) e = few_prepare<2, true, false>();
-    if (e == hipSuccess) e = few_prepare<2, true, true>();
-    if (e == hipSuccess) e = few_prepare<2, false, false>();
-    if (e == hipSuccess) e = few_prepare<2, false, true>();
-    if (e == hipSuccess) e = few_prepare<4, true, false>();
-    if (e == hipSuccess) e = few_prepare<4, true, true>();
+    hipError_t e = few_prepare<1, BOTH_PASSES, false>();
+    if (e == hipSuccess) e = few_prepare<1, BOTH_PASSES, true>();
+    if (e == hipSuccess) e = few_prepare<1, ONE_PASS, false>();
+    if (e == hipSuccess) e = few_prepare<1, ONE_PASS, true>();
+    if (e == hipSuccess) e = few_prepare<2, BOTH_PASSES, false>();
+    if (e == hipSuccess) e = few_prepare<2, BOTH_PASSES, true>();
+    if (e == hipSuccess) e = few_prepare<2, ONE_PASS, false>();
+    if (e == hipSuccess) e = few_prepare<2, ONE_PASS, true>();
+    if (e == hipSuccess) e = few_prepare<4, BOTH_PASSES, false>();
+    if (e == hipSuccess) e = few_prepare<4, BOTH_PASSES, true>();
+    if (e == hipSuccess) e = few_prepare<2, PASS_EACH, false>();
+    if (e == hipSuccess) e = few_prepare<2, PASS_EACH, true>();
     if (e != hipSuccess) return e;
     ready = true;
   }
   if (!a.xsum || a.xp.M != a.M || a.xp.rows != few_pack(a.M, a.dual != 0).rows) return hipErrorInvalidValue;
   switch (a.xp.rows >> 5) {
-    case 1: return a.dual ? few_launch<1, true>(a, ws, ks, per, st) : few_launch<1, false>(a, ws, ks, per, st);
-    case 2: return a.dual ? few_launch<2, true>(a, ws, ks, per, st) : few_launch<2, false>(a, ws, ks, per, st);
-    case 4: return a.dual ? few_launch<4, true>(a, ws, ks, per, st) : hipErrorInvalidValue;
+    case 1: return a.dual ? few_launch<1, BOTH_PASSES>(a, ws, ks, per, st) : few_launch<1, ONE_PASS>(a, ws, ks, per, st);
+    case 2: return a.dual ? few_launch<2, BOTH_PASSES>(a, ws, ks, per, st) : few_launch<2, ONE_PASS>(a, ws, ks, per, st);
+    case 4: return a.dual ? few_launch_wide(a, ws, ks, per, st) : hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 }

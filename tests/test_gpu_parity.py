@@ -978,9 +978,9 @@ def test_attention_that_adds_up_slices_equals_reduction_and_attention(B, S, H, d
     # slices of three groups that start on odd ones; ragged last workgroups
     (1, 2, 5, 1152, "int4"), (1, 16, 5, 1144, "zp"), (4, 4, 5, 640, "zp16"), (3, 5, 5, 1152, "int4"), (1, 17, 5, 1144, "int4"),
     (4, 8, 5, 640, "zp16"), (3, 11, 5, 1152, "zp"), (1, 64, 5, 1144, "int4"),
-    # slices of eight groups: the ring of activations is refilled once around with two and four token tiles
+    # slices of eight groups: the ring of activations is refilled with two and four token tiles (16384 rows: a workgroup for each pass)
     (1, 16, 32, 8200, "int4"), (1, 24, 32, 8200, "zp"), (1, 32, 32, 12288, "int4"), (1, 57, 32, 12288, "int4"), (1, 57, 32, 8200, "zp"),
-    (4, 16, 32, 8200, "zp16"),
+    (4, 16, 32, 8200, "zp16"), (1, 57, 32, 16384, "int4"), (3, 21, 32, 16360, "zp"),
     # slices of fourteen: a second pass of the K loop, over six
     (1, 16, 40, 27648, "zp"), (1, 24, 40, 27648, "int4"), (1, 57, 40, 27640, "int4"), (2, 32, 40, 27648, "zp")])
 def test_linear_behind_attention_that_packs_equals_plain_layout(B, S, H, N, fmt, passes):

@@ -124,7 +124,7 @@ def test_kernels_with_counted_waits_do_not_spill(tmp_path):
             if name and re.search("few_gemm_kernel|w4_gemm_kernel|mid_gemm_kernel", name[1]):
                 seen += 1
                 assert re.search(r"\.vgpr_spill_count: +0$", kernel, flags=re.M), name[1]
-    assert seen == 10 + 24 + 6          # tiles, passes, zero-points; tile heights, formats; widths, formats
+    assert seen == 12 + 24 + 6          # tiles, passes, zero-points; tile heights, formats; widths, formats
 
 
 def test_scale_count_is_table2(oracle):
