@@ -673,6 +673,19 @@ hipError_t w4_prepare() {
   if constexpr (MT > 1) return e != hipSuccess ? e : w4_prepare<MT - 1, FMT>();
   return e;
 }
+// W4Args lists the kernel's parameters: where each one begins, by its type's alignment, and the last one's place.
+template <class F>
+struct LastParameter;
+template <class... P>
+struct LastParameter<void (*)(P...)> {
+  static constexpr size_t place() {
+    size_t begin = 0, end = 0;
+    ((begin = (end + alignof(P) - 1) / alignof(P) * alignof(P), end = begin + sizeof(P)), ...);
+    return begin;
+  }
+};
+static_assert(LastParameter<decltype(&w4_gemm_kernel<8, W4_INT4>)>::place() == offsetof(W4Args, rest) &&
+              sizeof(W4Args) - offsetof(W4Args, rest) == sizeof(W4Rest), "w4_rest() reads the last parameter");
 template <int MT>
 void w4_launch(const GemmArgs& a, const W4Plan& p, hipStream_t st) {
   const W4Rest r = {a.y, a.resid, a.bias, a.partials, a.split_ws, a.rope, a.rope_S, a.ldy, a.row_base, a.seed_lo, a.seed_hi, a.eps_signed};
