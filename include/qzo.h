@@ -441,7 +441,8 @@ qzo_status qzo_debug_reduce_norm(const float* part_dev, uint32_t slices, uint32_
                                  void* stream);
 
 /* Inspection: the kernel that serves int4 and NormalFloat-4 linears of many tokens, K uncut, with the height of its output
- * tiles given: *height (host) is 1 to 8, for 32 to 256 tokens, or 0 for the library's choice, which is stored there.  Operands as
+ * tiles given: *height (host) is 1 to 8, for 32 to 256 tokens, or 0 for the library's choice, which is stored there (of two
+ * launches: the first one's columns' height in the lower half, the other columns' in the upper half).  Operands as
  * for qzo_dequant_gemm(_zp) with bf16 scales (zp_dev null: symmetric) or, with nf4, as for qzo_nf4_gemm.  passes = 2: x, y and
  * resid hold 2 M rows, the second M of which take -sign.  epilogue: a sum of 1 (+ bias_dev, bf16 [N]), 2 (+ resid_dev,
  * like y), 4 (ReLU), or one of 0, 16 (N = 2 F, F % 128 == 0: y [rows, F] = silu(first half) * second half), 32 (the rotary embedding of

@@ -360,7 +360,8 @@ def qzo_debug_reduce_norm(part, bias, resid, gain, norm_bias, eps, joined, y, ou
 
 def qzo_debug_fused_linear(x, q, s, zp, row_base, seed, eps, sign, y, passes=1, nf4=False, epilogue=0, bias=None, resid=None,
                            rope=None, head_dim=0, height=0, stream=None) -> int:
-    """Returns the height of the output tiles, in units of 32 tokens.  rope [seq, head_dim / 2, 2]."""
+    """Returns the height of the output tiles, in units of 32 tokens; of two launches, + 65536 times the second one's.
+    rope [seq, head_dim / 2, 2]."""
     N, K, mt = q.shape[0], x.shape[1], C.c_uint32(height)
     assert x.shape[0] % passes == 0 and y.shape == (x.shape[0], N // 2 if epilogue == 16 else N)
     _check(lib().qzo_debug_fused_linear(_ptr(x), _ptr(q), _ptr(s), _ptr(zp), C.c_int(int(nf4)), C.c_uint32(row_base),

@@ -1402,7 +1402,8 @@ qzo_status qzo_debug_fused_linear(const void* x_dev, const void* q_dev, const vo
   g.epi = epilogue; g.rope = rope_dev; g.rope_S = rope_seq; g.rope_dh = rope_head_dim;
   const W4Plan p = w4_plan(M, g.flip_row, N, K, 1, 0, 0, *height);
   QZO_HIP(*height ? launch_w4_tiles(g, p, (hipStream_t)stream) : launch_w4(g, p, (hipStream_t)stream));
-  *height = p.mt;
+  W4Plan head, tail;
+  *height = !*height && w4_two_heights(p, M, K, &head, &tail) ? head.mt | tail.mt << 16 : p.mt;
   return QZO_OK;
 }
 

@@ -1735,8 +1735,9 @@ def test_fused_linear_of_two_tile_heights(M, N, K, epilogue, head_dim, fmt):
     for height in (8, 0):
         guard = torch.full(((2 * M + 32) * cols,), 7.0, dtype=torch.bfloat16, device=DEV)
         y = guard[:2 * M * cols].view(2 * M, cols)
-        qb.qzo_debug_fused_linear(x, q, s, z, 11, 31, 1e-2, 1, y, passes=2, nf4=fmt == "nf4", epilogue=epilogue, bias=bias,
-                                  resid=resid, rope=rope, head_dim=head_dim, height=height)
+        used = qb.qzo_debug_fused_linear(x, q, s, z, 11, 31, 1e-2, 1, y, passes=2, nf4=fmt == "nf4", epilogue=epilogue, bias=bias,
+                                         resid=resid, rope=rope, head_dim=head_dim, height=height)
+        assert used == height if height else used >> 16 != used & 0xffff and (used >> 16) * (used & 0xffff)
         assert bool((guard[2 * M * cols:] == 7.0).all())
         ys.append(y)
     assert torch.equal(ys[0], ys[1])
