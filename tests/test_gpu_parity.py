@@ -495,6 +495,18 @@ def test_few_token_layers_with_odd_slices(oracle, arch, var, batch, seq):
         assert [res["loss_plus"], res["loss_minus"]] == single
 
 
+@pytest.mark.parametrize("name,seq,var", [("llama-2-7b", 24, ""), ("llama-2-7b", 57, True), ("llama-2-13b", 24, True), ("llama-2-13b", 57, "")])
+def test_few_token_layers_of_real_width(oracle, name, seq, var):
+    """Slices of eight groups, and of fourteen in the widest gate/up linear: the ring of packed activations is refilled, and the K loop
+    run twice, with both passes in two and in four tiles.  Hidden states of both passes against the oracle's, element by element."""
+    shape = dict(synth.SHAPES[name], n_layers=1, batch=1, seq=seq, max_seq=64, vocab=500)
+    om, dm = _models(oracle, shape, 77, 2.0, **_variant_args(var))
+    tok = synth.tokens(shape, 99)
+    _, both = _step_hidden(dm, _dev(tok), 5, 1e-2)
+    _check_both_passes(oracle, om, tok, 5, 1e-2, both)
+    dm.close()
+
+
 def test_few_token_step_of_a_layer_with_millions_of_rows():
     """64 tokens through a gate/up linear of 2^22 rows: the partial sums of both passes would need 2^31 bytes, those of one
     pass half of that, so the step runs two forwards: bit-identical to forward_loss."""
