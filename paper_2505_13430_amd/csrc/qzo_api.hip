@@ -215,7 +215,9 @@ bool nf4_tile_route(const qzo_model* m, uint64_t M1) {
 // tokens), 1.19 (132), 1.14 (192); 13B widths 1.19 (96), 1.24 (128); OPT-1.3B widths 1.03 (96), 0.97 (128), 1.04 (132), 0.94 (256).
 // The range stays, for its precision.  Up to 64 tokens, over the few-token kernel's with a workgroup
 // per pass: 7B widths 0.91-0.94, 13B 0.88-0.89, 2560 x 10240 and 3072 x 8192 0.93-0.96, but OPT-1.3B 1.01-1.04, 2048 x 5632
-// 1.05-1.07, smaller models 0.97-1.02: there the few-token kernel stays, whose losses are those of two separate passes.
+// 1.05-1.07, smaller models 0.97-1.02: there the few-token kernel stays, whose losses are those of two separate passes.  (That kernel was
+// skinny_gemm_kernel.  few_gemm_kernel is the faster one: six layers of 7B widths, 33 / 64 tokens, 0.73 / 0.79 ms with bf16 scales, here
+// 0.82 / 0.86; the range stays, with its results.)
 // A route that the caller chose stays: 1 (fused) keeps the tile kernel beyond the few-token kernel's 64 tokens.
 //   NormalFloat-4: the tile kernel where nf4_tile_route says so.  Whole steps of this kernel against two forwards / one
 // stacked forward on expanded matrices: 7B widths 0.27 / 0.26 (16 tokens), 0.33 / 0.32 (57), 0.50 / 0.59 (192), 0.49 / 0.63 (256), 0.86 / 0.90 (400), 0.77 / 0.83
@@ -289,9 +291,8 @@ bool nf4_stack_pays(const qzo_model* m, uint64_t M1) {
 }
 
 // Whether qzo_step runs its two perturbed passes as one forward over 2 * batch sequences.  With at
-// most 32 tokens the few-token kernel reads the int4 weights once for both, with up to 64 its launches hold a
-// workgroup of either pass (half the launches, bit-identical to separate passes); on the route above mid_gemm_kernel
-// serves both.
+// most 64 tokens the few-token kernels serve both in one launch (half the launches, bit-identical to separate passes); on the route
+// above mid_gemm_kernel serves both.
 // Beyond (at most 4096 tokens per pass), a launch of
 // the tile kernel holds both passes' token tiles, the second pass's with -eps: twice the tiles per
 // launch for a chip that such token counts do not fill, half the launches.

@@ -3,24 +3,27 @@
 // P by MFMA, y += s_eff (P - (128 + zp) X) in fp32 - for activations that their producer has laid out for it (XPack) and
 // whose block sums X it has delivered.
 //
-// A workgroup of W wavefronts owns 32 W output rows and one K slice; W is chosen so that the launch is one workgroup per
-// compute unit and one round.  The slice's activations come by direct-to-LDS loads in the order in which the MFMA wants them
+// A workgroup of W wavefronts owns 32 W output rows and one K slice; W (4 to 12 with one token tile, 4 to 8 with two) is the one whose
+// rounds of a workgroup per compute unit take the least time: at 16 tokens one round for every linear of the 7B shape.  With four tiles
+// W is 6, and 22016 rows take two rounds (115 x 4 workgroups).  The slice's activations come by direct-to-LDS loads in the order in which the MFMA wants them
 // (1 KB a load, no permutation, no address arithmetic in the loop), weights two rounds (four groups) ahead into registers;
 // everyone's first round is requested before anyone's second, or the youngest wavefront's first weights queue behind all of the
 // oldest one's.  The arguments of the first loads arrive in registers (read from memory: 1.2 us); the noise of the eight groups
 // is drawn while the first loads are on their way, either half of a wavefront half of the variates.  With one token tile the K
 // loop holds no barrier: a wavefront waits for its own weights only.  With more tiles the activations are a ring of six (two
-// tiles) or four (four) groups, refilled by loads dealt out behind the MFMAs.  One wavefront serves the tokens of both passes: a weight is unpacked once for a step, where
-// a workgroup per pass unpacked it twice.
+// tiles) or four (four) groups, refilled by loads dealt out behind the MFMAs.  One wavefront serves the tokens of both passes: a weight is unpacked once for a step;
+// where a launch of 33 to 64 tokens would be short of workgroups, one of two tiles serves each pass (few_launch_wide).
 //
 // Bound, 1 x 16 tokens of the 7B shape, one launch of 12288 / 22016 / 4096 rows (25 / 45 / 23 MB): 7.2 / 10.1 / 8.2 us from its
 // first instruction to its last (before: 12.3 / 17.1 / 12.9), of which reading alone takes some 3.5 / 6.5 / 3.5 whatever the
 // pattern (128 bytes of eight rows, 512 of two, linear: 8.4 us a launch of 45 MB, all included); eight groups of 850 cycles
 // behind the first loads and 1400 cycles of stores are what does not overlap.  Step 2.67 -> 2.26 ms.
 // Four tiles (57 tokens), workgroups of 192 rows: a group takes 2000 cycles (two wavefronts on a SIMD, 1024 of MFMAs each), 2950
-// with the six loads of 1 KB that refill the ring, whatever places they take; then 4400 cycles of stores, 22 MB of partial sums
-// at the rate of the last-level cache.  12288 / 22016 / 4096 rows 17.4 / 33.7 / 17.9 us, step 4.81 -> 4.10 ms (refills in a
-// row and the barrier at the head of a group, 256 rows: 3600 cycles a group, 4.43 ms).
+// with the six loads of 1 KB that refill the ring, whatever places they take; then 4400 cycles of stores: 22 / 40 / 20 MB of partial sums
+// at the rate of the last-level cache.  12288 / 22016 / 4096 rows 17.4 / 33.7 / 17.9 us; refills in a row and the barrier at the head of a
+// group, 256 rows: 3600 cycles a group, a step of 4.43 ms for 4.10.  The weights are builtin loads, whose waits the compiler counts without
+// the refills (asm): before the third round's weights are stored (group 3) it waits until 4 loads are out where 16 could be, before the
+// fourth's (group 5) for all of them, the last group's activations among them.
 // Tried: all four rounds of weights requested at once (everything arrives, then everything is computed: 10.0 / 13.7 / 9.9 us);
 // activations of the later groups behind the first weights (no difference).
 #include "qzo_device.hpp"
@@ -194,8 +197,8 @@ __global__ __launch_bounds__(FewLds<MT>::W * 64) void few_gemm_kernel(const void
     wstore(std::integral_constant<int, 0>());
     wread(std::integral_constant<int, 0>());
 
-    // Group d and those behind it (nested, so that a wait for weights counts the loads that were issued in between and not the
-    // least of several paths).  Its last tile is rescaled behind the next group's first MFMAs, its first fragments are read
+    // Group d and those behind it (nested, so that a wait for weights counts the weight loads that were issued in between and not the
+    // least of several paths; the refills, in asm, it does not count and waits for).  Its last tile is rescaled behind the next group's first MFMAs, its first fragments are read
     // behind the last ones of the group before; the barrier of the ring stands in its second half, where nobody waits for
     // operands (at the head of a group, with everything begun and ended there: 3300 cycles a group of four tiles).
     constexpr int R = 4;                            // fragments read ahead of their MFMA

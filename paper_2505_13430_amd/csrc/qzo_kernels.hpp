@@ -100,9 +100,9 @@ struct GemmArgs {
   uint32_t epi;
   uint32_t s_fp16;      // int4 formats: s holds fp16 instead of bf16
   uint32_t nf4;         // mid_gemm_kernel and the fused kernel: w holds NormalFloat-4 indices, s bf16 [N,K/64], no block sums
-  // Few-token paths: block sums X[g][row] = sum of x[row, 128 g .. 128 g + 127] (fp32, [K/128][rows], rows = M or
-  // 2 M when dual), delivered by the kernel that wrote x (null: the kernel sums them itself), and the same for
-  // the output y of the K-slice reduction ([N_out/128][rows], N_out % 128 == 0; null: not wanted).
+  // few_gemm_kernel and mid_gemm_kernel: block sums X[g][row] = sum of x[row, 128 g .. 128 g + 127] (fp32, [K/128][rows], rows = M or
+  // 2 M when dual, or xp.rows), delivered by the kernel that wrote x, and the same for the output y of the K-slice reduction
+  // ([N_out/128][rows], rows as before or yp.rows, N_out % 128 == 0; null: not wanted).  skinny_gemm_kernel sums its blocks itself.
   const float* xsum;
   float* xsum_out;
   XPack xp, yp;               // layout of x and xsum, of the reduction's y and xsum_out
@@ -115,7 +115,7 @@ hipError_t launch_w4a16_gemm(const GemmArgs& a, hipStream_t st);
 // (output tile, K slice of kt_per k-tiles).  M: tokens of a pass; second_row: first row of the second pass (0: one pass).
 struct W4Plan {
   uint32_t mt, tiles_m, tiles_per_pass, tiles_n, ksplit, kt_per;
-  uint32_t second_row, rows;         // rows: of x, y and resid
+  uint32_t second_row;
   uint32_t wgs, rounds;              // persistent workgroups, units of the busiest one
   uint32_t last;                     // units of the last round
   uint32_t first_n, count_n;         // a launch of some feature tiles only: the first, how many (0: all of them)

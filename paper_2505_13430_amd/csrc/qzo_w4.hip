@@ -707,7 +707,7 @@ W4Plan w4_plan_of(uint32_t cus, uint32_t M, uint32_t second_row, uint32_t tiles_
   W4Plan p = {};
   p.mt = mt;
   p.ksplit = ksplit; p.kt_per = ksplit > 1 ? kt_per : K / BK;
-  p.second_row = second_row; p.rows = second_row ? second_row + M : M;
+  p.second_row = second_row;
   p.tiles_n = tiles_n;
   p.tiles_per_pass = (M + 32 * mt - 1) / (32 * mt);
   p.tiles_m = second_row ? 2 * p.tiles_per_pass : p.tiles_per_pass;
