@@ -17,7 +17,8 @@
 // Bound, 1 x 16 tokens of the 7B shape, one launch of 12288 / 22016 / 4096 rows (25 / 45 / 23 MB): 7.2 / 10.1 / 8.2 us from its
 // first instruction to its last (before: 12.3 / 17.1 / 12.9), of which reading alone takes some 3.5 / 6.5 / 3.5 whatever the
 // pattern (128 bytes of eight rows, 512 of two, linear: 8.4 us a launch of 45 MB, all included); eight groups of 850 cycles
-// behind the first loads and 1400 cycles of stores are what does not overlap.  Step 2.67 -> 2.26 ms.
+// behind the first loads and 1400 cycles of stores are what does not overlap.  Step 2.67 -> 2.26 ms (another board
+// 2.71 -> 2.39).
 // Four tiles (57 tokens), workgroups of 192 rows: a group takes 2000 cycles (two wavefronts on a SIMD, 1024 of MFMAs each), 2950
 // with the six loads of 1 KB that refill the ring, whatever places they take; then 4400 cycles of stores: 22 / 40 / 20 MB of partial sums
 // at the rate of the last-level cache.  12288 / 22016 / 4096 rows 17.4 / 33.7 / 17.9 us; refills in a row and the barrier at the head of a
